@@ -102,6 +102,16 @@ int check_block(const ivit_block_params* p, const ivit_dims* d) {
     return IVIT_OK;
 }
 
+ivit::AttentionArgs attention_args(const ivit_block_params* p, const ivit_dims* d, const Workspace& w, const ivit_debug_taps* taps) {
+    ivit::AttentionArgs aa{};
+    aa.qkv = w.qkv; aa.rel_bias = p->rel_bias; aa.o = w.o; aa.B = d->B; aa.T = d->T; aa.C = d->C; aa.H = d->H;
+    aa.mask = p->attn_mask; aa.n_mask = p->attn_mask ? p->n_mask : 1;
+    aa.tok_index = p->tok_index; aa.n_win = p->tok_index ? p->n_win : 1;
+    aa.qk_rq = dy(p->qk_rq); aa.sm = sp(p->softmax); aa.pv_rq = dy(p->pv_rq);
+    aa.tap_scores = taps ? taps->scores : nullptr; aa.tap_probs = taps ? taps->probs : nullptr;
+    return aa;
+}
+
 // Launch sequence of one block on buffers of the carved workspace.  Arguments already validated.
 hipError_t run_block(hipStream_t s, const int8_t* x, int8_t* y, const ivit_block_params* p, const ivit_dims* d,
                      const Workspace& w, const ivit_debug_taps* taps) {
@@ -122,13 +132,7 @@ hipError_t run_block(hipStream_t s, const int8_t* x, int8_t* y, const ivit_block
     if ((e = ivit::launch_linear(s, la))) return e;
     if (taps && (e = tap(taps->qkv, w.qkv, (size_t)R * 3 * C))) return e;
     // o = attention(qkv)
-    ivit::AttentionArgs aa{};
-    aa.qkv = w.qkv; aa.rel_bias = p->rel_bias; aa.o = w.o; aa.B = d->B; aa.T = d->T; aa.C = C; aa.H = d->H;
-    aa.mask = p->attn_mask; aa.n_mask = p->attn_mask ? p->n_mask : 1;
-    aa.tok_index = p->tok_index; aa.n_win = p->tok_index ? p->n_win : 1;
-    aa.qk_rq = dy(p->qk_rq); aa.sm = sp(p->softmax); aa.pv_rq = dy(p->pv_rq);
-    aa.tap_scores = taps ? taps->scores : nullptr; aa.tap_probs = taps ? taps->probs : nullptr;
-    if ((e = ivit::launch_attention(s, aa))) return e;
+    if ((e = ivit::launch_attention(s, attention_args(p, d, w, taps)))) return e;
     if (taps && (e = tap(taps->o, w.o, (size_t)R * C))) return e;
     // xhat = Dense(o) + x
     la = ivit::LinearArgs{};
@@ -151,6 +155,78 @@ hipError_t run_block(hipStream_t s, const int8_t* x, int8_t* y, const ivit_block
     la.x = w.h; la.w = p->w_fc2; la.bias = p->bias_fc2; la.rq_b = p->fc2_rq_b; la.rq_c = p->fc2_rq_c;
     la.residual = w.xhat; la.res_rq = dy(p->res2_rq); la.gelu = false; la.y = y; la.M = R; la.N = C; la.K = F;
     return ivit::launch_linear(s, la);
+}
+
+// Whether the token-wise layers of a block run as one kernel (token_block.hip): its widths, and 16-byte alignment of the
+// parameter arrays, which it fetches in such pieces.
+bool block_fuses(const ivit_block_params* p, const ivit_dims* d) {
+    if (!ivit::token_block_takes(d->C, d->F, (int64_t)d->B * d->T)) return false;
+    const void* i32s[] = {p->ln1_gamma, p->ln1_beta, p->bias_qkv, p->qkv_rq_b, p->qkv_rq_c, p->bias_proj, p->proj_rq_b,
+                          p->proj_rq_c, p->ln2_gamma, p->ln2_beta, p->bias_fc1, p->fc1_rq_b, p->fc1_rq_c};
+    for (const void* q : i32s)
+        if (!aligned(q, 16)) return false;
+    return true;
+}
+
+// Launch sequence of n_blocks blocks, the last of which writes y, or, with a final I-LayerNorm, hands its rows to it.
+// Arguments already validated; n_blocks >= 1.
+hipError_t run_blocks(hipStream_t s, const int8_t* x, int8_t* y, const ivit_block_params* blocks, int32_t n_blocks,
+                      const ivit_final_ln* final_ln, const ivit_dims* d, const Workspace& w) {
+    const int64_t R = (int64_t)d->B * d->T;
+    bool fuse = true;
+    for (int l = 0; l < n_blocks && fuse; ++l) fuse = block_fuses(&blocks[l], d);
+    if (final_ln && !(aligned(final_ln->gamma, 16) && aligned(final_ln->beta, 16))) fuse = false;
+    hipError_t e;
+    // block l reads cur and writes into the other ping-pong buffer; the last producer writes y directly
+    const int8_t* cur = x;
+    auto other = [&]() { return cur == w.act0 ? w.act1 : w.act0; };
+    if (!fuse) {
+        for (int l = 0; l < n_blocks; ++l) {
+            int8_t* dst = l == n_blocks - 1 && !final_ln ? y : other();
+            if ((e = run_block(s, cur, dst, &blocks[l], d, w, nullptr))) return e;
+            cur = dst;
+        }
+        if (!final_ln) return hipSuccess;
+        return ivit::launch_ilayernorm(s, cur, final_ln->gamma, final_ln->beta, y, R, d->C, final_ln->f_bits, final_ln->c_shift);
+    }
+    auto next_qkv = [&](ivit::TokenBlockArgs& t, const ivit_block_params& p) {
+        t.next = 2; t.out = w.qkv;
+        t.ln1_g = p.ln1_gamma; t.ln1_b = p.ln1_beta; t.ln1_f = p.ln1_f_bits; t.ln1_c = p.ln1_c_shift;
+        t.qkv_w = ivit::DenseW{p.w_qkv, p.bias_qkv, p.qkv_rq_b, p.qkv_rq_c};
+    };
+    ivit::TokenBlockArgs t{};
+    t.R = R; t.C = d->C; t.F = d->F; t.x = x;
+    next_qkv(t, blocks[0]);
+    if ((e = ivit::launch_token_block(s, t))) return e;
+    for (int l = 0; l < n_blocks; ++l) {
+        const ivit_block_params& p = blocks[l];
+        const bool last = l == n_blocks - 1;
+        if ((e = ivit::launch_attention(s, attention_args(&p, d, w, nullptr)))) return e;
+        t = ivit::TokenBlockArgs{};
+        t.R = R; t.C = d->C; t.F = d->F;
+        t.o = w.o; t.x = cur; t.xhat = w.xhat;
+        t.y = !last ? other() : final_ln ? nullptr : y;
+        t.ln2_g = p.ln2_gamma; t.ln2_b = p.ln2_beta; t.ln2_f = p.ln2_f_bits; t.ln2_c = p.ln2_c_shift;
+        t.proj = ivit::DenseW{p.w_proj, p.bias_proj, p.proj_rq_b, p.proj_rq_c};
+        t.fc1 = ivit::DenseW{p.w_fc1, p.bias_fc1, p.fc1_rq_b, p.fc1_rq_c};
+        t.fc2 = ivit::DenseW{p.w_fc2, p.bias_fc2, p.fc2_rq_b, p.fc2_rq_c};
+        t.res1 = dy(p.res1_rq); t.res2 = dy(p.res2_rq); t.gelu_p = sp(p.gelu); t.gelu_rq = dy(p.gelu_rq);
+        if (!last) {
+            next_qkv(t, blocks[l + 1]);
+        } else if (final_ln) {
+            t.next = 1; t.out = y;
+            t.ln1_g = final_ln->gamma; t.ln1_b = final_ln->beta; t.ln1_f = final_ln->f_bits; t.ln1_c = final_ln->c_shift;
+        }
+        if ((e = ivit::launch_token_block(s, t))) return e;
+        cur = t.y;
+    }
+    return hipSuccess;
+}
+
+hipError_t run_one(hipStream_t s, const int8_t* x, int8_t* y, const ivit_block_params* p, const ivit_dims* d, const Workspace& w,
+                   const ivit_debug_taps* taps) {
+    if ((int64_t)d->B * d->T == 0) return hipSuccess;
+    return taps ? run_block(s, x, y, p, d, w, taps) : run_blocks(s, x, y, p, 1, nullptr, d, w);
 }
 
 // Scratch of ivit_encoder_block_static: one array per GPU, allocated by the loader with the code object and held
@@ -344,7 +420,7 @@ int ivit_encoder_block(void* stream, const int8_t* x, int8_t* y, const ivit_bloc
     if (!aligned(workspace, 256) || !aligned(x, 16) || !aligned(y, 16)) return IVIT_ERR_ALIGN;
     Workspace w;
     carve(d, workspace, &w);
-    return hip_status(run_block(static_cast<hipStream_t>(stream), x, y, p, d, w, taps));
+    return hip_status(run_one(static_cast<hipStream_t>(stream), x, y, p, d, w, taps));
 }
 
 int ivit_encoder_block_static(void* stream, const int8_t* x, int8_t* y, const ivit_block_params* p, const ivit_dims* d,
@@ -362,7 +438,7 @@ int ivit_encoder_block_static(void* stream, const int8_t* x, int8_t* y, const iv
     // it, so what an earlier call left there never shows and nothing has to be cleared
     Workspace w;
     carve(d, base, &w);
-    return hip_status(run_block(static_cast<hipStream_t>(stream), x, y, p, d, w, taps));
+    return hip_status(run_one(static_cast<hipStream_t>(stream), x, y, p, d, w, taps));
 }
 
 int ivit_forward(void* stream, const int8_t* x, int8_t* y, const ivit_block_params* blocks, int32_t n_blocks,
@@ -386,20 +462,11 @@ int ivit_forward(void* stream, const int8_t* x, int8_t* y, const ivit_block_para
     carve(d, workspace, &w);
     const size_t n = (size_t)d->B * d->T * d->C;
     if (n == 0) return IVIT_OK;
-    // block l reads cur and writes into the other ping-pong buffer; the last producer writes y directly
-    const int8_t* cur = x;
-    for (int l = 0; l < n_blocks; ++l) {
-        const bool last = (l == n_blocks - 1) && !final_ln;
-        int8_t* dst = last ? y : (cur == w.act0 ? w.act1 : w.act0);
-        hipError_t e = run_block(s, cur, dst, &blocks[l], d, w, nullptr);
-        if (e != hipSuccess) return IVIT_ERR_HIP;
-        cur = dst;
-    }
+    if (n_blocks > 0) return hip_status(run_blocks(s, x, y, blocks, n_blocks, final_ln, d, w));
     if (final_ln)
-        return hip_status(ivit::launch_ilayernorm(s, cur, final_ln->gamma, final_ln->beta, y, (int64_t)d->B * d->T, d->C,
+        return hip_status(ivit::launch_ilayernorm(s, x, final_ln->gamma, final_ln->beta, y, (int64_t)d->B * d->T, d->C,
                                                   final_ln->f_bits, final_ln->c_shift));
-    if (n_blocks == 0) return hip_status(hipMemcpyAsync(y, x, n, hipMemcpyDeviceToDevice, s));
-    return IVIT_OK;
+    return hip_status(hipMemcpyAsync(y, x, n, hipMemcpyDeviceToDevice, s));
 }
 
 int ivit_embed_tokens(void* stream, const int8_t* patch_tok, const int8_t* cls, const int8_t* pos,

@@ -40,6 +40,24 @@ hipError_t launch_linear_ks(hipStream_t s, const LinearArgs& a);
 // Long rows, both operands streamed through LDS in 256 x 128 tiles (gemm_tl.hip).
 bool linear_tl_takes(const LinearArgs& a);
 hipError_t launch_linear_tl(hipStream_t s, const LinearArgs& a);
+
+// The token-wise part of an encoder block in one kernel (token_block.hip).
+struct DenseW { const int8_t* w; const int32_t* bias; const int32_t* rq_b; const int32_t* rq_c; };
+struct TokenBlockArgs {
+    const int8_t* o;                     // attention output [R, C]; nullptr: only the LN and the QKV layer below, on x
+    const int8_t* x;                     // block input [R, C]
+    int8_t* xhat; int8_t* y;             // scratch [R, C]; block output [R, C]
+    int8_t* out;                         // next == 1: LN output [R, C]; next == 2: qkv of the next block [R, 3 C]
+    int64_t R; int C, F;
+    int next;                            // what follows the block: 0 nothing, 1 an I-LayerNorm, 2 the next block's I-LayerNorm and QKV layer
+    const int32_t* ln2_g; const int32_t* ln2_b; int ln2_f, ln2_c;
+    const int32_t* ln1_g; const int32_t* ln1_b; int ln1_f, ln1_c;
+    DenseW proj, fc1, fc2, qkv_w;
+    Dyadic res1, res2; ShiftParams gelu_p; Dyadic gelu_rq;
+};
+bool token_block_takes(int C, int F, int64_t R);
+hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a);
+
 hipError_t launch_embed_tokens(hipStream_t s, const int8_t* patch_tok, const int8_t* cls, const int8_t* pos, Dyadic tok_rq,
                                Dyadic pos_rq, int8_t* tokens, int B, int P, int C);
 
@@ -62,7 +80,8 @@ int num_cus();
 
 // Kinds of launches reported by the trace (ivit_trace_end); values are part of the C ABI.
 enum LaunchKind { KIND_ILAYERNORM = 1, KIND_GEMM = 2, KIND_GEMM_RESIDUAL = 3, KIND_GEMM_GELU = 4,
-                  KIND_ATTENTION = 5, KIND_SHIFTMAX = 6, KIND_SHIFTGELU = 7, KIND_EMBED = 8, KIND_PATCH_MERGE = 9, KIND_MEAN_POOL = 10 };
+                  KIND_ATTENTION = 5, KIND_SHIFTMAX = 6, KIND_SHIFTGELU = 7, KIND_EMBED = 8, KIND_PATCH_MERGE = 9, KIND_MEAN_POOL = 10,
+                  KIND_TOKEN_BLOCK = 11 };
 
 // Brackets one kernel launch with two HIP events on its stream while a trace is active; otherwise a no-op.
 // ops = algorithmic integer operations (2 per int8 multiply-accumulate), bytes = algorithmic HBM bytes.

@@ -1,0 +1,920 @@
+// Everything of an encoder block that acts on single tokens, as one kernel (I-ViT, arXiv 2207.01405, Eq. 1-2 and 5 with
+// the dyadic pipeline of Sec. 3.2, ShiftGELU of Sec. 3.4 and I-LayerNorm of Sec. 3.5):
+//   xhat = Dense(o; proj) + x;  v = LN2(xhat);  y = Dense(ShiftGELU(Dense(v; fc1)); fc2) + xhat;
+//   then, for the block that follows, u = LN1'(y) and qkv' = Dense(u)   (or a final LN, or nothing).
+// Between two attentions a block is one launch instead of seven, and xhat, v, the hidden layer and u stay on the chip.
+//
+// A workgroup of four wavefronts (one per SIMD) takes M tokens through all layers.  Weights stream through two LDS
+// buffers in sets (128 to 192 rows of proj / fc1 / qkv, or 128 bytes of every row of fc2), each requested while its
+// predecessor is multiplied; every compute unit reads the same sets at about the same time, from its L2.  Activations
+// stand: those of proj, fc1 and qkv in registers as the "A" operand for all k-steps, the hidden layer in chunks of 128
+// channels in LDS, fc2's accumulators (M tokens x C channels) in registers through the whole MLP.  A lane holds one
+// channel and 16 tokens of a product, so requantisation constants are registers; results turn into token rows through
+// wavefront-private LDS with the transposing LDS read.  The LayerNorms work on the token tile in LDS.
+//
+// What bounds it is the rate at which one wavefront per SIMD issues instructions: a matrix instruction hides about six
+// others, and takes their time on top once there are more (measured: 1 + 6: 42 cycles, 1 + 8: 77).  So the results of a
+// channel tile are requantised between the products of the next one, spread evenly, and loads are three instructions.
+#include "regst_common.hpp"
+#include <algorithm>
+#include <type_traits>
+#include <utility>
+
+namespace ivit {
+
+namespace {
+
+using namespace regst;
+
+template <int N, class F> __device__ __forceinline__ void static_for(F&& f) {
+    [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }(std::make_integer_sequence<int, N>());
+}
+template <int I> using ic = std::integral_constant<int, I>;
+
+constexpr int FC = 128;                          // hidden channels per chunk of the MLP
+
+template <int C, int MT>
+struct TbLayout {
+    static constexpr int KS = C / 32, P = C / 16;                  // k-steps and 16-byte pieces of a row of C bytes
+    static constexpr int M = 32 * MT;                              // tokens of a workgroup
+    static constexpr int WNG = C / 96, WMG = 4 / WNG, TT = MT / WMG;      // wavefront grid of proj / fc2 / qkv, token tiles of a wavefront
+    static constexpr int WM1 = WNG == 4 ? (MT < 2 ? MT : 2) : WMG, WN1 = 4 / WM1;      // ... of fc1
+    static constexpr int T1 = MT / WM1, N1 = 4 / WN1;
+    static constexpr int PT = WNG == 4 ? 1 : 3;                    // channel tiles of a wavefront per weight set of proj / qkv
+    static constexpr int RS = PT * WNG * 32;                       // weight rows of such a set
+    static constexpr int NPROJ = C / RS, NQKV = 3 * C / RS;
+    static constexpr int G16 = (P & 15) == 0 ? 16 : (P & 7) == 0 ? 8 : (P & 3) == 0 ? 4 : (P & 1) == 0 ? 2 : 1;     // gcd(P, 16)
+    static constexpr int SETR = RS * C, SET1 = FC * C;             // bytes of a set of proj / qkv, of fc1 and fc2
+    static constexpr int SETW = SETR > SET1 ? SETR : SET1;
+    static constexpr int SETB = SETW + 3072;                       // weights, then rq_b, rq_c, bias of its rows (1 KB each)
+    static constexpr int HP = M + 16, HB = FC * HP;                // hidden chunk [channel][token]
+    static constexpr int LUT = 0, SET = 256;                       // the ShiftGELU table lies at address 0: an index is its address
+    static constexpr int ACT = SET + 2 * SETB;                     // token tile [row][C], or the two hidden chunks
+    static constexpr int ACTB = M * C > 2 * HB ? M * C : 2 * HB;
+    static constexpr int LN = ACT + ACTB;                          // gamma (2 KB), beta (2 KB)
+    static constexpr int STG = LN + 4096, STGB = 32 * 40;          // staging tile of a wavefront: [32 channels][40]
+    static constexpr int TOTAL = STG + 4 * STGB;
+    static_assert(C % 96 == 0 && 4 % WNG == 0 && MT % WMG == 0 && TT >= 1, "shape");
+    static_assert(C % RS == 0 && SETW >= M * C && (NPROJ == 1 || NPROJ == 3) && NQKV % 2 == 1, "sets");
+    static_assert(TOTAL <= 160 * 1024, "LDS");
+};
+
+// XOR applied to the piece number of row r of a tile of P 16-byte pieces per row, so that the same piece of 16 consecutive
+// rows meets every bank group once.
+template <int G16> __device__ __forceinline__ int swz(int r) { return (r / (16 / G16)) & (G16 - 1); }
+
+struct Rq { int32_t lo, hi, mb, ad; };
+
+// median of three as the pattern the compiler turns into one v_med3_i32
+__device__ __forceinline__ int32_t med3c(int32_t v, int32_t lo, int32_t hi) { return max(min(v, lo), min(max(v, lo), hi)); }
+template <class T> __device__ __forceinline__ void pin(T& v) { asm volatile("" : "+v"(v)); }      // keeps a value's computation in its place
+
+// Constants of the 24-bit requantisation of N channels of a lane (derivation in gemm_rs.hip), built in STEPS steps of a few
+// instructions each, which go between MFMAs.  The two bounds are divisions below 2^32 by b < 2^23 with quotients below
+// 2^23 (anything else takes the general form): a single-precision estimate, within a few of the quotient, and two repairs.
+template <int N>
+struct RqBuild {
+    static constexpr int STEPS = 9;
+    int32_t b[N], c[N], bias[N];
+    uint32_t n1[N], n2[N], q1[N], q2[N];
+    int32_t r1[N], r2[N];
+    float rb[N];
+    bool ok;
+    template <int S> __device__ __forceinline__ void step(const int32_t* cst, int stride, bool has_bias, uint32_t wlim, int sh24, bool may, Rq (&q)[N]) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if constexpr (S == 0) {
+                b[i] = cst[stride * i]; c[i] = cst[256 + stride * i]; bias[i] = cst[512 + stride * i];
+                if (i == 0) ok = may;
+            } else if constexpr (S == 1) {
+                rb[i] = __builtin_amdgcn_rcpf((float)b[i]);
+                if (!has_bias) bias[i] = 0;
+                pin(rb[i]);
+            } else if constexpr (S == 2) {
+                const uint32_t two_c = 1u << (c[i] & 31), half = two_c >> 1;
+                n1[i] = wlim * two_c - half + (uint32_t)b[i] - 1u;
+                n2[i] = (wlim - 1u) * two_c + half + (uint32_t)b[i];
+                pin(n1[i]); pin(n2[i]);
+            } else if constexpr (S == 3) {
+                q1[i] = (uint32_t)((float)n1[i] * rb[i]); q2[i] = (uint32_t)((float)n2[i] * rb[i]);
+                pin(q1[i]); pin(q2[i]);
+            } else if constexpr (S == 4) {
+                ok = ok && max(q1[i], q2[i]) < (1u << 23) && c[i] >= 1 && c[i] <= sh24 && b[i] >= 1 && b[i] < (1 << ((c[i] - 1) & 31));
+                r1[i] = (int32_t)(n1[i] - __umul24(q1[i], (uint32_t)b[i])); r2[i] = (int32_t)(n2[i] - __umul24(q2[i], (uint32_t)b[i]));
+                pin(r1[i]); pin(r2[i]);
+            } else if constexpr (S == 5) {
+                const int32_t t1 = (int32_t)__builtin_floorf((float)r1[i] * rb[i]), t2 = (int32_t)__builtin_floorf((float)r2[i] * rb[i]);
+                q1[i] += (uint32_t)t1; q2[i] += (uint32_t)t2;
+                r1[i] -= __mul24(t1, b[i]); r2[i] -= __mul24(t2, b[i]);
+                pin(r1[i]); pin(r2[i]);
+            } else if constexpr (S == 6) {
+                q1[i] += (r1[i] >= b[i]); q1[i] -= (r1[i] < 0);
+                q2[i] += (r2[i] >= b[i]); q2[i] -= (r2[i] < 0);
+                pin(q1[i]); pin(q2[i]);
+            } else if constexpr (S == 7) {
+                q[i].lo = (int32_t)(0u - q2[i] - (uint32_t)bias[i]); q[i].hi = (int32_t)(q1[i] - (uint32_t)bias[i]);
+                ok = ok && bias[i] > -(1 << 24) && bias[i] < (1 << 24) && q[i].lo >= -(1 << 23) && q[i].hi < (1 << 23);
+                pin(q[i].lo); pin(q[i].hi);
+            } else {
+                const int sh = (sh24 - c[i]) & 31;
+                q[i].mb = b[i] << sh;
+                q[i].ad = (int32_t)(((uint32_t)bias[i] * (uint32_t)b[i] + (1u << ((c[i] - 1) & 31))) << sh);
+                pin(q[i].mb); pin(q[i].ad);
+            }
+        }
+    }
+    // whether every channel of the wavefront takes the 24-bit form; if not, q gets the raw parameters instead
+    __device__ __forceinline__ bool finish(Rq (&q)[N]) {
+        if (__builtin_amdgcn_ballot_w64(ok) == ~0ull) return true;
+#pragma unroll
+        for (int i = 0; i < N; ++i) { q[i].lo = b[i]; q[i].hi = c[i]; q[i].mb = bias[i]; }
+        return false;
+    }
+};
+
+// Constants of a channel of a residual layer: its first term is bits c .. c + 31 of acc b + h, h = bias b + 2^(c-1).
+struct Rq64 { int32_t b, c; int64_t h; };
+__device__ __forceinline__ bool make_rq64(Rq64& q, int32_t b, int32_t c, int32_t bias) {
+    q.b = b; q.c = c; q.h = (int64_t)bias * b + (int64_t)(1u << ((c - 1) & 31));
+    return dyadic_fits32(b, c);
+}
+
+// v_mfma_i32_32x32x32_i8 with the register file of the accumulators (ACCA) and of the first operand (AA) chosen: the
+// kernel needs both files filled, and what vector instructions read must not sit in the accumulation registers.  The
+// compiler sees no matrix instruction here, so its results are read by others only after three more of them (or settle()).
+template <bool ACCA, bool AA> __device__ __forceinline__ void mfma(v16i& acc, const v4i& a, const v4i& b) {
+    if constexpr (ACCA && AA) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+a"(acc) : "a"(a), "v"(b));
+    else if constexpr (ACCA) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+    else if constexpr (AA) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(acc) : "a"(a), "v"(b));
+    else asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+template <bool AA> __device__ __forceinline__ void mfma_first(v16i& acc, const v4i& a, const v4i& b) {      // ... on a zero accumulator
+    if constexpr (AA) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0" : "=&v"(acc) : "a"(a), "v"(b));
+    else asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+}
+
+template <int C, int MT>
+__global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
+    using LY = TbLayout<C, MT>;
+    constexpr int KS = LY::KS, PP = LY::P, M = LY::M, TT = LY::TT, T1 = LY::T1, N1 = LY::N1, PT = LY::PT, RS = LY::RS;
+    constexpr int WNG = LY::WNG, WN1 = LY::WN1, G16 = LY::G16, SETW = LY::SETW, HP = LY::HP;
+    constexpr int NX = G16 / 2 > 0 ? G16 / 2 : 1;
+    constexpr int LPR = PP / 3;                                    // lanes of a row in the LayerNorm passes, three pieces each
+    constexpr int RD = KS == 12 ? 4 : 3;                           // ring of weight fragments: requested RD - 1 k-steps ahead
+    static_assert((KS % RD) == 0 || ((PT * KS) % RD == 0 && (N1 * KS) % RD == 0), "the ring must align with a set");
+
+    extern __shared__ __align__(1024) int8_t lds[];
+    int8_t* act = lds + LY::ACT;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wv % WNG, wm = wv / WNG, wn1 = wv % WN1, wm1 = wv / WN1;
+    const int lj = lane & 31, lg = lane >> 5, lb = lane >> 4;
+    int8_t* stg = lds + LY::STG + wv * LY::STGB;
+    const int64_t m0 = (int64_t)blockIdx.x * M;
+    const int rows = __builtin_amdgcn_readfirstlane((int)min64(P.R - m0, M));
+    const int F = P.F, NC = F / FC;
+    const uint32_t lds0 = lds_offset(lds);
+    const bool front = P.o != nullptr;
+    auto set_at = [&](int b) __attribute__((always_inline)) -> int8_t* { return lds + LY::SET + b * LY::SETB; };
+
+    auto sync = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    auto sync_lds = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    auto settle = []() __attribute__((always_inline)) {             // the matrix instructions issued so far have written their results
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // ---- loads into LDS.  A set of rows (proj, fc1, qkv) is contiguous in memory, a set of fc2 is 128 bytes of every row,
+    // a token tile has its rows permuted (LDS row i holds token 32 (i / 32) + token_of_row(i % 32)).  Load instruction
+    // n = 4 i + wavefront covers 16-byte slots 64 n .. 64 n + 63; what differs from piece i to i + 3 is a constant step.
+    uint32_t vr[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int s = 64 * (4 * i + wv) + lane, r = s / PP, p = s % PP;
+        vr[i] = (uint32_t)(r * C + 16 * (p ^ swz<G16>(r)));
+    }
+    const int r2 = 8 * wv + (lane >> 3);
+    const uint32_t v2 = (uint32_t)(r2 * F + 16 * ((lane & 7) ^ swz<8>(r2)));
+    auto buffer = [](const int8_t* p, uint32_t bytes) __attribute__((always_inline)) -> v4i {
+        const uint64_t a = (uint64_t)uniform_ptr(p);
+        return v4i{(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)bytes, 0x00020000};
+    };
+    struct Load { v4i rsrc; uint32_t so, d1, d3, v[3], dst; const int8_t* cst; };      // offset so far, its steps, per-lane offsets
+    auto load_rows = [&](const DenseW& W, int row0, int b) __attribute__((always_inline)) -> Load {
+        const int32_t* src = wv == 0 ? W.rq_b : wv == 1 || !W.bias ? W.rq_c : W.bias;
+        return Load{buffer(W.w + (int64_t)row0 * C, 0x7fffffffu), 0u - 12288u, 0, 12288, {vr[0], vr[1], vr[2]},
+                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + LY::SET + b * LY::SETB + wv * 1024)),
+                    uniform_ptr(reinterpret_cast<const int8_t*>(src + row0))};
+    };
+    auto load_f2 = [&](int chunk, int b) __attribute__((always_inline)) -> Load {
+        return Load{buffer(P.fc2.w + (int64_t)chunk * FC, 0x7fffffffu), 0u - 32u * (uint32_t)F, 32u * (uint32_t)F, 32u * (uint32_t)F, {v2, v2, v2},
+                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + LY::SET + b * LY::SETB + wv * 1024)), uniform_ptr(P.fc2.w)};
+    };
+    // piece i of a set of `bytes`; the last piece brings rq_b, rq_c and bias of the set's rows (wavefronts 0, 1 and 2; there
+    // is no such piece in a set of fc2, which fetches some bytes that nobody reads instead, so that nothing branches here)
+    auto load_piece = [&](Load& l, auto i_c, auto bytes_c) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_c)::value, NI = decltype(bytes_c)::value / 1024, NP = (NI + 3) / 4, nr = decltype(bytes_c)::value / C;
+        if constexpr (i < NP) {
+            // (the addition between the write of m0 and the load is the wait state that pair needs)
+            if (4 * i + 3 < NI || 4 * i + wv < NI)
+                asm volatile("s_add_u32 m0, %1, %5\n\ts_add_u32 %0, %0, %2\n\tbuffer_load_dwordx4 %3, %4, %0 offen lds"
+                             : "+s"(l.so) : "s"(l.dst), "s"(i % 3 == 0 ? l.d3 : l.d1), "v"(l.v[i % 3]), "s"(l.rsrc), "i"(i * 4096) : "memory", "m0", "scc");
+        } else {
+            dma16(l.cst, (uint32_t)(16 * min(lane, nr / 4 - 1)), l.dst + SETW - (wv == 3 ? 1024 : 0));      // (3 repeats 2)
+        }
+    };
+    auto load_range = [&](Load& l, auto lo_c, auto hi_c, auto bytes_c) __attribute__((always_inline)) {
+        static_for<decltype(hi_c)::value - decltype(lo_c)::value>([&](auto i) __attribute__((always_inline)) {
+            load_piece(l, ic<decltype(lo_c)::value + decltype(i)::value>(), bytes_c);
+        });
+    };
+    using BR = ic<LY::SETR>; using B1 = ic<LY::SET1>;
+    constexpr int NPR = (LY::SETR / 1024 + 3) / 4 + 1, NP1 = (LY::SET1 / 1024 + 3) / 4 + 1;      // pieces of a set
+    // a token tile: rows past the matrix read as zero (the buffer ends there)
+    constexpr int NPA = (M * PP / 64 + 3) / 4;
+    auto act_piece = [&](const v4i& rsrc, uint32_t dst, auto i_c) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_c)::value, NI = M * PP / 64;
+        const int s = 64 * (4 * (i % 3) + wv) + lane, r = s / PP, p = s % PP;
+        const uint32_t v = (uint32_t)(((r & ~31) + token_of_row(r & 31)) * C + 16 * (p ^ swz<G16>(r)));
+        if (4 * i + 3 < NI || 4 * i + wv < NI)
+            asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                         : : "s"(dst), "v"(v + (i / 3) * 12288), "s"(rsrc), "i"(i * 4096) : "memory", "m0", "scc");
+    };
+    auto tile_buffer = [&](const int8_t* src) __attribute__((always_inline)) -> v4i { return buffer(src + m0 * C, (uint32_t)(rows * C)); };
+    auto tile_dst = [&](int off) __attribute__((always_inline)) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + off + wv * 1024)); };
+    auto load_act = [&](const int8_t* src, int off) __attribute__((always_inline)) {
+        const v4i r = tile_buffer(src);
+        const uint32_t dst = tile_dst(off);
+        static_for<NPA>([&](auto i) __attribute__((always_inline)) { act_piece(r, dst, i); });
+    };
+    auto load_ln = [&](const int32_t* g, const int32_t* b) __attribute__((always_inline)) {
+        const int32_t* src = wv < 2 ? g : b;
+        const int at = (wv & 1) * 256 + 4 * lane;
+        if ((wv & 1) * 256 < C)
+            dma16(uniform_ptr(reinterpret_cast<const int8_t*>(src)), (uint32_t)(4 * min(at, C - 4)), lds0 + LY::LN + (wv >> 1) * 2048 + (wv & 1) * 1024);
+    };
+
+    // ---- fragments.  Lane (lj, lg) of k-step ks: piece 2 ks + lg of row lj of a tile.
+    int xr[NX];                                                     // tiles of rows of C bytes
+#pragma unroll
+    for (int i = 0; i < NX; ++i) xr[i] = lj * C + 16 * ((2 * i + lg) ^ swz<G16>(lj));
+    auto frag = [&](const int8_t* tile, int ks) __attribute__((always_inline)) -> v4i {
+        return *reinterpret_cast<const v4i*>(tile + xr[ks % NX] + 16 * G16 * (ks / NX));
+    };
+    int x2[4];                                                      // tiles of rows of 128 bytes
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x2[i] = lj * FC + 16 * ((2 * i + lg) ^ swz<8>(lj));
+
+    // ---- residual and staging addresses (see gemm_rs.hip for the transposing reads)
+    const int jb = (lane & 15) >> 1, jo = lane & 1;                 // source side of a transposing read
+    const int dj = lane & 7, d_o = (lane >> 3) & 1;                 // destination side
+    const int res_row_p = 8 * (jb >> 2) + 4 * lg + (jb & 3);        // + 16 h: row of the token of result 8 h + jb, A rows in permuted order
+    const int res_row_i = 16 * (jb >> 2) + 8 * lg + (jb & 3);       // + 4 h: ... A rows in natural order
+    const int out_row = 16 * (lb & 1) + 8 * (dj >> 2) + 4 * (lb >> 1) + (dj & 3);      // row of token 8 lb + dj
+    const int out_xor = swz<G16>(out_row);
+    auto res_read = [&](const int8_t* tile, int ct, auto perm_c, v2i (&rw)[2]) __attribute__((always_inline)) {
+        constexpr bool perm = decltype(perm_c)::value;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int r = perm ? res_row_p + 16 * h : res_row_i + 4 * h;
+            const int8_t* a = tile + r * C + 16 * ((2 * ct + (lb & 1)) ^ swz<G16>(r)) + 8 * jo;
+            rw[h] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3)))*)(a));
+        }
+    };
+    const int stg_src = (16 * jo + jb) * 40 + 8 * lb;
+    auto stg_put = [&](const v4i& w, auto perm_c) __attribute__((always_inline)) {
+        constexpr bool perm = decltype(perm_c)::value;
+        if (perm) {
+            v2i* d = reinterpret_cast<v2i*>(stg + lj * 40 + 16 * lg);
+            d[0] = v2i{w[0], w[1]}; d[1] = v2i{w[2], w[3]};
+        } else {
+            int* d = reinterpret_cast<int*>(stg + lj * 40 + 4 * lg);
+            d[0] = w[0]; d[2] = w[1]; d[4] = w[2]; d[6] = w[3];
+        }
+    };
+    auto stg_get = [&]() __attribute__((always_inline)) -> v4i {
+        const v2i a = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3)))*)(stg + stg_src));
+        const v2i b = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3)))*)(stg + stg_src + 8 * 40));
+        return v4i{a[0], a[1], b[0], b[1]};
+    };
+    auto act_put = [&](int tt, int ct, const v4i& w) __attribute__((always_inline)) {      // results of (token tile, channel tile) into the token tile
+        *reinterpret_cast<v4i*>(act + (32 * tt + out_row) * C + 16 * ((2 * ct + d_o) ^ out_xor)) = w;
+    };
+
+    struct ResRq { int32_t b, c, h; bool ok; };
+    auto make_res = [](Dyadic d) __attribute__((always_inline)) -> ResRq {
+        return ResRq{d.b, d.c, 1 << ((d.c - 1) & 31), d.b >= 1 && d.b < (1 << 23) && d.c >= 1 && d.c <= 30};
+    };
+    auto pack4 = [](const uint32_t (&o)[4], auto low_c) __attribute__((always_inline)) -> int {
+        constexpr bool low = decltype(low_c)::value;
+        const uint32_t p01 = __builtin_amdgcn_perm(o[1], o[0], low ? 0x0c0c0400u : 0x0c0c0703u);
+        const uint32_t p23 = __builtin_amdgcn_perm(o[3], o[2], low ? 0x04000c0cu : 0x07030c0cu);
+        return (int)(p01 | p23);
+    };
+    // one result, 24-bit form
+    auto out_top = [](int32_t a, const Rq& q) __attribute__((always_inline)) -> uint32_t { return (uint32_t)(__mul24(med3c(a, q.lo, q.hi), q.mb) + q.ad); };
+    // one result of a residual layer: one 64-bit multiply-add, a funnel shift, the residual term, the sum limited
+    auto out_res = [](int32_t a, const Rq64& q, const ResRq& rr, int32_t res) __attribute__((always_inline)) -> uint32_t {
+        const int64_t p = (int64_t)a * q.b + q.h;
+        const int32_t t1 = (int32_t)__builtin_amdgcn_alignbit((uint32_t)(p >> 32), (uint32_t)p, q.c);
+        return (uint32_t)clamp8(t1 + ((__mul24(res, rr.b) + rr.h) >> rr.c));
+    };
+    // a lane's 16 results of a tile in 64-bit arithmetic (q holds b, c, bias); results in the low byte
+    auto unit_slow = [&](const v16i& a, const Rq& q, bool gelu) __attribute__((always_inline)) -> v4i {
+        v4i w;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            uint32_t o[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                o[r] = (uint32_t)clamp8_64(rnd_shift64(a[4 * d + r] + q.mb, q.lo, q.hi));
+                if (gelu) o[r] = (uint32_t)(uint8_t)lds[LY::LUT + (o[r] & 0xffu)];
+            }
+            w[d] = pack4(o, std::true_type());
+        }
+        return w;
+    };
+    // ... of a residual layer; the residual rows come from global memory
+    auto unit_slow_res = [&](const v16i& a, const DenseW& W, const ResRq& rr, const int8_t* res, int tt, int ct, auto perm_c) __attribute__((always_inline)) -> v4i {
+        constexpr bool perm = decltype(perm_c)::value;
+        const int ch = 32 * ct + lj;
+        const int32_t b = W.rq_b[ch], c = W.rq_c[ch], bias = W.bias ? W.bias[ch] : 0;
+        v4i w;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            uint32_t o[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int tok = min(32 * tt + (perm ? 16 * lg + 4 * d : 8 * d + 4 * lg) + r, rows - 1);
+                o[r] = (uint32_t)clamp8_64(rnd_shift64(a[4 * d + r] + bias, b, c) + rnd_shift64(res[(m0 + tok) * C + ch], rr.b, rr.c));
+            }
+            w[d] = pack4(o, std::true_type());
+        }
+        return w;
+    };
+
+    // ---- I-LayerNorm of the token tile, in place; `st`: the rows before normalisation also go to global memory, `dst`:
+    // the normalised ones do
+    auto layernorm = [&](int f_bits, int c_shift, int8_t* st, int8_t* dst) __attribute__((always_inline)) {
+        const int q = lane % LPR, rl = lane / LPR;
+        constexpr int RPP = 64 / LPR, RW = M / 4;                   // rows per pass, rows of a wavefront
+        int32_t g[48], b[48];
+        const int32_t* gt = reinterpret_cast<const int32_t*>(lds + LY::LN);
+        const int32_t half = 1 << (c_shift - 1);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const v4i gv = *reinterpret_cast<const v4i*>(gt + 16 * (q + LPR * j) + 4 * e);
+                const v4i bv = *reinterpret_cast<const v4i*>(gt + 512 + 16 * (q + LPR * j) + 4 * e);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) { g[16 * j + 4 * e + r] = gv[r]; b[16 * j + 4 * e + r] = (int32_t)((uint32_t)bv[r] + (uint32_t)half); }
+            }
+        const __amdgpu_buffer_rsrc_t sb = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(st + m0 * C)), 0, st ? rows * C : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t db = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(dst + m0 * C)), 0, dst ? rows * C : 0, 0x00020000);
+        constexpr int NPASS = RW / RPP;
+        static_assert(RW % RPP == 0 && NPASS <= LPR, "rows of a wavefront");
+        v4i v[NPASS][3];
+        int32_t sm[NPASS], sq[NPASS];
+        const int i0 = wv * RW + rl;                                // row of pass k: i0 + k RPP
+#pragma unroll
+        for (int k = 0; k < NPASS; ++k) {
+            const int i = i0 + k * RPP;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) v[k][j] = *reinterpret_cast<const v4i*>(act + i * C + 16 * ((q + LPR * j) ^ swz<G16>(i)));
+        }
+#pragma unroll
+        for (int k = 0; k < NPASS; ++k) {
+            const int i = i0 + k * RPP, tok = (i & ~31) + token_of_row(i & 31);
+            int32_t s = 0, ss = 0;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                if (st) __builtin_amdgcn_raw_buffer_store_b128(v[k][j], sb, tok * C + 16 * (q + LPR * j), 0, 0);
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    s = __builtin_amdgcn_sdot4(v[k][j][d], 0x01010101, s, false);
+                    ss = __builtin_amdgcn_sdot4(v[k][j][d], v[k][j][d], ss, false);
+                }
+            }
+            s += dpp_i32<0xB1>(s); ss += dpp_i32<0xB1>(ss);
+            if (LPR >= 4) { s += dpp_i32<0x4E>(s); ss += dpp_i32<0x4E>(ss); }
+            if (LPR >= 8) { s += dpp_i32<0x141>(s); ss += dpp_i32<0x141>(ss); }
+            sm[k] = s; sq[k] = ss;
+        }
+        // the scalar chain of a row once: lane q of a row's lanes takes pass q
+        int32_t s = sm[0], ss = sq[0];
+#pragma unroll
+        for (int k = 1; k < NPASS; ++k) { s = q == k ? sm[k] : s; ss = q == k ? sq[k] : ss; }
+        const int32_t mean = floordiv_small(s + (C >> 1), C);
+        const uint32_t var = div_small_quotient((uint32_t)(ss - 2 * mean * s + C * mean * mean), (uint32_t)C);
+        const int32_t f = (int32_t)div_small(1u << f_bits, max(isqrt10(var), 1u));
+#pragma unroll
+        for (int k = 0; k < NPASS; ++k) {
+            const int i = i0 + k * RPP, tok = (i & ~31) + token_of_row(i & 31);
+            const int from = 4 * ((lane & ~(LPR - 1)) + k);
+            const int32_t mk = __builtin_amdgcn_ds_bpermute(from, mean), fk = __builtin_amdgcn_ds_bpermute(from, f);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                v4i w;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    uint32_t o[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int32_t xe = (int32_t)(int8_t)((uint32_t)v[k][j][d] >> (8 * r));
+                        const int32_t dg = mul_i24(xe - mk, g[16 * j + 4 * d + r]);
+                        o[r] = (uint32_t)clamp8((__mul24(dg, fk) + b[16 * j + 4 * d + r]) >> c_shift);
+                    }
+                    w[d] = pack4(o, std::true_type());
+                }
+                if (dst) __builtin_amdgcn_raw_buffer_store_b128(w, db, tok * C + 16 * (q + LPR * j), 0, 0);
+                *reinterpret_cast<v4i*>(act + i * C + 16 * ((q + LPR * j) ^ swz<G16>(i))) = w;
+            }
+        }
+    };
+
+    // ---- products.  A stream of channel tiles of C bytes a row: tile p at w0 + p stride, its k-steps one after the other,
+    // NT products a step: mm(p, t, ks) issues one, aux(m) is the work that goes with product m.  The first RD - 1 fragments
+    // are in the ring already.  TAIL: before the last RD - 1 steps, when every fragment of the set is in registers, tail()
+    // meets the other wavefronts, after which the next set is there and this one's memory is free; next(k) then requests
+    // the first fragments of the next set between the remaining products.
+    v4i bf[RD];
+    auto stream = [&](auto nb_c, auto nt_c, const int8_t* w0, auto stride_c, auto tail_c, auto mm, auto aux, auto tail, auto next) __attribute__((always_inline)) {
+        constexpr int NB = decltype(nb_c)::value, NT = decltype(nt_c)::value, stride = decltype(stride_c)::value, NS = NB * KS;
+        static_for<NS>([&](auto q_c) __attribute__((always_inline)) {
+            constexpr int q = decltype(q_c)::value, qn = q + RD - 1;
+            if constexpr (decltype(tail_c)::value && q == NS - RD + 1) tail();
+            if constexpr (qn < NS) bf[qn % RD] = frag(w0 + (qn / KS) * stride, qn % KS);
+            else if constexpr (decltype(tail_c)::value) next(ic<qn - NS>());
+            static_for<NT>([&](auto t_c) __attribute__((always_inline)) {
+                mm(ic<q / KS>(), t_c, ic<q % KS>(), bf[q % RD]);
+                aux(ic<q * NT + decltype(t_c)::value>());
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+    };
+    auto first_frags = [&](const int8_t* w0) __attribute__((always_inline)) {
+        static_for<RD - 1>([&](auto k) __attribute__((always_inline)) { bf[k] = frag(w0, k); });
+    };
+    // `n` pieces of work (numbered from lo) spread over the products from .. to - 1
+    auto spread = [&](auto lo_c, auto n_c, auto from_c, auto to_c, auto m_c, auto f) __attribute__((always_inline)) {
+        constexpr int n = decltype(n_c)::value, from = decltype(from_c)::value, to = decltype(to_c)::value, m = decltype(m_c)::value, w = to - from;
+        static_assert(w > 0, "somewhere to go");
+        if constexpr (m >= from && m < to) {
+            constexpr int lo = (m - from) * n / w, hi = (m - from + 1) * n / w;
+            static_for<hi - lo>([&](auto i) __attribute__((always_inline)) { f(ic<decltype(lo_c)::value + lo + decltype(i)::value>()); });
+        }
+    };
+
+    v4i ar[TT][KS];                                                 // this wavefront's activations in proj and qkv
+    auto load_ar = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                ar[t][ks] = frag(act + 32 * (wm * TT + t) * C, ks);
+                asm volatile("" : "+a"(ar[t][ks]));
+            }
+    };
+
+    // ---- proj and qkv: tile g of a wavefront goes to accumulators g % 2 and is requantised while tile g + 1 is multiplied
+    constexpr int NMT = KS * TT, NOT = TT * 16;                     // products and results of a lane per tile
+    constexpr int EF = NMT > 3 ? 3 : NMT - 1;                       // first product after which the previous tile's results can be read
+    v16i pa[2][TT];
+    uint32_t eo[4];
+    v4i ew = {}, es = {};
+    v2i rw[2] = {}, rwn[2] = {};
+    bool fast = false;
+    const int32_t* const cst0 = reinterpret_cast<const int32_t*>(set_at(0) + SETW);
+    const int32_t* const cst1 = reinterpret_cast<const int32_t*>(set_at(1) + SETW);
+
+    if (front) {
+        Load L0 = load_rows(P.proj, 0, 0), L1 = LY::NPROJ > 1 ? load_rows(P.proj, RS, 1) : load_rows(P.fc1, 0, 1);
+        load_act(P.o, LY::ACT);
+        load_ln(P.ln2_g, P.ln2_b);
+        load_range(L0, ic<0>(), ic<NPR>(), BR());
+        if constexpr (LY::NPROJ > 1) load_range(L1, ic<0>(), ic<NPR>(), BR()); else load_range(L1, ic<0>(), ic<NP1>(), B1());
+        lds[LY::LUT + tid] = (int8_t)requant64(shiftgelu_raw((int32_t)(int8_t)tid, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c);
+        const ResRq rr1 = make_res(P.res1);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(LY::NPROJ > 1 && LY::SETR % 4096 == 0 ? NPR : 0) : "memory");
+        load_ar();
+        first_frags(set_at(0) + wn * 32 * C);
+        sync_lds();
+        load_act(P.x, LY::ACT);
+        // ---- proj.  Sets 0 .. NPROJ - 1, then fc1's first two, alternate between the two buffers.
+        Rq64 pq = {}, pqn = {};
+        auto ct_of = [&](int g) __attribute__((always_inline)) -> int { return g * WNG + wn; };        // channel tile of tile g
+        auto proj_res = [&](int g, int t) __attribute__((always_inline)) { res_read(act + 32 * (wm * TT + t) * C, ct_of(g), std::true_type(), rwn); };
+        auto proj_out = [&](int g, auto par_c, auto i_c) __attribute__((always_inline)) {      // piece i of tile g: 16 TT results, then its last rows
+            constexpr int i = decltype(i_c)::value, t = i / 16, e = i % 16, par = decltype(par_c)::value;
+            if constexpr (i == NOT) { es = stg_get(); return; }
+            else if constexpr (i == NOT + 1) { act_put(wm * TT + TT - 1, ct_of(g), es); return; }
+            else {
+                if constexpr (e == 0) { rw[0] = rwn[0]; rw[1] = rwn[1]; }
+                eo[e & 3] = out_res(pa[par][t][e], pq, rr1, (int32_t)(int8_t)((uint32_t)rw[e >> 3][(e >> 2) & 1] >> (8 * (e & 3))));
+                if constexpr ((e & 3) == 3) { int w = pack4(eo, std::true_type()); pin(w); ew[e >> 2] = w; }
+                if constexpr (e == 8 && t + 1 < TT) proj_res(g, t + 1);
+                if constexpr (e == 3 && t > 0) es = stg_get();
+                if constexpr (e == 11 && t > 0) act_put(wm * TT + t - 1, ct_of(g), es);
+                if constexpr (e == 15) stg_put(ew, std::true_type());
+            }
+        };
+        auto proj_slow = [&](int g, auto par_c) __attribute__((always_inline)) {
+            if (fast) return;
+            static_for<TT>([&](auto t_c) __attribute__((always_inline)) {
+                constexpr int t = decltype(t_c)::value;
+                stg_put(unit_slow_res(pa[decltype(par_c)::value][t], P.proj, rr1, P.x, wm * TT + t, ct_of(g), std::true_type()), std::true_type());
+                act_put(wm * TT + t, ct_of(g), stg_get());
+            });
+        };
+        bool ok64 = true;
+        static_for<LY::NPROJ>([&](auto s_c) __attribute__((always_inline)) {
+            constexpr int s = decltype(s_c)::value, b = s & 1;
+            constexpr bool last = s + 1 == LY::NPROJ;
+            const int32_t* cst = (b ? cst1 : cst0) + wn * 32 + lj;
+            Load L = s >= 1 ? (last ? load_rows(P.fc1, 0, b ^ 1) : load_rows(P.proj, (s + 1) * RS, b ^ 1)) : Load{};
+            stream(ic<PT>(), ic<TT>(), set_at(b) + wn * 32 * C, ic<WNG * 32 * C>(), std::bool_constant<!last>(),
+                [&](auto p_c, auto t_c, auto ks_c, const v4i& f) __attribute__((always_inline)) {
+                    constexpr int par = (s * PT + decltype(p_c)::value) & 1, t = decltype(t_c)::value, ks = decltype(ks_c)::value;
+                    if constexpr (ks == 0) mfma_first<true>(pa[par][t], ar[t][ks], f); else mfma<false, true>(pa[par][t], ar[t][ks], f);
+                },
+                [&](auto m_c) __attribute__((always_inline)) {
+                    constexpr int m = decltype(m_c)::value, p = m / NMT, mt = m % NMT, g = s * PT + p;
+                    if constexpr (s >= 1) spread(ic<0>(), ic<NPR>(), ic<0>(), ic<PT * NMT * 3 / 4>(), m_c, [&](auto i) __attribute__((always_inline)) { load_piece(L, i, BR()); });
+                    if constexpr (LY::NPROJ == 1 && g == 1 && mt == 0) sync();       // the residual rows are there
+                    if constexpr (g > 0) {
+                        if constexpr (mt == 0) proj_res(g - 1, 0);
+                        spread(ic<0>(), ic<NOT + 2>(), ic<EF>(), ic<NMT>(), ic<mt>(), [&](auto i) __attribute__((always_inline)) { proj_out(g - 1, ic<(g - 1) & 1>(), i); });
+                        if constexpr (mt == NMT - 1) proj_slow(g - 1, ic<(g - 1) & 1>());
+                    }
+                    if constexpr (mt == 0) {
+                        const int at = p * WNG * 32;
+                        ok64 = make_rq64(pqn, cst[at], cst[256 + at], P.proj.bias ? cst[512 + at] : 0) && rr1.ok;
+                    }
+                    if constexpr (mt == NMT - 1) { pq = pqn; fast = __builtin_amdgcn_ballot_w64(ok64) == ~0ull; }
+                },
+                [&]() __attribute__((always_inline)) { sync(); },
+                [&](auto k) __attribute__((always_inline)) { bf[k] = frag(set_at(b ^ 1) + wn * 32 * C, k); });
+        });
+        {
+            constexpr int g = LY::NPROJ * PT - 1;
+            proj_res(g, 0);
+            settle();
+            static_for<NOT + 2>([&](auto i) __attribute__((always_inline)) { proj_out(g, ic<g & 1>(), i); });
+            proj_slow(g, ic<g & 1>());
+        }
+        sync_lds();
+        // ---- LN2
+        Load L = load_rows(P.fc1, FC, 0);
+        load_range(L, ic<0>(), ic<NP1>(), B1());
+        layernorm(P.ln2_f, P.ln2_c, P.xhat, nullptr);
+        sync();
+        if (P.next) load_ln(P.ln1_g, P.ln1_b);
+        // ---- MLP.  Sets: F1(0), F1(1), F2(0), F1(2), F2(1), ..., F1(NC - 1), F2(NC - 2), F2(NC - 1), the rows of xhat; F1(0) is in
+        // buffer 1, from then on F1 sets are in buffer 0, F2 sets in buffer 1 (the last one, having no F1 set after its
+        // predecessor, in buffer 0).  Results of fc1: channel tile n is requantised while tile n + 1 is multiplied, the last
+        // one during the next F2.
+        constexpr int NM1 = KS * T1, NO1 = T1 * 16, NM2 = 12 * TT, LAG = 8;
+        constexpr int EF1 = NM1 > 3 ? 3 : NM1 - 1;
+        constexpr int TP = NP1 / 3;                                 // pieces of a set requested before the end of the set before its predecessor
+        constexpr auto vv_acc = [](int t, int ks) constexpr { return 3 * TT * 16 + 4 * (t * KS + ks + 1) <= 256; };      // fits beside fc2's accumulators
+        v4i vv[T1][KS];
+        static_for<T1>([&](auto t) __attribute__((always_inline)) {
+            static_for<KS>([&](auto ks) __attribute__((always_inline)) {
+                vv[t][ks] = frag(act + 32 * (wm1 * T1 + decltype(t)::value) * C, ks);
+                if constexpr (vv_acc(decltype(t)::value, decltype(ks)::value)) asm volatile("" : "+a"(vv[t][ks]));
+            });
+        });
+        v16i acc[3][TT], ha[N1][T1];
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int t = 0; t < TT; ++t) { acc[j][t] = v16i{}; asm volatile("" : "+a"(acc[j][t])); }
+        const int8_t* f1w0 = set_at(0) + wn1 * N1 * 32 * C;
+        const int8_t* f1w1 = set_at(1) + wn1 * N1 * 32 * C;
+        first_frags(f1w1);
+        sync_lds();
+        // requantisation constants: with two tiles or more, a lane builds those of one channel of a pair of tiles and the
+        // two halves of the wavefront exchange them
+        constexpr int NBLD = (N1 + 1) / 2;
+        Rq hq[2 * NBLD], hb_q[NBLD];
+        RqBuild<NBLD> hb;
+        bool hfast = false;
+        auto consts_step = [&](const int32_t* cst, auto k_c) __attribute__((always_inline)) {
+            constexpr int k = decltype(k_c)::value;
+            if constexpr (k < RqBuild<NBLD>::STEPS) {
+                hb.template step<k>(cst + wn1 * N1 * 32 + (N1 > 1 ? lane : lj), 64, P.fc1.bias != nullptr, 127, 24, true, hb_q);
+            } else {
+                hfast = hb.finish(hb_q);
+#pragma unroll
+                for (int i = 0; i < NBLD; ++i) {
+                    auto both = [&](int32_t v, int32_t& a, int32_t& b) __attribute__((always_inline)) {
+                        if (N1 == 1) { a = v; return; }
+                        const auto s = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+                        a = (int32_t)s[0]; b = (int32_t)s[1];
+                    };
+                    both(hb_q[i].lo, hq[2 * i].lo, hq[2 * i + 1].lo); both(hb_q[i].hi, hq[2 * i].hi, hq[2 * i + 1].hi);
+                    both(hb_q[i].mb, hq[2 * i].mb, hq[2 * i + 1].mb); both(hb_q[i].ad, hq[2 * i].ad, hq[2 * i + 1].ad);
+                }
+            }
+        };
+        uint32_t gl[LAG + 4];
+        auto h_at = [&](int hbuf, int u) __attribute__((always_inline)) -> int8_t* {
+            return act + hbuf * LY::HB + ((wn1 * N1 + u / T1) * 32 + lj) * HP + 32 * (wm1 * T1 + u % T1) + 16 * lg;
+        };
+        // piece i of a channel tile's results, or of the last ones' packing; u0: first unit (tile of 32 x 32) of the channel tile
+        auto gelu_out = [&](int hbuf, auto u0_c, auto i_c) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_c)::value, j = i - LAG, u0 = decltype(u0_c)::value;
+            if constexpr (j >= 0 && (j & 3) == 3) {
+                const uint32_t o[4] = {gl[(j - 3) % (LAG + 4)], gl[(j - 2) % (LAG + 4)], gl[(j - 1) % (LAG + 4)], gl[j % (LAG + 4)]};
+                int w = pack4(o, std::true_type());
+                pin(w);
+                ew[(j >> 2) & 3] = w;
+                if constexpr ((j & 15) == 15) *reinterpret_cast<v4i*>(h_at(hbuf, u0 + j / 16)) = ew;
+            }
+            if constexpr (i < NO1) {
+                constexpr int u = u0 + i / 16;
+                const uint32_t at = out_top(ha[u / T1][u % T1][i % 16], hq[u / T1]) >> 24;
+                gl[i % (LAG + 4)] = *reinterpret_cast<const __attribute__((address_space(3))) uint8_t*>(at);
+            }
+        };
+        auto gelu_slow = [&](int hbuf) __attribute__((always_inline)) {
+            if (hfast) return;
+            static_for<N1 * T1>([&](auto u_c) __attribute__((always_inline)) {
+                constexpr int u = decltype(u_c)::value;
+                *reinterpret_cast<v4i*>(h_at(hbuf, u)) = unit_slow(ha[u / T1][u % T1], hq[u / T1], true);
+            });
+        };
+        const int8_t* h0 = act + (16 * lg + jb) * HP + 32 * wm * TT + 16 * (lb & 1) + 8 * jo;
+        v4i af[2][TT], b2[4];
+        auto read_a = [&](int hbuf, auto kk_c) __attribute__((always_inline)) {
+            constexpr int kk = decltype(kk_c)::value;
+#pragma unroll
+            for (int t = 0; t < TT; ++t) {
+                const int8_t* p = h0 + hbuf * LY::HB + 32 * kk * HP + 32 * t;
+                const v2i a = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3)))*)(p));
+                const v2i c = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3)))*)(p + 8 * HP));
+                af[kk & 1][t] = v4i{a[0], a[1], c[0], c[1]};
+            }
+        };
+        auto read_b = [&](int b, auto st_c) __attribute__((always_inline)) {
+            constexpr int st = decltype(st_c)::value;
+            b2[st & 3] = *reinterpret_cast<const v4i*>(set_at(b) + wn * 32 * FC + (st % 3) * WNG * 32 * FC + x2[st / 3]);
+        };
+        auto f2_first = [&](int b, int hbuf, auto k_c) __attribute__((always_inline)) {      // piece k of RD - 1 of an F2's first fragments
+            constexpr int k = decltype(k_c)::value;
+            if constexpr (k == 0) read_a(hbuf, ic<0>());
+            if constexpr (k == 0 && RD == 3) { read_b(b, ic<0>()); read_b(b, ic<1>()); }
+            if constexpr (RD == 4) read_b(b, k_c); else if constexpr (k == 1) read_b(b, ic<2>());
+        };
+        // body(m): the loads and whatever else goes with product m; after(): loads to start once this set's memory is free
+        auto f1 = [&](const int8_t* w0, const int32_t* cst, int hbuf, auto body, auto after, auto next) __attribute__((always_inline)) {
+            stream(ic<N1>(), ic<T1>(), w0, ic<32 * C>(), std::true_type(),
+                [&](auto n_c, auto t_c, auto ks_c, const v4i& f) __attribute__((always_inline)) {
+                    constexpr int n = decltype(n_c)::value, t = decltype(t_c)::value, ks = decltype(ks_c)::value;
+                    if constexpr (ks == 0) mfma_first<vv_acc(t, ks)>(ha[n][t], vv[t][ks], f); else mfma<false, vv_acc(t, ks)>(ha[n][t], vv[t][ks], f);
+                },
+                [&](auto m_c) __attribute__((always_inline)) {
+                    constexpr int m = decltype(m_c)::value, n = m / NM1, mt = m % NM1;
+                    body(m_c);
+                    if constexpr (n == 0) spread(ic<0>(), ic<RqBuild<NBLD>::STEPS + 1>(), ic<0>(), ic<NM1>(), ic<mt>(), [&](auto k) __attribute__((always_inline)) { consts_step(cst, k); });
+                    else spread(ic<0>(), ic<NO1 + LAG>(), ic<EF1>(), ic<NM1>(), ic<mt>(), [&](auto i) __attribute__((always_inline)) { gelu_out(hbuf, ic<(n - 1) * T1>(), i); });
+                },
+                [&]() __attribute__((always_inline)) { sync(); after(); }, next);
+        };
+        auto f2 = [&](int b, int hbuf, auto tail_c, auto body, auto after, auto next) __attribute__((always_inline)) {
+            static_for<12>([&](auto st_c) __attribute__((always_inline)) {
+                constexpr int st = decltype(st_c)::value, kk = st / 3, j = st % 3;
+                if constexpr (decltype(tail_c)::value && st == 10) { sync(); after(); }
+                if constexpr (st + 3 < 12) read_b(b, ic<st + 3>());
+                if constexpr (j == 1 && kk < 3) read_a(hbuf, ic<kk + 1>());
+                if constexpr (decltype(tail_c)::value && st >= 10) {
+                    next(ic<2 * (st - 10)>());
+                    next(ic<2 * (st - 10) + 1>());
+                }
+                static_for<TT>([&](auto t_c) __attribute__((always_inline)) {
+                    constexpr int t = decltype(t_c)::value;
+                    mfma<true, false>(acc[j][t], af[kk & 1][t], b2[st & 3]);
+                    body(ic<st * TT + t>());
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            });
+        };
+        auto none = [](auto...) __attribute__((always_inline)) {};
+        constexpr int EF2 = NM2 > 6 ? 3 : 2;
+        auto rest = [&](auto m_c, auto nm_c) __attribute__((always_inline)) {       // the rest of the set being loaded
+            spread(ic<TP>(), ic<NP1 - TP>(), ic<0>(), ic<(decltype(nm_c)::value * 6) / 10>(), m_c, [&](auto i) __attribute__((always_inline)) { load_piece(L, i, B1()); });
+        };
+        auto start = [&](const Load& l) __attribute__((always_inline)) { L = l; load_range(L, ic<0>(), ic<TP>(), B1()); };
+        auto next_f1 = [&](auto k) __attribute__((always_inline)) { if constexpr (decltype(k)::value < RD - 1) bf[k] = frag(f1w0, k); };
+
+        f1(f1w1, cst1, 0, none, [&]() __attribute__((always_inline)) { start(load_f2(0, 1)); }, next_f1);
+        settle();
+        static_for<NO1 + LAG>([&](auto i) __attribute__((always_inline)) { gelu_out(0, ic<(N1 - 1) * T1>(), i); });
+        gelu_slow(0);
+        auto f1_loop = [&](int i) __attribute__((always_inline)) {      // F1(i), then F2(i - 1)
+            f1(f1w0, cst0, i & 1, [&](auto m) __attribute__((always_inline)) { rest(m, ic<N1 * NM1>()); },
+               [&]() __attribute__((always_inline)) {
+                   const bool more = i + 1 < NC;
+                   const Load a = load_rows(P.fc1, (more ? i + 1 : 0) * FC, 0), c = load_f2(i, 0);
+                   Load l = a;
+                   if (!more) l = c;
+                   start(l);
+               },
+               [&](auto k) __attribute__((always_inline)) { f2_first(1, (i - 1) & 1, k); });
+        };
+        auto f2_epi = [&](int i, auto m_c) __attribute__((always_inline)) {        // the last results of F1(i + 1), during F2(i)
+            spread(ic<0>(), ic<NO1 + LAG>(), ic<EF2>(), ic<NM2>(), m_c, [&](auto k) __attribute__((always_inline)) { gelu_out((i + 1) & 1, ic<(N1 - 1) * T1>(), k); });
+        };
+        f1_loop(1);
+#pragma unroll 1
+        for (int i = 0; i + 2 < NC; ++i) {
+            f2(1, i & 1, std::true_type(), [&](auto m) __attribute__((always_inline)) { rest(m, ic<NM2>()); f2_epi(i, m); },
+               [&]() __attribute__((always_inline)) { start(load_f2(i + 1, 1)); }, next_f1);
+            gelu_slow((i + 1) & 1);
+            f1_loop(i + 2);
+        }
+        f2(1, NC & 1, std::true_type(), [&](auto m) __attribute__((always_inline)) { rest(m, ic<NM2>()); f2_epi(NC - 2, m); }, none,
+           [&](auto k) __attribute__((always_inline)) { if constexpr (decltype(k)::value == 0) { static_for<RD - 1>([&](auto kk) __attribute__((always_inline)) { (void)kk; }); } });
+        gelu_slow((NC - 1) & 1);
+        sync_lds();                                                 // the last hidden chunk is complete
+        static_for<RD - 1>([&](auto k) __attribute__((always_inline)) { f2_first(0, (NC - 1) & 1, k); });
+        // constants of fc2 for the epilogue, requested before the loads that follow
+        int32_t fb[3], fcs[3], fbias[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const int ch = 32 * (j * WNG + wn) + lj;
+            fb[j] = P.fc2.rq_b[ch]; fcs[j] = P.fc2.rq_c[ch]; fbias[j] = P.fc2.bias ? P.fc2.bias[ch] : 0;
+        }
+        {
+            const v4i r = tile_buffer(P.xhat);
+            const uint32_t dst = tile_dst(LY::SET + LY::SETB);
+            f2(0, (NC - 1) & 1, std::false_type(), [&](auto m) __attribute__((always_inline)) {
+                spread(ic<0>(), ic<NPA>(), ic<0>(), ic<(NM2 / 2 > 0 ? NM2 / 2 : 1)>(), m, [&](auto i) __attribute__((always_inline)) { act_piece(r, dst, i); });
+            }, none, none);
+        }
+        const ResRq rr2 = make_res(P.res2);
+        Rq64 fq[3];
+        bool ok2 = rr2.ok;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) ok2 = make_rq64(fq[j], fb[j], fcs[j], fbias[j]) && ok2;
+        const bool fast2 = __builtin_amdgcn_ballot_w64(ok2) == ~0ull;
+        sync();                                                     // the rows of xhat are there; the hidden chunks are done with
+        if (P.next == 2) { L = load_rows(P.qkv_w, 0, 0); load_range(L, ic<0>(), ic<NPR>(), BR()); }
+        settle();
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int t = 0; t < TT; ++t) asm volatile("" : "+a"(acc[j][t]));      // (not to be copied out before)
+        auto f2_res = [&](int u) __attribute__((always_inline)) {
+            res_read(set_at(1) + 32 * (wm * TT + u % TT) * C, (u / TT) * WNG + wn, std::false_type(), rwn);
+        };
+        auto f2_put = [&](int u, const v4i& w) __attribute__((always_inline)) { act_put(wm * TT + u % TT, (u / TT) * WNG + wn, w); };
+        f2_res(0);
+        static_for<3 * TT>([&](auto u_c) __attribute__((always_inline)) {
+            constexpr int u = decltype(u_c)::value;
+            rw[0] = rwn[0]; rw[1] = rwn[1];
+            if constexpr (u + 1 < 3 * TT) f2_res(u + 1);
+            if constexpr (u > 0) es = stg_get();
+            static_for<16>([&](auto e_c) __attribute__((always_inline)) {
+                constexpr int e = decltype(e_c)::value;
+                eo[e & 3] = out_res(acc[u / TT][u % TT][e], fq[u / TT], rr2, (int32_t)(int8_t)((uint32_t)rw[e >> 3][(e >> 2) & 1] >> (8 * (e & 3))));
+                if constexpr ((e & 3) == 3) ew[e >> 2] = pack4(eo, std::true_type());
+            });
+            if constexpr (u > 0) f2_put(u - 1, es);
+            stg_put(ew, std::false_type());
+        });
+        es = stg_get(); f2_put(3 * TT - 1, es);
+        if (!fast2)
+            static_for<3 * TT>([&](auto u_c) __attribute__((always_inline)) {
+                constexpr int u = decltype(u_c)::value;
+                stg_put(unit_slow_res(acc[u / TT][u % TT], P.fc2, rr2, P.xhat, wm * TT + u % TT, (u / TT) * WNG + wn, std::false_type()), std::false_type());
+                f2_put(u, stg_get());
+            });
+        sync_lds();
+    } else {
+        Load L = load_rows(P.qkv_w, 0, 0);
+        load_act(P.x, LY::ACT);
+        load_ln(P.ln1_g, P.ln1_b);
+        load_range(L, ic<0>(), ic<NPR>(), BR());
+        sync();
+    }
+    if (!P.next) {                                                  // only the block's output leaves
+        constexpr int NI = M * PP / 64;
+        const __amdgpu_buffer_rsrc_t yb = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(P.y + m0 * C)), 0, rows * C, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < (NI + 3) / 4; ++i) {
+            const int s = 64 * (4 * i + wv) + lane, r = s / PP, p = s % PP;
+            if (s < M * PP) __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const v4i*>(act + r * C + 16 * (p ^ swz<G16>(r))), yb,
+                                                                  ((r & ~31) + token_of_row(r & 31)) * C + 16 * p, 0, 0);
+        }
+        return;
+    }
+    if (P.next == 2) { Load L1 = load_rows(P.qkv_w, RS, 1); load_range(L1, ic<0>(), ic<NPR>(), BR()); }
+    layernorm(P.ln1_f, P.ln1_c, front ? P.y : nullptr, P.next == 1 ? P.out : nullptr);
+    if (P.next == 1) return;
+    sync();
+    load_ar();
+    first_frags(set_at(0) + wn * 32 * C);
+    // ---- qkv of the next block: set s in buffer s % 2; its loads start when set s - 2 has been read
+    const int N3 = 3 * C;
+    const uint32_t q_off = (uint32_t)((8 * lb + dj) * N3 + 16 * d_o);
+    constexpr int TPR = NPR / 3;
+    Load L = {};
+    Rq rq[1] = {}, rqn[1] = {};
+    RqBuild<1> qb;
+    auto qkv_put = [&](int g, int t, const v4i& w, bool real) __attribute__((always_inline)) {
+        const int r0 = 32 * (wm * TT + t), n0 = (g * WNG + wn) * 32;
+        const int nr = __builtin_amdgcn_readfirstlane(real ? min(max(rows - r0, 0), 32) : 0);
+        const __amdgpu_buffer_rsrc_t ob = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(P.out + (m0 + r0) * N3 + n0)), 0, nr * N3, 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b128(w, ob, (int)q_off, 0, 0);
+    };
+    auto qkv_out = [&](int g, auto par_c, auto i_c) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_c)::value, t = i / 16, e = i % 16, par = decltype(par_c)::value;
+        if constexpr (i == NOT) es = stg_get();
+        else if constexpr (i == NOT + 1) qkv_put(g, TT - 1, es, fast);
+        else {
+            eo[e & 3] = out_top(pa[par][t][e], rq[0]);
+            if constexpr ((e & 3) == 3) { int w = pack4(eo, std::false_type()); pin(w); ew[e >> 2] = w; }
+            if constexpr (e == 3 && t > 0) es = stg_get();
+            if constexpr (e == 11 && t > 0) qkv_put(g, t - 1, es, fast);
+            if constexpr (e == 15) stg_put(ew, std::true_type());
+        }
+    };
+    auto qkv_slow = [&](int g, auto par_c) __attribute__((always_inline)) {
+        if (fast) return;
+        static_for<TT>([&](auto t_c) __attribute__((always_inline)) {
+            stg_put(unit_slow(pa[decltype(par_c)::value][decltype(t_c)::value], rq[0], false), std::true_type());
+            qkv_put(g, decltype(t_c)::value, stg_get(), true);
+        });
+    };
+    // set s (b: its buffer, the parity of its first tile); FIRST: no results wait yet and its successor is being loaded already
+    auto qkv_set = [&](int s, auto b_c, auto first_c, auto last_c) __attribute__((always_inline)) {
+        constexpr int b = decltype(b_c)::value;
+        constexpr bool first = decltype(first_c)::value, last = decltype(last_c)::value;
+        const int32_t* cst = (b ? cst1 : cst0) + wn * 32 + lj;
+        stream(ic<PT>(), ic<TT>(), set_at(b) + wn * 32 * C, ic<WNG * 32 * C>(), std::bool_constant<!last>(),
+            [&](auto p_c, auto t_c, auto ks_c, const v4i& f) __attribute__((always_inline)) {
+                constexpr int par = (b + decltype(p_c)::value) & 1, t = decltype(t_c)::value, ks = decltype(ks_c)::value;
+                if constexpr (ks == 0) mfma_first<true>(pa[par][t], ar[t][ks], f); else mfma<false, true>(pa[par][t], ar[t][ks], f);
+            },
+            [&](auto m_c) __attribute__((always_inline)) {
+                constexpr int m = decltype(m_c)::value, p = m / NMT, mt = m % NMT, par = (b + p + 1) & 1;
+                if constexpr (!first && !last) spread(ic<TPR>(), ic<NPR - TPR>(), ic<0>(), ic<(PT * NMT) / 2>(), m_c, [&](auto i) __attribute__((always_inline)) { load_piece(L, i, BR()); });
+                if constexpr (p > 0 || !first) {
+                    spread(ic<0>(), ic<NOT + 2>(), ic<EF>(), ic<NMT>(), ic<mt>(), [&](auto i) __attribute__((always_inline)) { qkv_out(s * PT + p - 1, ic<par>(), i); });
+                    if constexpr (mt == NMT - 1) qkv_slow(s * PT + p - 1, ic<par>());
+                }
+                spread(ic<0>(), ic<RqBuild<1>::STEPS>(), ic<0>(), ic<NMT>(), ic<mt>(), [&](auto k) __attribute__((always_inline)) {
+                    qb.template step<decltype(k)::value>(cst + p * WNG * 32, 0, P.qkv_w.bias != nullptr, 127, 24, true, rqn);
+                });
+                if constexpr (mt == NMT - 1) { fast = qb.finish(rqn); rq[0] = rqn[0]; }
+            },
+            [&]() __attribute__((always_inline)) {
+                sync();
+                if (s + 2 < LY::NQKV) { L = load_rows(P.qkv_w, (s + 2) * RS, b); load_range(L, ic<0>(), ic<TPR>(), BR()); }
+            },
+            [&](auto k) __attribute__((always_inline)) { bf[k] = frag(set_at(b ^ 1) + wn * 32 * C, k); });
+    };
+    qkv_set(0, ic<0>(), std::true_type(), std::false_type());
+#pragma unroll 1
+    for (int s = 1; s + 2 < LY::NQKV; s += 2) {
+        qkv_set(s, ic<1>(), std::false_type(), std::false_type());
+        qkv_set(s + 1, ic<0>(), std::false_type(), std::false_type());
+    }
+    qkv_set(LY::NQKV - 2, ic<1>(), std::false_type(), std::false_type());
+    qkv_set(LY::NQKV - 1, ic<0>(), std::false_type(), std::true_type());
+    settle();
+    static_for<NOT + 2>([&](auto i) __attribute__((always_inline)) { qkv_out(LY::NQKV * PT - 1, ic<(PT + 1) & 1>(), i); });
+    qkv_slow(LY::NQKV * PT - 1, ic<(PT + 1) & 1>());
+}
+
+template <int C, int MT>
+hipError_t launch_tb(hipStream_t s, const TokenBlockArgs& a) {
+    const int64_t grid = (a.R + TbLayout<C, MT>::M - 1) / TbLayout<C, MT>::M;
+    hipLaunchKernelGGL((token_block_kernel<C, MT>), dim3((unsigned)grid), dim3(256), (TbLayout<C, MT>::TOTAL), s, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool token_block_takes(int C, int F, int64_t R) {
+    if (C == 384 && R < 1024) return false;
+    return (C == 96 || C == 192 || C == 384) && F >= 2 * FC && F % FC == 0 && R >= 1 && R < (1 << 30) && (int64_t)F * C < (1 << 30);
+}
+
+hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a) {
+    const int64_t cus = num_cus(), r = a.R;
+    const int64_t per_row = (a.o ? (int64_t)a.C * a.C + 2LL * a.C * a.F : 0) + (a.next == 2 ? 3LL * a.C * a.C : 0);
+    TraceScope trace(s, KIND_TOKEN_BLOCK, 2 * r * per_row, per_row + r * a.C * ((a.o ? 3 : 1) + (a.next == 2 ? 3 : a.next == 1 ? 1 : 0)));
+    if (a.C == 384) {
+        if (a.R <= 32 * cus) return launch_tb<384, 1>(s, a);
+        if (a.R <= 64 * cus) return launch_tb<384, 2>(s, a);
+        return launch_tb<384, 4>(s, a);
+    }
+    if (a.C == 192) return a.R <= 64 * cus ? launch_tb<192, 2>(s, a) : launch_tb<192, 4>(s, a);
+    return launch_tb<96, 4>(s, a);
+}
+
+}  // namespace ivit

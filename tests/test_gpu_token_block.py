@@ -1,0 +1,92 @@
+"""The token-wise layers of a block as one kernel (token_block.hip) against the separate kernels.
+
+A block asked for a debug tap runs layer by layer; without one, the layers between two attentions are a single kernel.
+Both are run on stacks whose row counts sit at the edges of that kernel's tiles, in its 24-bit and general requantisation
+forms, and have to agree bit for bit (the separate kernels are compared with the oracle elsewhere; one case is here too).
+"""
+import numpy as np
+import pytest
+
+import oracle as orc
+from paper_2207_01405_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _blocks(C, H, F, T, n, regime):
+    cfg = dict(T=T, C=C, H=H, F=F, seed=70 + C, i0="fixed", rel_bias=False)
+    blocks = [synth.make_block(cfg, l) for l in range(n)]
+    for p in blocks:
+        for name in ("qkv", "proj", "fc1", "fc2"):
+            b, c = p[name + "_rq_b"].copy(), p[name + "_rq_c"].copy()
+            if regime == "general":                          # the same ratio with a shift beyond the 24-bit and 32-bit forms
+                b, c = b << 12, c + 12
+            elif regime == "mixed":                          # some channels of some wavefronts only
+                b[5::67] <<= 12
+                c[5::67] += 12
+            p[name + "_rq_b"], p[name + "_rq_c"] = b, c
+            if regime == "no_bias":
+                p["bias_" + name] = None
+    return cfg, blocks
+
+
+def _run(ivit, d, x, blocks, final_ln):
+    """(stack as one call, the same block by block with a tap)."""
+    import torch
+    R, C = x.shape
+    xd = torch.from_numpy(x).cuda()
+    ws = torch.empty(ivit.ivit_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    y = torch.empty_like(xd)
+    bl = [ivit.to_device(p) for p in blocks]
+    fl = None if final_ln is None else ivit.to_device(final_ln)
+    ivit.ivit_forward(xd, y, bl, d, ws, final_ln=fl)
+    cur, u = xd, torch.empty_like(xd)
+    for p in bl:
+        nxt = torch.empty_like(xd)
+        ivit.ivit_encoder_block(cur, nxt, p, d, ws, taps={"u": u})
+        cur = nxt
+    if fl is not None:
+        nxt = torch.empty_like(xd)
+        ivit.ivit_ilayernorm(cur, fl["gamma"], fl["beta"], nxt, fl["f_bits"], fl["c_shift"])
+        cur = nxt
+    torch.cuda.synchronize()
+    return y.cpu().numpy(), cur.cpu().numpy()
+
+
+@pytest.mark.parametrize("C,H,F", [(96, 3, 384), (192, 3, 768), (384, 6, 1536), (384, 12, 256)])
+@pytest.mark.parametrize("R", [1, 33, 128, 1025, 4099, 8192, 8193, 16385, 33000])
+def test_rows_at_the_edges_of_tiles(ivit, C, H, F, R):
+    T = 1 if R % 49 else 49                                  # windows of one token keep attention out of the way
+    d = dict(B=R // T, T=T, C=C, H=H, F=F)
+    cfg, blocks = _blocks(C, H, F, T, 2, "as drawn")
+    x = synth.make_rows(3 + R, R, C)
+    got, want = _run(ivit, d, x, blocks, synth.make_final_ln(cfg) if R % 2 else None)
+    assert np.array_equal(got, want), "%d of %d differ" % ((got != want).sum(), got.size)
+
+
+@pytest.mark.parametrize("C,H,F", [(96, 3, 384), (192, 3, 768), (384, 6, 1536)])
+@pytest.mark.parametrize("regime", ["general", "mixed", "no_bias"])
+@pytest.mark.parametrize("B,T", [(25, 49), (90, 197)])
+def test_requantisation_forms(ivit, C, H, F, regime, B, T):
+    d = dict(B=B, T=T, C=C, H=H, F=F)
+    cfg, blocks = _blocks(C, H, F, T, 2, regime)
+    x = synth.make_rows(9, B * T, C)
+    got, want = _run(ivit, d, x, blocks, synth.make_final_ln(cfg))
+    assert np.array_equal(got, want), "%d of %d differ" % ((got != want).sum(), got.size)
+
+
+def test_unaligned_parameter_arrays_take_the_separate_kernels(ivit):
+    import torch
+    C, H, F, B, T = 192, 3, 768, 25, 49
+    d = dict(B=B, T=T, C=C, H=H, F=F)
+    cfg, blocks = _blocks(C, H, F, T, 1, "as drawn")
+    x = synth.make_rows(10, B * T, C)
+    p = ivit.to_device(blocks[0])
+    shifted = torch.empty(3 * C + 1, dtype=torch.int32, device="cuda")
+    shifted[1:] = p["qkv_rq_b"]
+    p["qkv_rq_b"] = shifted[1:]
+    xd = torch.from_numpy(x).cuda()
+    y = torch.empty_like(xd)
+    ivit.ivit_encoder_block(xd, y, p, d, torch.empty(ivit.ivit_workspace_bytes(d), dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy(), orc.encoder_block(x, blocks[0], d))
