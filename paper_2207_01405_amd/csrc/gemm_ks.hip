@@ -229,26 +229,18 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(KsParams P) {
     }
 
     // ---- requantisation constants of the lane's channel (24-bit form, derivation in gemm_rs.hip): the sum is limited to
-    // [lo, hi], then one 24-bit multiply-add leaves the int8 result in the top byte (residual layers: one bit lower, the
-    // residual term by a second multiply-add).  A workgroup with a channel outside the conditions of that form takes the
+    // [lo, hi], then one 24-bit multiply-add leaves the int8 result in the top byte (residual layers: a 64-bit multiply-add,
+    // regst_common.hpp, the residual term by a 24-bit one).  A workgroup with a channel outside the conditions of that form takes the
     // general 64-bit form for all of its channels.
     int32_t c_lo = 0, c_hi = 0, c_mb = 0, c_ad = 0;
     bool chan_24 = true;
-    int64_t wlim = 127;
-    int sh24 = 24;
     if (EPI == EPI_RESIDUAL) {
-        const int64_t br = P.res_rq.b, cr = P.res_rq.c;
-        bool res_ok = br >= 1 && br < (1 << 23) && cr >= 1 && cr <= 30;
-        if (res_ok) {
-            const int64_t hr = (int64_t)P.rnd << (cr - 1);
-            const int64_t r2 = max((127 * br + hr) >> cr, -((-128 * br + hr) >> cr));
-            res_ok = r2 <= 128;
-            wlim = 127 + r2;
-        }
-        sh24 = 23;
-        chan_24 = res_ok;
-    }
-    {
+        Residual64 q;
+        chan_24 = residual64_of(q, pb, pc, pbias, P.rnd) && residual_term_24(P.res_rq);
+        c_lo = q.b; c_hi = q.c; c_mb = q.h_lo; c_ad = q.h_hi;
+    } else {
+        constexpr int64_t wlim = 127;
+        constexpr int sh24 = 24;
         bool ok = chan_24 && pc >= 1 && pc <= sh24 && pb >= 1 && pb < (1 << ((pc - 1) & 31));
         if (ok) {
             const int64_t half = (int64_t)P.rnd << (pc - 1), two_c = (int64_t)1 << pc;
@@ -290,13 +282,13 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(KsParams P) {
         uint32_t o[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int32_t m = med3(a[4 * d + r], c_lo, c_hi);
             if (EPI == EPI_RESIDUAL) {
-                const int32_t t1 = (__mul24(m, c_mb) + c_ad) >> 23;
+                const int32_t t1 = residual64_first(a[4 * d + r], c_lo, c_hi, c_mb, c_ad);
                 const int32_t res = (int32_t)(int8_t)((uint32_t)rw[d >> 1][d & 1] >> (8 * r));
                 const int32_t t2 = (__mul24(res, rb) + rh) >> rc;
                 o[r] = (uint32_t)clamp8(t1 + t2);
             } else {
+                const int32_t m = med3(a[4 * d + r], c_lo, c_hi);
                 o[r] = (uint32_t)(__mul24(m, c_mb) + c_ad);                       // result in the top byte
                 if (EPI == EPI_GELU) o[r] = (uint32_t)gelu_lut[o[r] >> 24];        // result in the low byte
             }

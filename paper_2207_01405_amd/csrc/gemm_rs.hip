@@ -253,28 +253,20 @@ __global__ __launch_bounds__(256 * GR) void gemm_rs_kernel(RsParams P) {
     // [Ln - bias, Lp - bias] first (one median of three), after
     // which T = v b + h lies in (-128 2^c, 128 2^c), T 2^(24-c) fits 32 bits and its top byte is the result: one
     // 24-bit multiply-add by b 2^(24-c), the addend (modulo 2^32) carrying bias and rounding.  Needs c <= 24,
-    // b < 2^(c-1) and bounds within 24 bits.  Residual layers: the first term only has to be exact within
-    // +-(127 + R2), R2 the largest magnitude of the residual term (<= 128 required), because beyond that the clamped
-    // sum is +-127 whatever is added; it then needs nine bits and is kept one bit lower.  A workgroup with a channel
-    // outside these conditions takes the general 64-bit form for all of its channels.
+    // b < 2^(c-1) and bounds within 24 bits.  Residual layers take a 64-bit multiply-add instead (regst_common.hpp).  A
+    // workgroup with a channel outside these conditions takes the general 64-bit form for all of its channels.
     int32_t c_lo[NCB], c_hi[NCB], c_mb[NCB], c_ad[NCB];
     bool chan_24 = true;
-    int64_t wlim = 127;
-    int sh24 = 24;
-    if (EPI == EPI_RESIDUAL) {
-        const int64_t br = P.res_rq.b, cr = P.res_rq.c;
-        bool res_ok = br >= 1 && br < (1 << 23) && cr >= 1 && cr <= 30;
-        if (res_ok) {
-            const int64_t hr = (int64_t)P.rnd << (cr - 1);
-            const int64_t r2 = max((127 * br + hr) >> cr, -((-128 * br + hr) >> cr));
-            res_ok = r2 <= 128;
-            wlim = 127 + r2;
-        }
-        sh24 = 23;
-        chan_24 = res_ok;
-    }
+    constexpr int64_t wlim = 127;
+    constexpr int sh24 = 24;
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
+        if (EPI == EPI_RESIDUAL) {
+            Residual64 q;
+            chan_24 = residual64_of(q, pb[cb], pc[cb], pbias[cb], P.rnd) && residual_term_24(P.res_rq) && chan_24;
+            c_lo[cb] = q.b; c_hi[cb] = q.c; c_mb[cb] = q.h_lo; c_ad[cb] = q.h_hi;
+            continue;
+        }
         int32_t lo = 0, hi = 0, mb = 0, ad = 0;
         bool ok = chan_24 && pc[cb] >= 1 && pc[cb] <= sh24 && pb[cb] >= 1 && pb[cb] < (1 << ((pc[cb] - 1) & 31));
         if (ok) {
@@ -340,13 +332,13 @@ __global__ __launch_bounds__(256 * GR) void gemm_rs_kernel(RsParams P) {
         uint32_t o[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int32_t m = med3(a[4 * d + r], c_lo[cb], c_hi[cb]);
             if (EPI == EPI_RESIDUAL) {
-                const int32_t t1 = (__mul24(m, c_mb[cb]) + c_ad[cb]) >> 23;
+                const int32_t t1 = residual64_first(a[4 * d + r], c_lo[cb], c_hi[cb], c_mb[cb], c_ad[cb]);
                 const int32_t res = (int32_t)(int8_t)((uint32_t)rw[cb][d >> 1][d & 1] >> (8 * r));
                 const int32_t t2 = (__mul24(res, rb) + rh) >> rc;
                 o[r] = (uint32_t)clamp8(t1 + t2);
             } else {
+                const int32_t m = med3(a[4 * d + r], c_lo[cb], c_hi[cb]);
                 o[r] = (uint32_t)(__mul24(m, c_mb[cb]) + c_ad[cb]);              // result in the top byte
                 if (EPI == EPI_GELU) o[r] = (uint32_t)gelu_lut[o[r] >> 24];        // result in the low byte
             }

@@ -171,21 +171,7 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
         st_dst[s] = (uint32_t)((8 * (hd / 4) + j) * N + 16 * (hd % 4));
     }
     const int32_t rb = P.res_rq.b, rc = P.res_rq.c, rh = P.rnd << ((P.res_rq.c - 1) & 31);
-    int64_t wlim = 127;
-    int sh24 = 24;
-    bool res_24 = true;
-    if (EPI == EPI_RESIDUAL) {
-        const int64_t br = P.res_rq.b, cr = P.res_rq.c;
-        bool res_ok = br >= 1 && br < (1 << 23) && cr >= 1 && cr <= 30;
-        if (res_ok) {
-            const int64_t hr = (int64_t)P.rnd << (cr - 1);
-            const int64_t r2 = max((127 * br + hr) >> cr, -((-128 * br + hr) >> cr));
-            res_ok = r2 <= 128;
-            wlim = 127 + r2;
-        }
-        sh24 = 23;
-        res_24 = res_ok;
-    }
+    const bool res_24 = EPI != EPI_RESIDUAL || residual_term_24(P.res_rq);
     // of the tile whose results wait in prev
     int64_t p_row = 0;                                          // first token of the wavefront's part
     int p_n0 = 0;                                               // first channel
@@ -220,6 +206,14 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
         }
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
+            if (EPI == EPI_RESIDUAL) {                          // (regst_common.hpp)
+                Residual64 q;
+                chan_24 = residual64_of(q, pb[cb], pc[cb], pbias[cb], P.rnd) && chan_24;
+                c_lo[cb] = q.b; c_hi[cb] = q.c; c_mb[cb] = q.h_lo; c_ad[cb] = q.h_hi;
+                continue;
+            }
+            constexpr int64_t wlim = 127;
+            constexpr int sh24 = 24;
             int32_t lo = 0, hi = 0, mb = 0, ad = 0;
             bool ok = chan_24 && pc[cb] >= 1 && pc[cb] <= sh24 && pb[cb] >= 1 && pb[cb] < (1 << ((pc[cb] - 1) & 31));
             if (ok) {
@@ -242,14 +236,14 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
         constexpr int mt = decltype(mtc)::value, cb = decltype(cbc)::value, d = decltype(dc)::value, r0 = decltype(r0c)::value;
 #pragma unroll
         for (int r = r0; r < r0 + 2; ++r) {
-            const int32_t m = med3(prev[mt][cb][4 * d + r], c_lo[cb], c_hi[cb]);
             uint32_t o;
             if (EPI == EPI_RESIDUAL) {
-                const int32_t t1 = (__mul24(m, c_mb[cb]) + c_ad[cb]) >> 23;
+                const int32_t t1 = residual64_first(prev[mt][cb][4 * d + r], c_lo[cb], c_hi[cb], c_mb[cb], c_ad[cb]);
                 const int32_t res = (int32_t)(int8_t)((uint32_t)rw[d >> 1][d & 1] >> (8 * r));
                 const int32_t t2 = (__mul24(res, rb) + rh) >> rc;
                 o = (uint32_t)clamp8(t1 + t2) & 0xffu;
             } else {
+                const int32_t m = med3(prev[mt][cb][4 * d + r], c_lo[cb], c_hi[cb]);
                 o = (uint32_t)(__mul24(m, c_mb[cb]) + c_ad[cb]) >> 24;
                 if (EPI == EPI_GELU) o = (uint32_t)(uint8_t)gelu_lut[o];
             }
@@ -373,9 +367,8 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
                     // four results of a register are put together by two byte permutes
                     const int v = 2 * kk + (mt >> 1), d = 2 * ph + (v >> 2), r = v & 3;     // (constants once the loops are unrolled)
                     if ((mt & 1) == 0) {
-                        const int32_t m = med3(prev[emt][cb][4 * d + r], c_lo[cb], c_hi[cb]);
-                        if (RES) tq = (__mul24(m, c_mb[cb]) + c_ad[cb]) >> 23;
-                        else tq = __mul24(m, c_mb[cb]) + c_ad[cb];                          // result in the top byte
+                        if (RES) tq = residual64_first(prev[emt][cb][4 * d + r], c_lo[cb], c_hi[cb], c_mb[cb], c_ad[cb]);
+                        else tq = __mul24(med3(prev[emt][cb][4 * d + r], c_lo[cb], c_hi[cb]), c_mb[cb]) + c_ad[cb];      // result in the top byte
                         if (EPI == EPI_GELU) tq = (int32_t)(uint8_t)gelu_lut[(uint32_t)tq >> 24];   // result in the low byte
                         asm volatile("" : "+v"(tq));
                     } else {

@@ -44,6 +44,23 @@ __device__ __forceinline__ int32_t med3(int32_t v, int32_t lo, int32_t hi) {
     return m;
 }
 
+// Residual layers: the first term of a result is bits c .. c + 31 of acc b + h, h = bias b + rounding addend, one 64-bit
+// multiply-add and a funnel shift.  It holds for every dyadic_fits32 pair; a form with 24-bit multiplies, which has to keep
+// the sum's nine bits above the fraction, ends at c = 23, and layers with long rows need c = 24 (ViT-B's second MLP layer,
+// 50432 rows: 150 us with the general 64-bit form, see the launch rules for the time with this one).
+struct Residual64 { int32_t b, c, h_lo, h_hi; };
+__device__ __forceinline__ bool residual64_of(Residual64& q, int32_t b, int32_t c, int32_t bias, int32_t rnd) {
+    const int64_t h = (int64_t)bias * b + (int64_t)((uint32_t)rnd << ((c - 1) & 31));
+    q = Residual64{b, c, (int32_t)(uint32_t)h, (int32_t)(h >> 32)};
+    return dyadic_fits32(b, c);
+}
+__device__ __forceinline__ int32_t residual64_first(int32_t acc, int32_t b, int32_t c, int32_t h_lo, int32_t h_hi) {
+    const int64_t p = (int64_t)acc * b + (int64_t)(((uint64_t)(uint32_t)h_hi << 32) | (uint32_t)h_lo);
+    return (int32_t)__builtin_amdgcn_alignbit((uint32_t)(p >> 32), (uint32_t)p, c);
+}
+// The residual term round(b_r r / 2^c_r) takes one 24-bit multiply-add under these conditions.
+__device__ __forceinline__ bool residual_term_24(Dyadic d) { return d.b >= 1 && d.b < (1 << 23) && d.c >= 1 && d.c <= 30; }
+
 // Token of the tile that sits in row i of the MFMA "A" operand.  Accumulator register e = 4 q + r of lane group g is
 // row 8 q + 4 g + r of the product; with this assignment it is token 16 g + e: a lane holds 16 consecutive tokens.
 __device__ __forceinline__ int token_of_row(int i) { return 16 * ((i >> 2) & 1) + 4 * (i >> 3) + (i & 3); }
