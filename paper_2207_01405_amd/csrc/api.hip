@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <mutex>
+#include <vector>
 
 #include "ivit_kernels.hpp"
 
@@ -157,30 +158,19 @@ hipError_t run_block(hipStream_t s, const int8_t* x, int8_t* y, const ivit_block
     return ivit::launch_linear(s, la);
 }
 
-// Whether the token-wise layers of a block run as one kernel (token_block.hip): its widths, and 16-byte alignment of the
-// parameter arrays, which it fetches in such pieces.
-bool block_fuses(const ivit_block_params* p, const ivit_dims* d) {
-    if (!ivit::token_block_takes(d->C, d->F, (int64_t)d->B * d->T)) return false;
-    const void* i32s[] = {p->ln1_gamma, p->ln1_beta, p->bias_qkv, p->qkv_rq_b, p->qkv_rq_c, p->bias_proj, p->proj_rq_b,
-                          p->proj_rq_c, p->ln2_gamma, p->ln2_beta, p->bias_fc1, p->fc1_rq_b, p->fc1_rq_c};
-    for (const void* q : i32s)
-        if (!aligned(q, 16)) return false;
-    return true;
-}
-
 // Launch sequence of n_blocks blocks, the last of which writes y, or, with a final I-LayerNorm, hands its rows to it.
 // Arguments already validated; n_blocks >= 1.
 hipError_t run_blocks(hipStream_t s, const int8_t* x, int8_t* y, const ivit_block_params* blocks, int32_t n_blocks,
                       const ivit_final_ln* final_ln, const ivit_dims* d, const Workspace& w) {
     const int64_t R = (int64_t)d->B * d->T;
-    bool fuse = true;
-    for (int l = 0; l < n_blocks && fuse; ++l) fuse = block_fuses(&blocks[l], d);
-    if (final_ln && !(aligned(final_ln->gamma, 16) && aligned(final_ln->beta, 16))) fuse = false;
     hipError_t e;
     // block l reads cur and writes into the other ping-pong buffer; the last producer writes y directly
     const int8_t* cur = x;
     auto other = [&]() { return cur == w.act0 ? w.act1 : w.act0; };
-    if (!fuse) {
+    // the constants of the fused launches live where the separate kernels would have put the hidden layer
+    const size_t slot = up256(ivit::token_block_table_bytes(d->C, d->F));
+    const int slots = (int)std::min<size_t>((size_t)R * d->F / slot, (size_t)n_blocks + 1);
+    if (!ivit::token_block_takes(d->C, d->F, R) || slots < 1) {
         for (int l = 0; l < n_blocks; ++l) {
             int8_t* dst = l == n_blocks - 1 && !final_ln ? y : other();
             if ((e = run_block(s, cur, dst, &blocks[l], d, w, nullptr))) return e;
@@ -189,36 +179,39 @@ hipError_t run_blocks(hipStream_t s, const int8_t* x, int8_t* y, const ivit_bloc
         if (!final_ln) return hipSuccess;
         return ivit::launch_ilayernorm(s, cur, final_ln->gamma, final_ln->beta, y, R, d->C, final_ln->f_bits, final_ln->c_shift);
     }
-    auto next_qkv = [&](ivit::TokenBlockArgs& t, const ivit_block_params& p) {
-        t.next = 2; t.out = w.qkv;
-        t.ln1_g = p.ln1_gamma; t.ln1_b = p.ln1_beta; t.ln1_f = p.ln1_f_bits; t.ln1_c = p.ln1_c_shift;
-        t.qkv_w = ivit::DenseW{p.w_qkv, p.bias_qkv, p.qkv_rq_b, p.qkv_rq_c};
-    };
-    ivit::TokenBlockArgs t{};
-    t.R = R; t.C = d->C; t.F = d->F; t.x = x;
-    next_qkv(t, blocks[0]);
-    if ((e = ivit::launch_token_block(s, t))) return e;
-    for (int l = 0; l < n_blocks; ++l) {
-        const ivit_block_params& p = blocks[l];
-        const bool last = l == n_blocks - 1;
-        if ((e = ivit::launch_attention(s, attention_args(&p, d, w, nullptr)))) return e;
+    // launch 0: LN1 and QKV of block 0; launch j: the token-wise rest of block j - 1, then LN1 and QKV of block j, the
+    // final I-LayerNorm, or nothing
+    std::vector<ivit::TokenBlockArgs> ts((size_t)n_blocks + 1);
+    for (int j = 0; j <= n_blocks; ++j) {
+        ivit::TokenBlockArgs& t = ts[j];
         t = ivit::TokenBlockArgs{};
-        t.R = R; t.C = d->C; t.F = d->F;
-        t.o = w.o; t.x = cur; t.xhat = w.xhat;
-        t.y = !last ? other() : final_ln ? nullptr : y;
-        t.ln2_g = p.ln2_gamma; t.ln2_b = p.ln2_beta; t.ln2_f = p.ln2_f_bits; t.ln2_c = p.ln2_c_shift;
-        t.proj = ivit::DenseW{p.w_proj, p.bias_proj, p.proj_rq_b, p.proj_rq_c};
-        t.fc1 = ivit::DenseW{p.w_fc1, p.bias_fc1, p.fc1_rq_b, p.fc1_rq_c};
-        t.fc2 = ivit::DenseW{p.w_fc2, p.bias_fc2, p.fc2_rq_b, p.fc2_rq_c};
-        t.res1 = dy(p.res1_rq); t.res2 = dy(p.res2_rq); t.gelu_p = sp(p.gelu); t.gelu_rq = dy(p.gelu_rq);
-        if (!last) {
-            next_qkv(t, blocks[l + 1]);
+        t.R = R; t.C = d->C; t.F = d->F; t.x = cur;
+        t.table = w.h + (size_t)(j % slots) * slot;
+        if (j > 0) {
+            const ivit_block_params& p = blocks[j - 1];
+            t.o = w.o; t.xhat = w.xhat;
+            t.y = j < n_blocks ? other() : final_ln ? nullptr : y;
+            t.ln2_g = p.ln2_gamma; t.ln2_b = p.ln2_beta; t.ln2_f = p.ln2_f_bits; t.ln2_c = p.ln2_c_shift;
+            t.proj = ivit::DenseW{p.w_proj, p.bias_proj, p.proj_rq_b, p.proj_rq_c};
+            t.fc1 = ivit::DenseW{p.w_fc1, p.bias_fc1, p.fc1_rq_b, p.fc1_rq_c};
+            t.fc2 = ivit::DenseW{p.w_fc2, p.bias_fc2, p.fc2_rq_b, p.fc2_rq_c};
+            t.res1 = dy(p.res1_rq); t.res2 = dy(p.res2_rq); t.gelu_p = sp(p.gelu); t.gelu_rq = dy(p.gelu_rq);
+            cur = t.y;
+        }
+        if (j < n_blocks) {
+            const ivit_block_params& p = blocks[j];
+            t.next = 2; t.out = w.qkv;
+            t.ln1_g = p.ln1_gamma; t.ln1_b = p.ln1_beta; t.ln1_f = p.ln1_f_bits; t.ln1_c = p.ln1_c_shift;
+            t.qkv_w = ivit::DenseW{p.w_qkv, p.bias_qkv, p.qkv_rq_b, p.qkv_rq_c};
         } else if (final_ln) {
             t.next = 1; t.out = y;
             t.ln1_g = final_ln->gamma; t.ln1_b = final_ln->beta; t.ln1_f = final_ln->f_bits; t.ln1_c = final_ln->c_shift;
         }
-        if ((e = ivit::launch_token_block(s, t))) return e;
-        cur = t.y;
+    }
+    for (int j = 0; j <= n_blocks; ++j) {
+        if (j % slots == 0 && (e = ivit::launch_token_tables(s, &ts[j], std::min(slots, n_blocks + 1 - j)))) return e;
+        if (j > 0 && (e = ivit::launch_attention(s, attention_args(&blocks[j - 1], d, w, nullptr)))) return e;
+        if ((e = ivit::launch_token_block(s, ts[j]))) return e;
     }
     return hipSuccess;
 }

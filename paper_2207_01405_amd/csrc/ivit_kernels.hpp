@@ -54,7 +54,10 @@ struct TokenBlockArgs {
     const int32_t* ln1_g; const int32_t* ln1_b; int ln1_f, ln1_c;
     DenseW proj, fc1, fc2, qkv_w;
     Dyadic res1, res2; ShiftParams gelu_p; Dyadic gelu_rq;
+    const int8_t* table;                 // token_block_table_bytes of constants, filled by launch_token_tables before the launch; 16-byte aligned
 };
+size_t token_block_table_bytes(int C, int F);
+hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n);
 bool token_block_takes(int C, int F, int64_t R);
 hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a);
 

@@ -33,6 +33,13 @@ template <int I> using ic = std::integral_constant<int, I>;
 
 constexpr int FC = 128;                          // hidden channels per chunk of the MLP
 
+// Offsets in the table of one launch: LN2 (gamma, beta), LN1 or the final LN, then 16 bytes per channel of proj, fc2, fc1, qkv.
+__host__ __device__ constexpr int TB_LN1(int C) { return 8 * C; }
+__host__ __device__ constexpr int TB_PROJ(int C) { return 16 * C; }
+__host__ __device__ constexpr int TB_FC2(int C) { return 32 * C; }
+__host__ __device__ constexpr int TB_FC1(int C) { return 48 * C; }
+__host__ __device__ constexpr int TB_QKV(int C, int F) { return 48 * C + 16 * F; }
+
 template <int C, int MT>
 struct TbLayout {
     static constexpr int KS = C / 32, P = C / 16;                  // k-steps and 16-byte pieces of a row of C bytes
@@ -46,7 +53,7 @@ struct TbLayout {
     static constexpr int G16 = (P & 15) == 0 ? 16 : (P & 7) == 0 ? 8 : (P & 3) == 0 ? 4 : (P & 1) == 0 ? 2 : 1;     // gcd(P, 16)
     static constexpr int SETR = RS * C, SET1 = FC * C;             // bytes of a set of proj / qkv, of fc1 and fc2
     static constexpr int SETW = SETR > SET1 ? SETR : SET1;
-    static constexpr int SETB = SETW + 3072;                       // weights, then rq_b, rq_c, bias of its rows (1 KB each)
+    static constexpr int SETB = SETW + 3072;                       // weights, then the constants of up to 192 rows
     static constexpr int HP = M + 16, HB = FC * HP;                // hidden chunk [channel][token]
     static constexpr int LUT = 0, SET = 256;                       // the ShiftGELU table lies at address 0: an index is its address
     static constexpr int ACT = SET + 2 * SETB;                     // token tile [row][C], or the two hidden chunks
@@ -63,80 +70,49 @@ struct TbLayout {
 // rows meets every bank group once.
 template <int G16> __device__ __forceinline__ int swz(int r) { return (r / (16 / G16)) & (G16 - 1); }
 
+// Requantisation constants of a channel, 16 bytes in the tables that table_kernel prepares.
+//   Rq     24-bit form (derivation in gemm_rs.hip); lo > hi: the channel needs the general form
+//   Rq64   residual layers: the first term is bits c .. c + 31 of acc b + h; c = 0: the channel needs the general form
 struct Rq { int32_t lo, hi, mb, ad; };
+struct Rq64 { int32_t b, c, h_lo, h_hi; };
 
 // median of three as the pattern the compiler turns into one v_med3_i32
 __device__ __forceinline__ int32_t med3c(int32_t v, int32_t lo, int32_t hi) { return max(min(v, lo), min(max(v, lo), hi)); }
 template <class T> __device__ __forceinline__ void pin(T& v) { asm volatile("" : "+v"(v)); }      // keeps a value's computation in its place
 
-// Constants of the 24-bit requantisation of N channels of a lane (derivation in gemm_rs.hip), built in STEPS steps of a few
-// instructions each, which go between MFMAs.  The two bounds are divisions below 2^32 by b < 2^23 with quotients below
-// 2^23 (anything else takes the general form): a single-precision estimate, within a few of the quotient, and two repairs.
-template <int N>
-struct RqBuild {
-    static constexpr int STEPS = 9;
-    int32_t b[N], c[N], bias[N];
-    uint32_t n1[N], n2[N], q1[N], q2[N];
-    int32_t r1[N], r2[N];
-    float rb[N];
-    bool ok;
-    template <int S> __device__ __forceinline__ void step(const int32_t* cst, int stride, bool has_bias, uint32_t wlim, int sh24, bool may, Rq (&q)[N]) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            if constexpr (S == 0) {
-                b[i] = cst[stride * i]; c[i] = cst[256 + stride * i]; bias[i] = cst[512 + stride * i];
-                if (i == 0) ok = may;
-            } else if constexpr (S == 1) {
-                rb[i] = __builtin_amdgcn_rcpf((float)b[i]);
-                if (!has_bias) bias[i] = 0;
-                pin(rb[i]);
-            } else if constexpr (S == 2) {
-                const uint32_t two_c = 1u << (c[i] & 31), half = two_c >> 1;
-                n1[i] = wlim * two_c - half + (uint32_t)b[i] - 1u;
-                n2[i] = (wlim - 1u) * two_c + half + (uint32_t)b[i];
-                pin(n1[i]); pin(n2[i]);
-            } else if constexpr (S == 3) {
-                q1[i] = (uint32_t)((float)n1[i] * rb[i]); q2[i] = (uint32_t)((float)n2[i] * rb[i]);
-                pin(q1[i]); pin(q2[i]);
-            } else if constexpr (S == 4) {
-                ok = ok && max(q1[i], q2[i]) < (1u << 23) && c[i] >= 1 && c[i] <= sh24 && b[i] >= 1 && b[i] < (1 << ((c[i] - 1) & 31));
-                r1[i] = (int32_t)(n1[i] - __umul24(q1[i], (uint32_t)b[i])); r2[i] = (int32_t)(n2[i] - __umul24(q2[i], (uint32_t)b[i]));
-                pin(r1[i]); pin(r2[i]);
-            } else if constexpr (S == 5) {
-                const int32_t t1 = (int32_t)__builtin_floorf((float)r1[i] * rb[i]), t2 = (int32_t)__builtin_floorf((float)r2[i] * rb[i]);
-                q1[i] += (uint32_t)t1; q2[i] += (uint32_t)t2;
-                r1[i] -= __mul24(t1, b[i]); r2[i] -= __mul24(t2, b[i]);
-                pin(r1[i]); pin(r2[i]);
-            } else if constexpr (S == 6) {
-                q1[i] += (r1[i] >= b[i]); q1[i] -= (r1[i] < 0);
-                q2[i] += (r2[i] >= b[i]); q2[i] -= (r2[i] < 0);
-                pin(q1[i]); pin(q2[i]);
-            } else if constexpr (S == 7) {
-                q[i].lo = (int32_t)(0u - q2[i] - (uint32_t)bias[i]); q[i].hi = (int32_t)(q1[i] - (uint32_t)bias[i]);
-                ok = ok && bias[i] > -(1 << 24) && bias[i] < (1 << 24) && q[i].lo >= -(1 << 23) && q[i].hi < (1 << 23);
-                pin(q[i].lo); pin(q[i].hi);
-            } else {
-                const int sh = (sh24 - c[i]) & 31;
-                q[i].mb = b[i] << sh;
-                q[i].ad = (int32_t)(((uint32_t)bias[i] * (uint32_t)b[i] + (1u << ((c[i] - 1) & 31))) << sh);
-                pin(q[i].mb); pin(q[i].ad);
-            }
+// The constants of up to MAXJ layers: one thread per channel, one row of workgroups per layer.  Prepared by a launch of
+// its own because the two divisions per channel, done by every workgroup for every channel, cost the block kernel more
+// than requantising the results (C = 384, 25216 rows: 10 of 60 thousand cycles of its MLP).
+constexpr int MAXJ = 88;
+struct TableJob { const int32_t* b; const int32_t* c; const int32_t* bias; int32_t* dst; int n; int kind; };      // kind 0 Rq, 1 Rq64, 2 LayerNorm (b gamma, c beta, bias unused)
+struct TableJobs { TableJob j[MAXJ]; int half[MAXJ]; };
+
+__global__ __launch_bounds__(256) void table_kernel(TableJobs J) {
+    const TableJob t = J.j[blockIdx.y];
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= t.n) return;
+    if (t.kind == 2) {                                              // gamma, then beta + 2^(c-1)
+        t.dst[i] = t.b[i];
+        t.dst[t.n + i] = (int32_t)((uint32_t)t.c[i] + (uint32_t)J.half[blockIdx.y]);
+        return;
+    }
+    const int32_t b = t.b[i], c = t.c[i], bias = t.bias ? t.bias[i] : 0;
+    v4i e;
+    if (t.kind == 1) {
+        const int64_t h = (int64_t)bias * b + (int64_t)(1u << ((c - 1) & 31));
+        e = v4i{b, dyadic_fits32(b, c) ? c : 0, (int32_t)(uint32_t)h, (int32_t)(h >> 32)};
+    } else {
+        e = v4i{1, 0, 0, 0};
+        if (c >= 1 && c <= 24 && b >= 1 && b < (1 << ((c - 1) & 31))) {
+            const int64_t half = (int64_t)1 << (c - 1), two_c = (int64_t)1 << c;
+            const int64_t Lp = (int64_t)((uint32_t)(127 * two_c - half + b - 1) / (uint32_t)b);
+            const int64_t Ln = -(int64_t)((uint32_t)(126 * two_c + 1 + half + b - 1) / (uint32_t)b);
+            const int64_t l = Ln - bias, h = Lp - bias;
+            if (l >= -(1 << 23) && h < (1 << 23))
+                e = v4i{(int32_t)l, (int32_t)h, b << (24 - c), (int32_t)(uint32_t)((uint64_t)((int64_t)bias * b + half) << (24 - c))};
         }
     }
-    // whether every channel of the wavefront takes the 24-bit form; if not, q gets the raw parameters instead
-    __device__ __forceinline__ bool finish(Rq (&q)[N]) {
-        if (__builtin_amdgcn_ballot_w64(ok) == ~0ull) return true;
-#pragma unroll
-        for (int i = 0; i < N; ++i) { q[i].lo = b[i]; q[i].hi = c[i]; q[i].mb = bias[i]; }
-        return false;
-    }
-};
-
-// Constants of a channel of a residual layer: its first term is bits c .. c + 31 of acc b + h, h = bias b + 2^(c-1).
-struct Rq64 { int32_t b, c; int64_t h; };
-__device__ __forceinline__ bool make_rq64(Rq64& q, int32_t b, int32_t c, int32_t bias) {
-    q.b = b; q.c = c; q.h = (int64_t)bias * b + (int64_t)(1u << ((c - 1) & 31));
-    return dyadic_fits32(b, c);
+    *reinterpret_cast<v4i*>(t.dst + 4 * i) = e;
 }
 
 // v_mfma_i32_32x32x32_i8 with the register file of the accumulators (ACCA) and of the first operand (AA) chosen: the
@@ -200,19 +176,19 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         const uint64_t a = (uint64_t)uniform_ptr(p);
         return v4i{(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)bytes, 0x00020000};
     };
-    struct Load { v4i rsrc; uint32_t so, d1, d3, v[3], dst; const int8_t* cst; };      // offset so far, its steps, per-lane offsets
-    auto load_rows = [&](const DenseW& W, int row0, int b) __attribute__((always_inline)) -> Load {
-        const int32_t* src = wv == 0 ? W.rq_b : wv == 1 || !W.bias ? W.rq_c : W.bias;
-        return Load{buffer(W.w + (int64_t)row0 * C, 0x7fffffffu), 0u - 12288u, 0, 12288, {vr[0], vr[1], vr[2]},
-                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + LY::SET + b * LY::SETB + wv * 1024)),
-                    uniform_ptr(reinterpret_cast<const int8_t*>(src + row0))};
+    struct Load { v4i rsrc; uint32_t so, d1, d3, v[3], dst; const int8_t* cst; };      // offset so far, its steps, per-lane offsets; constants
+    auto set_dst = [&](int b) __attribute__((always_inline)) -> uint32_t {
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + LY::SET + b * LY::SETB + wv * 1024));
+    };
+    auto load_rows = [&](const int8_t* w, const int8_t* cst, int row0, int b) __attribute__((always_inline)) -> Load {
+        return Load{buffer(w + row0 * C, 0x7fffffffu), 0u - 12288u, 0, 12288, {vr[0], vr[1], vr[2]}, set_dst(b), uniform_ptr(cst + row0 * 16)};
     };
     auto load_f2 = [&](int chunk, int b) __attribute__((always_inline)) -> Load {
-        return Load{buffer(P.fc2.w + (int64_t)chunk * FC, 0x7fffffffu), 0u - 32u * (uint32_t)F, 32u * (uint32_t)F, 32u * (uint32_t)F, {v2, v2, v2},
-                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + LY::SET + b * LY::SETB + wv * 1024)), uniform_ptr(P.fc2.w)};
+        return Load{buffer(P.fc2.w + chunk * FC, 0x7fffffffu), 0u - 32u * (uint32_t)F, 32u * (uint32_t)F, 32u * (uint32_t)F, {v2, v2, v2}, set_dst(b),
+                    uniform_ptr(P.fc2.w)};
     };
-    // piece i of a set of `bytes`; the last piece brings rq_b, rq_c and bias of the set's rows (wavefronts 0, 1 and 2; there
-    // is no such piece in a set of fc2, which fetches some bytes that nobody reads instead, so that nothing branches here)
+    // piece i of a set of `bytes`; the last piece brings the constants of the set's rows (64 rows a wavefront, the fourth repeats
+    // the third; a set of fc2 has none and fetches some bytes that nobody reads instead, so that nothing branches here)
     auto load_piece = [&](Load& l, auto i_c, auto bytes_c) __attribute__((always_inline)) {
         constexpr int i = decltype(i_c)::value, NI = decltype(bytes_c)::value / 1024, NP = (NI + 3) / 4, nr = decltype(bytes_c)::value / C;
         if constexpr (i < NP) {
@@ -221,7 +197,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                 asm volatile("s_add_u32 m0, %1, %5\n\ts_add_u32 %0, %0, %2\n\tbuffer_load_dwordx4 %3, %4, %0 offen lds"
                              : "+s"(l.so) : "s"(l.dst), "s"(i % 3 == 0 ? l.d3 : l.d1), "v"(l.v[i % 3]), "s"(l.rsrc), "i"(i * 4096) : "memory", "m0", "scc");
         } else {
-            dma16(l.cst, (uint32_t)(16 * min(lane, nr / 4 - 1)), l.dst + SETW - (wv == 3 ? 1024 : 0));      // (3 repeats 2)
+            dma16(l.cst, (uint32_t)(16 * min(64 * min(wv, 2) + lane, nr - 1)), l.dst + SETW - (wv == 3 ? 1024 : 0));
         }
     };
     auto load_range = [&](Load& l, auto lo_c, auto hi_c, auto bytes_c) __attribute__((always_inline)) {
@@ -248,13 +224,10 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         const uint32_t dst = tile_dst(off);
         static_for<NPA>([&](auto i) __attribute__((always_inline)) { act_piece(r, dst, i); });
     };
-    auto load_ln = [&](const int32_t* g, const int32_t* b) __attribute__((always_inline)) {
-        const int32_t* src = wv < 2 ? g : b;
-        const int at = (wv & 1) * 256 + 4 * lane;
-        if ((wv & 1) * 256 < C)
-            dma16(uniform_ptr(reinterpret_cast<const int8_t*>(src)), (uint32_t)(4 * min(at, C - 4)), lds0 + LY::LN + (wv >> 1) * 2048 + (wv & 1) * 1024);
+    auto load_ln = [&](const int8_t* src) __attribute__((always_inline)) {       // gamma, beta: 8 C bytes, one after the other
+        const int at = 1024 * wv + 16 * lane;
+        if (1024 * wv < 8 * C) dma16(uniform_ptr(src), (uint32_t)min(at, 8 * C - 16), lds0 + LY::LN + wv * 1024);
     };
-
     // ---- fragments.  Lane (lj, lg) of k-step ks: piece 2 ks + lg of row lj of a tile.
     int xr[NX];                                                     // tiles of rows of C bytes
 #pragma unroll
@@ -316,19 +289,18 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     auto out_top = [](int32_t a, const Rq& q) __attribute__((always_inline)) -> uint32_t { return (uint32_t)(__mul24(med3c(a, q.lo, q.hi), q.mb) + q.ad); };
     // one result of a residual layer: one 64-bit multiply-add, a funnel shift, the residual term, the sum limited
     auto out_res = [](int32_t a, const Rq64& q, const ResRq& rr, int32_t res) __attribute__((always_inline)) -> uint32_t {
-        const int64_t p = (int64_t)a * q.b + q.h;
-        const int32_t t1 = (int32_t)__builtin_amdgcn_alignbit((uint32_t)(p >> 32), (uint32_t)p, q.c);
-        return (uint32_t)clamp8(t1 + ((__mul24(res, rr.b) + rr.h) >> rr.c));
+        return (uint32_t)clamp8(residual64_first(a, q.b, q.c, q.h_lo, q.h_hi) + ((__mul24(res, rr.b) + rr.h) >> rr.c));
     };
-    // a lane's 16 results of a tile in 64-bit arithmetic (q holds b, c, bias); results in the low byte
-    auto unit_slow = [&](const v16i& a, const Rq& q, bool gelu) __attribute__((always_inline)) -> v4i {
+    // a lane's 16 results of a tile in 64-bit arithmetic, channel ch of W; results in the low byte
+    auto unit_slow = [&](const v16i& a, const DenseW& W, int ch, bool gelu) __attribute__((always_inline)) -> v4i {
+        const int32_t b = W.rq_b[ch], c = W.rq_c[ch], bias = W.bias ? W.bias[ch] : 0;
         v4i w;
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
             uint32_t o[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                o[r] = (uint32_t)clamp8_64(rnd_shift64(a[4 * d + r] + q.mb, q.lo, q.hi));
+                o[r] = (uint32_t)clamp8_64(rnd_shift64(a[4 * d + r] + bias, b, c));
                 if (gelu) o[r] = (uint32_t)(uint8_t)lds[LY::LUT + (o[r] & 0xffu)];
             }
             w[d] = pack4(o, std::true_type());
@@ -361,15 +333,14 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         constexpr int RPP = 64 / LPR, RW = M / 4;                   // rows per pass, rows of a wavefront
         int32_t g[48], b[48];
         const int32_t* gt = reinterpret_cast<const int32_t*>(lds + LY::LN);
-        const int32_t half = 1 << (c_shift - 1);
 #pragma unroll
         for (int j = 0; j < 3; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const v4i gv = *reinterpret_cast<const v4i*>(gt + 16 * (q + LPR * j) + 4 * e);
-                const v4i bv = *reinterpret_cast<const v4i*>(gt + 512 + 16 * (q + LPR * j) + 4 * e);
+                const v4i bv = *reinterpret_cast<const v4i*>(gt + C + 16 * (q + LPR * j) + 4 * e);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) { g[16 * j + 4 * e + r] = gv[r]; b[16 * j + 4 * e + r] = (int32_t)((uint32_t)bv[r] + (uint32_t)half); }
+                for (int r = 0; r < 4; ++r) { g[16 * j + 4 * e + r] = gv[r]; b[16 * j + 4 * e + r] = bv[r]; }
             }
         const __amdgpu_buffer_rsrc_t sb = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(st + m0 * C)), 0, st ? rows * C : 0, 0x00020000);
         const __amdgpu_buffer_rsrc_t db = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(dst + m0 * C)), 0, dst ? rows * C : 0, 0x00020000);
@@ -486,13 +457,15 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     v4i ew = {}, es = {};
     v2i rw[2] = {}, rwn[2] = {};
     bool fast = false;
-    const int32_t* const cst0 = reinterpret_cast<const int32_t*>(set_at(0) + SETW);
-    const int32_t* const cst1 = reinterpret_cast<const int32_t*>(set_at(1) + SETW);
+    auto cst_at = [&](int b, int row) __attribute__((always_inline)) -> v4i { return *reinterpret_cast<const v4i*>(set_at(b) + SETW + 16 * row); };
+    auto as_rq = [](const v4i& v) __attribute__((always_inline)) -> Rq { return Rq{v[0], v[1], v[2], v[3]}; };
+    auto as_rq64 = [](const v4i& v) __attribute__((always_inline)) -> Rq64 { return Rq64{v[0], v[1], v[2], v[3]}; };
+    const int8_t* const tab = P.table;
 
     if (front) {
-        Load L0 = load_rows(P.proj, 0, 0), L1 = LY::NPROJ > 1 ? load_rows(P.proj, RS, 1) : load_rows(P.fc1, 0, 1);
+        Load L0 = load_rows(P.proj.w, tab + TB_PROJ(C), 0, 0), L1 = LY::NPROJ > 1 ? load_rows(P.proj.w, tab + TB_PROJ(C), RS, 1) : load_rows(P.fc1.w, tab + TB_FC1(C), 0, 1);
         load_act(P.o, LY::ACT);
-        load_ln(P.ln2_g, P.ln2_b);
+        load_ln(tab);
         load_range(L0, ic<0>(), ic<NPR>(), BR());
         if constexpr (LY::NPROJ > 1) load_range(L1, ic<0>(), ic<NPR>(), BR()); else load_range(L1, ic<0>(), ic<NP1>(), B1());
         lds[LY::LUT + tid] = (int8_t)requant64(shiftgelu_raw((int32_t)(int8_t)tid, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c);
@@ -503,7 +476,8 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         sync_lds();
         load_act(P.x, LY::ACT);
         // ---- proj.  Sets 0 .. NPROJ - 1, then fc1's first two, alternate between the two buffers.
-        Rq64 pq = {}, pqn = {};
+        Rq64 pq = {};
+        v4i pqn = {};
         auto ct_of = [&](int g) __attribute__((always_inline)) -> int { return g * WNG + wn; };        // channel tile of tile g
         auto proj_res = [&](int g, int t) __attribute__((always_inline)) { res_read(act + 32 * (wm * TT + t) * C, ct_of(g), std::true_type(), rwn); };
         auto proj_out = [&](int g, auto par_c, auto i_c) __attribute__((always_inline)) {      // piece i of tile g: 16 TT results, then its last rows
@@ -528,12 +502,10 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                 act_put(wm * TT + t, ct_of(g), stg_get());
             });
         };
-        bool ok64 = true;
         static_for<LY::NPROJ>([&](auto s_c) __attribute__((always_inline)) {
             constexpr int s = decltype(s_c)::value, b = s & 1;
             constexpr bool last = s + 1 == LY::NPROJ;
-            const int32_t* cst = (b ? cst1 : cst0) + wn * 32 + lj;
-            Load L = s >= 1 ? (last ? load_rows(P.fc1, 0, b ^ 1) : load_rows(P.proj, (s + 1) * RS, b ^ 1)) : Load{};
+            Load L = s >= 1 ? (last ? load_rows(P.fc1.w, tab + TB_FC1(C), 0, b ^ 1) : load_rows(P.proj.w, tab + TB_PROJ(C), (s + 1) * RS, b ^ 1)) : Load{};
             stream(ic<PT>(), ic<TT>(), set_at(b) + wn * 32 * C, ic<WNG * 32 * C>(), std::bool_constant<!last>(),
                 [&](auto p_c, auto t_c, auto ks_c, const v4i& f) __attribute__((always_inline)) {
                     constexpr int par = (s * PT + decltype(p_c)::value) & 1, t = decltype(t_c)::value, ks = decltype(ks_c)::value;
@@ -548,11 +520,8 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                         spread(ic<0>(), ic<NOT + 2>(), ic<EF>(), ic<NMT>(), ic<mt>(), [&](auto i) __attribute__((always_inline)) { proj_out(g - 1, ic<(g - 1) & 1>(), i); });
                         if constexpr (mt == NMT - 1) proj_slow(g - 1, ic<(g - 1) & 1>());
                     }
-                    if constexpr (mt == 0) {
-                        const int at = p * WNG * 32;
-                        ok64 = make_rq64(pqn, cst[at], cst[256 + at], P.proj.bias ? cst[512 + at] : 0) && rr1.ok;
-                    }
-                    if constexpr (mt == NMT - 1) { pq = pqn; fast = __builtin_amdgcn_ballot_w64(ok64) == ~0ull; }
+                    if constexpr (mt == 0) pqn = cst_at(b, (p * WNG + wn) * 32 + lj);
+                    if constexpr (mt == NMT - 1) { pq = as_rq64(pqn); fast = __builtin_amdgcn_ballot_w64(pq.c != 0 && rr1.ok) == ~0ull; }
                 },
                 [&]() __attribute__((always_inline)) { sync(); },
                 [&](auto k) __attribute__((always_inline)) { bf[k] = frag(set_at(b ^ 1) + wn * 32 * C, k); });
@@ -566,11 +535,11 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         }
         sync_lds();
         // ---- LN2
-        Load L = load_rows(P.fc1, FC, 0);
+        Load L = load_rows(P.fc1.w, tab + TB_FC1(C), FC, 0);
         load_range(L, ic<0>(), ic<NP1>(), B1());
         layernorm(P.ln2_f, P.ln2_c, P.xhat, nullptr);
         sync();
-        if (P.next) load_ln(P.ln1_g, P.ln1_b);
+        if (P.next) load_ln(tab + TB_LN1(C));
         // ---- MLP.  Sets: F1(0), F1(1), F2(0), F1(2), F2(1), ..., F1(NC - 1), F2(NC - 2), F2(NC - 1), the rows of xhat; F1(0) is in
         // buffer 1, from then on F1 sets are in buffer 0, F2 sets in buffer 1 (the last one, having no F1 set after its
         // predecessor, in buffer 0).  Results of fc1: channel tile n is requantised while tile n + 1 is multiplied, the last
@@ -595,30 +564,8 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         const int8_t* f1w1 = set_at(1) + wn1 * N1 * 32 * C;
         first_frags(f1w1);
         sync_lds();
-        // requantisation constants: with two tiles or more, a lane builds those of one channel of a pair of tiles and the
-        // two halves of the wavefront exchange them
-        constexpr int NBLD = (N1 + 1) / 2;
-        Rq hq[2 * NBLD], hb_q[NBLD];
-        RqBuild<NBLD> hb;
+        Rq hq[N1];
         bool hfast = false;
-        auto consts_step = [&](const int32_t* cst, auto k_c) __attribute__((always_inline)) {
-            constexpr int k = decltype(k_c)::value;
-            if constexpr (k < RqBuild<NBLD>::STEPS) {
-                hb.template step<k>(cst + wn1 * N1 * 32 + (N1 > 1 ? lane : lj), 64, P.fc1.bias != nullptr, 127, 24, true, hb_q);
-            } else {
-                hfast = hb.finish(hb_q);
-#pragma unroll
-                for (int i = 0; i < NBLD; ++i) {
-                    auto both = [&](int32_t v, int32_t& a, int32_t& b) __attribute__((always_inline)) {
-                        if (N1 == 1) { a = v; return; }
-                        const auto s = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
-                        a = (int32_t)s[0]; b = (int32_t)s[1];
-                    };
-                    both(hb_q[i].lo, hq[2 * i].lo, hq[2 * i + 1].lo); both(hb_q[i].hi, hq[2 * i].hi, hq[2 * i + 1].hi);
-                    both(hb_q[i].mb, hq[2 * i].mb, hq[2 * i + 1].mb); both(hb_q[i].ad, hq[2 * i].ad, hq[2 * i + 1].ad);
-                }
-            }
-        };
         uint32_t gl[LAG + 4];
         auto h_at = [&](int hbuf, int u) __attribute__((always_inline)) -> int8_t* {
             return act + hbuf * LY::HB + ((wn1 * N1 + u / T1) * 32 + lj) * HP + 32 * (wm1 * T1 + u % T1) + 16 * lg;
@@ -639,11 +586,11 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                 gl[i % (LAG + 4)] = *reinterpret_cast<const __attribute__((address_space(3))) uint8_t*>(at);
             }
         };
-        auto gelu_slow = [&](int hbuf) __attribute__((always_inline)) {
+        auto gelu_slow = [&](int hbuf, int chunk) __attribute__((always_inline)) {
             if (hfast) return;
             static_for<N1 * T1>([&](auto u_c) __attribute__((always_inline)) {
                 constexpr int u = decltype(u_c)::value;
-                *reinterpret_cast<v4i*>(h_at(hbuf, u)) = unit_slow(ha[u / T1][u % T1], hq[u / T1], true);
+                *reinterpret_cast<v4i*>(h_at(hbuf, u)) = unit_slow(ha[u / T1][u % T1], P.fc1, chunk * FC + (wn1 * N1 + u / T1) * 32 + lj, true);
             });
         };
         const int8_t* h0 = act + (16 * lg + jb) * HP + 32 * wm * TT + 16 * (lb & 1) + 8 * jo;
@@ -669,7 +616,8 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
             if constexpr (RD == 4) read_b(b, k_c); else if constexpr (k == 1) read_b(b, ic<2>());
         };
         // body(m): the loads and whatever else goes with product m; after(): loads to start once this set's memory is free
-        auto f1 = [&](const int8_t* w0, const int32_t* cst, int hbuf, auto body, auto after, auto next) __attribute__((always_inline)) {
+        auto f1 = [&](const int8_t* w0, int b, int hbuf, auto body, auto after, auto next) __attribute__((always_inline)) {
+            v4i hc[N1];
             stream(ic<N1>(), ic<T1>(), w0, ic<32 * C>(), std::true_type(),
                 [&](auto n_c, auto t_c, auto ks_c, const v4i& f) __attribute__((always_inline)) {
                     constexpr int n = decltype(n_c)::value, t = decltype(t_c)::value, ks = decltype(ks_c)::value;
@@ -678,7 +626,17 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                 [&](auto m_c) __attribute__((always_inline)) {
                     constexpr int m = decltype(m_c)::value, n = m / NM1, mt = m % NM1;
                     body(m_c);
-                    if constexpr (n == 0) spread(ic<0>(), ic<RqBuild<NBLD>::STEPS + 1>(), ic<0>(), ic<NM1>(), ic<mt>(), [&](auto k) __attribute__((always_inline)) { consts_step(cst, k); });
+                    if constexpr (m == 0) {
+#pragma unroll
+                        for (int k = 0; k < N1; ++k) hc[k] = cst_at(b, (wn1 * N1 + k) * 32 + lj);
+                    }
+                    if constexpr (m == NM1 - 1) {
+                        bool ok = true;
+#pragma unroll
+                        for (int k = 0; k < N1; ++k) { hq[k] = as_rq(hc[k]); ok = ok && hq[k].lo <= hq[k].hi; }
+                        hfast = __builtin_amdgcn_ballot_w64(ok) == ~0ull;
+                    }
+                    if constexpr (n == 0) { }
                     else spread(ic<0>(), ic<NO1 + LAG>(), ic<EF1>(), ic<NM1>(), ic<mt>(), [&](auto i) __attribute__((always_inline)) { gelu_out(hbuf, ic<(n - 1) * T1>(), i); });
                 },
                 [&]() __attribute__((always_inline)) { sync(); after(); }, next);
@@ -709,15 +667,15 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         auto start = [&](const Load& l) __attribute__((always_inline)) { L = l; load_range(L, ic<0>(), ic<TP>(), B1()); };
         auto next_f1 = [&](auto k) __attribute__((always_inline)) { if constexpr (decltype(k)::value < RD - 1) bf[k] = frag(f1w0, k); };
 
-        f1(f1w1, cst1, 0, none, [&]() __attribute__((always_inline)) { start(load_f2(0, 1)); }, next_f1);
+        f1(f1w1, 1, 0, none, [&]() __attribute__((always_inline)) { start(load_f2(0, 1)); }, next_f1);
         settle();
         static_for<NO1 + LAG>([&](auto i) __attribute__((always_inline)) { gelu_out(0, ic<(N1 - 1) * T1>(), i); });
-        gelu_slow(0);
+        gelu_slow(0, 0);
         auto f1_loop = [&](int i) __attribute__((always_inline)) {      // F1(i), then F2(i - 1)
-            f1(f1w0, cst0, i & 1, [&](auto m) __attribute__((always_inline)) { rest(m, ic<N1 * NM1>()); },
+            f1(f1w0, 0, i & 1, [&](auto m) __attribute__((always_inline)) { rest(m, ic<N1 * NM1>()); },
                [&]() __attribute__((always_inline)) {
                    const bool more = i + 1 < NC;
-                   const Load a = load_rows(P.fc1, (more ? i + 1 : 0) * FC, 0), c = load_f2(i, 0);
+                   const Load a = load_rows(P.fc1.w, tab + TB_FC1(C), (more ? i + 1 : 0) * FC, 0), c = load_f2(i, 0);
                    Load l = a;
                    if (!more) l = c;
                    start(l);
@@ -732,21 +690,18 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         for (int i = 0; i + 2 < NC; ++i) {
             f2(1, i & 1, std::true_type(), [&](auto m) __attribute__((always_inline)) { rest(m, ic<NM2>()); f2_epi(i, m); },
                [&]() __attribute__((always_inline)) { start(load_f2(i + 1, 1)); }, next_f1);
-            gelu_slow((i + 1) & 1);
+            gelu_slow((i + 1) & 1, i + 1);
             f1_loop(i + 2);
         }
         f2(1, NC & 1, std::true_type(), [&](auto m) __attribute__((always_inline)) { rest(m, ic<NM2>()); f2_epi(NC - 2, m); }, none,
            [&](auto k) __attribute__((always_inline)) { if constexpr (decltype(k)::value == 0) { static_for<RD - 1>([&](auto kk) __attribute__((always_inline)) { (void)kk; }); } });
-        gelu_slow((NC - 1) & 1);
+        gelu_slow((NC - 1) & 1, NC - 1);
         sync_lds();                                                 // the last hidden chunk is complete
         static_for<RD - 1>([&](auto k) __attribute__((always_inline)) { f2_first(0, (NC - 1) & 1, k); });
         // constants of fc2 for the epilogue, requested before the loads that follow
-        int32_t fb[3], fcs[3], fbias[3];
+        v4i fb[3];
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const int ch = 32 * (j * WNG + wn) + lj;
-            fb[j] = P.fc2.rq_b[ch]; fcs[j] = P.fc2.rq_c[ch]; fbias[j] = P.fc2.bias ? P.fc2.bias[ch] : 0;
-        }
+        for (int j = 0; j < 3; ++j) fb[j] = *reinterpret_cast<const v4i*>(tab + TB_FC2(C) + 16 * (32 * (j * WNG + wn) + lj));
         {
             const v4i r = tile_buffer(P.xhat);
             const uint32_t dst = tile_dst(LY::SET + LY::SETB);
@@ -758,10 +713,10 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         Rq64 fq[3];
         bool ok2 = rr2.ok;
 #pragma unroll
-        for (int j = 0; j < 3; ++j) ok2 = make_rq64(fq[j], fb[j], fcs[j], fbias[j]) && ok2;
+        for (int j = 0; j < 3; ++j) { fq[j] = as_rq64(fb[j]); ok2 = ok2 && fq[j].c != 0; }
         const bool fast2 = __builtin_amdgcn_ballot_w64(ok2) == ~0ull;
         sync();                                                     // the rows of xhat are there; the hidden chunks are done with
-        if (P.next == 2) { L = load_rows(P.qkv_w, 0, 0); load_range(L, ic<0>(), ic<NPR>(), BR()); }
+        if (P.next == 2) { L = load_rows(P.qkv_w.w, tab + TB_QKV(C, F), 0, 0); load_range(L, ic<0>(), ic<NPR>(), BR()); }
         settle();
 #pragma unroll
         for (int j = 0; j < 3; ++j)
@@ -794,9 +749,9 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
             });
         sync_lds();
     } else {
-        Load L = load_rows(P.qkv_w, 0, 0);
+        Load L = load_rows(P.qkv_w.w, tab + TB_QKV(C, F), 0, 0);
         load_act(P.x, LY::ACT);
-        load_ln(P.ln1_g, P.ln1_b);
+        load_ln(tab + TB_LN1(C));
         load_range(L, ic<0>(), ic<NPR>(), BR());
         sync();
     }
@@ -811,7 +766,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         }
         return;
     }
-    if (P.next == 2) { Load L1 = load_rows(P.qkv_w, RS, 1); load_range(L1, ic<0>(), ic<NPR>(), BR()); }
+    if (P.next == 2) { Load L1 = load_rows(P.qkv_w.w, tab + TB_QKV(C, F), RS, 1); load_range(L1, ic<0>(), ic<NPR>(), BR()); }
     layernorm(P.ln1_f, P.ln1_c, front ? P.y : nullptr, P.next == 1 ? P.out : nullptr);
     if (P.next == 1) return;
     sync();
@@ -819,23 +774,25 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     first_frags(set_at(0) + wn * 32 * C);
     // ---- qkv of the next block: set s in buffer s % 2; its loads start when set s - 2 has been read
     const int N3 = 3 * C;
-    const uint32_t q_off = (uint32_t)((8 * lb + dj) * N3 + 16 * d_o);
+    // rows of qkv from this workgroup's first one on, as a buffer that ends with the matrix
+    const uint64_t q_base = (uint64_t)uniform_ptr(P.out + m0 * N3);
+    uint32_t q_off[TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) q_off[t] = (uint32_t)((32 * (wm * TT + t) + 8 * lb + dj) * N3 + 16 * d_o);
     constexpr int TPR = NPR / 3;
     Load L = {};
-    Rq rq[1] = {}, rqn[1] = {};
-    RqBuild<1> qb;
+    Rq rq = {};
+    v4i rqn = {};
     auto qkv_put = [&](int g, int t, const v4i& w, bool real) __attribute__((always_inline)) {
-        const int r0 = 32 * (wm * TT + t), n0 = (g * WNG + wn) * 32;
-        const int nr = __builtin_amdgcn_readfirstlane(real ? min(max(rows - r0, 0), 32) : 0);
-        const __amdgpu_buffer_rsrc_t ob = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(P.out + (m0 + r0) * N3 + n0)), 0, nr * N3, 0x00020000);
-        __builtin_amdgcn_raw_buffer_store_b128(w, ob, (int)q_off, 0, 0);
+        const __amdgpu_buffer_rsrc_t ob = __builtin_amdgcn_make_buffer_rsrc((int8_t*)q_base, 0, real ? rows * N3 : 0, 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b128(w, ob, (int)q_off[t], (g * WNG + wn) * 32, 0);
     };
     auto qkv_out = [&](int g, auto par_c, auto i_c) __attribute__((always_inline)) {
         constexpr int i = decltype(i_c)::value, t = i / 16, e = i % 16, par = decltype(par_c)::value;
         if constexpr (i == NOT) es = stg_get();
         else if constexpr (i == NOT + 1) qkv_put(g, TT - 1, es, fast);
         else {
-            eo[e & 3] = out_top(pa[par][t][e], rq[0]);
+            eo[e & 3] = out_top(pa[par][t][e], rq);
             if constexpr ((e & 3) == 3) { int w = pack4(eo, std::false_type()); pin(w); ew[e >> 2] = w; }
             if constexpr (e == 3 && t > 0) es = stg_get();
             if constexpr (e == 11 && t > 0) qkv_put(g, t - 1, es, fast);
@@ -845,7 +802,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     auto qkv_slow = [&](int g, auto par_c) __attribute__((always_inline)) {
         if (fast) return;
         static_for<TT>([&](auto t_c) __attribute__((always_inline)) {
-            stg_put(unit_slow(pa[decltype(par_c)::value][decltype(t_c)::value], rq[0], false), std::true_type());
+            stg_put(unit_slow(pa[decltype(par_c)::value][decltype(t_c)::value], P.qkv_w, (g * WNG + wn) * 32 + lj, false), std::true_type());
             qkv_put(g, decltype(t_c)::value, stg_get(), true);
         });
     };
@@ -853,7 +810,6 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     auto qkv_set = [&](int s, auto b_c, auto first_c, auto last_c) __attribute__((always_inline)) {
         constexpr int b = decltype(b_c)::value;
         constexpr bool first = decltype(first_c)::value, last = decltype(last_c)::value;
-        const int32_t* cst = (b ? cst1 : cst0) + wn * 32 + lj;
         stream(ic<PT>(), ic<TT>(), set_at(b) + wn * 32 * C, ic<WNG * 32 * C>(), std::bool_constant<!last>(),
             [&](auto p_c, auto t_c, auto ks_c, const v4i& f) __attribute__((always_inline)) {
                 constexpr int par = (b + decltype(p_c)::value) & 1, t = decltype(t_c)::value, ks = decltype(ks_c)::value;
@@ -866,14 +822,12 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                     spread(ic<0>(), ic<NOT + 2>(), ic<EF>(), ic<NMT>(), ic<mt>(), [&](auto i) __attribute__((always_inline)) { qkv_out(s * PT + p - 1, ic<par>(), i); });
                     if constexpr (mt == NMT - 1) qkv_slow(s * PT + p - 1, ic<par>());
                 }
-                spread(ic<0>(), ic<RqBuild<1>::STEPS>(), ic<0>(), ic<NMT>(), ic<mt>(), [&](auto k) __attribute__((always_inline)) {
-                    qb.template step<decltype(k)::value>(cst + p * WNG * 32, 0, P.qkv_w.bias != nullptr, 127, 24, true, rqn);
-                });
-                if constexpr (mt == NMT - 1) { fast = qb.finish(rqn); rq[0] = rqn[0]; }
+                if constexpr (mt == 0) rqn = cst_at(b, (p * WNG + wn) * 32 + lj);
+                if constexpr (mt == NMT - 1) { rq = as_rq(rqn); fast = __builtin_amdgcn_ballot_w64(rq.lo <= rq.hi) == ~0ull; }
             },
             [&]() __attribute__((always_inline)) {
                 sync();
-                if (s + 2 < LY::NQKV) { L = load_rows(P.qkv_w, (s + 2) * RS, b); load_range(L, ic<0>(), ic<TPR>(), BR()); }
+                if (s + 2 < LY::NQKV) { L = load_rows(P.qkv_w.w, tab + TB_QKV(C, F), (s + 2) * RS, b); load_range(L, ic<0>(), ic<TPR>(), BR()); }
             },
             [&](auto k) __attribute__((always_inline)) { bf[k] = frag(set_at(b ^ 1) + wn * 32 * C, k); });
     };
@@ -902,6 +856,38 @@ hipError_t launch_tb(hipStream_t s, const TokenBlockArgs& a) {
 bool token_block_takes(int C, int F, int64_t R) {
     if (C == 384 && R < 1024) return false;
     return (C == 96 || C == 192 || C == 384) && F >= 2 * FC && F % FC == 0 && R >= 1 && R < (1 << 30) && (int64_t)F * C < (1 << 30);
+}
+
+size_t token_block_table_bytes(int C, int F) { return (size_t)TB_QKV(C, F) + 48 * (size_t)C; }
+
+hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n) {
+    TableJobs J;
+    int nj = 0, most = 0;
+    auto flush = [&]() -> hipError_t {
+        if (nj == 0) return hipSuccess;
+        hipLaunchKernelGGL(table_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)nj), dim3(256), 0, s, J);
+        nj = most = 0;
+        return hipGetLastError();
+    };
+    auto job = [&](const int32_t* b, const int32_t* c, const int32_t* bias, const int8_t* dst, int off, int cnt, int kind, int c_shift) {
+        J.j[nj] = TableJob{b, c, bias, reinterpret_cast<int32_t*>(const_cast<int8_t*>(dst) + off), cnt, kind};
+        J.half[nj] = kind == 2 ? 1 << (c_shift - 1) : 0;
+        ++nj; most = std::max(most, cnt);
+    };
+    for (int i = 0; i < n; ++i) {
+        const TokenBlockArgs& t = a[i];
+        hipError_t e;
+        if (nj + 6 > MAXJ && (e = flush())) return e;
+        if (t.o) {
+            job(t.ln2_g, t.ln2_b, nullptr, t.table, 0, t.C, 2, t.ln2_c);
+            job(t.proj.rq_b, t.proj.rq_c, t.proj.bias, t.table, TB_PROJ(t.C), t.C, 1, 0);
+            job(t.fc2.rq_b, t.fc2.rq_c, t.fc2.bias, t.table, TB_FC2(t.C), t.C, 1, 0);
+            job(t.fc1.rq_b, t.fc1.rq_c, t.fc1.bias, t.table, TB_FC1(t.C), t.F, 0, 0);
+        }
+        if (t.next) job(t.ln1_g, t.ln1_b, nullptr, t.table, TB_LN1(t.C), t.C, 2, t.ln1_c);
+        if (t.next == 2) job(t.qkv_w.rq_b, t.qkv_w.rq_c, t.qkv_w.bias, t.table, TB_QKV(t.C, t.F), 3 * t.C, 0, 0);
+    }
+    return flush();
 }
 
 hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a) {

@@ -75,7 +75,7 @@ def test_requantisation_forms(ivit, C, H, F, regime, B, T):
     assert np.array_equal(got, want), "%d of %d differ" % ((got != want).sum(), got.size)
 
 
-def test_unaligned_parameter_arrays_take_the_separate_kernels(ivit):
+def test_parameter_arrays_at_four_byte_alignment(ivit):
     import torch
     C, H, F, B, T = 192, 3, 768, 25, 49
     d = dict(B=B, T=T, C=C, H=H, F=F)
