@@ -12,8 +12,8 @@
 // channel and 16 tokens of a product, so requantisation constants are registers; results turn into token rows through
 // wavefront-private LDS with the transposing LDS read.  The LayerNorms work on the token tile in LDS.
 //
-// What bounds it is the rate at which one wavefront per SIMD issues instructions: a matrix instruction hides about six
-// others, and takes their time on top once there are more (measured: 1 + 6: 42 cycles, 1 + 8: 77).  So the results of a
+// What bounds it is the rate at which one wavefront per SIMD issues instructions (one per 4 to 4.5 cycles): a matrix
+// instruction of 32 cycles hides about seven others, and every further one adds its own time.  So the results of a
 // channel tile are requantised between the products of the next one, spread evenly, and loads are three instructions.
 #include "regst_common.hpp"
 #include <algorithm>
@@ -127,6 +127,13 @@ template <bool ACCA, bool AA> __device__ __forceinline__ void mfma(v16i& acc, co
 template <bool AA> __device__ __forceinline__ void mfma_first(v16i& acc, const v4i& a, const v4i& b) {      // ... on a zero accumulator
     if constexpr (AA) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0" : "=&v"(acc) : "a"(a), "v"(b));
     else asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+}
+
+// The product that piece i of n goes with when they are spread over the products from .. to - 1.
+constexpr int spread_slot(int i, int n, int from, int to) {
+    for (int m = from; m < to; ++m)
+        if (i < (m - from + 1) * n / (to - from)) return m;
+    return to;
 }
 
 template <int C, int MT>
@@ -328,10 +335,9 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
 
     // ---- I-LayerNorm of the token tile, in place; `st`: the rows before normalisation also go to global memory, `dst`:
     // the normalised ones do
-    auto layernorm = [&](int f_bits, int c_shift, int8_t* st, int8_t* dst) __attribute__((always_inline)) {
-        const int q = lane % LPR, rl = lane / LPR;
-        constexpr int RPP = 64 / LPR, RW = M / 4;                   // rows per pass, rows of a wavefront
-        int32_t g[48], b[48];
+    int32_t g[48], b[48];
+    const int q = lane % LPR, rl = lane / LPR;
+    auto ln_params = [&]() __attribute__((always_inline)) {
         const int32_t* gt = reinterpret_cast<const int32_t*>(lds + LY::LN);
 #pragma unroll
         for (int j = 0; j < 3; ++j)
@@ -342,6 +348,9 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) { g[16 * j + 4 * e + r] = gv[r]; b[16 * j + 4 * e + r] = bv[r]; }
             }
+    };
+    auto layernorm = [&](int f_bits, int c_shift, int8_t* st, int8_t* dst) __attribute__((always_inline)) {
+        constexpr int RPP = 64 / LPR, RW = M / 4;                   // rows per pass, rows of a wavefront
         const __amdgpu_buffer_rsrc_t sb = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(st + m0 * C)), 0, st ? rows * C : 0, 0x00020000);
         const __amdgpu_buffer_rsrc_t db = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(dst + m0 * C)), 0, dst ? rows * C : 0, 0x00020000);
         constexpr int NPASS = RW / RPP;
@@ -533,6 +542,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
             static_for<NOT + 2>([&](auto i) __attribute__((always_inline)) { proj_out(g, ic<g & 1>(), i); });
             proj_slow(g, ic<g & 1>());
         }
+        ln_params();
         sync_lds();
         // ---- LN2
         Load L = load_rows(P.fc1.w, tab + TB_FC1(C), FC, 0);
@@ -747,6 +757,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                 stg_put(unit_slow_res(acc[u / TT][u % TT], P.fc2, rr2, P.xhat, wm * TT + u % TT, (u / TT) * WNG + wn, std::false_type()), std::false_type());
                 f2_put(u, stg_get());
             });
+        ln_params();
         sync_lds();
     } else {
         Load L = load_rows(P.qkv_w.w, tab + TB_QKV(C, F), 0, 0);
@@ -754,6 +765,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         load_ln(tab + TB_LN1(C));
         load_range(L, ic<0>(), ic<NPR>(), BR());
         sync();
+        ln_params();
     }
     if (!P.next) {                                                  // only the block's output leaves
         constexpr int NI = M * PP / 64;
@@ -783,6 +795,19 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     Load L = {};
     Rq rq = {};
     v4i rqn = {};
+    // Stores that follow the last piece of a set's loads and come before its tail: the wait for the loads leaves them out.
+    constexpr int QL = PT * NMT * 4 / 10 > 0 ? PT * NMT * 4 / 10 : 1;      // the loads of the next set go with the first QL products
+    constexpr auto stores_after_loads = []() constexpr {
+        const int from = spread_slot(NPR - TPR - 1, NPR - TPR, 0, QL), to = (PT * KS - RD + 1) * TT;
+        int n = 0;
+        for (int p = 0; p < PT; ++p)
+            for (int t = 0; t < TT; ++t) {
+                const int at = p * NMT + spread_slot(t + 1 < TT ? 16 * (t + 1) + 11 : NOT + 1, NOT + 2, EF, NMT);
+                n += at > from && at < to;
+            }
+        return n;
+    };
+    constexpr int NSA = stores_after_loads();
     auto qkv_put = [&](int g, int t, const v4i& w, bool real) __attribute__((always_inline)) {
         const __amdgpu_buffer_rsrc_t ob = __builtin_amdgcn_make_buffer_rsrc((int8_t*)q_base, 0, real ? rows * N3 : 0, 0x00020000);
         __builtin_amdgcn_raw_buffer_store_b128(w, ob, (int)q_off[t], (g * WNG + wn) * 32, 0);
@@ -817,7 +842,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
             },
             [&](auto m_c) __attribute__((always_inline)) {
                 constexpr int m = decltype(m_c)::value, p = m / NMT, mt = m % NMT, par = (b + p + 1) & 1;
-                if constexpr (!first && !last) spread(ic<TPR>(), ic<NPR - TPR>(), ic<0>(), ic<(PT * NMT) / 2>(), m_c, [&](auto i) __attribute__((always_inline)) { load_piece(L, i, BR()); });
+                if constexpr (!first && !last) spread(ic<TPR>(), ic<NPR - TPR>(), ic<0>(), ic<QL>(), m_c, [&](auto i) __attribute__((always_inline)) { load_piece(L, i, BR()); });
                 if constexpr (p > 0 || !first) {
                     spread(ic<0>(), ic<NOT + 2>(), ic<EF>(), ic<NMT>(), ic<mt>(), [&](auto i) __attribute__((always_inline)) { qkv_out(s * PT + p - 1, ic<par>(), i); });
                     if constexpr (mt == NMT - 1) qkv_slow(s * PT + p - 1, ic<par>());
@@ -826,7 +851,8 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                 if constexpr (mt == NMT - 1) { rq = as_rq(rqn); fast = __builtin_amdgcn_ballot_w64(rq.lo <= rq.hi) == ~0ull; }
             },
             [&]() __attribute__((always_inline)) {
-                sync();
+                // (the first set's successor was requested before it, with nothing in between)
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(first ? 0 : NSA) : "memory");
                 if (s + 2 < LY::NQKV) { L = load_rows(P.qkv_w.w, tab + TB_QKV(C, F), (s + 2) * RS, b); load_range(L, ic<0>(), ic<TPR>(), BR()); }
             },
             [&](auto k) __attribute__((always_inline)) { bf[k] = frag(set_at(b ^ 1) + wn * 32 * C, k); });
