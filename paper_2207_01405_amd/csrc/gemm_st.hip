@@ -1,0 +1,283 @@
+// int8 x int8 -> int32 Dense / MatMul on the gfx950 matrix cores with the dyadic requantisation of I-ViT (arXiv
+// 2207.01405, Sec. 3.2, Eq. 7-10) fused into the epilogue, optionally with the residual add of Eq. 1-2 or with ShiftGELU
+// (Sec. 3.4, Algorithm 2) and its rescale: the form for any K % 16 == 0, any N and any number of rows.
+//
+// A workgroup (256 threads = 2 x 2 wavefronts) computes one tile of 64 MT tokens x 64 NT channels.  Both operands stream
+// through S LDS stages of 128 bytes of K, filled by LDS-direct loads S - 1 stages ahead (no register pass, one barrier
+// per stage); 16-byte pieces of a row are permuted by an XOR with bits of the row number, which costs the loads nothing
+// and spreads the fragment reads over the banks.  Several workgroups share a compute unit, so one's prologue and
+// epilogue run under another's multiplies.  The weights are the MFMA "A" operand and the loads put the channel rows in
+// such an order that a lane ends up with 16 NT consecutive channels of one token: results leave as 16-byte stores at
+// whatever alignment the row has.
+#include <type_traits>
+
+#include "regst_common.hpp"
+
+namespace ivit {
+namespace {
+
+using namespace regst;
+
+constexpr int BK = 128;                       // bytes of K per stage
+
+struct StParams {
+    const int8_t* x; const int8_t* w; const int32_t* bias; const int32_t* rq_b; const int32_t* rq_c;
+    const int8_t* residual; Dyadic res_rq; ShiftParams gelu_p; Dyadic gelu_rq;
+    int8_t* y; int64_t M; int N; int K; int tiles_n; int64_t tiles; int64_t per_xcd;
+    int64_t ldx;                              // bytes between rows of x
+    int rnd;                                  // 1: round to nearest, 0: floor (every requantisation of the epilogue)
+};
+
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));   // 16 bytes at any address
+
+// 4 bytes per lane from global memory into LDS (as dma16 of regst_common.hpp)
+__device__ __forceinline__ void dma4(const void* base, uint32_t off, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+                 : : "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(off), "s"(base) : "memory", "m0");
+}
+
+// every load but the newest N of this wavefront has arrived, its LDS reads have returned, and so for all wavefronts
+template <int N> __device__ __forceinline__ void arrive() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+}
+
+template <int EPI, int MT, int NT, int S>
+__global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
+    constexpr int TM = 64 * MT, TN = 64 * NT, STG = (TM + TN) * BK, XI = 2 * MT, DPW = 2 * (MT + NT);
+    __shared__ __align__(16) int8_t lds[S * STG];
+    __shared__ __align__(16) int32_t qb_s[TN], qc_s[TN], bias_s[TN];
+    __shared__ int8_t gelu_lut[256];
+
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, lg = lane >> 5, wm = wv >> 1, wn = wv & 1;
+
+    // each XCD takes a contiguous range of tiles; within it the channel tile index runs fastest
+    const int64_t tile = (int64_t)(blockIdx.x % NXCD) * P.per_xcd + blockIdx.x / NXCD;
+    if (tile >= P.tiles) return;
+    const int64_t m0 = (tile / P.tiles_n) * TM;
+    const int n0 = (int)(tile % P.tiles_n) * TN;
+    const int K = P.K, N = P.N;
+    const int rows = (int)min64(P.M - m0, TM);
+
+    // this lane's outputs: tokens row0 + 32 tt, channels n_l + 16 ct .. + 15
+    const int row0 = wm * 32 * MT + li, cl = wn * 32 * NT + 16 * NT * lg, n_l = n0 + cl;
+    v4i res[MT][NT] = {};
+    if (EPI == EPI_RESIDUAL) {                // requested first: the wait for the first stage covers them
+#pragma unroll
+        for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+            for (int ct = 0; ct < NT; ++ct)
+                if (row0 + 32 * tt < rows && n_l + 16 * ct + 16 <= N)
+                    res[tt][ct] = *reinterpret_cast<const v4i_any*>(P.residual + (m0 + row0 + 32 * tt) * N + n_l + 16 * ct);
+    }
+
+    // the channels' constants: one array per wavefront
+    if (wv < 3) {
+        const int32_t* src = wv == 0 ? P.rq_b : wv == 1 ? P.rq_c : P.bias;
+        int32_t* dst = wv == 0 ? qb_s : wv == 1 ? qc_s : bias_s;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            if (src) dma4(uniform_ptr(reinterpret_cast<const int8_t*>(src)), 4u * min(n0 + 64 * t + lane, N - 1), lds_offset(reinterpret_cast<const int8_t*>(dst + 64 * t)));
+            else dst[64 * t + lane] = 0;
+        }
+    }
+
+    // Load instruction i of a wavefront fills LDS rows 32 i + r, r = 8 wavefront + lane / 8, eight lanes a row; the lane
+    // lands in physical piece lane % 8 and fetches piece (lane % 8) ^ ((r / 2) % 8).  Rows past the last token or channel
+    // repeat it (never stored), pieces past the end of a row its last piece (never multiplied, see below).
+    const int ld_r = 8 * wv + (lane >> 3), ld_col = 16 * ((lane & 7) ^ ((ld_r >> 1) & 7));
+    const int8_t* xg = uniform_ptr(P.x + m0 * P.ldx);
+    const int8_t* wg = uniform_ptr(P.w + (int64_t)n0 * K);
+    uint32_t off[DPW];
+#pragma unroll
+    for (int i = 0; i < DPW; ++i) {
+        if (i < XI) {
+            off[i] = (uint32_t)min(32 * i + ld_r, rows - 1) * (uint32_t)P.ldx + ld_col;
+        } else {
+            // row 8 q + 4 g + r of MFMA tile ct holds channel 16 NT g + 16 ct + 4 q + r of the wavefront's 32 NT: that is
+            // accumulator register 4 q + r of lane group g
+            const int R = 32 * (i - XI) + ld_r, ct = (R >> 5) % NT, rr = R & 31;
+            const int ch = (R / (32 * NT)) * 32 * NT + 16 * NT * ((rr >> 2) & 1) + 16 * ct + 4 * (rr >> 3) + (rr & 3);
+            off[i] = (uint32_t)min(ch, N - 1 - n0) * (uint32_t)K + ld_col;
+        }
+    }
+    const int stages = (K + BK - 1) / BK, k_last = K - (stages - 1) * BK;      // bytes of K in the last stage: 16 .. 128
+    const uint32_t lds0 = lds_offset(lds) + wv * 1024;
+    // the stage being requested: its number, bases and buffer, and how far a lane's piece moves back (last stage only)
+    int is = 0, is_buf = 0;
+    auto issue_one = [&](int i) __attribute__((always_inline)) {
+        const uint32_t back = is == stages - 1 ? (uint32_t)max(ld_col - (k_last - 16), 0) : 0u;
+        dma16(i < XI ? xg : wg, off[i] - back, lds0 + is_buf * STG + i * 4096);
+    };
+    auto issue_done = [&]() __attribute__((always_inline)) {
+        ++is;
+        if (++is_buf == S) is_buf = 0;
+        xg += BK; wg += BK;
+    };
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s)
+        if (s < stages) {
+#pragma unroll
+            for (int i = 0; i < DPW; ++i) issue_one(i);
+            issue_done();
+        }
+    if (EPI == EPI_GELU) {
+        const int32_t I = (int32_t)(int8_t)tid;
+        gelu_lut[tid] = (int8_t)requant64(shiftgelu_raw(I, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c, P.rnd);
+    }
+
+    v16i acc[NT][MT] = {};
+    const int x_row = row0 * BK, w_row = (TM + wn * 32 * NT + li) * BK, sw = (li >> 1) & 7;
+    struct Frag { v4i a[NT], b[MT]; };
+    auto read_frag = [&](Frag& f, const int8_t* st, int kk) __attribute__((always_inline)) {
+        const int col = 16 * ((2 * kk + lg) ^ sw);
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) f.a[ct] = *reinterpret_cast<const v4i*>(st + w_row + ct * 32 * BK + col);
+#pragma unroll
+        for (int tt = 0; tt < MT; ++tt) f.b[tt] = *reinterpret_cast<const v4i*>(st + x_row + tt * 32 * BK + col);
+    };
+    auto multiply = [&](const Frag& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+            for (int tt = 0; tt < MT; ++tt) acc[ct][tt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.a[ct], f.b[tt], acc[ct][tt], 0, 0, 0);
+    };
+    // Stage s: its loads have arrived when at most those of the later stages requested so far (S - 2, fewer at the end)
+    // are outstanding; behind the barrier nobody reads stage s - 1 any more and its buffer takes stage s + S - 1.  Those
+    // loads go out between the multiplies: a compute unit accepts one every few dozen cycles, and in one go they would
+    // hold back the fragment reads of the stage.
+    int buf = 0;
+    for (int s = 0; s < stages; ++s) {
+        const int later = min(S - 2, stages - 1 - s);
+        if (later == 0) arrive<0>();
+        else if (later == 1) arrive<DPW>();
+        else arrive<2 * DPW>();
+        const int8_t* st = lds + buf * STG;
+        if (++buf == S) buf = 0;
+        if (s + 1 < stages || k_last == BK) {
+            constexpr int KS = BK / 32;
+            const bool more = is < stages;
+            Frag f[2];
+            read_frag(f[0], st, 0);
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) {
+                if (kk + 1 < KS) read_frag(f[(kk + 1) & 1], st, kk + 1);
+                if (more) {
+#pragma unroll
+                    for (int i = kk * DPW / KS; i < (kk + 1) * DPW / KS; ++i) issue_one(i);
+                }
+                multiply(f[kk & 1]);
+            }
+            if (more) issue_done();
+        } else {                                          // what is left of K; of its last 32 bytes maybe the first half only
+#pragma unroll 1
+            for (int kk = 0; 32 * kk < k_last; ++kk) {
+                Frag f;
+                read_frag(f, st, kk);
+                if (32 * kk + 16 >= k_last && lg) {
+#pragma unroll
+                    for (int ct = 0; ct < NT; ++ct) f.a[ct] = v4i{0, 0, 0, 0};
+                }
+                multiply(f);
+            }
+        }
+    }
+    static_assert(S >= 2 && S <= 4, "wait counts");
+
+    // ---- epilogue.  32-bit results where every channel of the wavefront has 1 <= c <= 31 and b <= 2^c
+    bool fits = true;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) fits = fits && dyadic_fits32(qb_s[32 * (wn * NT + t) + li], qc_s[32 * (wn * NT + t) + li]);
+    const bool fast = __builtin_amdgcn_ballot_w64(fits) == ~0ull && (EPI != EPI_RESIDUAL || dyadic_fits32(P.res_rq.b, P.res_rq.c));
+    auto finish = [&](auto fastc) __attribute__((always_inline)) {
+        constexpr bool FAST = decltype(fastc)::value;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const int n = n_l + 16 * ct;
+            v4i out[MT];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {                 // 4 channels per packed output word
+                const v4i qb = *reinterpret_cast<const v4i*>(&qb_s[cl + 16 * ct + 4 * d]);
+                const v4i qc = *reinterpret_cast<const v4i*>(&qc_s[cl + 16 * ct + 4 * d]);
+                const v4i bi = *reinterpret_cast<const v4i*>(&bias_s[cl + 16 * ct + 4 * d]);
+#pragma unroll
+                for (int tt = 0; tt < MT; ++tt) {
+                    uint32_t o[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int32_t a32 = acc[ct][tt][4 * d + r] + bi[r];
+                        int32_t rv = 0;
+                        if (EPI == EPI_RESIDUAL) {
+                            if (n + 16 <= N) rv = (int32_t)(int8_t)((uint32_t)res[tt][ct][d] >> (8 * r));
+                            else if (n + 4 * d + r < N && row0 + 32 * tt < rows) rv = P.residual[(m0 + row0 + 32 * tt) * N + n + 4 * d + r];
+                        }
+                        int32_t v;
+                        if (FAST) {
+                            v = rnd_shift_fit32(a32, qb[r], qc[r], P.rnd);
+                            if (EPI == EPI_RESIDUAL) v += rnd_shift_fit32(rv, P.res_rq.b, P.res_rq.c, P.rnd);
+                            v = clamp8(v);
+                        } else {
+                            int64_t r64 = rnd_shift64(a32, qb[r], qc[r], P.rnd);
+                            if (EPI == EPI_RESIDUAL) r64 += rnd_shift64(rv, P.res_rq.b, P.res_rq.c, P.rnd);
+                            v = clamp8_64(r64);
+                        }
+                        if (EPI == EPI_GELU) v = gelu_lut[(uint8_t)v];
+                        o[r] = (uint32_t)v;
+                    }
+                    // low bytes of o[0..3] -> one word
+                    out[tt][d] = (int)(__builtin_amdgcn_perm(o[1], o[0], 0x0c0c0400u) | __builtin_amdgcn_perm(o[3], o[2], 0x04000c0cu));
+                }
+                __builtin_amdgcn_sched_barrier(0);        // keep the register footprint of the epilogue small
+            }
+#pragma unroll
+            for (int tt = 0; tt < MT; ++tt) {
+                if (row0 + 32 * tt >= rows || n >= N) continue;
+                int8_t* yp = P.y + (m0 + row0 + 32 * tt) * N + n;
+                if (n + 16 <= N) {
+                    *reinterpret_cast<v4i_any*>(yp) = out[tt];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 15; ++e)
+                        if (n + e < N) yp[e] = (int8_t)((uint32_t)out[tt][e >> 2] >> (8 * (e & 3)));
+                }
+            }
+        }
+    };
+    if (fast) finish(std::true_type()); else finish(std::false_type());
+}
+
+template <int MT, int NT, int S>
+hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
+    StParams P;
+    P.x = a.x; P.w = a.w; P.bias = a.bias; P.rq_b = a.rq_b; P.rq_c = a.rq_c;
+    P.residual = a.residual; P.res_rq = a.res_rq; P.gelu_p = a.gelu_p; P.gelu_rq = a.gelu_rq;
+    P.y = a.y; P.M = a.M; P.N = a.N; P.K = a.K; P.ldx = a.ldx ? a.ldx : a.K; P.rnd = a.floor_shift ? 0 : 1;
+    P.tiles_n = (a.N + 64 * NT - 1) / (64 * NT);
+    P.tiles = (a.M + 64 * MT - 1) / (64 * MT) * P.tiles_n;
+    P.per_xcd = (P.tiles + NXCD - 1) / NXCD;
+    const int64_t grid = P.per_xcd * NXCD;
+    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 g((unsigned)grid), b(256);
+    if (a.residual) hipLaunchKernelGGL((gemm_st_kernel<EPI_RESIDUAL, MT, NT, S>), g, b, 0, s, P);
+    else if (a.gelu) hipLaunchKernelGGL((gemm_st_kernel<EPI_GELU, MT, NT, S>), g, b, 0, s, P);
+    else hipLaunchKernelGGL((gemm_st_kernel<EPI_PLAIN, MT, NT, S>), g, b, 0, s, P);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
+    // The tile grows with the number of 64 x 64 tiles: larger ones load less per multiply, smaller ones leave no CU idle and
+    // have shorter chains.  Measured with 256 CUs (times with 64 x 64, 128 x 64 and 128 x 128): 1576 x 768 x 3072 (300 tiles)
+    // 12.9, 15.7 and 19.2 us; 3137 x 768 x 768 (600) 6.9, 6.5 and 7.1; 1576 x 2304 x 768 (900) 9.5, 7.4 and 7.6;
+    // 6000 x 1000 x 768 (1504) 12.5, 10.3 and 10.8; 25216 x 1000 x 768 (6304) 44, 36 and 34; with longer rows the larger
+    // tile pays earlier: 6000 x 768 x 3072 (1128) 29.4, 38.6 and 26.7, 3137 x 1000 x 3072 (800) 27.0, 24.3 and 28.8.
+    // Stages: two workgroups of 128 x 128 share a CU with two stages, one with four: 6000 x 1000 x 768 10.8 against 15.3 us;
+    // 64 x 64 with three stages against four (three workgroups per CU against two): 12.5 against 15.5 us.
+    const int64_t tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64), cus = num_cus();
+    if (2 * tiles <= 5 * cus) return launch_tile<1, 1, 3>(s, a);
+    if (tiles * (a.K > 1024 ? 2 : 1) <= 6 * cus) return launch_tile<2, 1, 2>(s, a);
+    return launch_tile<2, 2, 2>(s, a);
+}
+
+}  // namespace ivit

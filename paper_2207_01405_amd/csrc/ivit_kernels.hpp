@@ -40,6 +40,8 @@ hipError_t launch_linear_ks(hipStream_t s, const LinearArgs& a);
 // Long rows, both operands streamed through LDS in 256 x 128 tiles (gemm_tl.hip).
 bool linear_tl_takes(const LinearArgs& a);
 hipError_t launch_linear_tl(hipStream_t s, const LinearArgs& a);
+// Any shape, both operands streamed through LDS in small tiles (gemm_st.hip).
+hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a);
 
 // The token-wise part of an encoder block in one kernel (token_block.hip).
 struct DenseW { const int8_t* w; const int32_t* bias; const int32_t* rq_b; const int32_t* rq_c; };
