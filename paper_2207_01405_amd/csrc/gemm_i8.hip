@@ -1,7 +1,7 @@
 // int8 x int8 -> int32 Dense / MatMul on the gfx950 matrix cores with the dyadic requantisation of
 // I-ViT (arXiv 2207.01405, Sec. 3.2, Eq. 7-10) fused into the epilogue, optionally with the residual
 // add of Eq. 1-2 or with ShiftGELU (Sec. 3.4, Algorithm 2) and its rescale: the weight-stationary kernel for slabs that
-// fit LDS, the kernel for few rows and long K, and the choice between all Dense kernels (launch_linear, at the end).
+// fit LDS, and the choice between all Dense kernels (launch_linear, at the end).
 #include "ivit_kernels.hpp"
 #include <algorithm>
 #include <type_traits>
@@ -429,85 +429,6 @@ __global__ __launch_bounds__(WS_THREADS) void gemm_ws_kernel(WsParams W) {
     }
 }
 
-// ------------------------------------------------------------------------------------------------
-// Kernel for few rows and long K: latency, not throughput, is what counts there.  One
-// workgroup of four wavefronts computes one 32-token x 32-channel tile; the wavefronts split K between them (k-steps
-// w, w + 4, ...), read both operands straight from memory in MFMA layout (16 bytes per lane and k-step; nothing is
-// staged or reused, the whole problem is a few hundred tiles), add their partial tiles through LDS, and the first
-// wavefront requantises with the general 64-bit formulas and writes the 32 x 32 outputs.  Without a residual only.
-constexpr int SM_WAVES = 4, SM_MAXSTEPS = 8;            // k-steps whose loads are in flight together per wavefront
-
-template <int EPI>
-__global__ __launch_bounds__(64 * SM_WAVES) void gemm_small_kernel(GemmParams P) {
-    __shared__ int32_t part[SM_WAVES - 1][16][64];      // partial tiles of wavefronts 1..3, [register][lane]
-    __shared__ int8_t gelu_lut[256];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int li = lane & 31, lg = lane >> 5;
-    const int K = P.K, N = P.N;
-    const int64_t M = P.M;
-    const int tiles_n = (N + 31) / 32;
-    const int64_t tile = blockIdx.x;
-    const int64_t m0 = (tile / tiles_n) * 32;
-    const int n0 = (int)(tile % tiles_n) * 32;
-    if (EPI == EPI_GELU) {
-        const int32_t I = (int32_t)(int8_t)tid;
-        gelu_lut[tid] = (int8_t)requant64(shiftgelu_raw(I, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c, P.rnd);
-    }
-    // rows past the end repeat the last one (their results are not stored); K % 32 == 16: the upper half of the last step is zero
-    const int8_t* xr = P.x + min64(m0 + li, M - 1) * P.ldx + 16 * lg;
-    const int8_t* wr = P.w + (int64_t)min(n0 + li, N - 1) * K + 16 * lg;
-    const int nsteps = (K + 31) / 32;
-    // the first wavefront's requantisation constants are requested before the operands, not after the multiply
-    int32_t qb[16], qc[16], qbias[16];
-    if (wv == 0) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int n = min(n0 + 8 * (i >> 2) + 4 * lg + (i & 3), N - 1);
-            qb[i] = P.rq_b[n]; qc[i] = P.rq_c[n]; qbias[i] = P.bias ? P.bias[n] : 0;
-        }
-    }
-    v16i acc = {};
-    for (int s0 = wv; s0 < nsteps; s0 += SM_WAVES * SM_MAXSTEPS) {
-        v4i xf[SM_MAXSTEPS], wf[SM_MAXSTEPS];
-#pragma unroll
-        for (int u = 0; u < SM_MAXSTEPS; ++u) {
-            const int ks = s0 + u * SM_WAVES;
-            const bool in = ks < nsteps && 32 * ks + 16 * lg < K;
-            const int off = in ? 32 * ks : 0;
-            const v4i xv = *reinterpret_cast<const v4i*>(xr + off - (in ? 0 : 16 * lg));
-            const v4i wv4 = *reinterpret_cast<const v4i*>(wr + off - (in ? 0 : 16 * lg));
-            xf[u] = in ? xv : v4i{0, 0, 0, 0};
-            wf[u] = in ? wv4 : v4i{0, 0, 0, 0};
-        }
-#pragma unroll
-        for (int u = 0; u < SM_MAXSTEPS; ++u) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[u], xf[u], acc, 0, 0, 0);
-    }
-    if (wv > 0) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) part[wv - 1][i][lane] = acc[i];
-    }
-    __syncthreads();
-    if (wv > 0) return;
-    // lane (li, lg): token m0 + li; register i = 4 q + r is channel n0 + 8 q + 4 lg + r
-    const int64_t tok = m0 + li;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = 4 * q + r;
-            const int n = n0 + 8 * q + 4 * lg + r;
-            int32_t a = acc[i] + part[0][i][lane] + part[1][i][lane] + part[2][i][lane];
-            if (tok < M && n < N) {
-                a += qbias[i];
-                const int64_t r64 = rnd_shift64(a, qb[i], qc[i], P.rnd);
-                int32_t v = clamp8_64(r64);
-                if (EPI == EPI_GELU) v = gelu_lut[(uint8_t)v];
-                P.y[tok * N + n] = (int8_t)v;
-            }
-        }
-    }
-}
-
 static bool ws_plan(const LinearArgs& a, int& ncb, int& unit, int& nunits, int& pitch, size_t& lds_bytes) {
     if ((a.N & 15) != 0 || (a.K & 15) != 0) return false;
     unit = a.K % (3 * WS_CHUNK) == 0 ? 3 : 1;
@@ -561,22 +482,14 @@ hipError_t launch_linear(hipStream_t s, const LinearArgs& a) {
     const int64_t bytes = a.M * a.K + (int64_t)a.N * a.K + a.M * a.N * (a.residual ? 2 : 1) + 8LL * a.N + (a.bias ? 4LL * a.N : 0);
     TraceScope trace(s, a.residual ? KIND_GEMM_RESIDUAL : (a.gelu ? KIND_GEMM_GELU : KIND_GEMM), 2 * a.M * a.N * a.K, bytes);
     if (a.kernel == LINEAR_AUTO) {
-        // Few rows and long rows of weights: one workgroup per 32 x 32 tile with K split over its wavefronts, while there is
-        // no more than a tile per CU (197 x 1032 x 2000: 7.6 us against 8.4 with streamed tiles, 64 x 512 x 2000: 6.3 against
-        // 7.7; at K = 1296 it loses, 6.4 against 6.1, and so it does with a residual, 37 x 384 x 1536: 9.2 against 6.9)
-        if (!a.residual && a.K > 1536 && ((a.M + 31) / 32) * ((a.N + 31) / 32) <= num_cus()) {
-            const dim3 g((unsigned)(((a.M + 31) / 32) * ((a.N + 31) / 32))), b(64 * SM_WAVES);
-            if (a.gelu) hipLaunchKernelGGL(gemm_small_kernel<EPI_GELU>, g, b, 0, s, P);
-            else hipLaunchKernelGGL(gemm_small_kernel<EPI_PLAIN>, g, b, 0, s, P);
-            return hipGetLastError();
-        }
         // Up to a few 64 x 64 tiles per CU: streamed tiles (gemm_st.hip).  The kernels below keep weights in registers or LDS
         // or use large tiles, which pays once a workgroup has many rows to apply them to.  Measured with 256 CUs, time with
         // streamed tiles against the kernel it replaces: rows x N = 1576 x 2304 (900 tiles), K = 768: 7.4 against 9.5 us;
-        // 6000 x 768 (1128): 9.2 against 10.5; 4100 x 2304 (2340): 15.2 against 14.0.  With a residual 4100 x 768 (780),
-        // K = 768: 9.1 against 10.5; 6272 x 768 (1176): 14.0 against 12.2; K = 3072, 1576 rows (300): 12.9 against 25.0,
-        // 6000 rows (1128): 26.7 against 27.7, 25216 rows (4728): 80.6 against 77.6.  K = 192 without one, 4100 x 768 (780):
-        // 5.8 against 6.3; 12544 x 576 (1764): 8.6 against 8.1.
+        // 6000 x 768 (1128): 8.8 against 10.5; 4100 x 2304 (2340): 15.2 against 14.0.  With a residual 4100 x 768 (780),
+        // K = 768: 9.1 against 10.5; 6272 x 768 (1176): 14.0 against 12.2; K = 3072, 1576 rows (300): 10.4 against 25.0,
+        // 6000 rows (1128): 27.1 against 27.7, 25216 rows (4728): 80.6 against 77.6.  K = 192 without one, 4100 x 768 (780):
+        // 5.8 against 6.3; 12544 x 576 (1764): 8.6 against 8.1.  One 32 x 32 tile per workgroup with K split over its wavefronts was
+        // no faster even for few rows (197 x 1032 x 2000: 7.6 against 6.6 us, 37 x 384 x 1536 with a residual 9.2 against 6.0).
         const int64_t limit = !a.residual && a.K >= 384 && a.K < 1536 ? 7 : 4;
         if (((a.M + 63) / 64) * ((a.N + 63) / 64) <= limit * num_cus()) return launch_linear_st(s, a);
     }

@@ -146,43 +146,52 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
     // are outstanding; behind the barrier nobody reads stage s - 1 any more and its buffer takes stage s + S - 1.  Those
     // loads go out between the multiplies: a compute unit accepts one every few dozen cycles, and in one go they would
     // hold back the fragment reads of the stage.
+    constexpr int KS = BK / 32, AHEAD = MT * NT == 1 ? KS : 2;      // fragments are read AHEAD k-steps before their use
     int buf = 0;
-    for (int s = 0; s < stages; ++s) {
-        const int later = min(S - 2, stages - 1 - s);
-        if (later == 0) arrive<0>();
-        else if (later == 1) arrive<DPW>();
-        else arrive<2 * DPW>();
+    auto stage = [&](auto more) __attribute__((always_inline)) {
         const int8_t* st = lds + buf * STG;
+        Frag f[AHEAD];
+#pragma unroll
+        for (int kk = 0; kk + 1 < AHEAD; ++kk) read_frag(f[kk], st, kk);
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+            if (kk + AHEAD - 1 < KS) read_frag(f[(kk + AHEAD - 1) % AHEAD], st, kk + AHEAD - 1);
+            if (decltype(more)::value) {
+#pragma unroll
+                for (int i = kk * DPW / KS; i < (kk + 1) * DPW / KS; ++i) issue_one(i);
+            }
+            multiply(f[kk % AHEAD]);
+        }
+        if (decltype(more)::value) issue_done();
         if (++buf == S) buf = 0;
-        if (s + 1 < stages || k_last == BK) {
-            constexpr int KS = BK / 32;
-            const bool more = is < stages;
-            Frag f[2];
-            read_frag(f[0], st, 0);
-#pragma unroll
-            for (int kk = 0; kk < KS; ++kk) {
-                if (kk + 1 < KS) read_frag(f[(kk + 1) & 1], st, kk + 1);
-                if (more) {
-#pragma unroll
-                    for (int i = kk * DPW / KS; i < (kk + 1) * DPW / KS; ++i) issue_one(i);
-                }
-                multiply(f[kk & 1]);
-            }
-            if (more) issue_done();
-        } else {                                          // what is left of K; of its last 32 bytes maybe the first half only
+    };
+    int s = 0;
 #pragma unroll 1
-            for (int kk = 0; 32 * kk < k_last; ++kk) {
-                Frag f;
-                read_frag(f, st, kk);
-                if (32 * kk + 16 >= k_last && lg) {
+    for (; s + S - 1 < stages; ++s) {
+        arrive<(S - 2) * DPW>();
+        stage(std::true_type());
+    }
+#pragma unroll 1
+    for (; s < stages - 1; ++s) {
+        arrive<DPW>();                                    // (S = 3; with two stages there is only the last one left)
+        stage(std::false_type());
+    }
+    arrive<0>();
+    if (k_last == BK) {
+        stage(std::false_type());
+    } else {                                              // what is left of K; of its last 32 bytes maybe the first half only
+#pragma unroll 1
+        for (int kk = 0; 32 * kk < k_last; ++kk) {
+            Frag f;
+            read_frag(f, lds + buf * STG, kk);
+            if (32 * kk + 16 >= k_last && lg) {
 #pragma unroll
-                    for (int ct = 0; ct < NT; ++ct) f.a[ct] = v4i{0, 0, 0, 0};
-                }
-                multiply(f);
+                for (int ct = 0; ct < NT; ++ct) f.a[ct] = v4i{0, 0, 0, 0};
             }
+            multiply(f);
         }
     }
-    static_assert(S >= 2 && S <= 4, "wait counts");
+    static_assert(S >= 2 && S <= 3, "wait counts");
 
     // ---- epilogue.  32-bit results where every channel of the wavefront has 1 <= c <= 31 and b <= 2^c
     bool fits = true;
@@ -269,11 +278,11 @@ hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
 hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
     // The tile grows with the number of 64 x 64 tiles: larger ones load less per multiply, smaller ones leave no CU idle and
     // have shorter chains.  Measured with 256 CUs (times with 64 x 64, 128 x 64 and 128 x 128): 1576 x 768 x 3072 (300 tiles)
-    // 12.9, 15.7 and 19.2 us; 3137 x 768 x 768 (600) 6.9, 6.5 and 7.1; 1576 x 2304 x 768 (900) 9.5, 7.4 and 7.6;
-    // 6000 x 1000 x 768 (1504) 12.5, 10.3 and 10.8; 25216 x 1000 x 768 (6304) 44, 36 and 34; with longer rows the larger
-    // tile pays earlier: 6000 x 768 x 3072 (1128) 29.4, 38.6 and 26.7, 3137 x 1000 x 3072 (800) 27.0, 24.3 and 28.8.
+    // 10.4, 15.9 and 20.1 us; 3137 x 768 x 768 (600) 6.5, 6.6 and 7.3; 1576 x 2304 x 768 (900) 8.8, 7.4 and 7.9;
+    // 6000 x 1000 x 768 (1504) 11.7, 10.3 and 10.9; 25216 x 1000 x 768 (6304) 44, 36 and 34; with longer rows the largest
+    // tile pays earlier: 6000 x 768 x 3072 (1128) 27.2, 38.6 and 27.1, 3137 x 1000 x 3072 (800) 24.7, 24.5 and 29.3.
     // Stages: two workgroups of 128 x 128 share a CU with two stages, one with four: 6000 x 1000 x 768 10.8 against 15.3 us;
-    // 64 x 64 with three stages against four (three workgroups per CU against two): 12.5 against 15.5 us.
+    // 64 x 64 with three stages against four (three workgroups per CU against two): 11.7 against 13.6 us.
     const int64_t tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64), cus = num_cus();
     if (2 * tiles <= 5 * cus) return launch_tile<1, 1, 3>(s, a);
     if (tiles * (a.K > 1024 ? 2 : 1) <= 6 * cus) return launch_tile<2, 1, 2>(s, a);
