@@ -883,7 +883,10 @@ bool token_block_takes(int C, int F, int64_t R) {
     // C = 384: with few tiles a CU spends its time on fetching the layers' 1.7 MB of weights through one workgroup; the
     // separate kernels spread each layer over the chip.  Whole forwards, fused against separate: DeiT-S batch 1 533 against
     // 421 us, 16 (3152 rows) 538 against 509, 24 (4728 rows) 570 against 556, 32 (6304 rows) 591 against 661.
-    if (C == 384 && R < 5120) return false;
+    // A little more than one full round of workgroups (see launch_token_block) is where the separate kernels win once more:
+    // DeiT-S batch 168 (33096 rows) 1737 against 1642 us, 184 (36248) 1861 against 1858, 192 (37824) 1930 against 1988.
+    const int64_t round = 128 * (int64_t)num_cus();
+    if (C == 384 && (R < 5120 || (R > round && R < round + round / 9))) return false;
     return (C == 96 || C == 192 || C == 384) && F >= 2 * FC && F % FC == 0 && R >= 1 && R < (1 << 30) && (int64_t)F * C < (1 << 30);
 }
 
@@ -923,13 +926,27 @@ hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a) {
     const int64_t cus = num_cus(), r = a.R;
     const int64_t per_row = (a.o ? (int64_t)a.C * a.C + 2LL * a.C * a.F : 0) + (a.next == 2 ? 3LL * a.C * a.C : 0);
     TraceScope trace(s, KIND_TOKEN_BLOCK, 2 * r * per_row, per_row + r * a.C * ((a.o ? 3 : 1) + (a.next == 2 ? 3 : a.next == 1 ? 1 : 0)));
-    if (a.C == 384) {
-        if (a.R <= 32 * cus) return launch_tb<384, 1>(s, a);
-        if (a.R <= 64 * cus) return launch_tb<384, 2>(s, a);
-        return launch_tb<384, 4>(s, a);
-    }
-    if (a.C == 192) return a.R <= 64 * cus ? launch_tb<192, 2>(s, a) : launch_tb<192, 4>(s, a);
-    return launch_tb<96, 4>(s, a);
+    auto tile = [&](const TokenBlockArgs& t) -> hipError_t {
+        if (t.C == 384) {
+            if (t.R <= 32 * cus) return launch_tb<384, 1>(s, t);
+            if (t.R <= 64 * cus) return launch_tb<384, 2>(s, t);
+            return launch_tb<384, 4>(s, t);
+        }
+        if (t.C == 192) return t.R <= 64 * cus ? launch_tb<192, 2>(s, t) : launch_tb<192, 4>(s, t);
+        return launch_tb<96, 4>(s, t);
+    };
+    // One workgroup fits a CU (C = 192, 384), so the last round of 128-row tiles takes as long as a full one however few rows
+    // it has: what is left beyond full rounds goes to a launch with tiles of its own size (forwards: DeiT-S batch 192 2220 ->
+    // 1930 us, batch 224 2250 -> 2060 us, DeiT-T batch 200 1042 -> 993 us, Swin-T batch 180 2796 -> 2586 us).
+    const int64_t rest = r % (128 * cus);
+    if (a.C == 96 || r < 128 * cus || rest == 0 || rest > 64 * cus) return tile(a);
+    TokenBlockArgs t = a;
+    t.R = r - rest;
+    if (hipError_t e = tile(t)) return e;
+    t.R = rest;
+    auto skip = [&](auto& p, int64_t width) { if (p) p += (r - rest) * width; };
+    skip(t.o, a.C); skip(t.x, a.C); skip(t.xhat, a.C); skip(t.y, a.C); skip(t.out, a.next == 2 ? 3 * a.C : a.C);
+    return tile(t);
 }
 
 }  // namespace ivit

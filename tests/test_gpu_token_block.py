@@ -90,3 +90,16 @@ def test_parameter_arrays_at_four_byte_alignment(ivit):
     ivit.ivit_encoder_block(xd, y, p, d, torch.empty(ivit.ivit_workspace_bytes(d), dtype=torch.uint8, device="cuda"))
     torch.cuda.synchronize()
     assert np.array_equal(y.cpu().numpy(), orc.encoder_block(x, blocks[0], d))
+
+
+@pytest.mark.parametrize("C,H,F", [(192, 3, 256), (384, 6, 256)])
+@pytest.mark.parametrize("rows_per_cu,more", [(128, 0), (128, 31), (144, 5), (192, 0), (192, 1), (256, 33)])
+def test_rows_beyond_full_rounds_of_workgroups(ivit, C, H, F, rows_per_cu, more):
+    import torch
+    R = rows_per_cu * torch.cuda.get_device_properties(0).multi_processor_count + more
+    d = dict(B=R, T=1, C=C, H=H, F=F)
+    cfg, blocks = _blocks(C, H, F, 1, 2, "as drawn")
+    x = synth.make_rows(5, R, C)
+    for final_ln in (None, synth.make_final_ln(cfg)):
+        got, want = _run(ivit, d, x, blocks, final_ln)
+        assert np.array_equal(got, want), "%d of %d differ" % ((got != want).sum(), got.size)
