@@ -348,7 +348,9 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
                 // stores after the stage before last, the request of the last stage, its loads, the stores after it, the
                 // request of this stage), and once every wavefront is here nobody reads this stage's buffer any more (all
                 // its fragments are in registers: the barrier waits for the LDS reads too)
-                wait_vm<DPW + (U >= 2 && U % 2 == 1 ? extras(U - 2) : 0) + (U >= 1 ? extras(U - 1) : 0) + extras(U)>();
+                // (the stores of an odd U follow its stage: they are not out yet and must not be counted here, or the last two
+                // loads of the next stage may still be missing)
+                wait_vm<DPW + (U >= 2 && U % 2 == 1 ? extras(U - 2) : 0) + (U >= 1 ? extras(U - 1) : 0) + (U % 2 == 0 ? extras(U) : 0)>();
                 __syncthreads();
             }
             read_frags(kk < 2 ? cur : nxt, (kk + 2) % 4);
