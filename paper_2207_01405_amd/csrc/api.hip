@@ -123,13 +123,22 @@ hipError_t run_block(hipStream_t s, const int8_t* x, int8_t* y, const ivit_block
     auto tap = [&](int8_t* dst, const int8_t* src, size_t n) -> hipError_t {
         return dst ? hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToDevice, s) : hipSuccess;
     };
-    // u = LN1(x)
-    if ((e = ivit::launch_ilayernorm(s, x, p->ln1_gamma, p->ln1_beta, w.u, R, C, p->ln1_f_bits, p->ln1_c_shift))) return e;
-    if (taps && (e = tap(taps->u, w.u, (size_t)R * C))) return e;
-    // qkv = Dense(u)
+    // the I-LayerNorm ahead of a Dense layer: inside its kernel, or into the u buffer
+    auto normalise = [&](ivit::LinearArgs& a, const int8_t* rows, const int32_t* g, const int32_t* b, int f, int c) -> hipError_t {
+        if (!taps && ivit::linear_ln_takes(a)) {
+            a.x = rows; a.ln_g = g; a.ln_b = b; a.ln_f = f; a.ln_c = c;
+            return hipSuccess;
+        }
+        a.x = w.u;
+        return ivit::launch_ilayernorm(s, rows, g, b, w.u, R, C, f, c);
+    };
+    // u = LN1(x), qkv = Dense(u)
     ivit::LinearArgs la{};
-    la.x = w.u; la.w = p->w_qkv; la.bias = p->bias_qkv; la.rq_b = p->qkv_rq_b; la.rq_c = p->qkv_rq_c;
-    la.residual = nullptr; la.gelu = false; la.y = w.qkv; la.M = R; la.N = 3 * C; la.K = C;
+    la.M = R; la.N = 3 * C; la.K = C;
+    if ((e = normalise(la, x, p->ln1_gamma, p->ln1_beta, p->ln1_f_bits, p->ln1_c_shift))) return e;
+    if (taps && (e = tap(taps->u, w.u, (size_t)R * C))) return e;
+    la.w = p->w_qkv; la.bias = p->bias_qkv; la.rq_b = p->qkv_rq_b; la.rq_c = p->qkv_rq_c;
+    la.residual = nullptr; la.gelu = false; la.y = w.qkv;
     if ((e = ivit::launch_linear(s, la))) return e;
     if (taps && (e = tap(taps->qkv, w.qkv, (size_t)R * 3 * C))) return e;
     // o = attention(qkv)
@@ -141,14 +150,14 @@ hipError_t run_block(hipStream_t s, const int8_t* x, int8_t* y, const ivit_block
     la.residual = x; la.res_rq = dy(p->res1_rq); la.gelu = false; la.y = w.xhat; la.M = R; la.N = C; la.K = C;
     if ((e = ivit::launch_linear(s, la))) return e;
     if (taps && (e = tap(taps->xhat, w.xhat, (size_t)R * C))) return e;
-    // v = LN2(xhat)   (reuses the u buffer)
-    if ((e = ivit::launch_ilayernorm(s, w.xhat, p->ln2_gamma, p->ln2_beta, w.u, R, C, p->ln2_f_bits, p->ln2_c_shift))) return e;
-    if (taps && (e = tap(taps->v, w.u, (size_t)R * C))) return e;
-    // h = ShiftGELU(Dense(v))
+    // v = LN2(xhat) (reuses the u buffer), h = ShiftGELU(Dense(v))
     la = ivit::LinearArgs{};
-    la.x = w.u; la.w = p->w_fc1; la.bias = p->bias_fc1; la.rq_b = p->fc1_rq_b; la.rq_c = p->fc1_rq_c;
+    la.M = R; la.N = F; la.K = C;
+    if ((e = normalise(la, w.xhat, p->ln2_gamma, p->ln2_beta, p->ln2_f_bits, p->ln2_c_shift))) return e;
+    if (taps && (e = tap(taps->v, w.u, (size_t)R * C))) return e;
+    la.w = p->w_fc1; la.bias = p->bias_fc1; la.rq_b = p->fc1_rq_b; la.rq_c = p->fc1_rq_c;
     la.residual = nullptr; la.gelu = true; la.gelu_p = sp(p->gelu); la.gelu_rq = dy(p->gelu_rq);
-    la.y = w.h; la.M = R; la.N = F; la.K = C;
+    la.y = w.h;
     if ((e = ivit::launch_linear(s, la))) return e;
     if (taps && (e = tap(taps->h, w.h, (size_t)R * F))) return e;
     // y = Dense(h) + xhat

@@ -481,6 +481,7 @@ hipError_t launch_linear(hipStream_t s, const LinearArgs& a) {
     P.y = a.y; P.M = a.M; P.N = a.N; P.K = a.K; P.ldx = a.ldx ? a.ldx : a.K; P.rnd = a.floor_shift ? 0 : 1;
     const int64_t bytes = a.M * a.K + (int64_t)a.N * a.K + a.M * a.N * (a.residual ? 2 : 1) + 8LL * a.N + (a.bias ? 4LL * a.N : 0);
     TraceScope trace(s, a.residual ? KIND_GEMM_RESIDUAL : (a.gelu ? KIND_GEMM_GELU : KIND_GEMM), 2 * a.M * a.N * a.K, bytes);
+    if (a.ln_g) return launch_linear_st(s, a);
     if (a.kernel == LINEAR_AUTO) {
         // Up to a few 64 x 64 tiles per CU: streamed tiles (gemm_st.hip).  The kernels below keep weights in registers or LDS
         // or use large tiles, which pays once a workgroup has many rows to apply them to.  Measured with 256 CUs, time with

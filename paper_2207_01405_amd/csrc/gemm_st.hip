@@ -26,8 +26,10 @@ struct StParams {
     int8_t* y; int64_t M; int N; int K; int tiles_n; int64_t tiles; int64_t per_xcd;
     int64_t ldx;                              // bytes between rows of x
     int rnd;                                  // 1: round to nearest, 0: floor (every requantisation of the epilogue)
+    const int32_t* ln_g; const int32_t* ln_b; int ln_f, ln_c;   // XS > 0: I-LayerNorm of the rows of x
 };
 
+typedef int v4i_w __attribute__((ext_vector_type(4), aligned(4)));     // 16 bytes at any address of words
 typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));   // 16 bytes at any address
 
 // 4 bytes per lane from global memory into LDS (as dma16 of regst_common.hpp)
@@ -41,15 +43,25 @@ template <int N> __device__ __forceinline__ void arrive() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
 }
 
-template <int EPI, int MT, int NT, int S>
+// XS > 0: the rows of x are normalised first (I-LayerNorm, Sec. 3.5, Eq. 19-20).  The token rows of the tile, all of K
+// (K <= 128 XS), are fetched at once and stay in LDS, where they are normalised in place; only the weights stream.  Every
+// workgroup of a row of tiles repeats that work, so the four wavefronts stand side by side: 32 tokens x 128 channels.
+template <int MT, int NT, int XS> struct StTile {
+    static constexpr int WGM = XS > 0 ? 1 : 2, WGN = 4 / WGM, TM = 32 * MT * WGM, TN = 32 * NT * WGN;
+};
+
+template <int EPI, int MT, int NT, int S, int XS>
 __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
-    constexpr int TM = 64 * MT, TN = 64 * NT, STG = (TM + TN) * BK, XI = 2 * MT, DPW = 2 * (MT + NT);
-    __shared__ __align__(16) int8_t lds[S * STG];
+    using TL = StTile<MT, NT, XS>;
+    constexpr int TM = TL::TM, TN = TL::TN, XI = TM / 32;
+    constexpr int DPX = XS > 0 ? 0 : XI, DPW = DPX + TN / 32;           // load instructions of a wavefront and streamed stage: of x, in all
+    constexpr int XB = XS * TM * BK, WR = XS > 0 ? 0 : TM, STG = (WR + TN) * BK;    // resident bytes of x; rows of x in a streamed stage
+    __shared__ __align__(16) int8_t lds[XB + S * STG];
     __shared__ __align__(16) int32_t qb_s[TN], qc_s[TN], bias_s[TN];
     __shared__ int8_t gelu_lut[256];
 
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int li = lane & 31, lg = lane >> 5, wm = wv >> 1, wn = wv & 1;
+    const int li = lane & 31, lg = lane >> 5, wm = wv / TL::WGN, wn = wv % TL::WGN;
 
     // each XCD takes a contiguous range of tiles; within it the channel tile index runs fastest
     const int64_t tile = (int64_t)(blockIdx.x % NXCD) * P.per_xcd + blockIdx.x / NXCD;
@@ -76,9 +88,20 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
         const int32_t* src = wv == 0 ? P.rq_b : wv == 1 ? P.rq_c : P.bias;
         int32_t* dst = wv == 0 ? qb_s : wv == 1 ? qc_s : bias_s;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
+        for (int t = 0; t < TN / 64; ++t) {
             if (src) dma4(uniform_ptr(reinterpret_cast<const int8_t*>(src)), 4u * min(n0 + 64 * t + lane, N - 1), lds_offset(reinterpret_cast<const int8_t*>(dst + 64 * t)));
             else dst[64 * t + lane] = 0;
+        }
+    }
+
+    // I-LayerNorm: a thread normalises piece n_p of rows n_r, n_r + n_rows, ...; its 16 channels' parameters are requested now
+    const int pieces = K >> 4, n_rows = 256 / max(pieces, 4), n_r = tid / pieces, n_p = tid - n_r * pieces;
+    v4i g[4] = {}, bt[4] = {};
+    if (XS > 0 && n_r < n_rows) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            g[e] = *reinterpret_cast<const v4i_w*>(P.ln_g + 16 * n_p + 4 * e);
+            bt[e] = *reinterpret_cast<const v4i_w*>(P.ln_b + 16 * n_p + 4 * e);
         }
     }
 
@@ -88,9 +111,9 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
     const int ld_r = 8 * wv + (lane >> 3), ld_col = 16 * ((lane & 7) ^ ((ld_r >> 1) & 7));
     const int8_t* xg = uniform_ptr(P.x + m0 * P.ldx);
     const int8_t* wg = uniform_ptr(P.w + (int64_t)n0 * K);
-    uint32_t off[DPW];
+    uint32_t off[XI + TN / 32];
 #pragma unroll
-    for (int i = 0; i < DPW; ++i) {
+    for (int i = 0; i < XI + TN / 32; ++i) {
         if (i < XI) {
             off[i] = (uint32_t)min(32 * i + ld_r, rows - 1) * (uint32_t)P.ldx + ld_col;
         } else {
@@ -102,12 +125,20 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
         }
     }
     const int stages = (K + BK - 1) / BK, k_last = K - (stages - 1) * BK;      // bytes of K in the last stage: 16 .. 128
-    const uint32_t lds0 = lds_offset(lds) + wv * 1024;
+    const uint32_t lds0 = lds_offset(lds) + XB + wv * 1024;
+    if (XS > 0) {
+#pragma unroll 1
+        for (int s = 0; s < stages; ++s) {
+            const uint32_t back = s == stages - 1 ? (uint32_t)max(ld_col - (k_last - 16), 0) : 0u;
+#pragma unroll
+            for (int i = 0; i < XI; ++i) dma16(xg + s * BK, off[i] - back, lds0 - XB + s * TM * BK + i * 4096);
+        }
+    }
     // the stage being requested: its number, bases and buffer, and how far a lane's piece moves back (last stage only)
     int is = 0, is_buf = 0;
     auto issue_one = [&](int i) __attribute__((always_inline)) {
         const uint32_t back = is == stages - 1 ? (uint32_t)max(ld_col - (k_last - 16), 0) : 0u;
-        dma16(i < XI ? xg : wg, off[i] - back, lds0 + is_buf * STG + i * 4096);
+        dma16(i < DPX ? xg : wg, off[XI - DPX + i] - back, lds0 + is_buf * STG + i * 4096);
     };
     auto issue_done = [&]() __attribute__((always_inline)) {
         ++is;
@@ -126,15 +157,69 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
         gelu_lut[tid] = (int8_t)requant64(shiftgelu_raw(I, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c, P.rnd);
     }
 
+    if constexpr (XS > 0) {
+        __shared__ int2 stat[TM];                          // (mean, f) of a row
+        if (stages >= S - 1) arrive<(S - 1) * DPW>(); else arrive<0>();
+        auto at = [&](int row, int p) __attribute__((always_inline)) {      // piece p of a row
+            return reinterpret_cast<v4i*>(lds + (p >> 3) * TM * BK + row * BK + 16 * ((p & 7) ^ ((row >> 1) & 7)));
+        };
+        constexpr int TPR = 256 / TM;                      // threads that add up a row
+        static_assert(TPR == 8, "lanes of a row");
+        const int row = tid / TPR;
+        int32_t sm = 0, sq = 0;
+        for (int p = tid % TPR; p < pieces; p += TPR) {
+            const v4i v = *at(row, p);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                sm = __builtin_amdgcn_sdot4(v[d], 0x01010101, sm, false);
+                sq = __builtin_amdgcn_sdot4(v[d], v[d], sq, false);
+            }
+        }
+        sm += dpp_i32<0xB1>(sm); sq += dpp_i32<0xB1>(sq);
+        sm += dpp_i32<0x4E>(sm); sq += dpp_i32<0x4E>(sq);
+        sm += dpp_i32<0x141>(sm); sq += dpp_i32<0x141>(sq);
+        // (the ranges that let one reciprocal and a repair step settle these divisions: see ilayernorm_tiled_kernel)
+        const int32_t mean = floordiv_small(sm + (K >> 1), K);
+        const uint32_t var = div_small_quotient((uint32_t)(sq - 2 * mean * sm + K * mean * mean), (uint32_t)K);
+        const int32_t f = (int32_t)div_small(1u << P.ln_f, max(isqrt10(var), 1u));
+        if (tid % TPR == 0) stat[row] = make_int2(mean, f);
+        __syncthreads();
+        if (n_r < n_rows) {
+            const int32_t half = 1 << (P.ln_c - 1);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) bt[e][r] = (int32_t)((uint32_t)bt[e][r] + (uint32_t)half);
+#pragma unroll 1
+            for (int i = n_r; i < TM; i += n_rows) {
+                const int2 mf = stat[i];
+                const v4i v = *at(i, n_p);
+                v4i w;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    uint32_t o[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int32_t xe = (int32_t)(int8_t)((uint32_t)v[d] >> (8 * r));
+                        o[r] = (uint32_t)clamp8((__mul24(mul_i24(xe - mf.x, g[d][r]), mf.y) + bt[d][r]) >> P.ln_c);
+                    }
+                    w[d] = (int)(__builtin_amdgcn_perm(o[1], o[0], 0x0c0c0400u) | __builtin_amdgcn_perm(o[3], o[2], 0x04000c0cu));
+                }
+                *at(i, n_p) = w;
+            }
+        }
+        // (the barrier of the first stage is the one that makes the normalised rows everybody's)
+    }
+
     v16i acc[NT][MT] = {};
-    const int x_row = row0 * BK, w_row = (TM + wn * 32 * NT + li) * BK, sw = (li >> 1) & 7;
+    const int x_row = row0 * BK, w_row = (WR + wn * 32 * NT + li) * BK, sw = (li >> 1) & 7;
     struct Frag { v4i a[NT], b[MT]; };
-    auto read_frag = [&](Frag& f, const int8_t* st, int kk) __attribute__((always_inline)) {
+    auto read_frag = [&](Frag& f, const int8_t* xs, const int8_t* st, int kk) __attribute__((always_inline)) {
         const int col = 16 * ((2 * kk + lg) ^ sw);
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) f.a[ct] = *reinterpret_cast<const v4i*>(st + w_row + ct * 32 * BK + col);
 #pragma unroll
-        for (int tt = 0; tt < MT; ++tt) f.b[tt] = *reinterpret_cast<const v4i*>(st + x_row + tt * 32 * BK + col);
+        for (int tt = 0; tt < MT; ++tt) f.b[tt] = *reinterpret_cast<const v4i*>(xs + x_row + tt * 32 * BK + col);
     };
     auto multiply = [&](const Frag& f) __attribute__((always_inline)) {
 #pragma unroll
@@ -147,15 +232,16 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
     // loads go out between the multiplies: a compute unit accepts one every few dozen cycles, and in one go they would
     // hold back the fragment reads of the stage.
     constexpr int KS = BK / 32, AHEAD = MT * NT == 1 ? KS : 2;      // fragments are read AHEAD k-steps before their use
-    int buf = 0;
+    int buf = 0, s = 0;
     auto stage = [&](auto more) __attribute__((always_inline)) {
-        const int8_t* st = lds + buf * STG;
+        const int8_t* st = lds + XB + buf * STG;
+        const int8_t* xs = XS > 0 ? lds + s * TM * BK : st;
         Frag f[AHEAD];
 #pragma unroll
-        for (int kk = 0; kk + 1 < AHEAD; ++kk) read_frag(f[kk], st, kk);
+        for (int kk = 0; kk + 1 < AHEAD; ++kk) read_frag(f[kk], xs, st, kk);
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
-            if (kk + AHEAD - 1 < KS) read_frag(f[(kk + AHEAD - 1) % AHEAD], st, kk + AHEAD - 1);
+            if (kk + AHEAD - 1 < KS) read_frag(f[(kk + AHEAD - 1) % AHEAD], xs, st, kk + AHEAD - 1);
             if (decltype(more)::value) {
 #pragma unroll
                 for (int i = kk * DPW / KS; i < (kk + 1) * DPW / KS; ++i) issue_one(i);
@@ -165,7 +251,6 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
         if (decltype(more)::value) issue_done();
         if (++buf == S) buf = 0;
     };
-    int s = 0;
 #pragma unroll 1
     for (; s + S - 1 < stages; ++s) {
         arrive<(S - 2) * DPW>();
@@ -183,7 +268,7 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
 #pragma unroll 1
         for (int kk = 0; 32 * kk < k_last; ++kk) {
             Frag f;
-            read_frag(f, lds + buf * STG, kk);
+            read_frag(f, XS > 0 ? lds + s * TM * BK : lds + XB + buf * STG, lds + XB + buf * STG, kk);
             if (32 * kk + 16 >= k_last && lg) {
 #pragma unroll
                 for (int ct = 0; ct < NT; ++ct) f.a[ct] = v4i{0, 0, 0, 0};
@@ -255,27 +340,45 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
     if (fast) finish(std::true_type()); else finish(std::false_type());
 }
 
-template <int MT, int NT, int S>
+template <int MT, int NT, int S, int XS>
 hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
     StParams P;
     P.x = a.x; P.w = a.w; P.bias = a.bias; P.rq_b = a.rq_b; P.rq_c = a.rq_c;
     P.residual = a.residual; P.res_rq = a.res_rq; P.gelu_p = a.gelu_p; P.gelu_rq = a.gelu_rq;
     P.y = a.y; P.M = a.M; P.N = a.N; P.K = a.K; P.ldx = a.ldx ? a.ldx : a.K; P.rnd = a.floor_shift ? 0 : 1;
-    P.tiles_n = (a.N + 64 * NT - 1) / (64 * NT);
-    P.tiles = (a.M + 64 * MT - 1) / (64 * MT) * P.tiles_n;
+    P.ln_g = a.ln_g; P.ln_b = a.ln_b; P.ln_f = a.ln_f; P.ln_c = a.ln_c;
+    constexpr int TM = StTile<MT, NT, XS>::TM, TN = StTile<MT, NT, XS>::TN;
+    P.tiles_n = (a.N + TN - 1) / TN;
+    P.tiles = (a.M + TM - 1) / TM * P.tiles_n;
     P.per_xcd = (P.tiles + NXCD - 1) / NXCD;
     const int64_t grid = P.per_xcd * NXCD;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 g((unsigned)grid), b(256);
-    if (a.residual) hipLaunchKernelGGL((gemm_st_kernel<EPI_RESIDUAL, MT, NT, S>), g, b, 0, s, P);
-    else if (a.gelu) hipLaunchKernelGGL((gemm_st_kernel<EPI_GELU, MT, NT, S>), g, b, 0, s, P);
-    else hipLaunchKernelGGL((gemm_st_kernel<EPI_PLAIN, MT, NT, S>), g, b, 0, s, P);
+    if constexpr (XS == 0) {
+        if (a.residual) {
+            hipLaunchKernelGGL((gemm_st_kernel<EPI_RESIDUAL, MT, NT, S, XS>), g, b, 0, s, P);
+            return hipGetLastError();
+        }
+    }
+    if (a.gelu) hipLaunchKernelGGL((gemm_st_kernel<EPI_GELU, MT, NT, S, XS>), g, b, 0, s, P);
+    else hipLaunchKernelGGL((gemm_st_kernel<EPI_PLAIN, MT, NT, S, XS>), g, b, 0, s, P);
     return hipGetLastError();
 }
 
 }  // namespace
 
+// Up to two of these tiles per CU the repeated normalisation takes less than the launch it saves, beyond that more.  Forwards
+// with it against without: DeiT-S batch 1 357 against 386 us, batch 4 374 against 396, ViT-B batch 1 455 against 473, Swin-S
+// batch 2 760 against 807, batch 8 873 against 881; with up to four tiles per CU ViT-B batch 4 560 against 518, Swin-S batch 8
+// 917 against 881.  With 64 x 64 tiles, twice the rows to normalise: DeiT-S batch 1 390, ViT-B batch 1 515 us.
+bool linear_ln_takes(const LinearArgs& a) {
+    using TL = StTile<1, 1, 6>;
+    return !a.residual && (a.K & 15) == 0 && a.K >= 64 && a.K <= 768 &&
+           ((a.M + TL::TM - 1) / TL::TM) * ((a.N + TL::TN - 1) / TL::TN) <= 2 * num_cus();
+}
+
 hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
+    if (a.ln_g) return a.K <= 384 ? launch_tile<1, 1, 3, 3>(s, a) : launch_tile<1, 1, 3, 6>(s, a);
     // The tile grows with the number of 64 x 64 tiles: larger ones load less per multiply, smaller ones leave no CU idle and
     // have shorter chains.  Measured with 256 CUs (times with 64 x 64, 128 x 64 and 128 x 128): 1576 x 768 x 3072 (300 tiles)
     // 10.4, 15.9 and 20.1 us; 3137 x 768 x 768 (600) 6.5, 6.6 and 7.3; 1576 x 2304 x 768 (900) 8.8, 7.4 and 7.9;
@@ -284,9 +387,9 @@ hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
     // Stages: two workgroups of 128 x 128 share a CU with two stages, one with four: 6000 x 1000 x 768 10.8 against 15.3 us;
     // 64 x 64 with three stages against four (three workgroups per CU against two): 11.7 against 13.6 us.
     const int64_t tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64), cus = num_cus();
-    if (2 * tiles <= 5 * cus) return launch_tile<1, 1, 3>(s, a);
-    if (tiles * (a.K > 1024 ? 2 : 1) <= 6 * cus) return launch_tile<2, 1, 2>(s, a);
-    return launch_tile<2, 2, 2>(s, a);
+    if (2 * tiles <= 5 * cus) return launch_tile<1, 1, 3, 0>(s, a);
+    if (tiles * (a.K > 1024 ? 2 : 1) <= 6 * cus) return launch_tile<2, 1, 2, 0>(s, a);
+    return launch_tile<2, 2, 2, 0>(s, a);
 }
 
 }  // namespace ivit

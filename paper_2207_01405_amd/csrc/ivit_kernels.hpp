@@ -28,6 +28,8 @@ struct LinearArgs {
     int64_t ldx;                         // bytes between rows of x; 0 means K (dense rows)
     int kernel;                          // 0: chosen from the shape; otherwise one of LinearKernel, forced (tests, measurements)
     int floor_shift;                     // 0: requantisations round to nearest (Eq. 8 through Eq. 10); 1: bare shift of Eq. 10 (floor)
+    // an I-LayerNorm over the rows of x first (K = its C; only where linear_ln_takes says so); nullptr: none
+    const int32_t* ln_g; const int32_t* ln_b; int ln_f, ln_c;
 };
 enum LinearKernel { LINEAR_AUTO = 0, LINEAR_MANY_ROWS = 1, LINEAR_REG_STATIONARY = 2, LINEAR_BIG_TILES = 3 };
 hipError_t launch_linear(hipStream_t s, const LinearArgs& a);
@@ -42,6 +44,7 @@ bool linear_tl_takes(const LinearArgs& a);
 hipError_t launch_linear_tl(hipStream_t s, const LinearArgs& a);
 // Any shape, both operands streamed through LDS in small tiles (gemm_st.hip).
 hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a);
+bool linear_ln_takes(const LinearArgs& a);
 
 // The token-wise part of an encoder block in one kernel (token_block.hip).
 struct DenseW { const int8_t* w; const int32_t* bias; const int32_t* rq_b; const int32_t* rq_c; };

@@ -69,3 +69,20 @@ def test_larger_tiles(ivit, M, N, K, epi, regime):
     if epi == "residual":
         kw_o["residual"] = kw_o["residual"][rows]
     assert np.array_equal(got[rows], orc.linear_requant(host[0][rows], *host[1:], **kw_o))
+
+
+@pytest.mark.parametrize("C,H,F", [(64, 2, 256), (96, 3, 144), (128, 4, 208), (160, 5, 64), (384, 6, 1536), (416, 13, 400), (736, 23, 272), (768, 12, 3072)])
+@pytest.mark.parametrize("B,T", [(1, 1), (3, 21), (5, 13), (2, 65)])
+def test_layernorm_inside_the_dense_kernel(ivit, C, H, F, B, T):
+    """A block whose I-LayerNorms run in the kernels of the QKV and the first MLP layer, against the oracle."""
+    import torch
+    d = dict(B=B, T=T, C=C, H=H, F=F)
+    p = synth.make_block(dict(T=T, C=C, H=H, F=F, seed=C + F, i0="fixed", rel_bias=False), 0)
+    x = synth.make_rows(17 + C, B * T, C)
+    x[0] = 5                                                 # a constant row: variance 0
+    x[-1, ::2] = -128                                        # the largest variance
+    x[-1, 1::2] = 127
+    xd, y = torch.from_numpy(x).cuda(), torch.empty((B * T, C), dtype=torch.int8, device="cuda")
+    ivit.ivit_encoder_block(xd, y, ivit.to_device(p), d, torch.empty(ivit.ivit_workspace_bytes(d), dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy(), orc.encoder_block(x, p, d))
