@@ -3,6 +3,7 @@
 // add of Eq. 1-2 or with ShiftGELU (Sec. 3.4, Algorithm 2) and its rescale: the weight-stationary kernel for slabs that
 // fit LDS, and the choice between all Dense kernels (launch_linear, at the end).
 #include "ivit_kernels.hpp"
+#include "linear_rows.hpp"
 #include <algorithm>
 #include <type_traits>
 
@@ -475,6 +476,20 @@ static void launch_ws(hipStream_t s, const WsParams& W, int ncb, int unit, int g
 
 hipError_t launch_linear(hipStream_t s, const LinearArgs& a) {
     if (a.M == 0) return hipSuccess;
+    // Rows too far apart for one launch (a classifier head over images of 16 MB and more): a launch for each few of them,
+    // 135 at most for a tensor that fits this part's memory.
+    const int64_t most = linear_rows_per_launch(a.ldx ? a.ldx : a.K, a.K);
+    if (a.M > most) {
+        LinearArgs part = a;
+        for (int64_t m = 0; m < a.M; m += most) {
+            part.M = std::min(most, a.M - m);
+            part.x = a.x + m * a.ldx;
+            part.residual = a.residual ? a.residual + m * a.N : nullptr;
+            part.y = a.y + m * a.N;
+            if (hipError_t e = launch_linear(s, part)) return e;
+        }
+        return hipSuccess;
+    }
     GemmParams P;
     P.x = a.x; P.w = a.w; P.bias = a.bias; P.rq_b = a.rq_b; P.rq_c = a.rq_c;
     P.residual = a.residual; P.res_rq = a.res_rq; P.gelu_p = a.gelu_p; P.gelu_rq = a.gelu_rq;

@@ -11,6 +11,7 @@
 // whatever alignment the row has.
 #include <type_traits>
 
+#include "linear_rows.hpp"
 #include "regst_common.hpp"
 
 namespace ivit {
@@ -105,6 +106,7 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
         }
     }
 
+    // (32-bit offsets from the tile's first row: linear_rows_per_launch sees to it that they are enough)
     // Load instruction i of a wavefront fills LDS rows 32 i + r, r = 8 wavefront + lane / 8, eight lanes a row; the lane
     // lands in physical piece lane % 8 and fetches piece (lane % 8) ^ ((r / 2) % 8).  Rows past the last token or channel
     // repeat it (never stored), pieces past the end of a row its last piece (never multiplied, see below).
@@ -348,6 +350,7 @@ hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
     P.y = a.y; P.M = a.M; P.N = a.N; P.K = a.K; P.ldx = a.ldx ? a.ldx : a.K; P.rnd = a.floor_shift ? 0 : 1;
     P.ln_g = a.ln_g; P.ln_b = a.ln_b; P.ln_f = a.ln_f; P.ln_c = a.ln_c;
     constexpr int TM = StTile<MT, NT, XS>::TM, TN = StTile<MT, NT, XS>::TN;
+    static_assert(TM <= kTileRows, "row offsets");
     P.tiles_n = (a.N + TN - 1) / TN;
     P.tiles = (a.M + TM - 1) / TM * P.tiles_n;
     P.per_xcd = (P.tiles + NXCD - 1) / NXCD;
