@@ -349,9 +349,10 @@ __global__ __launch_bounds__(WS_THREADS) void gemm_ws_kernel(WsParams W) {
                         int32_t v = (int32_t)__builtin_amdgcn_alignbit((uint32_t)(pr >> 32), (uint32_t)pr, qc[r]);
                         if (EPI == EPI_RESIDUAL) {
                             const int32_t res = (int32_t)(int8_t)((uint32_t)resv[w4] >> (8 * r));
-                            v += rnd_shift_fit32(res, P.res_rq.b, P.res_rq.c, P.rnd);
+                            v = clamp8_sum(v, rnd_shift_fit32(res, P.res_rq.b, P.res_rq.c, P.rnd));
+                        } else {
+                            v = clamp8(v);
                         }
-                        v = clamp8(v);
                         if (EPI == EPI_GELU) v = gelu_lut[(uint8_t)v];
                         o[r] = (uint32_t)v;
                     }

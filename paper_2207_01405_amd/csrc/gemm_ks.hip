@@ -286,7 +286,7 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(KsParams P) {
                 const int32_t t1 = residual64_first(a[4 * d + r], c_lo, c_hi, c_mb, c_ad);
                 const int32_t res = (int32_t)(int8_t)((uint32_t)rw[d >> 1][d & 1] >> (8 * r));
                 const int32_t t2 = (__mul24(res, rb) + rh) >> rc;
-                o[r] = (uint32_t)clamp8(t1 + t2);
+                o[r] = (uint32_t)clamp8_sum(t1, t2);
             } else {
                 const int32_t m = med3(a[4 * d + r], c_lo, c_hi);
                 o[r] = (uint32_t)(__mul24(m, c_mb) + c_ad);                       // result in the top byte

@@ -310,8 +310,7 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
                         int32_t v;
                         if (FAST) {
                             v = rnd_shift_fit32(a32, qb[r], qc[r], P.rnd);
-                            if (EPI == EPI_RESIDUAL) v += rnd_shift_fit32(rv, P.res_rq.b, P.res_rq.c, P.rnd);
-                            v = clamp8(v);
+                            v = EPI == EPI_RESIDUAL ? clamp8_sum(v, rnd_shift_fit32(rv, P.res_rq.b, P.res_rq.c, P.rnd)) : clamp8(v);
                         } else {
                             int64_t r64 = rnd_shift64(a32, qb[r], qc[r], P.rnd);
                             if (EPI == EPI_RESIDUAL) r64 += rnd_shift64(rv, P.res_rq.b, P.res_rq.c, P.rnd);

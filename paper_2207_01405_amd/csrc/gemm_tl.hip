@@ -241,7 +241,7 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
                 const int32_t t1 = residual64_first(prev[mt][cb][4 * d + r], c_lo[cb], c_hi[cb], c_mb[cb], c_ad[cb]);
                 const int32_t res = (int32_t)(int8_t)((uint32_t)rw[d >> 1][d & 1] >> (8 * r));
                 const int32_t t2 = (__mul24(res, rb) + rh) >> rc;
-                o = (uint32_t)clamp8(t1 + t2) & 0xffu;
+                o = (uint32_t)clamp8_sum(t1, t2) & 0xffu;
             } else {
                 const int32_t m = med3(prev[mt][cb][4 * d + r], c_lo[cb], c_hi[cb]);
                 o = (uint32_t)(__mul24(m, c_mb[cb]) + c_ad[cb]) >> 24;
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
                         if (RES) {
                             const int32_t res = (int32_t)(int8_t)((uint32_t)rw[d >> 1][d & 1] >> (8 * r));
                             const int32_t t2 = (__mul24(res, rb) + rh) >> rc;
-                            o = clamp8(tq + t2);                                            // result in the low byte
+                            o = clamp8_sum(tq, t2);                                            // result in the low byte
                         }
                         if (r == 3) {
                             constexpr bool low = EPI != EPI_PLAIN;

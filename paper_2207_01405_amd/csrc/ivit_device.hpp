@@ -17,6 +17,10 @@ constexpr int kWave = 64;
 
 __device__ __forceinline__ int32_t clamp8(int32_t v) { return min(max(v, -127), 127); }
 
+// clamp8(a + b) of the exact sum, for any two int32: the sum stops at the ends of int32 (one instruction, as the plain
+// addition).  The two terms of a residual result need it: the first alone may be any int32.
+__device__ __forceinline__ int32_t clamp8_sum(int32_t a, int32_t b) { return clamp8(__builtin_elementwise_add_sat(a, b)); }
+
 // 64-bit minimum / maximum as a compare and a select (the min / max templates of the HIP headers, instantiated for
 // int64_t, go through double precision).
 __device__ __forceinline__ int64_t min64(int64_t a, int64_t b) { return a < b ? a : b; }

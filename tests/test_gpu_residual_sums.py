@@ -1,0 +1,68 @@
+"""Residual layers whose two terms leave 32 bits when they are added, against the oracle.
+
+The first term of a residual result may be any int32 (a sum of 2^31 - 1 rescaled by 2^20 / 2^20), the second one up to
+127 * 2^22, and the result is the clamped exact sum.  Every Dense kernel with a residual epilogue meets rows whose sum is
+the largest or the smallest int32 and a residual that carries it further, at pairs its 32-bit epilogue takes; and so do
+the projection and the second MLP layer inside the block kernels.
+"""
+import numpy as np
+import pytest
+
+import oracle as orc
+from paper_2207_01405_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# (rows, N, K, kernel): streamed tiles of each size, weight slab, weights in registers, K split, big tiles alone and with
+# the epilogue inside the next tile's k-loop
+LAYERS = [(130, 130, 144, None), (5000, 601, 144, None), (9000, 1017, 144, None), (333, 208, 96, "many_rows"),
+          (300, 384, 384, "reg_stationary"), (300, 256, 768, "reg_stationary"), (300, 384, 1536, "reg_stationary"),
+          (700, 256, 512, "big_tiles"), (40000, 256, 2304, "big_tiles")]
+
+
+@pytest.mark.parametrize("M,N,K,kernel", LAYERS)
+@pytest.mark.parametrize("rounding", ["nearest", "floor"])
+@pytest.mark.parametrize("res_rq", [(2 ** 15, 15), (2 ** 22, 1)])
+def test_dense(ivit, M, N, K, kernel, rounding, res_rq):
+    import torch
+    rng = np.random.default_rng(M + K)
+    x = rng.integers(-128, 128, size=(M, K)).astype(np.int8)
+    x[0::97], x[1::97] = 127, -128
+    w = rng.integers(0, 3, size=(N, K)).astype(np.int8)      # no negative weight: rows 0 and 1 are the extremes of every channel
+    total = w.astype(np.int64).sum(axis=1)
+    bias = np.where(np.arange(N) % 2, 128 * total - 2 ** 31, 2 ** 31 - 1 - 127 * total).astype(np.int32)
+    rq_b, rq_c = np.full(N, 2 ** 20, np.int32), np.full(N, 20, np.int32)
+    res = rng.integers(-128, 128, size=(M, N)).astype(np.int8)
+    res[0::97], res[1::97] = 127, -128
+    dev = lambda a: torch.from_numpy(a).cuda()
+    y = torch.empty((M, N), dtype=torch.int8, device="cuda")
+    ivit.ivit_linear_requant(dev(x), dev(w), dev(bias), dev(rq_b), dev(rq_c), y, residual=dev(res), res_rq=res_rq,
+                             kernel=kernel, rounding=rounding)
+    rows = np.unique(np.concatenate([np.arange(0, M, 97), np.arange(1, M, 97), np.arange(0, M, 61)]))
+    want = orc.linear_requant(x[rows], w, bias, rq_b, rq_c, residual=res[rows], res_rq=res_rq, floor_shift=rounding == "floor")
+    got = y.cpu().numpy()[rows]
+    assert np.array_equal(got, want), "%d of %d differ" % ((got != want).sum(), got.size)
+
+
+@pytest.mark.parametrize("C,H,F", [(64, 2, 256), (96, 3, 384), (192, 3, 768), (384, 6, 1536)])
+@pytest.mark.parametrize("R", [70, 5200])
+@pytest.mark.parametrize("large", [1000000000, 2000000000])          # (the smaller one leaves the sums within 32 bits)
+def test_block(ivit, C, H, F, R, large):
+    import torch
+    cfg = dict(T=1, C=C, H=H, F=F, seed=C, i0="fixed", rel_bias=False)
+    blocks = [synth.make_block(cfg, l) for l in range(2)]
+    for p in blocks:
+        for name in ("proj", "fc2"):
+            p["bias_" + name][0::5], p["bias_" + name][1::5] = large, -large
+            p[name + "_rq_b"][0::5] = p[name + "_rq_b"][1::5] = 2 ** 20
+            p[name + "_rq_c"][0::5] = p[name + "_rq_c"][1::5] = 20
+        p["res1_rq"] = p["res2_rq"] = (2 ** 22, 1)
+    x = synth.make_rows(R, R, C)
+    xd = torch.from_numpy(x).cuda()
+    y = torch.empty_like(xd)
+    d = dict(B=R, T=1, C=C, H=H, F=F)
+    ws = torch.empty(ivit.ivit_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    ivit.ivit_forward(xd, y, [ivit.to_device(p) for p in blocks], d, ws)
+    rows = np.arange(0, R, max(1, R // 100))
+    got, want = y.cpu().numpy()[rows], orc.forward(x[rows], blocks, dict(d, B=len(rows)))
+    assert np.array_equal(got, want), "%d of %d differ" % ((got != want).sum(), got.size)
