@@ -901,16 +901,20 @@ size_t token_block_table_bytes(int C, int F) { return (size_t)TB_QKV(C, F) + 48 
 hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n) {
     TableJobs J;
     int nj = 0, most = 0;
+    int64_t bytes = 0;
     auto flush = [&]() -> hipError_t {
         if (nj == 0) return hipSuccess;
+        TraceScope trace(s, KIND_TOKEN_TABLES, 0, bytes);
         hipLaunchKernelGGL(table_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)nj), dim3(256), 0, s, J);
         nj = most = 0;
+        bytes = 0;
         return hipGetLastError();
     };
     auto job = [&](const int32_t* b, const int32_t* c, const int32_t* bias, const int8_t* dst, int off, int cnt, int kind, int arg) {
         J.j[nj] = TableJob{b, c, bias, reinterpret_cast<int32_t*>(const_cast<int8_t*>(dst) + off), cnt, kind};
         J.arg[nj] = arg;
         ++nj; most = std::max(most, cnt);
+        bytes += cnt * (kind == 2 ? 16LL : bias ? 28LL : 24LL);
     };
     for (int i = 0; i < n; ++i) {
         const TokenBlockArgs& t = a[i];
@@ -931,8 +935,9 @@ hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n) {
 hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a) {
     const int64_t cus = num_cus(), r = a.R;
     const int64_t per_row = (a.o ? (int64_t)a.C * a.C + 2LL * a.C * a.F : 0) + (a.next == 2 ? 3LL * a.C * a.C : 0);
-    TraceScope trace(s, KIND_TOKEN_BLOCK, 2 * r * per_row, per_row + r * a.C * ((a.o ? 3 : 1) + (a.next == 2 ? 3 : a.next == 1 ? 1 : 0)));
+    const int64_t row_bytes = (int64_t)a.C * ((a.o ? 3 : 1) + (a.next == 2 ? 3 : a.next == 1 ? 1 : 0));
     auto tile = [&](const TokenBlockArgs& t) -> hipError_t {
+        TraceScope trace(s, KIND_TOKEN_BLOCK, 2 * t.R * per_row, per_row + t.R * row_bytes);
         if (t.C == 384) {
             if (t.R <= 32 * cus) return launch_tb<384, 1>(s, t);
             if (t.R <= 64 * cus) return launch_tb<384, 2>(s, t);
