@@ -891,6 +891,18 @@ bool token_block_takes(int C, int F, int64_t R) {
     // 421 us, 16 (3152 rows) 538 against 509, 24 (4728 rows) 570 against 556, 32 (6304 rows) 591 against 661.
     // A little more than one full round of workgroups (see launch_token_block) is where the separate kernels win once more:
     // DeiT-S batch 168 (33096 rows) 1737 against 1642 us, 184 (36248) 1861 against 1858, 192 (37824) 1930 against 1988.
+    // A workgroup walks the F / 128 chunks of the MLP one after the other, where a separate layer spreads them over the chip,
+    // so a long MLP needs rows.  us a block, fused against separate: up to F = 4 C + 128 any number of rows (C = 96, F = 384,
+    // 197 rows 24.2 against 24.4, F = 512 25.3 against 27.1; C = 192, F = 768 25.4 against 26.1, F = 896 28.3 against 30.1);
+    // beyond, C = 96: F = 1536, 3152 rows 37.9 against 36.4, 4728 38.1 against 39.8; F = 8192, 12608 rows 121 against 94,
+    // 16548 120 against 121, 23640 129 against 159; C = 192: F = 1536, 2364 rows 36.4 against 35.1, 3152 36.7 against 38.7;
+    // F = 3072, 4728 rows 56 against 53, 6304 57 against 58; F = 8192, 197 rows 102 against 43, 12608 117 against 113; F = 16384,
+    // 12608 rows 186 against 166, 16548 244 against 267; C = 384: F = 3072, 5122 rows 66 against 55, 6304 68 against 62, 9456 83
+    // against 86; F = 8192, 9850 rows 143 against 135; F = 16384, 16548 rows 333 against 290, 19700 337 against 338.
+    if (F > 4 * C + FC) {
+        const int64_t need = (C == 96 ? 3 : 2) * (int64_t)F;
+        if (R < (C == 384 ? need : std::min(need, 64 * (int64_t)num_cus()))) return false;
+    }
     const int64_t round = 128 * (int64_t)num_cus();
     if (C == 384 && (R < 5120 || (R > round && R < round + round / 9))) return false;
     return (C == 96 || C == 192 || C == 384) && F >= 2 * FC && F % FC == 0 && R >= 1 && R < (1 << 30) && (int64_t)F * C < (1 << 30);
