@@ -6,7 +6,6 @@
 #include <cstdio>
 #include <cstdlib>
 #include <mutex>
-#include <vector>
 
 #include "ivit_kernels.hpp"
 
@@ -173,15 +172,14 @@ hipError_t run_blocks(hipStream_t s, const int8_t* x, int8_t* y, const ivit_bloc
                       const ivit_final_ln* final_ln, const ivit_dims* d, const Workspace& w) {
     const int64_t R = (int64_t)d->B * d->T;
     hipError_t e;
-    // block l reads cur and writes into the other ping-pong buffer; the last producer writes y directly
-    const int8_t* cur = x;
-    auto other = [&]() { return cur == w.act0 ? w.act1 : w.act0; };
     // the constants of the fused launches live where the separate kernels would have put the hidden layer
     const size_t slot = up256(ivit::token_block_table_bytes(d->C, d->F));
     const int slots = (int)std::min<size_t>((size_t)R * d->F / slot, (size_t)n_blocks + 1);
     if (!ivit::token_block_takes(d->C, d->F, R) || slots < 1) {
+        // block l reads cur and writes into the other ping-pong buffer; the last producer writes y directly
+        const int8_t* cur = x;
         for (int l = 0; l < n_blocks; ++l) {
-            int8_t* dst = l == n_blocks - 1 && !final_ln ? y : other();
+            int8_t* dst = l == n_blocks - 1 && !final_ln ? y : cur == w.act0 ? w.act1 : w.act0;
             if ((e = run_block(s, cur, dst, &blocks[l], d, w, nullptr))) return e;
             cur = dst;
         }
@@ -190,22 +188,19 @@ hipError_t run_blocks(hipStream_t s, const int8_t* x, int8_t* y, const ivit_bloc
     }
     // launch 0: LN1 and QKV of block 0; launch j: the token-wise rest of block j - 1, then LN1 and QKV of block j, the
     // final I-LayerNorm, or nothing
-    std::vector<ivit::TokenBlockArgs> ts((size_t)n_blocks + 1);
-    for (int j = 0; j <= n_blocks; ++j) {
-        ivit::TokenBlockArgs& t = ts[j];
-        t = ivit::TokenBlockArgs{};
-        t.R = R; t.C = d->C; t.F = d->F; t.x = cur;
+    auto launch_args = [&](int j) {
+        ivit::TokenBlockArgs t{};
+        t.R = R; t.C = d->C; t.F = d->F; t.x = j <= 1 ? x : j & 1 ? w.act1 : w.act0;
         t.table = w.h + (size_t)(j % slots) * slot;
         if (j > 0) {
             const ivit_block_params& p = blocks[j - 1];
             t.o = w.o; t.xhat = w.xhat;
-            t.y = j < n_blocks ? other() : final_ln ? nullptr : y;
+            t.y = j < n_blocks ? (j & 1 ? w.act0 : w.act1) : final_ln ? nullptr : y;      // odd launches write act0, even ones act1
             t.ln2_g = p.ln2_gamma; t.ln2_b = p.ln2_beta; t.ln2_f = p.ln2_f_bits; t.ln2_c = p.ln2_c_shift;
             t.proj = ivit::DenseW{p.w_proj, p.bias_proj, p.proj_rq_b, p.proj_rq_c};
             t.fc1 = ivit::DenseW{p.w_fc1, p.bias_fc1, p.fc1_rq_b, p.fc1_rq_c};
             t.fc2 = ivit::DenseW{p.w_fc2, p.bias_fc2, p.fc2_rq_b, p.fc2_rq_c};
             t.res1 = dy(p.res1_rq); t.res2 = dy(p.res2_rq); t.gelu_p = sp(p.gelu); t.gelu_rq = dy(p.gelu_rq);
-            cur = t.y;
         }
         if (j < n_blocks) {
             const ivit_block_params& p = blocks[j];
@@ -216,11 +211,19 @@ hipError_t run_blocks(hipStream_t s, const int8_t* x, int8_t* y, const ivit_bloc
             t.next = 1; t.out = y;
             t.ln1_g = final_ln->gamma; t.ln1_b = final_ln->beta; t.ln1_f = final_ln->f_bits; t.ln1_c = final_ln->c_shift;
         }
-    }
+        return t;
+    };
+    // (an array on the stack, filled for as many launches as one table launch serves: an entry point allocates nothing)
+    ivit::TokenBlockArgs ts[ivit::kTableLaunches];
     for (int j = 0; j <= n_blocks; ++j) {
-        if (j % slots == 0 && (e = ivit::launch_token_tables(s, &ts[j], std::min(slots, n_blocks + 1 - j)))) return e;
+        for (int n = j % slots ? 0 : std::min(slots, n_blocks + 1 - j), i = j; n > 0;) {
+            const int m = std::min(n, ivit::kTableLaunches);
+            for (int k = 0; k < m; ++k) ts[k] = launch_args(i + k);
+            if ((e = ivit::launch_token_tables(s, ts, m))) return e;
+            i += m; n -= m;
+        }
         if (j > 0 && (e = ivit::launch_attention(s, attention_args(&blocks[j - 1], d, w, nullptr)))) return e;
-        if ((e = ivit::launch_token_block(s, ts[j]))) return e;
+        if ((e = ivit::launch_token_block(s, launch_args(j)))) return e;
     }
     return hipSuccess;
 }

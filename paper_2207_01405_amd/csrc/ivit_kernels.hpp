@@ -62,7 +62,8 @@ struct TokenBlockArgs {
     const int8_t* table;                 // token_block_table_bytes of constants, filled by launch_token_tables before the launch; 16-byte aligned
 };
 size_t token_block_table_bytes(int C, int F);
-hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n);
+constexpr int kTableLaunches = 15;       // launches whose constants one table launch prepares
+hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n);      // n <= kTableLaunches
 bool token_block_takes(int C, int F, int64_t R);
 hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a);
 

@@ -84,7 +84,7 @@ template <class T> __device__ __forceinline__ void pin(T& v) { asm volatile("" :
 // The constants of up to MAXJ layers: one thread per channel, one row of workgroups per layer.  Prepared by a launch of
 // its own because the two divisions per channel, done by every workgroup for every channel, cost the block kernel more
 // than requantising the results (C = 384, 25216 rows: 10 of 60 thousand cycles of its MLP).
-constexpr int MAXJ = 88;
+constexpr int MAXJ = 6 * kTableLaunches;
 struct TableJob { const int32_t* b; const int32_t* c; const int32_t* bias; int32_t* dst; int n; int kind; };      // kind 0 Rq, 1 Rq64, 2 LayerNorm (b gamma, c beta, bias unused)
 struct TableJobs { TableJob j[MAXJ]; int arg[MAXJ]; };      // arg: kind 1 the layer's K, kind 2 the rounding addend
 
@@ -914,14 +914,6 @@ hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n) {
     TableJobs J;
     int nj = 0, most = 0;
     int64_t bytes = 0;
-    auto flush = [&]() -> hipError_t {
-        if (nj == 0) return hipSuccess;
-        TraceScope trace(s, KIND_TOKEN_TABLES, 0, bytes);
-        hipLaunchKernelGGL(table_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)nj), dim3(256), 0, s, J);
-        nj = most = 0;
-        bytes = 0;
-        return hipGetLastError();
-    };
     auto job = [&](const int32_t* b, const int32_t* c, const int32_t* bias, const int8_t* dst, int off, int cnt, int kind, int arg) {
         J.j[nj] = TableJob{b, c, bias, reinterpret_cast<int32_t*>(const_cast<int8_t*>(dst) + off), cnt, kind};
         J.arg[nj] = arg;
@@ -930,8 +922,6 @@ hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n) {
     };
     for (int i = 0; i < n; ++i) {
         const TokenBlockArgs& t = a[i];
-        hipError_t e;
-        if (nj + 6 > MAXJ && (e = flush())) return e;
         if (t.o) {
             job(t.ln2_g, t.ln2_b, nullptr, t.table, 0, t.C, 2, 1 << (t.ln2_c - 1));
             job(t.proj.rq_b, t.proj.rq_c, t.proj.bias, t.table, TB_PROJ(t.C), t.C, 1, t.C);
@@ -941,7 +931,10 @@ hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n) {
         if (t.next) job(t.ln1_g, t.ln1_b, nullptr, t.table, TB_LN1(t.C), t.C, 2, 1 << (t.ln1_c - 1));
         if (t.next == 2) job(t.qkv_w.rq_b, t.qkv_w.rq_c, t.qkv_w.bias, t.table, TB_QKV(t.C, t.F), 3 * t.C, 0, 0);
     }
-    return flush();
+    if (nj == 0) return hipSuccess;
+    TraceScope trace(s, KIND_TOKEN_TABLES, 0, bytes);
+    hipLaunchKernelGGL(table_kernel, dim3((unsigned)((most + 255) / 256), (unsigned)nj), dim3(256), 0, s, J);
+    return hipGetLastError();
 }
 
 hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a) {

@@ -2,7 +2,7 @@
 // While a trace is active every kernel launch of the library is bracketed by two events recorded on the
 // stream the kernel is launched on; ivit_trace_end synchronises the last event and reports the elapsed
 // time, the kind and the algorithmic work of every launch.  Inactive, the cost is one pointer test per launch.
-#include <vector>
+#include <new>
 
 #include "../../include/ivit.h"
 #include "ivit_kernels.hpp"
@@ -10,12 +10,26 @@
 namespace ivit {
 
 namespace {
+struct Record { hipEvent_t start, stop; int32_t kind; int64_t ops, bytes; };
 struct Trace {
-    std::vector<hipEvent_t> start, stop;
-    std::vector<int32_t> kind;
-    std::vector<int64_t> ops, bytes;
-    int count = 0;
+    Record* rec = nullptr;                   // room for `capacity` launches, allocated without exceptions
+    int capacity = 0, count = 0;
     bool failed = false;
+
+    bool create(int n) {
+        rec = new (std::nothrow) Record[n]();
+        if (!rec) return false;
+        for (; capacity < n; ++capacity) {
+            Record& r = rec[capacity];
+            if (hipEventCreate(&r.start) != hipSuccess) return false;
+            if (hipEventCreate(&r.stop) != hipSuccess) { (void)hipEventDestroy(r.start); return false; }
+        }
+        return true;
+    }
+    ~Trace() {
+        for (int i = 0; i < capacity; ++i) { (void)hipEventDestroy(rec[i].start); (void)hipEventDestroy(rec[i].stop); }
+        delete[] rec;
+    }
 };
 Trace* g_trace = nullptr;
 }  // namespace
@@ -23,16 +37,17 @@ Trace* g_trace = nullptr;
 TraceScope::TraceScope(hipStream_t s, int kind, int64_t ops, int64_t bytes) : stream_(s), slot_(-1) {
     Trace* t = g_trace;
     if (!t) return;
-    if (t->count >= (int)t->start.size()) { t->failed = true; return; }
+    if (t->count >= t->capacity) { t->failed = true; return; }
     slot_ = t->count++;
-    t->kind[slot_] = kind; t->ops[slot_] = ops; t->bytes[slot_] = bytes;
-    if (hipEventRecord(t->start[slot_], s) != hipSuccess) t->failed = true;
+    Record& r = t->rec[slot_];
+    r.kind = kind; r.ops = ops; r.bytes = bytes;
+    if (hipEventRecord(r.start, s) != hipSuccess) t->failed = true;
 }
 
 TraceScope::~TraceScope() {
     Trace* t = g_trace;
     if (!t || slot_ < 0) return;
-    if (hipEventRecord(t->stop[slot_], stream_) != hipSuccess) t->failed = true;
+    if (hipEventRecord(t->rec[slot_].stop, stream_) != hipSuccess) t->failed = true;
 }
 
 }  // namespace ivit
@@ -43,17 +58,8 @@ int ivit_trace_begin(int32_t max_launches) {
     using namespace ivit;
     if (max_launches < 1 || max_launches > (1 << 22)) return IVIT_ERR_SHAPE;
     if (g_trace) return IVIT_ERR_PARAM;                       // a trace is already active
-    Trace* t = new Trace();
-    t->start.assign(max_launches, nullptr); t->stop.assign(max_launches, nullptr);
-    t->kind.resize(max_launches); t->ops.resize(max_launches); t->bytes.resize(max_launches);
-    bool ok = true;
-    for (int i = 0; i < max_launches && ok; ++i)
-        ok = hipEventCreate(&t->start[i]) == hipSuccess && hipEventCreate(&t->stop[i]) == hipSuccess;
-    if (!ok) {
-        for (int i = 0; i < max_launches; ++i) {
-            if (t->start[i]) (void)hipEventDestroy(t->start[i]);
-            if (t->stop[i]) (void)hipEventDestroy(t->stop[i]);
-        }
+    Trace* t = new (std::nothrow) Trace();
+    if (!t || !t->create(max_launches)) {
         delete t;
         return IVIT_ERR_HIP;
     }
@@ -70,17 +76,15 @@ int ivit_trace_end(float* ms, int32_t* kind, int64_t* ops, int64_t* bytes, int32
     const int n = t->count;
     if (count) *count = n;
     for (int i = 0; i < n && status == IVIT_OK; ++i) {
-        if (hipEventSynchronize(t->stop[i]) != hipSuccess) { status = IVIT_ERR_HIP; break; }
+        const Record& r = t->rec[i];
+        if (hipEventSynchronize(r.stop) != hipSuccess) { status = IVIT_ERR_HIP; break; }
         if (i < capacity) {
-            float v = 0.f;
-            if (ms && hipEventElapsedTime(&v, t->start[i], t->stop[i]) != hipSuccess) { status = IVIT_ERR_HIP; break; }
-            if (ms) ms[i] = v;
-            if (kind) kind[i] = t->kind[i];
-            if (ops) ops[i] = t->ops[i];
-            if (bytes) bytes[i] = t->bytes[i];
+            if (ms && hipEventElapsedTime(&ms[i], r.start, r.stop) != hipSuccess) { status = IVIT_ERR_HIP; break; }
+            if (kind) kind[i] = r.kind;
+            if (ops) ops[i] = r.ops;
+            if (bytes) bytes[i] = r.bytes;
         }
     }
-    for (size_t i = 0; i < t->start.size(); ++i) { (void)hipEventDestroy(t->start[i]); (void)hipEventDestroy(t->stop[i]); }
     delete t;
     return status;
 }

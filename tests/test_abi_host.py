@@ -31,6 +31,15 @@ def test_every_declared_symbol_is_exported(lib):
         assert getattr(lib, name) is not None
 
 
+def test_nothing_behind_the_entry_points_allocates_with_exceptions(lib):
+    """The header says that nothing throws: the library does not even import the throwing allocation functions, or those
+    the standard containers report their errors through."""
+    out = subprocess.run(["nm", "-D", "--undefined-only", binding.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    names = {l.split()[-1].split("@")[0] for l in out.splitlines()}
+    assert len(names) > 5
+    assert not [n for n in names if n in ("_Znwm", "_Znam", "__cxa_throw", "__cxa_allocate_exception") or "throw_length" in n or "throw_bad" in n]
+
+
 def test_struct_layouts_match_the_header(lib):
     assert C.sizeof(binding.ShiftParams) == 16 and C.sizeof(binding.Dyadic) == 8 and C.sizeof(binding.Dims) == 20
     assert C.sizeof(binding.DebugTaps) == 64 and C.sizeof(binding.FinalLN) == 24

@@ -118,3 +118,14 @@ def test_long_mlps_need_rows(ivit, C, H, F, R, fused):
     got, want = _run(ivit, d, x, blocks, None)
     kinds = [r[1] for r in ivit.ivit_trace_end(64)]
     assert np.array_equal(got, want) and (11 in kinds) == fused
+
+
+@pytest.mark.parametrize("R,n", [(300, 5), (300, 6), (300, 17), (2000, 14), (2000, 15), (2000, 31)])
+def test_deep_stacks(ivit, R, n):
+    """More launches than one table launch prepares constants for, and than the workspace has room for at a time (300 rows: five)."""
+    C, H, F = 96, 3, 256
+    cfg, blocks = _blocks(C, H, F, 1, n, "as drawn")
+    x = synth.make_rows(8, R, C)
+    for final_ln in (None, synth.make_final_ln(cfg)):
+        got, want = _run(ivit, dict(B=R, T=1, C=C, H=H, F=F), x, blocks, final_ln)
+        assert np.array_equal(got, want), "%d of %d differ" % ((got != want).sum(), got.size)
