@@ -180,11 +180,8 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
         sm += dpp_i32<0xB1>(sm); sq += dpp_i32<0xB1>(sq);
         sm += dpp_i32<0x4E>(sm); sq += dpp_i32<0x4E>(sq);
         sm += dpp_i32<0x141>(sm); sq += dpp_i32<0x141>(sq);
-        // (the ranges that let one reciprocal and a repair step settle these divisions: see ilayernorm_tiled_kernel)
-        const int32_t mean = floordiv_small(sm + (K >> 1), K);
-        const uint32_t var = div_small_quotient((uint32_t)(sq - 2 * mean * sm + K * mean * mean), (uint32_t)K);
-        const int32_t f = (int32_t)div_small(1u << P.ln_f, max(isqrt10(var), 1u));
-        if (tid % TPR == 0) stat[row] = make_int2(mean, f);
+        const LnStat st = ln_stat(sm, sq, K, P.ln_f);
+        if (tid % TPR == 0) stat[row] = make_int2(st.mean, st.f);
         __syncthreads();
         if (n_r < n_rows) {
             const int32_t half = 1 << (P.ln_c - 1);
@@ -195,6 +192,7 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
 #pragma unroll 1
             for (int i = n_r; i < TM; i += n_rows) {
                 const int2 mf = stat[i];
+                const LnStat st{mf.x, mf.y};
                 const v4i v = *at(i, n_p);
                 v4i w;
 #pragma unroll
@@ -203,7 +201,7 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int32_t xe = (int32_t)(int8_t)((uint32_t)v[d] >> (8 * r));
-                        o[r] = (uint32_t)clamp8((__mul24(mul_i24(xe - mf.x, g[d][r]), mf.y) + bt[d][r]) >> P.ln_c);
+                        o[r] = (uint32_t)ln_value(xe, st, g[d][r], bt[d][r], P.ln_c);
                     }
                     w[d] = (int)(__builtin_amdgcn_perm(o[1], o[0], 0x0c0c0400u) | __builtin_amdgcn_perm(o[3], o[2], 0x04000c0cu));
                 }

@@ -61,9 +61,6 @@ struct TlLayout {
     static_assert(TOTAL + 1024 <= 160 * 1024, "LDS");
 };
 
-template <int N, class F> __device__ __forceinline__ void static_for(F&& f) {
-    [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }(std::make_integer_sequence<int, N>());
-}
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
 
 template <int EPI>

@@ -186,6 +186,21 @@ __device__ __forceinline__ uint32_t isqrt10(uint32_t v) {
     return osc ? s + bit : s;
 }
 
+// I-LayerNorm of a row of C int8 values (Sec. 3.5, Eq. 19-20) from their sum and sum of squares: mean to nearest and
+// f = floor(2^f_bits / std).  |sum| <= 128 C < 2^19, the variance is at most 255^2 and f at most 2^20: the three divisions
+// are of the kind one reciprocal and a repair step settle.
+struct LnStat { int32_t mean, f; };
+__device__ __forceinline__ LnStat ln_stat(int32_t sum, int32_t squares, int32_t C, int32_t f_bits) {
+    const int32_t mean = floordiv_small(sum + (C >> 1), C);
+    const uint32_t var = div_small_quotient((uint32_t)(squares - 2 * mean * sum + C * mean * mean), (uint32_t)C);      // (the sum of squared deviations is exact)
+    return LnStat{mean, (int32_t)div_small(1u << f_bits, max(isqrt10(var), 1u))};
+}
+// One normalised value; beta_r is beta_q + 2^(c_shift - 1).  |x - mean| <= 255, |gamma_q| < 2^15 and f <= 2^20: both products
+// have 24-bit factors, so the full-rate 24-bit multiply (low 32 bits of the product) gives what the 32-bit one would.
+__device__ __forceinline__ int32_t ln_value(int32_t x, LnStat st, int32_t gamma, int32_t beta_r, int32_t c_shift) {
+    return clamp8((__mul24(mul_i24(x - st.mean, gamma), st.f) + beta_r) >> c_shift);
+}
+
 // Reductions over the 64 lanes of a wavefront; every lane gets the result.  Inside each row of 16 lanes four DPP
 // exchanges (lane pairs, quad pairs, half-row mirror, row mirror: all of them read existing lanes, so "bound_ctrl with
 // old = 0" only serves to let the compiler fold the move into the operation); the four row results are then combined

@@ -1,6 +1,9 @@
-// Pieces shared by the Dense kernels built on LDS-direct loads (gemm_rs.hip, gemm_ks.hip, gemm_tl.hip): those
-// loads, scalar pointers, the median of three, the token order of the MFMA "A" operand.
+// Pieces shared by the Dense kernels built on LDS-direct loads (gemm_rs.hip, gemm_ks.hip, gemm_tl.hip, gemm_st.hip,
+// token_block.hip): those loads, scalar pointers, the median of three, the token order of the MFMA "A" operand.
 #pragma once
+#include <type_traits>
+#include <utility>
+
 #include "ivit_kernels.hpp"
 
 namespace ivit {
@@ -17,6 +20,11 @@ constexpr int OP = 48;                       // pitch (bytes) of a channel row o
 constexpr int WCK = 384;                     // bytes of K per weight chunk of the prologue
 constexpr int WPITCH = WCK + 16;             // its row pitch in LDS
 constexpr int WWI = 4 * 32 * (WPITCH / 16) / 64;    // load instructions (64 lanes x 16 bytes) per chunk: [4 wavefronts][32 channels][WPITCH]
+
+// f(0), .. f(N - 1), each with its number as a type
+template <int N, class F> __device__ __forceinline__ void static_for(F&& f) {
+    [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }(std::make_integer_sequence<int, N>());
+}
 
 __device__ __forceinline__ uint32_t lds_offset(const int8_t* p) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) int8_t*)p;

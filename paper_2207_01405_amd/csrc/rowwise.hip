@@ -144,13 +144,8 @@ __global__ __launch_bounds__(256) void ilayernorm_tiled_kernel(const int8_t* __r
         const int2* p = &part[j * 256 + rg];
         int32_t s = 0, ss = 0;
         for (int c = 0; c < CPR; ++c) { s += p[c * RP].x; ss += p[c * RP].y; }
-        // (|sum x| <= 128 C < 2^19, the variance is at most 255^2 and f at most 2^20: the three divisions are of the
-        // kind one reciprocal and a repair step settle)
-        const int32_t mean = floordiv_small(s + (C >> 1), C);
-        const int32_t sq = ss - 2 * mean * s + C * mean * mean;      // sum of squared deviations (exact)
-        const uint32_t var = div_small_quotient((uint32_t)sq, (uint32_t)C);
-        const uint32_t sd = max(isqrt10(var), 1u);
-        stat[r] = make_int2(mean, (int32_t)div_small(1u << f_bits, sd));
+        const LnStat st = ln_stat(s, ss, C, f_bits);
+        stat[r] = make_int2(st.mean, st.f);
     }
     __syncthreads();
     int32_t g[16], bt[16];
@@ -165,6 +160,7 @@ __global__ __launch_bounds__(256) void ilayernorm_tiled_kernel(const int8_t* __r
     for (int j = 0; j < J; ++j) {
         const int64_t row = row0 + j * RP + rgrp;
         const int2 mf = stat[j * RP + rgrp];
+        const LnStat st{mf.x, mf.y};
         uint32_t outw[4];
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
@@ -172,11 +168,7 @@ __global__ __launch_bounds__(256) void ilayernorm_tiled_kernel(const int8_t* __r
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int32_t xe = (int32_t)(int8_t)((uint32_t)xv[j][d] >> (8 * e));
-                // |x - mean| <= 255, |gamma_q| < 2^15 and f <= 2^20: both products have 24-bit factors, so the
-                // full-rate 24-bit multiply (low 32 bits of the product) gives what the 32-bit one would
-                const int32_t dg = mul_i24(xe - mf.x, g[4 * d + e]);                 // |.| < 2^23
-                const int32_t v = __mul24(dg, mf.y) + bt[4 * d + e];
-                o |= ((uint32_t)clamp8(v >> c_shift) & 0xffu) << (8 * e);
+                o |= ((uint32_t)ln_value(xe, st, g[4 * d + e], bt[4 * d + e], c_shift) & 0xffu) << (8 * e);
             }
             outw[d] = o;
         }

@@ -26,9 +26,6 @@ namespace {
 
 using namespace regst;
 
-template <int N, class F> __device__ __forceinline__ void static_for(F&& f) {
-    [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }(std::make_integer_sequence<int, N>());
-}
 template <int I> using ic = std::integral_constant<int, I>;
 
 constexpr int FC = 128;                          // hidden channels per chunk of the MLP
@@ -392,14 +389,12 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         int32_t s = sm[0], ss = sq[0];
 #pragma unroll
         for (int k = 1; k < NPASS; ++k) { s = q == k ? sm[k] : s; ss = q == k ? sq[k] : ss; }
-        const int32_t mean = floordiv_small(s + (C >> 1), C);
-        const uint32_t var = div_small_quotient((uint32_t)(ss - 2 * mean * s + C * mean * mean), (uint32_t)C);
-        const int32_t f = (int32_t)div_small(1u << f_bits, max(isqrt10(var), 1u));
+        const LnStat own = ln_stat(s, ss, C, f_bits);
 #pragma unroll
         for (int k = 0; k < NPASS; ++k) {
             const int i = i0 + k * RPP, tok = (i & ~31) + token_of_row(i & 31);
             const int from = 4 * ((lane & ~(LPR - 1)) + k);
-            const int32_t mk = __builtin_amdgcn_ds_bpermute(from, mean), fk = __builtin_amdgcn_ds_bpermute(from, f);
+            const LnStat row{__builtin_amdgcn_ds_bpermute(from, own.mean), __builtin_amdgcn_ds_bpermute(from, own.f)};
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 v4i w;
@@ -409,8 +404,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int32_t xe = (int32_t)(int8_t)((uint32_t)v[k][j][d] >> (8 * r));
-                        const int32_t dg = mul_i24(xe - mk, g[16 * j + 4 * d + r]);
-                        o[r] = (uint32_t)clamp8((__mul24(dg, fk) + b[16 * j + 4 * d + r]) >> c_shift);
+                        o[r] = (uint32_t)ln_value(xe, row, g[16 * j + 4 * d + r], b[16 * j + 4 * d + r], c_shift);
                     }
                     w[d] = pack4(o, std::true_type());
                 }
