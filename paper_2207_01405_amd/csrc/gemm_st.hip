@@ -386,6 +386,7 @@ hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
     // tile pays earlier: 6000 x 768 x 3072 (1128) 27.2, 38.6 and 27.1, 3137 x 1000 x 3072 (800) 24.7, 24.5 and 29.3.
     // Stages: two workgroups of 128 x 128 share a CU with two stages, one with four: 6000 x 1000 x 768 10.8 against 15.3 us;
     // 64 x 64 with three stages against four (three workgroups per CU against two): 11.7 against 13.6 us.
+    if (a.kernel == LINEAR_MANY_ROWS) return launch_tile<2, 2, 2, 0>(s, a);
     const int64_t tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64), cus = num_cus();
     if (2 * tiles <= 5 * cus) return launch_tile<1, 1, 3, 0>(s, a);
     if (tiles * (a.K > 1024 ? 2 : 1) <= 6 * cus) return launch_tile<2, 1, 2, 0>(s, a);

@@ -253,8 +253,9 @@ LIN_SHAPES = [(0, 64, 64), (1, 1, 16), (5, 7, 80), (65, 192, 64), (130, 40, 256)
 
 @pytest.fixture(params=[None, "many_rows"])
 def dense_path(request):
-    """Shapes with few rows take a kernel of their own; "many_rows" (an option of ivit_linear_requant_ex) keeps them on
-    the kernels for many rows, so that the small test shapes exercise both.  None calls ivit_linear_requant itself."""
+    """Shapes with few rows take small streamed tiles; "many_rows" (an option of ivit_linear_requant_ex) puts them on the
+    kernel with a weight slab in LDS or, where that does not take them, on the largest streamed tiles, so that the small
+    test shapes exercise both.  None calls ivit_linear_requant itself."""
     return request.param
 
 
@@ -371,8 +372,8 @@ def test_linear_requant_narrow_multiplier_path_at_its_limits(ivit, dense_path, K
         assert_same(host(y), want, "linear at the limits of the narrow path" + (" + gelu" if kw else ""))
     plain = orc.linear_requant(x, w, bias, b, c)
     assert (plain == 127).mean() > 0.02 and (plain == -127).mean() > 0.02 and (np.abs(plain) < 127).mean() > 0.3
-    # the residual layers' 24-bit form (shift <= 23, residual multiplier below 2^23, residual term at most 128 in
-    # magnitude) at and past its limits; the residual holds -128 as well, and saturated rows on both sides
+    # the residual layers' 24-bit form of the slab kernel (shift <= 23, residual multiplier below 2^23, residual term at most
+    # 128 in magnitude) at and past its limits, and pairs the other kernels' 32-bit form takes and refuses; the residual holds -128 as well, and saturated rows on both sides
     res = synth.make_rows(K + 2, M, N, "uniform")
     res[0:4] = 127; res[4:8] = -128; res[8:12] = -127; res[12:16] = 127; res[16:20] = -128
     for rq in ((2 ** 15, 15), (2 ** 15 - 1, 15), (2 ** 15 + 1, 15), (33000, 15), (2 ** 23 - 1, 23), (2 ** 23, 23),

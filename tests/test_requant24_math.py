@@ -1,8 +1,8 @@
 """The 24-bit requantisation used by the Dense epilogues and the attention kernel, checked as arithmetic on the CPU.
 
 The kernels limit the accumulator to per-channel bounds, multiply by b 2^(s-c) with a 24-bit multiply-add whose addend
-carries bias and rounding, and read the int8 result from the top of the 32-bit word (s = 24: top byte; residual layers,
-s = 23: top nine bits, then the residual term is added and the sum clamped).  This file re-derives the constants from
+carries bias and rounding, and read the int8 result from the top of the 32-bit word (s = 24: top byte; residual layers of
+the kernel with a weight slab in LDS, s = 23: top nine bits, then the residual term is added and the sum clamped).  This file re-derives the constants from
 their definition and compares the outcome with the plain definition (Eq. 7-10 with round-half-up and the symmetric
 clamp; and, as the selectable other reading, Eq. 10's bare shift, where the rounding addend is 0) over exhaustive or
 dense ranges.  Nothing here touches the GPU or the library: it pins the derivation.
