@@ -51,7 +51,7 @@ struct DenseW { const int8_t* w; const int32_t* bias; const int32_t* rq_b; const
 struct TokenBlockArgs {
     const int8_t* o;                     // attention output [R, C]; nullptr: only the LN and the QKV layer below, on x
     const int8_t* x;                     // block input [R, C]
-    int8_t* xhat; int8_t* y;             // scratch [R, C]; block output [R, C]
+    int8_t* xhat; int8_t* y;             // scratch [R, C], written and read back by the launch; block output [R, C]
     int8_t* out;                         // next == 1: LN output [R, C]; next == 2: qkv of the next block [R, 3 C]
     int64_t R; int C, F;
     int next;                            // what follows the block: 0 nothing, 1 an I-LayerNorm, 2 the next block's I-LayerNorm and QKV layer

@@ -2,7 +2,9 @@
 // the dyadic pipeline of Sec. 3.2, ShiftGELU of Sec. 3.4 and I-LayerNorm of Sec. 3.5):
 //   xhat = Dense(o; proj) + x;  v = LN2(xhat);  y = Dense(ShiftGELU(Dense(v; fc1)); fc2) + xhat;
 //   then, for the block that follows, u = LN1'(y) and qkv' = Dense(u)   (or a final LN, or nothing).
-// Between two attentions a block is one launch instead of seven, and xhat, v, the hidden layer and u stay on the chip.
+// Between two attentions a block is one launch instead of six, and v, the hidden layer and u stay on the chip.  xhat does
+// too until it has been normalised; its LDS then goes to the hidden layer, so it is written out once (to the workspace,
+// from where the L2 has it) and comes back as the residual of the last layer, during that layer's last products.
 //
 // A workgroup of four wavefronts (one per SIMD) takes M tokens through all layers.  Weights stream through two LDS
 // buffers in sets (128 to 192 rows of proj / fc1 / qkv, or 128 bytes of every row of fc2), each requested while its
