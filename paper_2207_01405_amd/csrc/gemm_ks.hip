@@ -233,11 +233,10 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(KsParams P) {
     // regst_common.hpp, the residual term by a 24-bit one).  A workgroup with a channel outside the conditions of that form takes the
     // general 64-bit form for all of its channels.
     int32_t c_lo = 0, c_hi = 0, c_mb = 0, c_ad = 0;
+    Residual64 c_r;
     bool chan_24 = true;
     if (EPI == EPI_RESIDUAL) {
-        Residual64 q;
-        chan_24 = residual64_of(q, pb, pc, pbias, P.rnd) && residual_term_24(P.res_rq);
-        c_lo = q.b; c_hi = q.c; c_mb = q.h_lo; c_ad = q.h_hi;
+        chan_24 = residual64_of(c_r, pb, pc, pbias, P.rnd) && residual_term_24(P.res_rq);
     } else {
         constexpr int64_t wlim = 127;
         constexpr int sh24 = 24;
@@ -283,7 +282,7 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(KsParams P) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             if (EPI == EPI_RESIDUAL) {
-                const int32_t t1 = residual64_first(a[4 * d + r], c_lo, c_hi, c_mb, c_ad);
+                const int32_t t1 = residual64_first(a[4 * d + r], c_r);
                 const int32_t res = (int32_t)(int8_t)((uint32_t)rw[d >> 1][d & 1] >> (8 * r));
                 const int32_t t2 = (__mul24(res, rb) + rh) >> rc;
                 o[r] = (uint32_t)clamp8_sum(t1, t2);

@@ -256,15 +256,15 @@ __global__ __launch_bounds__(256 * GR) void gemm_rs_kernel(RsParams P) {
     // b < 2^(c-1) and bounds within 24 bits.  Residual layers take a 64-bit multiply-add instead (regst_common.hpp).  A
     // workgroup with a channel outside these conditions takes the general 64-bit form for all of its channels.
     int32_t c_lo[NCB], c_hi[NCB], c_mb[NCB], c_ad[NCB];
+    Residual64 c_r[NCB];
     bool chan_24 = true;
     constexpr int64_t wlim = 127;
     constexpr int sh24 = 24;
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
         if (EPI == EPI_RESIDUAL) {
-            Residual64 q;
-            chan_24 = residual64_of(q, pb[cb], pc[cb], pbias[cb], P.rnd) && residual_term_24(P.res_rq) && chan_24;
-            c_lo[cb] = q.b; c_hi[cb] = q.c; c_mb[cb] = q.h_lo; c_ad[cb] = q.h_hi;
+            chan_24 = residual64_of(c_r[cb], pb[cb], pc[cb], pbias[cb], P.rnd) && residual_term_24(P.res_rq) && chan_24;
+            c_lo[cb] = c_hi[cb] = c_mb[cb] = c_ad[cb] = 0;
             continue;
         }
         int32_t lo = 0, hi = 0, mb = 0, ad = 0;
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(256 * GR) void gemm_rs_kernel(RsParams P) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             if (EPI == EPI_RESIDUAL) {
-                const int32_t t1 = residual64_first(a[4 * d + r], c_lo[cb], c_hi[cb], c_mb[cb], c_ad[cb]);
+                const int32_t t1 = residual64_first(a[4 * d + r], c_r[cb]);
                 const int32_t res = (int32_t)(int8_t)((uint32_t)rw[cb][d >> 1][d & 1] >> (8 * r));
                 const int32_t t2 = (__mul24(res, rb) + rh) >> rc;
                 o[r] = (uint32_t)clamp8_sum(t1, t2);

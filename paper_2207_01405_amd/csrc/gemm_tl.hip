@@ -173,6 +173,7 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
     int64_t p_row = 0;                                          // first token of the wavefront's part
     int p_n0 = 0;                                               // first channel
     int32_t c_lo[2], c_hi[2], c_mb[2], c_ad[2], pb[2], pc[2], pbias[2];
+    Residual64 c_r[2];
     bool fast24 = false;
     v2i rw[2] = {};                                             // the unit's residual values, as the accumulators lie
     v4i ow = {};                                                // its results, four tokens a register
@@ -204,9 +205,7 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
             if (EPI == EPI_RESIDUAL) {                          // (regst_common.hpp)
-                Residual64 q;
-                chan_24 = residual64_of(q, pb[cb], pc[cb], pbias[cb], P.rnd) && chan_24;
-                c_lo[cb] = q.b; c_hi[cb] = q.c; c_mb[cb] = q.h_lo; c_ad[cb] = q.h_hi;
+                chan_24 = residual64_of(c_r[cb], pb[cb], pc[cb], pbias[cb], P.rnd) && chan_24;
                 continue;
             }
             constexpr int64_t wlim = 127;
@@ -235,7 +234,7 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
         for (int r = r0; r < r0 + 2; ++r) {
             uint32_t o;
             if (EPI == EPI_RESIDUAL) {
-                const int32_t t1 = residual64_first(prev[mt][cb][4 * d + r], c_lo[cb], c_hi[cb], c_mb[cb], c_ad[cb]);
+                const int32_t t1 = residual64_first(prev[mt][cb][4 * d + r], c_r[cb]);
                 const int32_t res = (int32_t)(int8_t)((uint32_t)rw[d >> 1][d & 1] >> (8 * r));
                 const int32_t t2 = (__mul24(res, rb) + rh) >> rc;
                 o = (uint32_t)clamp8_sum(t1, t2) & 0xffu;
@@ -366,7 +365,7 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
                     // four results of a register are put together by two byte permutes
                     const int v = 2 * kk + (mt >> 1), d = 2 * ph + (v >> 2), r = v & 3;     // (constants once the loops are unrolled)
                     if ((mt & 1) == 0) {
-                        if (RES) tq = residual64_first(prev[emt][cb][4 * d + r], c_lo[cb], c_hi[cb], c_mb[cb], c_ad[cb]);
+                        if (RES) tq = residual64_first(prev[emt][cb][4 * d + r], c_r[cb]);
                         else tq = __mul24(med3(prev[emt][cb][4 * d + r], c_lo[cb], c_hi[cb]), c_mb[cb]) + c_ad[cb];      // result in the top byte
                         if (EPI == EPI_GELU) tq = (int32_t)(uint8_t)gelu_lut[(uint32_t)tq >> 24];   // result in the low byte
                         asm volatile("" : "+v"(tq));

@@ -52,20 +52,22 @@ __device__ __forceinline__ int32_t med3(int32_t v, int32_t lo, int32_t hi) {
     return m;
 }
 
-// Residual layers: the first term of a result is bits c .. c + 31 of acc b + h, h = bias b + rounding addend, one 64-bit
-// multiply-add and a funnel shift.  It holds for every dyadic_fits32 pair; a form with 24-bit multiplies, which has to keep
-// the sum's nine bits above the fraction, ends at c = 23, and layers with long rows need c = 24 (ViT-B's second MLP layer,
-// 50432 rows: 150 us with the general 64-bit form, 131.6 with this one).
-struct Residual64 { int32_t b, c, h_lo, h_hi; };
+// Residual layers: the first term floor((acc b + h) / 2^c), h = bias b + rounding addend, is the high word of one 64-bit
+// multiply-add by b 2^(32-c).  It needs b < 2^(c-1), so that the factor is an int32; a form with 24-bit multiplies, which has
+// to keep the sum's nine bits above the fraction, ends at c = 23, and layers with long rows need c = 24 (ViT-B's second MLP
+// layer, 50432 rows: 150 us with the general 64-bit form, 131.6 with a multiply-add by b, an addition and a shift; forwards
+// against that one: DeiT-S batch 128 1230 -> 1214 us, ViT-B batch 256 5580 -> 5548).  The addend is one
+// 64-bit register pair that the compiler cannot look into: it would add the two halves one after the other.
+struct Residual64 { int32_t b; int64_t h; };
+__device__ __forceinline__ bool residual64_takes(int32_t b, int32_t c) { return c >= 1 && c <= 31 && b >= 1 && b < (1 << ((c - 1) & 31)); }
 __device__ __forceinline__ bool residual64_of(Residual64& q, int32_t b, int32_t c, int32_t bias, int32_t rnd) {
-    const int64_t h = (int64_t)bias * b + (int64_t)((uint32_t)rnd << ((c - 1) & 31));
-    q = Residual64{b, c, (int32_t)(uint32_t)h, (int32_t)(h >> 32)};
-    return dyadic_fits32(b, c);
+    const int up = 32 - (c & 31);
+    q.b = (int32_t)((uint32_t)b << (up & 31));
+    q.h = (int64_t)((uint64_t)((int64_t)bias * b + (int64_t)((uint32_t)rnd << ((c - 1) & 31))) << up);
+    asm volatile("" : "+v"(q.h));
+    return residual64_takes(b, c);
 }
-__device__ __forceinline__ int32_t residual64_first(int32_t acc, int32_t b, int32_t c, int32_t h_lo, int32_t h_hi) {
-    const int64_t p = (int64_t)acc * b + (int64_t)(((uint64_t)(uint32_t)h_hi << 32) | (uint32_t)h_lo);
-    return (int32_t)__builtin_amdgcn_alignbit((uint32_t)(p >> 32), (uint32_t)p, c);
-}
+__device__ __forceinline__ int32_t residual64_first(int32_t acc, const Residual64& q) { return (int32_t)(((int64_t)acc * q.b + q.h) >> 32); }
 // The residual term round(b_r r / 2^c_r) takes one 24-bit multiply-add under these conditions.
 __device__ __forceinline__ bool residual_term_24(Dyadic d) { return d.b >= 1 && d.b < (1 << 23) && d.c >= 1 && d.c <= 30; }
 

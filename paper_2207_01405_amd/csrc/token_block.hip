@@ -71,10 +71,10 @@ template <int G16> __device__ __forceinline__ int swz(int r) { return (r / (16 /
 
 // Requantisation constants of a channel, 16 bytes in the tables that table_kernel prepares.
 //   Rq     24-bit form (derivation in gemm_rs.hip); lo > hi: the channel needs the general form
-//   Rq64   residual layers: the first term is bits c .. c + 31 of acc b + h and at most 2^30; c = 0: the channel needs the
-//          general form
+//   Rq64   residual layers: b and h of Residual64 (regst_common.hpp), the first term at most 2^30; b = 0: the channel needs
+//          the general form.  Bytes 4 .. 7 of the entry are unused.
 struct Rq { int32_t lo, hi, mb, ad; };
-struct Rq64 { int32_t b, c, h_lo, h_hi; };
+using Rq64 = Residual64;
 
 // median of three as the pattern the compiler turns into one v_med3_i32
 __device__ __forceinline__ int32_t med3c(int32_t v, int32_t lo, int32_t hi) { return max(min(v, lo), min(max(v, lo), hi)); }
@@ -99,12 +99,13 @@ __global__ __launch_bounds__(256) void table_kernel(TableJobs J) {
     const int32_t b = t.b[i], c = t.c[i], bias = t.bias ? t.bias[i] : 0;
     v4i e;
     if (t.kind == 1) {
-        const int64_t h = (int64_t)bias * b + (int64_t)(1u << ((c - 1) & 31));
+        Residual64 q;
+        residual64_of(q, b, c, bias, 1);
         // |acc| <= 2^14 K.  A term of up to 2^30 is asked for here, once per channel, so that its sum with the residual's needs
         // no saturating addition there (the longer instruction costs 0.6 % of a forward: DeiT-S batch 128 1216 -> 1223 us)
         const int64_t sum = (bias < 0 ? -(int64_t)bias : (int64_t)bias) + ((int64_t)J.arg[blockIdx.y] << 14);
-        const bool fits = dyadic_fits32(b, c) && sum * b < (int64_t)1 << (30 + c);
-        e = v4i{b, fits ? c : 0, (int32_t)(uint32_t)h, (int32_t)(h >> 32)};
+        const bool fits = residual64_takes(b, c) && sum * b < (int64_t)1 << (30 + c);
+        e = v4i{fits ? q.b : 0, 0, (int32_t)(uint32_t)q.h, (int32_t)(q.h >> 32)};
     } else {
         e = v4i{1, 0, 0, 0};
         if (c >= 1 && c <= 24 && b >= 1 && b < (1 << ((c - 1) & 31))) {
@@ -298,10 +299,10 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     };
     // one result, 24-bit form
     auto out_top = [](int32_t a, const Rq& q) __attribute__((always_inline)) -> uint32_t { return (uint32_t)(__mul24(med3c(a, q.lo, q.hi), q.mb) + q.ad); };
-    // one result of a residual layer: one 64-bit multiply-add, a funnel shift, the residual term, the sum limited (it fits
+    // one result of a residual layer: one 64-bit multiply-add, the residual term, the sum limited (it fits
     // 32 bits: at most 2^30 from channels with a 32-bit form, see table_kernel, and 2^29 from the residual)
     auto out_res = [](int32_t a, const Rq64& q, const ResRq& rr, int32_t res) __attribute__((always_inline)) -> uint32_t {
-        return (uint32_t)clamp8(residual64_first(a, q.b, q.c, q.h_lo, q.h_hi) + ((__mul24(res, rr.b) + rr.h) >> rr.c));
+        return (uint32_t)clamp8(residual64_first(a, q) + ((__mul24(res, rr.b) + rr.h) >> rr.c));
     };
     // a lane's 16 results of a tile in 64-bit arithmetic, channel ch of W; results in the low byte
     auto unit_slow = [&](const v16i& a, const DenseW& W, int ch, bool gelu) __attribute__((always_inline)) -> v4i {
@@ -470,7 +471,11 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     bool fast = false;
     auto cst_at = [&](int b, int row) __attribute__((always_inline)) -> v4i { return *reinterpret_cast<const v4i*>(set_at(b) + SETW + 16 * row); };
     auto as_rq = [](const v4i& v) __attribute__((always_inline)) -> Rq { return Rq{v[0], v[1], v[2], v[3]}; };
-    auto as_rq64 = [](const v4i& v) __attribute__((always_inline)) -> Rq64 { return Rq64{v[0], v[1], v[2], v[3]}; };
+    auto as_rq64 = [](const v4i& v) __attribute__((always_inline)) -> Rq64 {
+        Rq64 q{v[0], (int64_t)(((uint64_t)(uint32_t)v[3] << 32) | (uint32_t)v[2])};
+        pin(q.h);
+        return q;
+    };
     const int8_t* const tab = P.table;
 
     if (front) {
@@ -532,7 +537,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                         if constexpr (mt == NMT - 1) proj_slow(g - 1, ic<(g - 1) & 1>());
                     }
                     if constexpr (mt == 0) pqn = cst_at(b, (p * WNG + wn) * 32 + lj);
-                    if constexpr (mt == NMT - 1) { pq = as_rq64(pqn); fast = __builtin_amdgcn_ballot_w64(pq.c != 0 && rr1.ok) == ~0ull; }
+                    if constexpr (mt == NMT - 1) { pq = as_rq64(pqn); fast = __builtin_amdgcn_ballot_w64(pq.b != 0 && rr1.ok) == ~0ull; }
                 },
                 [&]() __attribute__((always_inline)) { sync(); },
                 [&](auto k) __attribute__((always_inline)) { bf[k] = frag(set_at(b ^ 1) + wn * 32 * C, k); });
@@ -725,7 +730,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         Rq64 fq[3];
         bool ok2 = rr2.ok;
 #pragma unroll
-        for (int j = 0; j < 3; ++j) { fq[j] = as_rq64(fb[j]); ok2 = ok2 && fq[j].c != 0; }
+        for (int j = 0; j < 3; ++j) { fq[j] = as_rq64(fb[j]); ok2 = ok2 && fq[j].b != 0; }
         const bool fast2 = __builtin_amdgcn_ballot_w64(ok2) == ~0ull;
         sync();                                                     // the rows of xhat are there; the hidden chunks are done with
         if (P.next == 2) { L = load_rows(P.qkv_w.w, tab + TB_QKV(C, F), 0, 0); load_range(L, ic<0>(), ic<NPR>(), BR()); }

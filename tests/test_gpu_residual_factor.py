@@ -1,0 +1,64 @@
+"""Residual layers at the edges of the 64-bit multiply-add by b 2^(32-c): it takes b < 2^(c-1) and c <= 31, anything else goes
+through general 64-bit arithmetic.  Whole numbers, compared for equality with the oracle."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from paper_2207_01405_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+PAIRS = [(1, 1), (1, 2), (2 ** 14 - 1, 15), (2 ** 14, 15), (2 ** 15, 15), (2 ** 23 - 1, 24), (2 ** 23, 24), (2 ** 30 - 1, 31), (2 ** 30, 31),
+         (2 ** 31 - 1, 31), (2 ** 31 - 1, 32), (20011, 46)]
+
+
+def _constants(n, rng):
+    """Every pair on some channels, biases over the whole int32 range."""
+    b, c = (np.array([PAIRS[j % len(PAIRS)][k] for j in range(n)], np.int32) for k in (0, 1))
+    bias = rng.integers(-2 ** 30, 2 ** 30, size=n).astype(np.int32)
+    bias[rng.random(n) < 0.5] >>= 18
+    return b, c, bias
+
+
+@pytest.mark.parametrize("uniform", [True, False])                 # a workgroup with one pair everywhere, or with all of them
+@pytest.mark.parametrize("M,N,K,kernel", [(130, 130, 144, None), (300, 384, 384, "reg_stationary"), (300, 256, 768, "reg_stationary"),
+                                          (300, 384, 1536, "reg_stationary"), (700, 256, 512, "big_tiles"), (40000, 256, 2304, "big_tiles")])
+@pytest.mark.parametrize("rounding", ["nearest", "floor"])
+def test_dense(ivit, M, N, K, kernel, rounding, uniform):
+    import torch
+    rng = np.random.default_rng(M + N + K)
+    x, w, res = (rng.integers(-128, 128, size=s).astype(np.int8) for s in ((M, K), (N, K), (M, N)))
+    rows = np.unique(np.linspace(0, M - 1, 60).astype(int))
+    dev = lambda a: torch.from_numpy(a).cuda()
+    b, c, bias = _constants(N, rng)
+    for pair in (PAIRS if uniform else PAIRS[:1]):
+        if uniform:
+            b[:], c[:] = pair
+        y = torch.empty((M, N), dtype=torch.int8, device="cuda")
+        ivit.ivit_linear_requant(dev(x), dev(w), dev(bias), dev(b), dev(c), y, residual=dev(res), res_rq=(20011, 15), kernel=kernel, rounding=rounding)
+        want = orc.linear_requant(x[rows], w, bias, b, c, residual=res[rows], res_rq=(20011, 15), floor_shift=rounding == "floor")
+        got = y.cpu().numpy()[rows]
+        assert np.array_equal(got, want), "%s: %d of %d differ" % (pair, (got != want).sum(), got.size)
+
+
+@pytest.mark.parametrize("C,H,F", [(96, 3, 384), (192, 3, 768), (384, 6, 1536)])
+@pytest.mark.parametrize("pair", PAIRS)
+def test_token_block(ivit, C, H, F, pair):
+    import torch
+    R = 5200
+    cfg = dict(T=1, C=C, H=H, F=F, seed=C, i0="fixed", rel_bias=False)
+    blocks = [synth.make_block(cfg, l) for l in range(2)]
+    for p in blocks:
+        for name in ("proj", "fc2"):
+            p[name + "_rq_b"][0::3], p[name + "_rq_c"][0::3] = pair
+            if C == 192:                                             # every channel: no wavefront mixes the two forms
+                p[name + "_rq_b"][:], p[name + "_rq_c"][:] = pair
+    x = synth.make_rows(R, R, C)
+    xd = torch.from_numpy(x).cuda()
+    y = torch.empty_like(xd)
+    d = dict(B=R, T=1, C=C, H=H, F=F)
+    ws = torch.empty(ivit.ivit_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    ivit.ivit_forward(xd, y, [ivit.to_device(p) for p in blocks], d, ws)
+    rows = np.arange(0, R, 52)
+    got, want = y.cpu().numpy()[rows], orc.forward(x[rows], blocks, dict(d, B=len(rows)))
+    assert np.array_equal(got, want), "%d of %d differ" % ((got != want).sum(), got.size)
