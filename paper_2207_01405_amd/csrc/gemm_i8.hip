@@ -497,16 +497,16 @@ hipError_t launch_linear(hipStream_t s, const LinearArgs& a) {
     P.y = a.y; P.M = a.M; P.N = a.N; P.K = a.K; P.ldx = a.ldx ? a.ldx : a.K; P.rnd = a.floor_shift ? 0 : 1;
     const int64_t bytes = a.M * a.K + (int64_t)a.N * a.K + a.M * a.N * (a.residual ? 2 : 1) + 8LL * a.N + (a.bias ? 4LL * a.N : 0);
     TraceScope trace(s, a.residual ? KIND_GEMM_RESIDUAL : (a.gelu ? KIND_GEMM_GELU : KIND_GEMM), 2 * a.M * a.N * a.K, bytes);
+    if (a.kernel == LINEAR_AUTO && linear_kq_takes(a)) return launch_linear_kq(s, a);
     if (a.ln_g) return launch_linear_st(s, a);
     if (a.kernel == LINEAR_AUTO) {
-        // Up to a few 64 x 64 tiles per CU: streamed tiles (gemm_st.hip).  The kernels below keep weights in registers or LDS
+        // Up to a few 64 x 64 tiles per CU, and more than gemm_kq.hip takes: streamed tiles (gemm_st.hip).  The kernels below keep weights in registers or LDS
         // or use large tiles, which pays once a workgroup has many rows to apply them to.  Measured with 256 CUs, time with
         // streamed tiles against the kernel it replaces: rows x N = 1576 x 2304 (900 tiles), K = 768: 7.4 against 9.5 us;
         // 6000 x 768 (1128): 8.8 against 10.5; 4100 x 2304 (2340): 15.2 against 14.0.  With a residual 4100 x 768 (780),
         // K = 768: 9.1 against 10.5; 6272 x 768 (1176): 14.0 against 12.2; K = 3072, 1576 rows (300): 10.4 against 25.0,
         // 6000 rows (1128): 27.1 against 27.7, 25216 rows (4728): 80.6 against 77.6.  K = 192 without one, 4100 x 768 (780):
-        // 5.8 against 6.3; 12544 x 576 (1764): 8.6 against 8.1.  One 32 x 32 tile per workgroup with K split over its wavefronts was
-        // no faster even for few rows (197 x 1032 x 2000: 7.6 against 6.6 us, 37 x 384 x 1536 with a residual 9.2 against 6.0).
+        // 5.8 against 6.3; 12544 x 576 (1764): 8.6 against 8.1.
         const int64_t limit = !a.residual && a.K >= 384 && a.K < 1536 ? 7 : 4;
         if (((a.M + 63) / 64) * ((a.N + 63) / 64) <= limit * num_cus()) return launch_linear_st(s, a);
     }

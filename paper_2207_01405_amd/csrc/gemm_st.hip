@@ -33,12 +33,6 @@ struct StParams {
 typedef int v4i_w __attribute__((ext_vector_type(4), aligned(4)));     // 16 bytes at any address of words
 typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));   // 16 bytes at any address
 
-// 4 bytes per lane from global memory into LDS (as dma16 of regst_common.hpp)
-__device__ __forceinline__ void dma4(const void* base, uint32_t off, uint32_t dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
-                 : : "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(off), "s"(base) : "memory", "m0");
-}
-
 // every load but the newest N of this wavefront has arrived, its LDS reads have returned, and so for all wavefronts
 template <int N> __device__ __forceinline__ void arrive() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
@@ -372,6 +366,7 @@ hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
 // batch 2 760 against 807, batch 8 873 against 881; with up to four tiles per CU ViT-B batch 4 560 against 518, Swin-S batch 8
 // 917 against 881.  With 64 x 64 tiles, twice the rows to normalise: DeiT-S batch 1 390, ViT-B batch 1 515 us.
 bool linear_ln_takes(const LinearArgs& a) {
+    if (!a.residual && a.K <= 768 && linear_kq_takes(a)) return true;
     using TL = StTile<1, 1, 6>;
     return !a.residual && (a.K & 15) == 0 && a.K >= 64 && a.K <= 768 &&
            ((a.M + TL::TM - 1) / TL::TM) * ((a.N + TL::TN - 1) / TL::TN) <= 2 * num_cus();

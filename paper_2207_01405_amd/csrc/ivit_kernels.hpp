@@ -42,6 +42,9 @@ hipError_t launch_linear_ks(hipStream_t s, const LinearArgs& a);
 // Long rows, both operands streamed through LDS in 256 x 128 tiles (gemm_tl.hip).
 bool linear_tl_takes(const LinearArgs& a);
 hipError_t launch_linear_tl(hipStream_t s, const LinearArgs& a);
+// Few rows, K split over the wavefronts of a workgroup (gemm_kq.hip).
+bool linear_kq_takes(const LinearArgs& a);
+hipError_t launch_linear_kq(hipStream_t s, const LinearArgs& a);
 // Any shape, both operands streamed through LDS in small tiles (gemm_st.hip).
 hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a);
 bool linear_ln_takes(const LinearArgs& a);

@@ -21,6 +21,21 @@ constexpr int WCK = 384;                     // bytes of K per weight chunk of t
 constexpr int WPITCH = WCK + 16;             // its row pitch in LDS
 constexpr int WWI = 4 * 32 * (WPITCH / 16) / 64;    // load instructions (64 lanes x 16 bytes) per chunk: [4 wavefronts][32 channels][WPITCH]
 
+// Division of a workgroup's number by a number the host knows, in scalar instructions (the 64-bit division that the compiler
+// writes out is 140 of them, a microsecond with one wavefront per SIMD).  With m = floor((2^32 - (d == 1)) / d) and t < 2^31
+// the estimate is at most one too small.
+struct FastDiv {
+    uint32_t d, m;
+    FastDiv() = default;
+    explicit FastDiv(uint32_t d_) : d(d_), m((uint32_t)((((uint64_t)1 << 32) - (d_ == 1)) / d_)) {}
+    __device__ __forceinline__ uint32_t divide(uint32_t t, uint32_t& rest) const {
+        uint32_t q = (uint32_t)(((uint64_t)t * m) >> 32);
+        rest = t - q * d;
+        if (rest >= d) { ++q; rest -= d; }
+        return q;
+    }
+};
+
 // f(0), .. f(N - 1), each with its number as a type
 template <int N, class F> __device__ __forceinline__ void static_for(F&& f) {
     [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }(std::make_integer_sequence<int, N>());
@@ -43,6 +58,11 @@ __device__ __forceinline__ const int8_t* uniform_ptr(const int8_t* p) {         
 __device__ __forceinline__ void dma16(const int8_t* base, uint32_t off, uint32_t lds_wave_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  : : "s"(__builtin_amdgcn_readfirstlane(lds_wave_base)), "v"(off), "s"(base) : "memory", "m0");
+}
+// ... 4 bytes per lane
+__device__ __forceinline__ void dma4(const void* base, uint32_t off, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+                 : : "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(off), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
