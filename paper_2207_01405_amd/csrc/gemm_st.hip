@@ -24,7 +24,7 @@ constexpr int BK = 128;                       // bytes of K per stage
 struct StParams {
     const int8_t* x; const int8_t* w; const int32_t* bias; const int32_t* rq_b; const int32_t* rq_c;
     const int8_t* residual; Dyadic res_rq; ShiftParams gelu_p; Dyadic gelu_rq;
-    int8_t* y; int64_t M; int N; int K; int tiles_n; int64_t tiles; int64_t per_xcd;
+    int8_t* y; int64_t M; int N; int K; FastDiv inner; uint32_t tiles, per_xcd; int m_fast;      // inner: tiles in the dimension that runs fastest
     int64_t ldx;                              // bytes between rows of x
     int rnd;                                  // 1: round to nearest, 0: floor (every requantisation of the epilogue)
     const int32_t* ln_g; const int32_t* ln_b; int ln_f, ln_c;   // XS > 0: I-LayerNorm of the rows of x
@@ -32,6 +32,12 @@ struct StParams {
 
 typedef int v4i_w __attribute__((ext_vector_type(4), aligned(4)));     // 16 bytes at any address of words
 typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));   // 16 bytes at any address
+
+// 16 bytes per lane from a buffer into LDS at lds + AT (the wait state is the one that such a load needs after m0 was written)
+template <int AT> __device__ __forceinline__ void load_lds(const v4i& buf, uint32_t off, uint32_t more, uint32_t lds) {
+    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 : : "s"(lds), "v"(off), "s"(buf), "s"(more), "i"(AT) : "memory", "m0", "scc");
+}
 
 // every load but the newest N of this wavefront has arrived, its LDS reads have returned, and so for all wavefronts
 template <int N> __device__ __forceinline__ void arrive() {
@@ -53,16 +59,20 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
     constexpr int XB = XS * TM * BK, WR = XS > 0 ? 0 : TM, STG = (WR + TN) * BK;    // resident bytes of x; rows of x in a streamed stage
     __shared__ __align__(16) int8_t lds[XB + S * STG];
     __shared__ __align__(16) int32_t qb_s[TN], qc_s[TN], bias_s[TN];
-    __shared__ int8_t gelu_lut[256];
+    __shared__ __align__(16) v4i cst[TN];     // a channel's factor, 0, and the two words of its addend (Residual64 of regst_common.hpp)
+    __shared__ int8_t gelu_lut[256];          // of the results -128 .. 127
 
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 31, lg = lane >> 5, wm = wv / TL::WGN, wn = wv % TL::WGN;
 
-    // each XCD takes a contiguous range of tiles; within it the channel tile index runs fastest
-    const int64_t tile = (int64_t)(blockIdx.x % NXCD) * P.per_xcd + blockIdx.x / NXCD;
+    // each XCD takes a contiguous range of tiles; the operand with fewer rows runs fastest, so that the other one is read by
+    // few XCDs
+    const uint32_t tile = (blockIdx.x % NXCD) * P.per_xcd + blockIdx.x / NXCD;
     if (tile >= P.tiles) return;
-    const int64_t m0 = (tile / P.tiles_n) * TM;
-    const int n0 = (int)(tile % P.tiles_n) * TN;
+    uint32_t in;
+    const uint32_t out = P.inner.divide(tile, in);
+    const int64_t m0 = (int64_t)(P.m_fast ? in : out) * TM;
+    const int n0 = (int)(P.m_fast ? out : in) * TN;
     const int K = P.K, N = P.N;
     const int rows = (int)min64(P.M - m0, TM);
 
@@ -78,15 +88,14 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
                     res[tt][ct] = *reinterpret_cast<const v4i_any*>(P.residual + (m0 + row0 + 32 * tt) * N + n_l + 16 * ct);
     }
 
-    // the channels' constants: one array per wavefront
-    if (wv < 3) {
-        const int32_t* src = wv == 0 ? P.rq_b : wv == 1 ? P.rq_c : P.bias;
-        int32_t* dst = wv == 0 ? qb_s : wv == 1 ? qc_s : bias_s;
-#pragma unroll
-        for (int t = 0; t < TN / 64; ++t) {
-            if (src) dma4(uniform_ptr(reinterpret_cast<const int8_t*>(src)), 4u * min(n0 + 64 * t + lane, N - 1), lds_offset(reinterpret_cast<const int8_t*>(dst + 64 * t)));
-            else dst[64 * t + lane] = 0;
-        }
+    // the channels' constants, 64 channels a wavefront
+    if (wv < TN / 64) {
+        const uint32_t off = 4u * min(n0 + 64 * wv + lane, N - 1);
+        auto fetch = [&](const int32_t* src, int32_t* dst) __attribute__((always_inline)) {
+            dma4(uniform_ptr(reinterpret_cast<const int8_t*>(src)), off, lds_offset(reinterpret_cast<const int8_t*>(dst + 64 * wv)));
+        };
+        fetch(P.rq_b, qb_s); fetch(P.rq_c, qc_s);
+        if (P.bias) fetch(P.bias, bias_s); else bias_s[64 * wv + lane] = 0;
     }
 
     // I-LayerNorm: a thread normalises piece n_p of rows n_r, n_r + n_rows, ...; its 16 channels' parameters are requested now
@@ -120,37 +129,57 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
             off[i] = (uint32_t)min(ch, N - 1 - n0) * (uint32_t)K + ld_col;
         }
     }
+    auto buffer = [](const int8_t* p) __attribute__((always_inline)) {
+        const uint64_t a = (uint64_t)p;
+        return v4i{(int)(uint32_t)a, (int)(uint32_t)(a >> 32), 0x7fffffff, 0x00020000};
+    };
     const int stages = (K + BK - 1) / BK, k_last = K - (stages - 1) * BK;      // bytes of K in the last stage: 16 .. 128
-    const uint32_t lds0 = lds_offset(lds) + XB + wv * 1024;
+    const uint32_t lds0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_offset(lds) + XB + wv * 1024));
     if (XS > 0) {
 #pragma unroll 1
         for (int s = 0; s < stages; ++s) {
-            const uint32_t back = s == stages - 1 ? (uint32_t)max(ld_col - (k_last - 16), 0) : 0u;
+            const uint32_t end = s == stages - 1 ? (uint32_t)max(ld_col - (k_last - 16), 0) : 0u;
 #pragma unroll
-            for (int i = 0; i < XI; ++i) dma16(xg + s * BK, off[i] - back, lds0 - XB + s * TM * BK + i * 4096);
+            for (int i = 0; i < XI; ++i) dma16(xg + s * BK, off[i] - end, lds0 - XB + s * TM * BK + i * 4096);
         }
     }
-    // the stage being requested: its number, bases and buffer, and how far a lane's piece moves back (last stage only)
-    int is = 0, is_buf = 0;
-    auto issue_one = [&](int i) __attribute__((always_inline)) {
-        const uint32_t back = is == stages - 1 ? (uint32_t)max(ld_col - (k_last - 16), 0) : 0u;
-        dma16(i < DPX ? xg : wg, off[XI - DPX + i] - back, lds0 + is_buf * STG + i * 4096);
+    // A stage's loads: stage `is` goes to buffer is % S, known where the loads stand.  A lane whose piece lies past the end of
+    // the rows moves back to the last one (the last stage only).  One scalar offset serves both operands.
+    const int back = max(ld_col - (k_last - 16), 0), moves = k_last < BK ? stages - 1 : -1;
+    const v4i x_buf = buffer(xg), w_buf = buffer(wg);
+    int is = 0;
+    uint32_t k_off = 0;
+    auto issue_one = [&](auto i_c, auto buf_c) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_c)::value;
+        load_lds<decltype(buf_c)::value * STG + i * 4096>(i < DPX ? x_buf : w_buf, off[XI - DPX + i], k_off, lds0);
     };
-    auto issue_done = [&]() __attribute__((always_inline)) {
-        ++is;
-        if (++is_buf == S) is_buf = 0;
-        xg += BK; wg += BK;
+    auto issue_begin = [&]() __attribute__((always_inline)) {
+        if (is == moves) {
+#pragma unroll
+            for (int i = XI - DPX; i < XI + TN / 32; ++i) off[i] -= back;
+        }
     };
-#pragma unroll
-    for (int s = 0; s < S - 1; ++s)
-        if (s < stages) {
-#pragma unroll
-            for (int i = 0; i < DPW; ++i) issue_one(i);
+    auto issue_done = [&]() __attribute__((always_inline)) { ++is; k_off += BK; };
+    static_for<S - 1>([&](auto buf) __attribute__((always_inline)) {
+        if (decltype(buf)::value < stages) {
+            issue_begin();
+            static_for<DPW>([&](auto i) __attribute__((always_inline)) { issue_one(i, buf); });
             issue_done();
         }
+    });
     if (EPI == EPI_GELU) {
         const int32_t I = (int32_t)(int8_t)tid;
-        gelu_lut[tid] = (int8_t)requant64(shiftgelu_raw(I, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c, P.rnd);
+        gelu_lut[(uint8_t)(I + 128)] = (int8_t)requant64(shiftgelu_raw(I, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c, P.rnd);
+    }
+    // a result is the high word of one 64-bit multiply-add, whatever the epilogue; with ShiftGELU it comes as 0 .. 255.  The epilogue
+    // of 16 results is 104 vector instructions with a residual (217 when every result needed its own shift and residual product).
+    if (wv < TN / 64) {
+        if (stages >= S - 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((S - 1) * DPW) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        const int ch = 64 * wv + lane;
+        Residual64 q;
+        const bool ok = residual64_of(q, qb_s[ch], qc_s[ch], bias_s[ch], P.rnd);
+        cst[ch] = v4i{ok ? q.b : 0, 0, (int32_t)(uint32_t)q.h, (int32_t)(q.h >> 32) + (EPI == EPI_GELU ? 128 : 0)};
     }
 
     if constexpr (XS > 0) {
@@ -206,14 +235,20 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
     }
 
     v16i acc[NT][MT] = {};
-    const int x_row = row0 * BK, w_row = (WR + wn * 32 * NT + li) * BK, sw = (li >> 1) & 7;
+    constexpr int KS = BK / 32, AHEAD = MT * NT == 1 ? KS : 2;      // fragments are read AHEAD k-steps before their use
+    int fx[KS], fw[KS];                                   // where this lane's fragments of k-step kk lie (buffer 0)
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+        const int col = 16 * ((2 * kk + lg) ^ ((li >> 1) & 7));
+        fx[kk] = (XS > 0 ? 0 : XB) + row0 * BK + col;
+        fw[kk] = XB + (WR + wn * 32 * NT + li) * BK + col;
+    }
     struct Frag { v4i a[NT], b[MT]; };
-    auto read_frag = [&](Frag& f, const int8_t* xs, const int8_t* st, int kk) __attribute__((always_inline)) {
-        const int col = 16 * ((2 * kk + lg) ^ sw);
+    auto read_frag = [&](Frag& f, int kk, int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int ct = 0; ct < NT; ++ct) f.a[ct] = *reinterpret_cast<const v4i*>(st + w_row + ct * 32 * BK + col);
+        for (int ct = 0; ct < NT; ++ct) f.a[ct] = *reinterpret_cast<const v4i*>(lds + fw[kk] + buf * STG + ct * 32 * BK);
 #pragma unroll
-        for (int tt = 0; tt < MT; ++tt) f.b[tt] = *reinterpret_cast<const v4i*>(xs + x_row + tt * 32 * BK + col);
+        for (int tt = 0; tt < MT; ++tt) f.b[tt] = *reinterpret_cast<const v4i*>(lds + fx[kk] + (XS > 0 ? 0 : buf * STG) + tt * 32 * BK);
     };
     auto multiply = [&](const Frag& f) __attribute__((always_inline)) {
 #pragma unroll
@@ -223,60 +258,65 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
     };
     // Stage s: its loads have arrived when at most those of the later stages requested so far (S - 2, fewer at the end)
     // are outstanding; behind the barrier nobody reads stage s - 1 any more and its buffer takes stage s + S - 1.  Those
-    // loads go out between the multiplies: a compute unit accepts one every few dozen cycles, and in one go they would
-    // hold back the fragment reads of the stage.
-    constexpr int KS = BK / 32, AHEAD = MT * NT == 1 ? KS : 2;      // fragments are read AHEAD k-steps before their use
-    int buf = 0, s = 0;
-    auto stage = [&](auto more) __attribute__((always_inline)) {
-        const int8_t* st = lds + XB + buf * STG;
-        const int8_t* xs = XS > 0 ? lds + s * TM * BK : st;
+    // loads go out behind the first fragment reads.  The loop is written out for the S buffers, so that addresses are constants
+    // and a stage of a 64 x 64 tile is 48 instructions instead of 70 (1576 x 2304 x 768 6.6 -> 6.0 us, 197 x 384 x 1536 5.4 -> 5.2).
+    // What bounds it then is the LDS: a 64 x 64 stage writes 16 KB and reads 32 KB, 384 cycles at 128 bytes a cycle, for 128
+    // cycles of products; the loads would come at 64 bytes a cycle and CU.
+    auto wait_stage = [&](int left) __attribute__((always_inline)) {      // left: stages after this one
+        if (S == 2 || left == 0) arrive<0>();
+        else if (S == 3 || left == 1) arrive<DPW>();
+        else if (S == 4 || left == 2) arrive<2 * DPW>();
+        else arrive<3 * DPW>();
+    };
+    int s = 0;
+    const int full = k_last == BK ? stages : stages - 1;  // a last stage of less than 128 bytes comes after the loop
+    auto body = [&](auto buf_c) __attribute__((always_inline)) {
+        constexpr int buf = decltype(buf_c)::value;
+        wait_stage(stages - 1 - s);
         Frag f[AHEAD];
-#pragma unroll
-        for (int kk = 0; kk + 1 < AHEAD; ++kk) read_frag(f[kk], xs, st, kk);
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-            if (kk + AHEAD - 1 < KS) read_frag(f[(kk + AHEAD - 1) % AHEAD], xs, st, kk + AHEAD - 1);
-            if (decltype(more)::value) {
-#pragma unroll
-                for (int i = kk * DPW / KS; i < (kk + 1) * DPW / KS; ++i) issue_one(i);
-            }
-            multiply(f[kk % AHEAD]);
+        static_for<AHEAD - 1>([&](auto kk) __attribute__((always_inline)) { read_frag(f[decltype(kk)::value], decltype(kk)::value, buf); });
+        if (is < stages) {
+            issue_begin();
+            static_for<DPW>([&](auto i) __attribute__((always_inline)) { issue_one(i, std::integral_constant<int, (buf + S - 1) % S>()); });
+            issue_done();
         }
-        if (decltype(more)::value) issue_done();
-        if (++buf == S) buf = 0;
+        static_for<KS>([&](auto kk_c) __attribute__((always_inline)) {
+            constexpr int kk = decltype(kk_c)::value;
+            if constexpr (kk + AHEAD - 1 < KS) read_frag(f[(kk + AHEAD - 1) % AHEAD], kk + AHEAD - 1, buf);
+            multiply(f[kk % AHEAD]);
+        });
+        if (XS > 0) {
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) fx[kk] += TM * BK;
+        }
+        ++s;
     };
 #pragma unroll 1
-    for (; s + S - 1 < stages; ++s) {
-        arrive<(S - 2) * DPW>();
-        stage(std::true_type());
-    }
-#pragma unroll 1
-    for (; s < stages - 1; ++s) {
-        arrive<DPW>();                                    // (S = 3; with two stages there is only the last one left)
-        stage(std::false_type());
-    }
-    arrive<0>();
-    if (k_last == BK) {
-        stage(std::false_type());
-    } else {                                              // what is left of K; of its last 32 bytes maybe the first half only
-#pragma unroll 1
-        for (int kk = 0; 32 * kk < k_last; ++kk) {
+    while (s < full)
+        static_for<S>([&](auto buf) __attribute__((always_inline)) { if (s < full) body(buf); });
+    if (full < stages) {                                  // what is left of K; of its last 32 bytes maybe the first half only
+        arrive<0>();
+        const int buf = s % S;
+        static_for<KS>([&](auto kk_c) __attribute__((always_inline)) {
+            constexpr int kk = decltype(kk_c)::value;
+            if (32 * kk >= k_last) return;
             Frag f;
-            read_frag(f, XS > 0 ? lds + s * TM * BK : lds + XB + buf * STG, lds + XB + buf * STG, kk);
+            read_frag(f, kk, buf);
             if (32 * kk + 16 >= k_last && lg) {
 #pragma unroll
                 for (int ct = 0; ct < NT; ++ct) f.a[ct] = v4i{0, 0, 0, 0};
             }
             multiply(f);
-        }
+        });
     }
-    static_assert(S >= 2 && S <= 3, "wait counts");
+    static_assert(S >= 2 && S <= 5 && (S - 1) * DPW + 2 <= 63, "wait counts");
 
-    // ---- epilogue.  32-bit results where every channel of the wavefront has 1 <= c <= 31 and b <= 2^c
-    bool fits = true;
+    // ---- epilogue
+    bool fits = EPI != EPI_RESIDUAL || residual_term_24(P.res_rq);
 #pragma unroll
-    for (int t = 0; t < NT; ++t) fits = fits && dyadic_fits32(qb_s[32 * (wn * NT + t) + li], qc_s[32 * (wn * NT + t) + li]);
-    const bool fast = __builtin_amdgcn_ballot_w64(fits) == ~0ull && (EPI != EPI_RESIDUAL || dyadic_fits32(P.res_rq.b, P.res_rq.c));
+    for (int t = 0; t < NT; ++t) fits = fits && cst[32 * (wn * NT + t) + li][0] != 0;
+    const bool fast = __builtin_amdgcn_ballot_w64(fits) == ~0ull;
+    const int32_t rb = P.res_rq.b, rc = P.res_rq.c, rh = P.rnd << ((P.res_rq.c - 1) & 31);
     auto finish = [&](auto fastc) __attribute__((always_inline)) {
         constexpr bool FAST = decltype(fastc)::value;
 #pragma unroll
@@ -285,15 +325,27 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
             v4i out[MT];
 #pragma unroll
             for (int d = 0; d < 4; ++d) {                 // 4 channels per packed output word
-                const v4i qb = *reinterpret_cast<const v4i*>(&qb_s[cl + 16 * ct + 4 * d]);
-                const v4i qc = *reinterpret_cast<const v4i*>(&qc_s[cl + 16 * ct + 4 * d]);
-                const v4i bi = *reinterpret_cast<const v4i*>(&bias_s[cl + 16 * ct + 4 * d]);
+                const int ch = cl + 16 * ct + 4 * d;
+                Residual64 q[4];
+                v4i qb, qc, bi;
+                if (FAST) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const v4i e = cst[ch + r];
+                        q[r] = Residual64{e[0], (int64_t)(((uint64_t)(uint32_t)e[3] << 32) | (uint32_t)e[2])};
+                        asm volatile("" : "+v"(q[r].h));  // (see regst_common.hpp)
+                    }
+                } else {
+                    qb = *reinterpret_cast<const v4i*>(&qb_s[ch]);
+                    qc = *reinterpret_cast<const v4i*>(&qc_s[ch]);
+                    bi = *reinterpret_cast<const v4i*>(&bias_s[ch]);
+                }
 #pragma unroll
                 for (int tt = 0; tt < MT; ++tt) {
                     uint32_t o[4];
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const int32_t a32 = acc[ct][tt][4 * d + r] + bi[r];
+                        const int32_t a32 = acc[ct][tt][4 * d + r];
                         int32_t rv = 0;
                         if (EPI == EPI_RESIDUAL) {
                             if (n + 16 <= N) rv = (int32_t)(int8_t)((uint32_t)res[tt][ct][d] >> (8 * r));
@@ -301,14 +353,16 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
                         }
                         int32_t v;
                         if (FAST) {
-                            v = rnd_shift_fit32(a32, qb[r], qc[r], P.rnd);
-                            v = EPI == EPI_RESIDUAL ? clamp8_sum(v, rnd_shift_fit32(rv, P.res_rq.b, P.res_rq.c, P.rnd)) : clamp8(v);
+                            v = residual64_first(a32, q[r]);
+                            if (EPI == EPI_RESIDUAL) v = clamp8_sum(v, (__mul24(rv, rb) + rh) >> rc);
+                            else if (EPI == EPI_GELU) v = min(max(v, 1), 255);
+                            else v = clamp8(v);
                         } else {
-                            int64_t r64 = rnd_shift64(a32, qb[r], qc[r], P.rnd);
+                            int64_t r64 = rnd_shift64(a32 + bi[r], qb[r], qc[r], P.rnd);
                             if (EPI == EPI_RESIDUAL) r64 += rnd_shift64(rv, P.res_rq.b, P.res_rq.c, P.rnd);
-                            v = clamp8_64(r64);
+                            v = clamp8_64(r64) + (EPI == EPI_GELU ? 128 : 0);
                         }
-                        if (EPI == EPI_GELU) v = gelu_lut[(uint8_t)v];
+                        if (EPI == EPI_GELU) v = gelu_lut[v];
                         o[r] = (uint32_t)v;
                     }
                     // low bytes of o[0..3] -> one word
@@ -342,11 +396,11 @@ hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
     P.ln_g = a.ln_g; P.ln_b = a.ln_b; P.ln_f = a.ln_f; P.ln_c = a.ln_c;
     constexpr int TM = StTile<MT, NT, XS>::TM, TN = StTile<MT, NT, XS>::TN;
     static_assert(TM <= kTileRows, "row offsets");
-    P.tiles_n = (a.N + TN - 1) / TN;
-    P.tiles = (a.M + TM - 1) / TM * P.tiles_n;
-    P.per_xcd = (P.tiles + NXCD - 1) / NXCD;
-    const int64_t grid = P.per_xcd * NXCD;
+    const int64_t tm = (a.M + TM - 1) / TM, tn = (a.N + TN - 1) / TN, grid = (tm * tn + NXCD - 1) / NXCD * NXCD;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+    P.m_fast = a.M < a.N;
+    P.inner = FastDiv((uint32_t)(P.m_fast ? tm : tn));
+    P.tiles = (uint32_t)(tm * tn); P.per_xcd = (uint32_t)(grid / NXCD);
     const dim3 g((unsigned)grid), b(256);
     if constexpr (XS == 0) {
         if (a.residual) {
