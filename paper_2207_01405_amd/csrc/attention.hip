@@ -20,6 +20,7 @@
 // bias and the 64-bit requantisation are compiled in only when asked for (template flags), and masking
 // of padded keys is done only for key tiles that are not completely valid.
 #include <algorithm>
+#include <type_traits>
 
 #include "ivit_kernels.hpp"
 
@@ -67,6 +68,51 @@ __device__ __forceinline__ void requant8x4(int32_t (&v)[4], Dyadic d, Narrow n, 
     }
 }
 
+// ---- pieces of the 24-bit form.  A result T has its int8 value in the top byte; sub-dword selects (SDWA) read and write bytes in
+// the instruction that needs them.  The asm statements read ordinary vector results and loads only (see requant8).
+__device__ __forceinline__ int32_t narrow_top(int32_t v, Narrow n) {
+    int32_t m;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(m) : "v"(v), "v"(n.lo), "v"(n.hi));
+    return __mul24(m, n.mb) + n.ad;
+}
+// twice the top byte: the byte offset of a 16-bit table entry
+__device__ __forceinline__ uint32_t twice_top(uint32_t d) {
+    uint32_t r;
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(r) : "v"(1), "v"(d));
+    return r;
+}
+// top byte of t plus byte R of w, both signed
+template <int R> __device__ __forceinline__ int32_t top_plus_byte(int32_t t, uint32_t w) {
+    int32_t r;
+    if constexpr (R == 0) asm("v_add_u32_sdwa %0, sext(%1), sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:BYTE_0" : "=v"(r) : "v"(t), "v"(w));
+    if constexpr (R == 1) asm("v_add_u32_sdwa %0, sext(%1), sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:BYTE_1" : "=v"(r) : "v"(t), "v"(w));
+    if constexpr (R == 2) asm("v_add_u32_sdwa %0, sext(%1), sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:BYTE_2" : "=v"(r) : "v"(t), "v"(w));
+    if constexpr (R == 3) asm("v_add_u32_sdwa %0, sext(%1), sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:BYTE_3" : "=v"(r) : "v"(t), "v"(w));
+    return r;
+}
+// Four words of probabilities: byte r of word i is (f e[i][r]) >> 32, f and e below 2^24.  Every product is written into its byte;
+// writes to one register stand four instructions apart (a byte write may not be followed directly by a reader of that register).
+__device__ __forceinline__ void div_pack4(uint32_t (&w)[4], uint32_t f, const int32_t (&e0)[4], const int32_t (&e1)[4], const int32_t (&e2)[4], const int32_t (&e3)[4]) {
+#define IVIT_DP(D, E, B, U) "v_mul_hi_u32_u24_sdwa %" #D ", %4, %" #E " dst_sel:BYTE_" #B " dst_unused:" U " src0_sel:DWORD src1_sel:DWORD\n\t"
+    asm(IVIT_DP(0, 5, 0, "UNUSED_PAD") IVIT_DP(1, 9, 0, "UNUSED_PAD") IVIT_DP(2, 13, 0, "UNUSED_PAD") IVIT_DP(3, 17, 0, "UNUSED_PAD")
+        IVIT_DP(0, 6, 1, "UNUSED_PRESERVE") IVIT_DP(1, 10, 1, "UNUSED_PRESERVE") IVIT_DP(2, 14, 1, "UNUSED_PRESERVE") IVIT_DP(3, 18, 1, "UNUSED_PRESERVE")
+        IVIT_DP(0, 7, 2, "UNUSED_PRESERVE") IVIT_DP(1, 11, 2, "UNUSED_PRESERVE") IVIT_DP(2, 15, 2, "UNUSED_PRESERVE") IVIT_DP(3, 19, 2, "UNUSED_PRESERVE")
+        IVIT_DP(0, 8, 3, "UNUSED_PRESERVE") IVIT_DP(1, 12, 3, "UNUSED_PRESERVE") IVIT_DP(2, 16, 3, "UNUSED_PRESERVE") IVIT_DP(3, 20, 3, "UNUSED_PRESERVE") "s_nop 0"
+        : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+        : "v"(f), "v"(e0[0]), "v"(e0[1]), "v"(e0[2]), "v"(e0[3]), "v"(e1[0]), "v"(e1[1]), "v"(e1[2]), "v"(e1[3]),
+          "v"(e2[0]), "v"(e2[1]), "v"(e2[2]), "v"(e2[3]), "v"(e3[0]), "v"(e3[1]), "v"(e3[2]), "v"(e3[3]));
+#undef IVIT_DP
+}
+// ... one word
+__device__ __forceinline__ uint32_t div_pack(uint32_t f, const int32_t (&e)[4]) {
+    uint32_t w;
+#define IVIT_DP(E, B, U) "v_mul_hi_u32_u24_sdwa %0, %1, %" #E " dst_sel:BYTE_" #B " dst_unused:" U " src0_sel:DWORD src1_sel:DWORD\n\ts_nop 0\n\t"
+    asm(IVIT_DP(2, 0, "UNUSED_PAD") IVIT_DP(3, 1, "UNUSED_PRESERVE") IVIT_DP(4, 2, "UNUSED_PRESERVE") IVIT_DP(5, 3, "UNUSED_PRESERVE")
+        : "=&v"(w) : "v"(f), "v"(e[0]), "v"(e[1]), "v"(e[2]), "v"(e[3]));
+#undef IVIT_DP
+    return w;
+}
+
 // FAST: both dyadic pairs are rescales by at most 1 with c <= 31 (32-bit requantisation) and the row sum always
 // exceeds 2^(k_out-1), so that IntDiv is one multiply-high by the pre-shifted reciprocal.
 // TFIX: 0, or the token count known at compile time (49, the 7 x 7 windows; 197, the 14 x 14 patches with a class token):
@@ -90,7 +136,12 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
     // table of ShiftExp(-delta): int8 scores give delta <= 254; with a bias and the mask the exact range is wider,
     // and beyond the table the value is 0 whenever it can occur (see the mask comment below)
     constexpr int NLUT = MASK ? 1024 : (BIAS ? 512 : 256);
-    __shared__ uint32_t lut[NLUT];                // (whole words: the value comes out of the read ready to use)
+    // 24-bit form: 16-bit entries (two to a bank, so that fewer lanes meet in one); with the mask its last entry is 0 whatever
+    // the parameters, which is exact: it stands for everything beyond, and at a delta of 1023 itself, which only a masked key
+    // reaches and only for I_0 <= 15, ShiftExp is 0
+    constexpr bool N24 = FAST == 2 && !TAPS;
+    using Entry = std::conditional_t<N24, uint16_t, uint32_t>;
+    __shared__ Entry lut[NLUT];
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int li = lane & 15, lg = lane >> 4;
@@ -171,7 +222,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             vreg[it] = *reinterpret_cast<const v4i*>(kv_row + 2 * C);
         }
         if (work == first) {                       // the table, while the first loads are in flight (visible after the barrier below)
-            for (int i = tid; i < NLUT; i += ATT_THREADS) lut[i] = shiftexp(-i, sm.i0, sm.n_shift);
+            for (int i = tid; i < NLUT; i += ATT_THREADS) lut[i] = N24 && MASK && i == NLUT - 1 ? (Entry)0 : (Entry)shiftexp(-i, sm.i0, sm.n_shift);
         }
         const int64_t orow0 = q_row(qt0);          // output row of the first query tile (before the indices move on)
         if (BIAS) {
@@ -230,6 +281,9 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
                 asm volatile("s_nop 3");
                 __builtin_amdgcn_sched_barrier(0);
             }
+            uint32_t pk[NKC * 4];
+#pragma unroll
+            for (int t = 0; t < NKC * 4; ++t) pk[t] = 0u;
             // ---- requantise, add the bias, row maximum.  Lane (li, lg) holds keys 16 t + 4 lg + r.
             const int64_t tap_row = ((int64_t)item * T + qc) * T;
             // BIAS: a relative-position bias and / or the shifted-window mask.  A masked key gets -100 I_0 (the -100
@@ -240,6 +294,103 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             const int8_t* brow = (BIAS && rel_bias) ? rel_bias + ((int64_t)h * T + qc) * T : nullptr;
             const int8_t* mrow = MASK ? mask + ((int64_t)(b % n_mask) * T + qc) * T : nullptr;
             const int32_t mask_add = -100 * sm.i0;
+            if constexpr (N24) {
+                // Five vector instructions and a table read per score (nine and a read with each step on its own: 3072 pairs of
+                // 197 tokens 63.7 -> 51.4 us, 768 pairs 21.0 -> 18.3).
+                uint32_t base = 0;                 // without a bias: what a score's product is subtracted from
+                int32_t mx = INT32_MIN;
+                if constexpr (!BIAS) {
+                    // the requantisation is monotonic: the row maximum is that of the accumulators.  With T the maximum's result,
+                    // (T | 2^24 - 1) - (m mb + ad), m a limited score, has max - value in its top byte.
+#pragma unroll
+                    for (int t = 0; t < NKT; ++t)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            if (t >= nfull && 16 * t + 4 * lg + r >= T) sc[t][r] = INT32_MIN;
+                            mx = max(mx, sc[t][r]);
+                        }
+                    mx = rows_allreduce(mx, [](int32_t a, int32_t b) { return max(a, b); });
+                    base = ((uint32_t)(__mul24(min(max(mx, nqk.lo), nqk.hi), nqk.mb) + nqk.ad) | 0xffffffu) - (uint32_t)nqk.ad;
+                } else {
+#pragma unroll
+                    for (int t = 0; t < NKT; ++t) {
+                        uint32_t bw = 0, mw = 0;
+                        if (t < nfull) {
+                            if (!MASK || brow) __builtin_memcpy(&bw, brow + 16 * t + 4 * lg, 4);
+                            if (MASK) __builtin_memcpy(&mw, mrow + 16 * t + 4 * lg, 4);
+                        } else {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                const int key = min(16 * t + 4 * lg + r, T - 1);
+                                if (!MASK || brow) bw |= (uint32_t)(uint8_t)brow[key] << (8 * r);
+                                if (MASK) mw |= (uint32_t)(uint8_t)mrow[key] << (8 * r);
+                            }
+                        }
+                        int32_t tp[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) tp[r] = narrow_top(sc[t][r], nqk);
+                        sc[t][0] = top_plus_byte<0>(tp[0], bw); sc[t][1] = top_plus_byte<1>(tp[1], bw);
+                        sc[t][2] = top_plus_byte<2>(tp[2], bw); sc[t][3] = top_plus_byte<3>(tp[3], bw);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            if (MASK) { if ((mw >> (8 * r)) & 0xffu) sc[t][r] += mask_add; }
+                            if (t < nfull || 16 * t + 4 * lg + r < T) mx = max(mx, sc[t][r]);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    mx = rows_allreduce(mx, [](int32_t a, int32_t b) { return max(a, b); });
+                }
+                // ---- ShiftExp by table, row sum
+                const char* lut_b = reinterpret_cast<const char*>(lut);
+                const int32_t mx2 = 2 * mx;
+                int32_t sum = 0;
+#pragma unroll
+                for (int t = 0; t < NKT; ++t) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        uint32_t at;
+                        if constexpr (!BIAS) {
+                            int32_t m;
+                            asm("v_med3_i32 %0, %1, %2, %3" : "=v"(m) : "v"(sc[t][r]), "v"(nqk.lo), "v"(nqk.hi));
+                            at = twice_top(base + (uint32_t)__mul24(m, -nqk.mb));
+                        } else {                   // (written out: the compiler cannot know that the score has 24 bits)
+                            asm("v_mad_i32_i24 %0, %1, -2, %2" : "=v"(at) : "v"(sc[t][r]), "v"(mx2));
+                            if constexpr (MASK) at = min(at, 2u * (NLUT - 1));
+                        }
+                        int32_t e;
+                        if (t < nfull) {
+                            e = (int32_t)*reinterpret_cast<const uint16_t*>(lut_b + at);
+                        } else {                   // (an absent key may stand above the maximum)
+                            const bool there = 16 * t + 4 * lg + r < T;
+                            e = (int32_t)*reinterpret_cast<const uint16_t*>(lut_b + (there ? at : 0u));
+                            e = there ? e : 0;
+                        }
+                        sc[t][r] = e;
+                        sum += e;
+                    }
+                    if (t & 1) __builtin_amdgcn_sched_barrier(0);
+                }
+                sum = rows_allreduce(sum, [](int32_t a, int32_t b) { return a + b; });
+                // ---- IntDiv: M - (k_out - 1) = 24 here and inv <= 2^16 (launch_flags sees to it), so (inv 2^8) e has the quotient
+                // in its upper word.  2^(k_out-1), which a byte may not become, is the quotient only where one key has
+                // the whole sum, ShiftExp(0); taking one from inv there gives 2^(k_out-1) - 1 and leaves every other row
+                // alone.  The reciprocal is recip_pow2_small for a sum in its range.
+                uint32_t inv = (uint32_t)((float)(1u << sm.m_bits) * __builtin_amdgcn_rcpf((float)(uint32_t)sum));
+                const int32_t rem = (int32_t)((1u << sm.m_bits) - inv * (uint32_t)sum);
+                inv += (rem >= sum);
+                inv -= (rem < 0);
+                inv -= sum == (sm.i0 << sm.n_shift);
+                const uint32_t f = inv << 8;
+#pragma unroll
+                for (int t = 0; t + 4 <= NKT; t += 4) {
+                    uint32_t w[4];
+                    div_pack4(w, f, sc[t], sc[t + 1], sc[t + 2], sc[t + 3]);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) pk[t + k] = w[k];
+                }
+#pragma unroll
+                for (int t = NKT & ~3; t < NKT; ++t) pk[t] = div_pack(f, sc[t]);
+            } else {
             int32_t mx = INT32_MIN;
 #pragma unroll
             for (int t = 0; t < NKT; ++t) {
@@ -318,20 +469,8 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             // ---- IntDiv and packing: the four keys of tile t become one word of the "B" operand
             const uint32_t inv = (1u << sm.m_bits) / (uint32_t)sum;
             const uint32_t inv_hi = FAST ? inv << (32 - sh) : 0u;      // FAST: inv < 2^sh, 1 <= sh <= 31
-            uint32_t pk[NKC * 4];
-#pragma unroll
-            for (int t = 0; t < NKC * 4; ++t) pk[t] = 0u;
 #pragma unroll
             for (int t = 0; t < NKT; ++t) {
-                if (FAST == 2 && !TAPS) {
-                    // M - (k_out - 1) = 24 here: inv < 2^24 and the ShiftExp values are below 2^16, so inv * e (at most
-                    // 2^31) is one 24-bit multiply and the quotient is its top byte
-                    uint32_t pr[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) pr[r] = mul_u24(inv, (uint32_t)sc[t][r]);
-                    pk[t] = __builtin_amdgcn_perm(pr[1], pr[0], 0x0c0c0703u) | __builtin_amdgcn_perm(pr[3], pr[2], 0x07030c0cu);
-                    continue;
-                }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     if (TAPS) {
@@ -350,6 +489,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             if (!TAPS) {
 #pragma unroll
                 for (int t = 0; t < NKT; ++t) pk[t] -= (pk[t] >> (sm.k_out - 1)) & 0x01010101u;   // bytewise min(p, 2^(k_out-1) - 1)
+            }
             }
             // ---- O^T = V^T P^T : "A" = V^T rows (features), "B" = packed probabilities (keys x queries).
             // Contraction position 16 lg + 4 j + r of chunk c is key 64 c + 16 j + 4 lg + r (the layout of pk).  A
@@ -386,6 +526,13 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             uint32_t ow[ND];
 #pragma unroll
             for (int n = 0; n < ND; ++n) {
+                if constexpr (FAST == 2) {         // result in the top byte
+                    uint32_t ov[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) ov[r] = (uint32_t)narrow_top(oacc[n][r], npv);
+                    ow[n] = __builtin_amdgcn_perm(ov[1], ov[0], 0x0c0c0703u) | __builtin_amdgcn_perm(ov[3], ov[2], 0x07030c0cu);
+                    continue;
+                }
                 uint32_t w = 0;
                 int32_t ov[4] = {oacc[n][0], oacc[n][1], oacc[n][2], oacc[n][3]};
                 requant8x4<FAST>(ov, pv, npv, rnd);
@@ -426,7 +573,10 @@ static void launch_flags(hipStream_t s, const AttentionArgs& a, int grid, int sp
     Narrow nqk{}, npv{};
     // the 24-bit forms: both requantisations, and IntDiv with its quotient in the top byte of a 24-bit product
     const int rnd = a.floor_shift ? 0 : 1;
-    const bool narrow = narrow_of(a.qk_rq, rnd, nqk) && narrow_of(a.pv_rq, rnd, npv) && a.sm.m_bits - (a.sm.k_out - 1) == 24;
+    // of at most 2^16 (a row's sum is at least ShiftExp(0) = I_0 << N), the reciprocal times 2^8 in 24 bits
+    const int64_t e0 = (int64_t)a.sm.i0 << a.sm.n_shift;
+    const bool narrow = narrow_of(a.qk_rq, rnd, nqk) && narrow_of(a.pv_rq, rnd, npv) && a.sm.m_bits - (a.sm.k_out - 1) == 24 &&
+                        e0 << 16 >= (int64_t)1 << a.sm.m_bits && e0 >= 512;
 #define IVIT_ATT(TAPS_, BIAS_, MASK_, FAST_, TFIX_)                                                                         \
     hipLaunchKernelGGL((attention_kernel<D, NKT, TAPS_, BIAS_, MASK_, FAST_, TFIX_>), dim3(grid), dim3(ATT_THREADS), 0, s,     \
                        a.qkv, a.rel_bias, a.mask, a.n_mask, a.tok_index, a.n_win, a.o, n_items, split, a.T, a.C, a.H, a.qk_rq, \
