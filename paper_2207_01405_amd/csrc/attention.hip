@@ -120,17 +120,18 @@ __device__ __forceinline__ uint32_t div_pack(uint32_t f, const int32_t (&e)[4]) 
 template <int D, int NKT, bool TAPS, bool BIAS, bool MASK, int FAST, int TFIX = 0>
 __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t* __restrict__ qkv,
                                                         const int8_t* __restrict__ rel_bias,
-                                                        const int8_t* __restrict__ mask, int n_mask,
-                                                        const int32_t* __restrict__ tok_index, int n_win,
-                                                        int8_t* __restrict__ o, int n_items, int split, int T_arg, int C, int H,
+                                                        const int8_t* __restrict__ mask, FastDiv n_mask,
+                                                        const int32_t* __restrict__ tok_index, FastDiv n_win,
+                                                        int8_t* __restrict__ o, int n_items, FastDiv split_d, int T_arg, int C, FastDiv H,
                                                         Dyadic qk, ShiftParams sm, Dyadic pv, Narrow nqk, Narrow npv, int rnd,
                                                         int8_t* __restrict__ tap_s, int8_t* __restrict__ tap_p) {
-    const int T = TFIX ? TFIX : T_arg;
+    const int T = TFIX ? TFIX : T_arg, split = (int)split_d.d;
     constexpr int KROW = D + 16;                  // K row pitch (bytes)
     constexpr int NKC = (NKT + 3) / 4;            // 64-key chunks of the P V contraction
     constexpr int VP = D == 64 ? 72 : 40;         // V row pitch (bytes): the transposing reads below meet no bank twice
     constexpr int ND = D / 16;                    // 16-feature tiles of the output
     constexpr int DCH = D / 16;                   // 16-byte chunks per K / V row
+    constexpr bool ONE = TFIX && TFIX <= 16 * ATT_WAVES;      // no wavefront has a second query tile
     __shared__ __align__(16) int8_t Ks[NKT * 16 * KROW];
     __shared__ __align__(16) int8_t Vs[NKC * 64 * VP];
     // table of ShiftExp(-delta): int8 scores give delta <= 254; with a bias and the mask the exact range is wider,
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
     using Entry = std::conditional_t<N24, uint16_t, uint32_t>;
     __shared__ Entry lut[NLUT];
 
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lg = lane >> 4;
     // (the ShiftExp table is filled inside the first item, once its loads of K, V and Q are on their way)
     // keys beyond the 16-key tiles but inside the last 64-key chunk multiply probabilities that are zero;
@@ -159,53 +160,59 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
     // qkv (two 64-byte head slices per line), which then meet in one L2
     const int G = gridDim.x, xcd = blockIdx.x % 8;
     const int first = xcd * (G / 8) + min(xcd, G % 8) + blockIdx.x / 8;
-    // Rows of qkv / o.  Without a table token t of window b is row b T + t.  With one (BIAS instances only) the rows
-    // come from the index table of the window's position inside its image; an entry outside the image is clamped,
-    // never followed.  The table entries this thread needs for an item (its K / V pieces and its first query tile) are
-    // fetched one item ahead, so that the loads of K, V and Q never wait for an index.
-    constexpr int NPC = (NKT * 16 * DCH + ATT_THREADS - 1) / ATT_THREADS;     // 16-byte pieces per thread and operand
-    const int tpi = n_win * T;                     // tokens per image
-    const bool gather = BIAS && tok_index != nullptr;
-    int kvrow[NPC], qrow0 = 0, kvnext[NPC], qnext = 0;
-    auto fetch_rows = [&](int work, int (&kv)[NPC], int& qr) {
-        const int item = work / split, b = item / H;
-        const int32_t* tr = tok_index + (b % n_win) * T;
-        const int r0 = (b / n_win) * tpi;
-#pragma unroll
-        for (int it = 0; it < NPC; ++it) {
-            const int key = min((tid + ATT_THREADS * it) / DCH, T - 1);
-            kv[it] = r0 + (int)min((uint32_t)tr[key], (uint32_t)(tpi - 1));
-        }
-        qr = r0 + (int)min((uint32_t)tr[min((work % split + split * ((wv + item) % ATT_WAVES)) * 16 + li, T - 1)], (uint32_t)(tpi - 1));
-    };
     // a work item is one (window, head) or, with split > 1, every split-th query tile of it: when there are too few
     // (window, head) pairs to give every workgroup slot of the device one, each pair is shared by `split` workgroups
     // (K and V are staged by each of them; they are small)
     const int n_work = n_items * split;
-    if (BIAS) { if (gather && first < n_work) fetch_rows(first, kvrow, qrow0); }
+    struct Item { uint32_t item, part, b, h, image, win; };                    // of a table: the image and the window's place in it
+    const bool gather = BIAS && tok_index != nullptr;
+    auto item_of = [&](int work) __attribute__((always_inline)) -> Item {
+        Item t{};
+        t.item = split_d.divide((uint32_t)work, t.part);
+        t.b = H.divide(t.item, t.h);
+        if (gather) t.image = n_win.divide(t.b, t.win);
+        return t;
+    };
+    // Rows of qkv / o, counted from the first row of the window or, with a table, of its image (that row's address is a
+    // scalar, a lane adds one 32 x 32-bit product to it).  Without a table token t is row t.  With one (BIAS instances
+    // only) the rows come from the index table of the window's position inside its image; an entry outside the image is
+    // clamped, never followed.  The table entries this thread needs for an item (its K / V pieces and its first query
+    // tile) are fetched one item ahead, so that the loads of K, V and Q never wait for an index.
+    constexpr int NPC = (NKT * 16 * DCH + ATT_THREADS - 1) / ATT_THREADS;     // 16-byte pieces per thread and operand
+    const int tpi = (int)n_win.d * T;              // tokens per image
+    const uint32_t C3 = 3 * (uint32_t)C;
+    uint32_t kvrow[NPC], qrow0 = 0;
+    // this wavefront's first query tile.  The tiles rarely divide evenly among the wavefronts (13 tiles of 197
+    // tokens: one wavefront gets four, the others three); which wavefront starts moves on with the item, so that
+    // the workgroups that share a compute unit do not all give the extra tile to the same SIMD.
+    auto first_tile = [&](const Item& t) __attribute__((always_inline)) { return (int)t.part + split * (int)((wv + t.item) % ATT_WAVES); };
+    auto fetch_rows = [&](const Item& t) __attribute__((always_inline)) {
+        const int32_t* tr = tok_index + t.win * T;
+#pragma unroll
+        for (int it = 0; it < NPC; ++it) kvrow[it] = min((uint32_t)tr[min((tid + ATT_THREADS * it) / DCH, T - 1)], (uint32_t)(tpi - 1));
+        qrow0 = min((uint32_t)tr[min(first_tile(t) * 16 + li, T - 1)], (uint32_t)(tpi - 1));
+    };
+    Item cur = item_of(first), nxt{};
+    if (BIAS) { if (gather && first < n_work) fetch_rows(cur); }
 
-    for (int work = first; work < n_work; work += G) {
-        const int item = work / split, part = work % split;
-        // this wavefront's first query tile.  The tiles rarely divide evenly among the wavefronts (13 tiles of 197
-        // tokens: one wavefront gets four, the others three); which wavefront starts moves on with the item, so that
-        // the workgroups that share a compute unit do not all give the extra tile to the same SIMD.
-        const int qt0 = part + split * ((wv + item) % ATT_WAVES);
-        const int b = item / H, h = item % H;
-        const int8_t* base = qkv + h * D;
-        const int32_t* trow = gather ? tok_index + (b % n_win) * T : nullptr;
-        const int64_t row0 = gather ? (int64_t)(b / n_win) * tpi : (int64_t)b * T;
-        auto row_of = [&](int t) -> int64_t {      // any token of this window (t < T)
-            if (BIAS) { if (trow) return row0 + (int)min((uint32_t)trow[t], (uint32_t)(tpi - 1)); }
-            return row0 + t;
+    for (int work = first; work < n_work; work += G, cur = nxt) {
+        const int item = (int)cur.item, b = (int)cur.b, h = (int)cur.h, qt0 = first_tile(cur);
+        const int64_t row0 = gather ? (int64_t)cur.image * tpi : (int64_t)b * T;
+        const int8_t* base = qkv + row0 * C3 + h * D;
+        const int32_t* trow = gather ? tok_index + cur.win * T : nullptr;
+        auto at = [&](uint32_t row) __attribute__((always_inline)) { return base + (uint64_t)row * C3; };
+        auto row_of = [&](int t) -> uint32_t {     // any token of this window (t < T)
+            if (BIAS) { if (trow) return min((uint32_t)trow[t], (uint32_t)(tpi - 1)); }
+            return (uint32_t)t;
         };
-        auto q_row = [&](int qt) -> int64_t {      // row of this lane's query of tile qt
+        auto q_row = [&](int qt) -> uint32_t {     // row of this lane's query of tile qt
             if (BIAS) { if (gather && qt == qt0) return qrow0; }
             return row_of(min(qt * 16 + li, T - 1));
         };
         __syncthreads();                           // table ready / previous item's readers done
         // the query fragment of a tile is requested one tile ahead, the first one together with K and V
-        auto load_q64 = [&](int qt) { return *reinterpret_cast<const v4i*>(base + q_row(qt) * 3 * C + 16 * lg); };
-        auto load_q32 = [&](int qt) { return *reinterpret_cast<const long*>(base + q_row(qt) * 3 * C + 8 * lg); };
+        auto load_q64 = [&](int qt) { return *reinterpret_cast<const v4i*>(at(q_row(qt)) + 16 * lg); };
+        auto load_q32 = [&](int qt) { return *reinterpret_cast<const long*>(at(q_row(qt)) + 8 * lg); };
         v4i qn64 = {0, 0, 0, 0};
         long qn32 = 0;
         if (D == 64) qn64 = load_q64(qt0); else qn32 = load_q32(qt0);
@@ -215,23 +222,19 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
         for (int it = 0; it < NPC; ++it) {
             const int c = tid + ATT_THREADS * it;
             const int key = min(c / DCH, T - 1), part = c % DCH;
-            int64_t row = row0 + key;
+            uint32_t row = (uint32_t)key;
             if (BIAS) { if (gather) row = kvrow[it]; }
-            const int8_t* kv_row = base + row * 3 * C + 16 * part;
+            const int8_t* kv_row = at(row) + 16 * part;
             kreg[it] = *reinterpret_cast<const v4i*>(kv_row + C);
             vreg[it] = *reinterpret_cast<const v4i*>(kv_row + 2 * C);
         }
         if (work == first) {                       // the table, while the first loads are in flight (visible after the barrier below)
             for (int i = tid; i < NLUT; i += ATT_THREADS) lut[i] = N24 && MASK && i == NLUT - 1 ? (Entry)0 : (Entry)shiftexp(-i, sm.i0, sm.n_shift);
         }
-        const int64_t orow0 = q_row(qt0);          // output row of the first query tile (before the indices move on)
-        if (BIAS) {
-            if (gather && work + G < n_work) {
-                fetch_rows(work + G, kvnext, qnext);
-#pragma unroll
-                for (int it = 0; it < NPC; ++it) kvrow[it] = kvnext[it];
-                qrow0 = qnext;
-            }
+        const uint32_t orow0 = q_row(qt0);         // output row of the first query tile (before the indices move on)
+        if (work + G < n_work) {
+            nxt = item_of(work + G);
+            if (BIAS) { if (gather) fetch_rows(nxt); }
         }
 #pragma unroll
         for (int it = 0; it < NPC; ++it) {
@@ -247,14 +250,14 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
         }
         __syncthreads();
 
-        for (int qt = qt0; qt < nqt; qt += split * ATT_WAVES) {
+        for (int qt = qt0; qt < nqt; qt = ONE ? nqt : qt + split * ATT_WAVES) {
             const int q = qt * 16 + li;            // this lane's query token
             const int qc = min(q, T - 1);
             int32_t sc[NKT][4];
             // ---- scores: S^T tile t = K_t (16 keys x D) . Q^T (D x 16 queries)
             if (D == 64) {
                 const v4i qf = qn64;
-                qn64 = load_q64(qt + split * ATT_WAVES);
+                if (!ONE) qn64 = load_q64(qt + split * ATT_WAVES);
 #pragma unroll
                 for (int t = 0; t < NKT; ++t) {
                     const v4i kf = *reinterpret_cast<const v4i*>(&Ks[(16 * t + li) * KROW + 16 * lg]);
@@ -264,7 +267,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
                 }
             } else {
                 const long qf = qn32;
-                qn32 = load_q32(qt + split * ATT_WAVES);
+                if (!ONE) qn32 = load_q32(qt + split * ATT_WAVES);
 #pragma unroll
                 for (int t = 0; t < NKT; ++t) {
                     const long kf = *reinterpret_cast<const long*>(&Ks[(16 * t + li) * KROW + 8 * lg]);
@@ -292,7 +295,9 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             // ShiftExp(-delta) is 0 for every delta >= 1024 it can reach (delta >= 100 I_0 - 508, and a non-zero
             // value needs delta < 23 I_0), so entries past the table read as 0.
             const int8_t* brow = (BIAS && rel_bias) ? rel_bias + ((int64_t)h * T + qc) * T : nullptr;
-            const int8_t* mrow = MASK ? mask + ((int64_t)(b % n_mask) * T + qc) * T : nullptr;
+            uint32_t of_mask = 0;
+            if (MASK) n_mask.divide((uint32_t)b, of_mask);
+            const int8_t* mrow = MASK ? mask + ((int64_t)of_mask * T + qc) * T : nullptr;
             const int32_t mask_add = -100 * sm.i0;
             if constexpr (N24) {
                 // Five vector instructions and a table read per score (nine and a read with each step on its own: 3072 pairs of
@@ -547,7 +552,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
                 ow[n] = sw[0]; ow[n + ND / 2] = sw[1];
             }
             if (q < T) {
-                int8_t* op = o + (qt == qt0 ? orow0 : row_of(q)) * C + h * D + lg * (D / 4);
+                int8_t* op = o + row0 * C + h * D + (uint64_t)(ONE || qt == qt0 ? orow0 : row_of(q)) * (uint32_t)C + lg * (D / 4);
                 if (D == 64) *reinterpret_cast<uint4*>(op) = make_uint4(ow[0], ow[2], ow[1], ow[3]);
                 else *reinterpret_cast<uint2*>(op) = make_uint2(ow[0], ow[1 % ND]);
             }
@@ -579,7 +584,8 @@ static void launch_flags(hipStream_t s, const AttentionArgs& a, int grid, int sp
                         e0 << 16 >= (int64_t)1 << a.sm.m_bits && e0 >= 512;
 #define IVIT_ATT(TAPS_, BIAS_, MASK_, FAST_, TFIX_)                                                                         \
     hipLaunchKernelGGL((attention_kernel<D, NKT, TAPS_, BIAS_, MASK_, FAST_, TFIX_>), dim3(grid), dim3(ATT_THREADS), 0, s,     \
-                       a.qkv, a.rel_bias, a.mask, a.n_mask, a.tok_index, a.n_win, a.o, n_items, split, a.T, a.C, a.H, a.qk_rq, \
+                       a.qkv, a.rel_bias, a.mask, FastDiv(std::max(a.n_mask, 1)), a.tok_index, FastDiv(std::max(a.n_win, 1)), a.o, \
+                       n_items, FastDiv(split), a.T, a.C, FastDiv(a.H), a.qk_rq, \
                        a.sm, a.pv_rq, nqk, npv, rnd, a.tap_scores, a.tap_probs)
     // the production paths are <no taps, fast>, with the 24-bit requantisation when both pairs allow it; everything else
     // shares one fully general instantiation per bias / mask combination (a mask is always compiled with the bias code,

@@ -15,6 +15,21 @@ struct Dyadic { int32_t b, c; };
 
 constexpr int kWave = 64;
 
+// Division of a workgroup's number by a number the host knows, in scalar instructions (the 64-bit division that the compiler
+// writes out is 140 of them, a microsecond with one wavefront per SIMD).  With m = floor((2^32 - (d == 1)) / d) and t < 2^31
+// the estimate is at most one too small.
+struct FastDiv {
+    uint32_t d, m;
+    FastDiv() = default;
+    explicit FastDiv(uint32_t d_) : d(d_), m((uint32_t)((((uint64_t)1 << 32) - (d_ == 1)) / d_)) {}
+    __device__ __forceinline__ uint32_t divide(uint32_t t, uint32_t& rest) const {
+        uint32_t q = (uint32_t)(((uint64_t)t * m) >> 32);
+        rest = t - q * d;
+        if (rest >= d) { ++q; rest -= d; }
+        return q;
+    }
+};
+
 __device__ __forceinline__ int32_t clamp8(int32_t v) { return min(max(v, -127), 127); }
 
 // clamp8(a + b) of the exact sum, for any two int32: the sum stops at the ends of int32 (one instruction, as the plain

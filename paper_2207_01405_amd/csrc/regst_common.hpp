@@ -21,21 +21,6 @@ constexpr int WCK = 384;                     // bytes of K per weight chunk of t
 constexpr int WPITCH = WCK + 16;             // its row pitch in LDS
 constexpr int WWI = 4 * 32 * (WPITCH / 16) / 64;    // load instructions (64 lanes x 16 bytes) per chunk: [4 wavefronts][32 channels][WPITCH]
 
-// Division of a workgroup's number by a number the host knows, in scalar instructions (the 64-bit division that the compiler
-// writes out is 140 of them, a microsecond with one wavefront per SIMD).  With m = floor((2^32 - (d == 1)) / d) and t < 2^31
-// the estimate is at most one too small.
-struct FastDiv {
-    uint32_t d, m;
-    FastDiv() = default;
-    explicit FastDiv(uint32_t d_) : d(d_), m((uint32_t)((((uint64_t)1 << 32) - (d_ == 1)) / d_)) {}
-    __device__ __forceinline__ uint32_t divide(uint32_t t, uint32_t& rest) const {
-        uint32_t q = (uint32_t)(((uint64_t)t * m) >> 32);
-        rest = t - q * d;
-        if (rest >= d) { ++q; rest -= d; }
-        return q;
-    }
-};
-
 // f(0), .. f(N - 1), each with its number as a type
 template <int N, class F> __device__ __forceinline__ void static_for(F&& f) {
     [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>()), ...); }(std::make_integer_sequence<int, N>());
