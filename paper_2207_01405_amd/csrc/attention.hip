@@ -70,10 +70,17 @@ __device__ __forceinline__ void requant8x4(int32_t (&v)[4], Dyadic d, Narrow n, 
 
 // ---- pieces of the 24-bit form.  A result T has its int8 value in the top byte; sub-dword selects (SDWA) read and write bytes in
 // the instruction that needs them.  The asm statements read ordinary vector results and loads only (see requant8).
-__device__ __forceinline__ int32_t narrow_top(int32_t v, Narrow n) {
+__device__ __forceinline__ int32_t med3_i32(int32_t v, int32_t lo, int32_t hi) {
     int32_t m;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(m) : "v"(v), "v"(n.lo), "v"(n.hi));
-    return __mul24(m, n.mb) + n.ad;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(m) : "v"(v), "v"(lo), "v"(hi));
+    return m;
+}
+__device__ __forceinline__ int32_t narrow_top(int32_t v, Narrow n) { return __mul24(med3_i32(v, n.lo, n.hi), n.mb) + n.ad; }
+// a - 2 v for a v of 24 bits (written out: the compiler cannot know that a score has no more)
+__device__ __forceinline__ uint32_t minus_twice(int32_t a, int32_t v) {
+    uint32_t r;
+    asm("v_mad_i32_i24 %0, %1, -2, %2" : "=v"(r) : "v"(v), "v"(a));
+    return r;
 }
 // twice the top byte: the byte offset of a 16-bit table entry
 __device__ __forceinline__ uint32_t twice_top(uint32_t d) {
@@ -228,6 +235,34 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             kreg[it] = *reinterpret_cast<const v4i*>(kv_row + C);
             vreg[it] = *reinterpret_cast<const v4i*>(kv_row + 2 * C);
         }
+        // The lane's bytes of the bias and of the mask: its four keys of a key tile are four consecutive bytes of the query's row,
+        // one (unaligned) word.  Of a tile with absent keys the last word of the row is read and moved down.
+        uint32_t bw[NKT], mw[NKT];
+        auto load_words = [&](int qt) __attribute__((always_inline)) {
+            const int qr = min(qt * 16 + li, T - 1);
+            const int8_t* br = (BIAS && rel_bias) ? rel_bias + ((int64_t)h * T + qr) * T : nullptr;
+            uint32_t of_mask = 0;
+            if (MASK) n_mask.divide((uint32_t)b, of_mask);
+            const int8_t* mr = MASK ? mask + ((int64_t)of_mask * T + qr) * T : nullptr;
+            auto word = [&](const int8_t* row, int key) __attribute__((always_inline)) {
+                uint32_t w = 0;
+                const int from = min(key, T - 4), up = key - from;
+                if (T >= 4) {
+                    __builtin_memcpy(&w, row + from, 4);
+                    w = up < 4 ? w >> (8 * up) : 0u;
+                } else {
+                    for (int r = 0; r < 4 && key + r < T; ++r) w |= (uint32_t)(uint8_t)row[key + r] << (8 * r);
+                }
+                return w;
+            };
+#pragma unroll
+            for (int t = 0; t < NKT; ++t) {
+                bw[t] = mw[t] = 0;
+                if (BIAS) { if (!MASK || br) bw[t] = word(br, 16 * t + 4 * lg); }
+                if (MASK) mw[t] = word(mr, 16 * t + 4 * lg);
+            }
+        };
+        if (N24 && BIAS && ONE) load_words(qt0);   // (with K, V and Q: behind the barrier nothing is waited for any more)
         if (work == first) {                       // the table, while the first loads are in flight (visible after the barrier below)
             for (int i = tid; i < NLUT; i += ATT_THREADS) lut[i] = N24 && MASK && i == NLUT - 1 ? (Entry)0 : (Entry)shiftexp(-i, sm.i0, sm.n_shift);
         }
@@ -302,7 +337,8 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             if constexpr (N24) {
                 // Five vector instructions and a table read per score (nine and a read with each step on its own: 3072 pairs of
                 // 197 tokens 63.7 -> 51.4 us, 768 pairs 21.0 -> 18.3).
-                uint32_t base = 0;                 // without a bias: what a score's product is subtracted from
+                uint32_t base = 0, any = 0;        // without a bias: what a score's product is subtracted from; mask bytes of this lane
+                bool masked = false;
                 int32_t mx = INT32_MIN;
                 if constexpr (!BIAS) {
                     // the requantisation is monotonic: the row maximum is that of the accumulators.  With T the maximum's result,
@@ -317,50 +353,48 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
                     mx = rows_allreduce(mx, [](int32_t a, int32_t b) { return max(a, b); });
                     base = ((uint32_t)(__mul24(min(max(mx, nqk.lo), nqk.hi), nqk.mb) + nqk.ad) | 0xffffffu) - (uint32_t)nqk.ad;
                 } else {
+if (!ONE) load_words(qt);
 #pragma unroll
                     for (int t = 0; t < NKT; ++t) {
-                        uint32_t bw = 0, mw = 0;
-                        if (t < nfull) {
-                            if (!MASK || brow) __builtin_memcpy(&bw, brow + 16 * t + 4 * lg, 4);
-                            if (MASK) __builtin_memcpy(&mw, mrow + 16 * t + 4 * lg, 4);
-                        } else {
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                const int key = min(16 * t + 4 * lg + r, T - 1);
-                                if (!MASK || brow) bw |= (uint32_t)(uint8_t)brow[key] << (8 * r);
-                                if (MASK) mw |= (uint32_t)(uint8_t)mrow[key] << (8 * r);
-                            }
-                        }
                         int32_t tp[4];
 #pragma unroll
                         for (int r = 0; r < 4; ++r) tp[r] = narrow_top(sc[t][r], nqk);
-                        sc[t][0] = top_plus_byte<0>(tp[0], bw); sc[t][1] = top_plus_byte<1>(tp[1], bw);
-                        sc[t][2] = top_plus_byte<2>(tp[2], bw); sc[t][3] = top_plus_byte<3>(tp[3], bw);
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            if (MASK) { if ((mw >> (8 * r)) & 0xffu) sc[t][r] += mask_add; }
-                            if (t < nfull || 16 * t + 4 * lg + r < T) mx = max(mx, sc[t][r]);
-                        }
+                        sc[t][0] = top_plus_byte<0>(tp[0], bw[t]); sc[t][1] = top_plus_byte<1>(tp[1], bw[t]);
+                        sc[t][2] = top_plus_byte<2>(tp[2], bw[t]); sc[t][3] = top_plus_byte<3>(tp[3], bw[t]);
+                        any |= mw[t];
                         __builtin_amdgcn_sched_barrier(0);
                     }
+                    // (most windows of a shifted grid have nothing masked)
+                    if (MASK) {
+                        masked = __builtin_amdgcn_ballot_w64(any != 0) != 0;
+                        if (masked) {
+#pragma unroll
+                            for (int t = 0; t < NKT; ++t)
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) if ((mw[t] >> (8 * r)) & 0xffu) sc[t][r] += mask_add;
+                        }
+                    }
+#pragma unroll
+                    for (int t = 0; t < NKT; ++t)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) if (t < nfull || 16 * t + 4 * lg + r < T) mx = max(mx, sc[t][r]);
                     mx = rows_allreduce(mx, [](int32_t a, int32_t b) { return max(a, b); });
                 }
                 // ---- ShiftExp by table, row sum
                 const char* lut_b = reinterpret_cast<const char*>(lut);
                 const int32_t mx2 = 2 * mx;
                 int32_t sum = 0;
+                auto look_up = [&](auto clamp_c) __attribute__((always_inline)) {
 #pragma unroll
                 for (int t = 0; t < NKT; ++t) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         uint32_t at;
                         if constexpr (!BIAS) {
-                            int32_t m;
-                            asm("v_med3_i32 %0, %1, %2, %3" : "=v"(m) : "v"(sc[t][r]), "v"(nqk.lo), "v"(nqk.hi));
-                            at = twice_top(base + (uint32_t)__mul24(m, -nqk.mb));
-                        } else {                   // (written out: the compiler cannot know that the score has 24 bits)
-                            asm("v_mad_i32_i24 %0, %1, -2, %2" : "=v"(at) : "v"(sc[t][r]), "v"(mx2));
-                            if constexpr (MASK) at = min(at, 2u * (NLUT - 1));
+                            at = twice_top(base + (uint32_t)__mul24(med3_i32(sc[t][r], nqk.lo, nqk.hi), -nqk.mb));
+                        } else {
+                            at = minus_twice(mx2, sc[t][r]);
+                            if constexpr (decltype(clamp_c)::value) at = min(at, 2u * (NLUT - 1));
                         }
                         int32_t e;
                         if (t < nfull) {
@@ -375,6 +409,8 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
                     }
                     if (t & 1) __builtin_amdgcn_sched_barrier(0);
                 }
+                };
+                if (MASK && masked) look_up(std::true_type()); else look_up(std::false_type());
                 sum = rows_allreduce(sum, [](int32_t a, int32_t b) { return a + b; });
                 // ---- IntDiv: M - (k_out - 1) = 24 here and inv <= 2^16 (launch_flags sees to it), so (inv 2^8) e has the quotient
                 // in its upper word.  2^(k_out-1), which a byte may not become, is the quotient only where one key has
