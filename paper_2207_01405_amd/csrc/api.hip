@@ -669,9 +669,14 @@ int ivit_forward_swin(void* stream, const int8_t* patches, int8_t* logits, const
         const int64_t R = (int64_t)B * g * g;
         if (s > 0) {     // patch merging: 2 x 2 concatenation, I-LayerNorm over 4 C_prev = 2 C, Dense to C without bias
             const int Cp = p->stages[s - 1].C;
-            if ((st = ivit_patch_merge_gather(stream, buf[cur], cat, B, 2 * g, Cp)) != IVIT_OK) return st;
-            if ((st = ivit_ilayernorm(stream, cat, sg.merge_ln.gamma, sg.merge_ln.beta, catn, R, 4 * Cp, sg.merge_ln.f_bits,
-                                      sg.merge_ln.c_shift)) != IVIT_OK) return st;
+            const ivit_final_ln& ml = sg.merge_ln;
+            if (ivit::merge_ilayernorm_takes(buf[cur], ml.gamma, ml.beta, catn, B, 2 * g, Cp)) {
+                if ((st = hip_status(ivit::launch_merge_ilayernorm(static_cast<hipStream_t>(stream), buf[cur], ml.gamma, ml.beta, catn, B, 2 * g,
+                                                                   Cp, ml.f_bits, ml.c_shift))) != IVIT_OK) return st;
+            } else {
+                if ((st = ivit_patch_merge_gather(stream, buf[cur], cat, B, 2 * g, Cp)) != IVIT_OK) return st;
+                if ((st = ivit_ilayernorm(stream, cat, ml.gamma, ml.beta, catn, R, 4 * Cp, ml.f_bits, ml.c_shift)) != IVIT_OK) return st;
+            }
             if ((st = ivit_linear_requant(stream, catn, sg.w_merge, nullptr, sg.merge_rq_b, sg.merge_rq_c, nullptr, one,
                                           nullptr, one, buf[cur ^ 1], R, sg.C, 4 * Cp)) != IVIT_OK) return st;
             cur ^= 1;

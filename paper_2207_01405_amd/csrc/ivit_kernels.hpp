@@ -11,6 +11,11 @@ namespace ivit {
 hipError_t launch_ilayernorm(hipStream_t s, const int8_t* x, const int32_t* gamma_q, const int32_t* beta_q,
                              int8_t* y, int64_t rows, int C, int f_bits, int c_shift);
 
+// The I-LayerNorm of patch merging (rows of 4 C bytes, see launch_patch_merge_gather), reading the tokens where they lie.
+bool merge_ilayernorm_takes(const int8_t* x, const int32_t* gamma_q, const int32_t* beta_q, const int8_t* y, int B, int g, int C);
+hipError_t launch_merge_ilayernorm(hipStream_t s, const int8_t* x, const int32_t* gamma_q, const int32_t* beta_q, int8_t* y, int B, int g,
+                                   int C, int f_bits, int c_shift);
+
 hipError_t launch_shiftmax(hipStream_t s, const int8_t* x, const int8_t* bias, int H, int T, int8_t* y,
                            int64_t rows, int cols, int ld, ShiftParams p);
 
