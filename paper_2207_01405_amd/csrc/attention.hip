@@ -120,6 +120,101 @@ __device__ __forceinline__ uint32_t div_pack(uint32_t f, const int32_t (&e)[4]) 
     return w;
 }
 
+// The rows of a 24-bit form with a relative-position bias and / or the shifted-window mask, up to the row maximum.  A masked key
+// gets mask_add.  Returns the maximum; masked: whether anything in the tile's rows is masked.
+template <bool MASK, int NKT>
+__device__ __forceinline__ int32_t biased_scores(int32_t (&sc)[NKT][4], const uint32_t (&bw)[NKT], const uint32_t (&mw)[NKT], Narrow nqk, int32_t mask_add,
+                                                 int T, int lg, bool& masked) {
+    const int nfull = T >> 4;
+    uint32_t any = 0;
+    int32_t mx = INT32_MIN;
+#pragma unroll
+    for (int t = 0; t < NKT; ++t) {
+        int32_t tp[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tp[r] = narrow_top(sc[t][r], nqk);
+        sc[t][0] = top_plus_byte<0>(tp[0], bw[t]); sc[t][1] = top_plus_byte<1>(tp[1], bw[t]);
+        sc[t][2] = top_plus_byte<2>(tp[2], bw[t]); sc[t][3] = top_plus_byte<3>(tp[3], bw[t]);
+        any |= mw[t];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // (most windows of a shifted grid have nothing masked)
+    masked = false;
+    if (MASK) {
+        masked = __builtin_amdgcn_ballot_w64(any != 0) != 0;
+        if (masked) {
+#pragma unroll
+            for (int t = 0; t < NKT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) if ((mw[t] >> (8 * r)) & 0xffu) sc[t][r] += mask_add;
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < NKT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) if (t < nfull || 16 * t + 4 * lg + r < T) mx = max(mx, sc[t][r]);
+    return rows_allreduce(mx, [](int32_t a, int32_t b) { return max(a, b); });
+}
+
+// ShiftExp of the scores by table (16-bit entries); returns the row sum.  !BIAS: the score's product is subtracted from `base`.
+// CLAMP: a delta may lie beyond the table, whose last entry stands for it.
+template <bool BIAS, bool CLAMP, int NKT>
+__device__ __forceinline__ int32_t look_up(int32_t (&sc)[NKT][4], const uint16_t* lut, int n_lut, int32_t mx, uint32_t base, Narrow nqk, int T, int lg) {
+    const int nfull = T >> 4;
+    const char* lut_b = reinterpret_cast<const char*>(lut);
+    const int32_t mx2 = 2 * mx;
+    int32_t sum = 0;
+#pragma unroll
+    for (int t = 0; t < NKT; ++t) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            uint32_t at;
+            if constexpr (!BIAS) {
+                at = twice_top(base + (uint32_t)__mul24(med3_i32(sc[t][r], nqk.lo, nqk.hi), -nqk.mb));
+            } else {
+                at = minus_twice(mx2, sc[t][r]);
+                if constexpr (CLAMP) at = min(at, 2u * (uint32_t)(n_lut - 1));
+            }
+            int32_t e;
+            if (t < nfull) {
+                e = (int32_t)*reinterpret_cast<const uint16_t*>(lut_b + at);
+            } else {                               // (an absent key may stand above the maximum)
+                const bool there = 16 * t + 4 * lg + r < T;
+                e = (int32_t)*reinterpret_cast<const uint16_t*>(lut_b + (there ? at : 0u));
+                e = there ? e : 0;
+            }
+            sc[t][r] = e;
+            sum += e;
+        }
+        if (t & 1) __builtin_amdgcn_sched_barrier(0);
+    }
+    return rows_allreduce(sum, [](int32_t a, int32_t b) { return a + b; });
+}
+
+// IntDiv of the 24-bit form: M - (k_out - 1) = 24 here and inv <= 2^16 (launch_flags sees to it), so (inv 2^8) e has the quotient
+// in its upper word; this is inv 2^8.  2^(k_out-1), which a byte may not become, is the quotient only where one key has
+// the whole sum, ShiftExp(0); taking one from inv there gives 2^(k_out-1) - 1 and leaves every other row
+// alone.  The reciprocal is recip_pow2_small for a sum in its range.
+__device__ __forceinline__ uint32_t div_factor(int32_t sum, ShiftParams sm) {
+    uint32_t inv = (uint32_t)((float)(1u << sm.m_bits) * __builtin_amdgcn_rcpf((float)(uint32_t)sum));
+    const int32_t rem = (int32_t)((1u << sm.m_bits) - inv * (uint32_t)sum);
+    inv += (rem >= sum);
+    inv -= (rem < 0);
+    inv -= sum == (sm.i0 << sm.n_shift);
+    return inv << 8;
+}
+
+// The lane's four output tiles requantised (24-bit form) to one word each
+template <int ND> __device__ __forceinline__ void narrow_words(uint32_t (&ow)[ND], const v4i (&oacc)[ND], Narrow npv) {
+#pragma unroll
+    for (int n = 0; n < ND; ++n) {
+        uint32_t ov[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ov[r] = (uint32_t)narrow_top(oacc[n][r], npv);
+        ow[n] = __builtin_amdgcn_perm(ov[1], ov[0], 0x0c0c0703u) | __builtin_amdgcn_perm(ov[3], ov[2], 0x07030c0cu);
+    }
+}
+
 // FAST: both dyadic pairs are rescales by at most 1 with c <= 31 (32-bit requantisation) and the row sum always
 // exceeds 2^(k_out-1), so that IntDiv is one multiply-high by the pre-shifted reciprocal.
 // TFIX: 0, or the token count known at compile time (49, the 7 x 7 windows; 197, the 14 x 14 patches with a class token):
@@ -184,7 +279,8 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
     // scalar, a lane adds one 32 x 32-bit product to it).  Without a table token t is row t.  With one (BIAS instances
     // only) the rows come from the index table of the window's position inside its image; an entry outside the image is
     // clamped, never followed.  The table entries this thread needs for an item (its K / V pieces and its first query
-    // tile) are fetched one item ahead, so that the loads of K, V and Q never wait for an index.
+    // tile) are fetched one item ahead and touched there only, so that the loads of K, V and Q never wait for an index and
+    // nothing waits for the entries themselves.
     constexpr int NPC = (NKT * 16 * DCH + ATT_THREADS - 1) / ATT_THREADS;     // 16-byte pieces per thread and operand
     const int tpi = (int)n_win.d * T;              // tokens per image
     const uint32_t C3 = 3 * (uint32_t)C;
@@ -196,8 +292,8 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
     auto fetch_rows = [&](const Item& t) __attribute__((always_inline)) {
         const int32_t* tr = tok_index + t.win * T;
 #pragma unroll
-        for (int it = 0; it < NPC; ++it) kvrow[it] = min((uint32_t)tr[min((tid + ATT_THREADS * it) / DCH, T - 1)], (uint32_t)(tpi - 1));
-        qrow0 = min((uint32_t)tr[min(first_tile(t) * 16 + li, T - 1)], (uint32_t)(tpi - 1));
+        for (int it = 0; it < NPC; ++it) kvrow[it] = (uint32_t)tr[min((tid + ATT_THREADS * it) / DCH, T - 1)];
+        qrow0 = (uint32_t)tr[min(first_tile(t) * 16 + li, T - 1)];
     };
     Item cur = item_of(first), nxt{};
     if (BIAS) { if (gather && first < n_work) fetch_rows(cur); }
@@ -213,7 +309,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             return (uint32_t)t;
         };
         auto q_row = [&](int qt) -> uint32_t {     // row of this lane's query of tile qt
-            if (BIAS) { if (gather && qt == qt0) return qrow0; }
+            if (BIAS) { if (gather && qt == qt0) return min(qrow0, (uint32_t)(tpi - 1)); }
             return row_of(min(qt * 16 + li, T - 1));
         };
         __syncthreads();                           // table ready / previous item's readers done
@@ -230,29 +326,26 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             const int c = tid + ATT_THREADS * it;
             const int key = min(c / DCH, T - 1), part = c % DCH;
             uint32_t row = (uint32_t)key;
-            if (BIAS) { if (gather) row = kvrow[it]; }
+            if (BIAS) { if (gather) row = min(kvrow[it], (uint32_t)(tpi - 1)); }
             const int8_t* kv_row = at(row) + 16 * part;
             kreg[it] = *reinterpret_cast<const v4i*>(kv_row + C);
             vreg[it] = *reinterpret_cast<const v4i*>(kv_row + 2 * C);
         }
         // The lane's bytes of the bias and of the mask: its four keys of a key tile are four consecutive bytes of the query's row,
-        // one (unaligned) word.  Of a tile with absent keys the last word of the row is read and moved down.
+        // one (unaligned) word.  Of a tile with absent keys the last word of the row is read, to be moved down where it is used
+        // (not here: nothing may wait for a load before all are requested).
         uint32_t bw[NKT], mw[NKT];
+        const int wfrom = T >= 4 ? T - 4 : T;      // the last word's place
         auto load_words = [&](int qt) __attribute__((always_inline)) {
-            const int qr = min(qt * 16 + li, T - 1);
-            const int8_t* br = (BIAS && rel_bias) ? rel_bias + ((int64_t)h * T + qr) * T : nullptr;
+            const uint32_t qr = (uint32_t)min(qt * 16 + li, T - 1) * (uint32_t)T;
+            const int8_t* br = (BIAS && rel_bias) ? rel_bias + (int64_t)h * T * T : nullptr;
             uint32_t of_mask = 0;
             if (MASK) n_mask.divide((uint32_t)b, of_mask);
-            const int8_t* mr = MASK ? mask + ((int64_t)of_mask * T + qr) * T : nullptr;
-            auto word = [&](const int8_t* row, int key) __attribute__((always_inline)) {
+            const int8_t* mr = MASK ? mask + (int64_t)of_mask * T * T : nullptr;
+            auto word = [&](const int8_t* table, int key) __attribute__((always_inline)) {
                 uint32_t w = 0;
-                const int from = min(key, T - 4), up = key - from;
-                if (T >= 4) {
-                    __builtin_memcpy(&w, row + from, 4);
-                    w = up < 4 ? w >> (8 * up) : 0u;
-                } else {
-                    for (int r = 0; r < 4 && key + r < T; ++r) w |= (uint32_t)(uint8_t)row[key + r] << (8 * r);
-                }
+                if (T >= 4) __builtin_memcpy(&w, table + (uint32_t)(qr + min(key, wfrom)), 4);
+                else for (int r = 0; r < 4 && key + r < T; ++r) w |= (uint32_t)(uint8_t)table[qr + key + r] << (8 * r);
                 return w;
             };
 #pragma unroll
@@ -261,6 +354,11 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
                 if (BIAS) { if (!MASK || br) bw[t] = word(br, 16 * t + 4 * lg); }
                 if (MASK) mw[t] = word(mr, 16 * t + 4 * lg);
             }
+        };
+        auto move_down = [&](uint32_t (&w)[NKT]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < NKT; ++t)
+                if (t >= nfull) w[t] = (uint32_t)((uint64_t)w[t] >> min(8 * max(16 * t + 4 * lg - wfrom, 0), 32));
         };
         if (N24 && BIAS && ONE) load_words(qt0);   // (with K, V and Q: behind the barrier nothing is waited for any more)
         if (work == first) {                       // the table, while the first loads are in flight (visible after the barrier below)
@@ -276,9 +374,8 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             const int c = tid + ATT_THREADS * it;
             if (c >= NKT * 16 * DCH) break;
             const int key = c / DCH, part = c % DCH;
-            const v4i kv = key < T ? kreg[it] : v4i{0, 0, 0, 0};
-            const v4i vv = key < T ? vreg[it] : v4i{0, 0, 0, 0};
-            *reinterpret_cast<v4i*>(&Ks[key * KROW + 16 * part]) = kv;
+            const v4i vv = vreg[it];               // (absent keys repeat the last one: their scores and probabilities are left out below)
+            *reinterpret_cast<v4i*>(&Ks[key * KROW + 16 * part]) = kreg[it];
             v2i_att* vdst = reinterpret_cast<v2i_att*>(&Vs[key * VP + 16 * part]);      // (rows are 8-byte aligned)
             vdst[0] = v2i_att{vv[0], vv[1]};
             vdst[1] = v2i_att{vv[2], vv[3]};
@@ -337,7 +434,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             if constexpr (N24) {
                 // Five vector instructions and a table read per score (nine and a read with each step on its own: 3072 pairs of
                 // 197 tokens 63.7 -> 51.4 us, 768 pairs 21.0 -> 18.3).
-                uint32_t base = 0, any = 0;        // without a bias: what a score's product is subtracted from; mask bytes of this lane
+                uint32_t base = 0;                 // without a bias: what a score's product is subtracted from
                 bool masked = false;
                 int32_t mx = INT32_MIN;
                 if constexpr (!BIAS) {
@@ -353,75 +450,15 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
                     mx = rows_allreduce(mx, [](int32_t a, int32_t b) { return max(a, b); });
                     base = ((uint32_t)(__mul24(min(max(mx, nqk.lo), nqk.hi), nqk.mb) + nqk.ad) | 0xffffffu) - (uint32_t)nqk.ad;
                 } else {
-if (!ONE) load_words(qt);
-#pragma unroll
-                    for (int t = 0; t < NKT; ++t) {
-                        int32_t tp[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) tp[r] = narrow_top(sc[t][r], nqk);
-                        sc[t][0] = top_plus_byte<0>(tp[0], bw[t]); sc[t][1] = top_plus_byte<1>(tp[1], bw[t]);
-                        sc[t][2] = top_plus_byte<2>(tp[2], bw[t]); sc[t][3] = top_plus_byte<3>(tp[3], bw[t]);
-                        any |= mw[t];
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    // (most windows of a shifted grid have nothing masked)
-                    if (MASK) {
-                        masked = __builtin_amdgcn_ballot_w64(any != 0) != 0;
-                        if (masked) {
-#pragma unroll
-                            for (int t = 0; t < NKT; ++t)
-#pragma unroll
-                                for (int r = 0; r < 4; ++r) if ((mw[t] >> (8 * r)) & 0xffu) sc[t][r] += mask_add;
-                        }
-                    }
-#pragma unroll
-                    for (int t = 0; t < NKT; ++t)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) if (t < nfull || 16 * t + 4 * lg + r < T) mx = max(mx, sc[t][r]);
-                    mx = rows_allreduce(mx, [](int32_t a, int32_t b) { return max(a, b); });
+                    if (!ONE) load_words(qt);
+                    move_down(bw);
+                    if (MASK) move_down(mw);
+                    mx = biased_scores<MASK>(sc, bw, mw, nqk, mask_add, T, lg, masked);
                 }
-                // ---- ShiftExp by table, row sum
-                const char* lut_b = reinterpret_cast<const char*>(lut);
-                const int32_t mx2 = 2 * mx;
-                int32_t sum = 0;
-                auto look_up = [&](auto clamp_c) __attribute__((always_inline)) {
-#pragma unroll
-                for (int t = 0; t < NKT; ++t) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        uint32_t at;
-                        if constexpr (!BIAS) {
-                            at = twice_top(base + (uint32_t)__mul24(med3_i32(sc[t][r], nqk.lo, nqk.hi), -nqk.mb));
-                        } else {
-                            at = minus_twice(mx2, sc[t][r]);
-                            if constexpr (decltype(clamp_c)::value) at = min(at, 2u * (NLUT - 1));
-                        }
-                        int32_t e;
-                        if (t < nfull) {
-                            e = (int32_t)*reinterpret_cast<const uint16_t*>(lut_b + at);
-                        } else {                   // (an absent key may stand above the maximum)
-                            const bool there = 16 * t + 4 * lg + r < T;
-                            e = (int32_t)*reinterpret_cast<const uint16_t*>(lut_b + (there ? at : 0u));
-                            e = there ? e : 0;
-                        }
-                        sc[t][r] = e;
-                        sum += e;
-                    }
-                    if (t & 1) __builtin_amdgcn_sched_barrier(0);
-                }
-                };
-                if (MASK && masked) look_up(std::true_type()); else look_up(std::false_type());
-                sum = rows_allreduce(sum, [](int32_t a, int32_t b) { return a + b; });
-                // ---- IntDiv: M - (k_out - 1) = 24 here and inv <= 2^16 (launch_flags sees to it), so (inv 2^8) e has the quotient
-                // in its upper word.  2^(k_out-1), which a byte may not become, is the quotient only where one key has
-                // the whole sum, ShiftExp(0); taking one from inv there gives 2^(k_out-1) - 1 and leaves every other row
-                // alone.  The reciprocal is recip_pow2_small for a sum in its range.
-                uint32_t inv = (uint32_t)((float)(1u << sm.m_bits) * __builtin_amdgcn_rcpf((float)(uint32_t)sum));
-                const int32_t rem = (int32_t)((1u << sm.m_bits) - inv * (uint32_t)sum);
-                inv += (rem >= sum);
-                inv -= (rem < 0);
-                inv -= sum == (sm.i0 << sm.n_shift);
-                const uint32_t f = inv << 8;
+                // ---- ShiftExp by table, row sum, IntDiv
+                const int32_t sum = MASK && masked ? look_up<BIAS, true>(sc, lut, NLUT, mx, base, nqk, T, lg)
+                                                   : look_up<BIAS, false>(sc, lut, NLUT, mx, base, nqk, T, lg);
+                const uint32_t f = div_factor(sum, sm);
 #pragma unroll
                 for (int t = 0; t + 4 <= NKT; t += 4) {
                     uint32_t w[4];
@@ -565,21 +602,18 @@ if (!ONE) load_words(qt);
                 __builtin_amdgcn_sched_barrier(0);
             }
             uint32_t ow[ND];
+            if constexpr (FAST == 2) {
+                narrow_words(ow, oacc, npv);
+            } else {
 #pragma unroll
-            for (int n = 0; n < ND; ++n) {
-                if constexpr (FAST == 2) {         // result in the top byte
-                    uint32_t ov[4];
+                for (int n = 0; n < ND; ++n) {
+                    uint32_t w = 0;
+                    int32_t ov[4] = {oacc[n][0], oacc[n][1], oacc[n][2], oacc[n][3]};
+                    requant8x4<FAST>(ov, pv, npv, rnd);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) ov[r] = (uint32_t)narrow_top(oacc[n][r], npv);
-                    ow[n] = __builtin_amdgcn_perm(ov[1], ov[0], 0x0c0c0703u) | __builtin_amdgcn_perm(ov[3], ov[2], 0x07030c0cu);
-                    continue;
+                    for (int r = 0; r < 4; ++r) w |= ((uint32_t)ov[r] & 0xffu) << (8 * r);
+                    ow[n] = w;
                 }
-                uint32_t w = 0;
-                int32_t ov[4] = {oacc[n][0], oacc[n][1], oacc[n][2], oacc[n][3]};
-                requant8x4<FAST>(ov, pv, npv, rnd);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) w |= ((uint32_t)ov[r] & 0xffu) << (8 * r);
-                ow[n] = w;
             }
 #pragma unroll
             for (int n = 0; n < ND / 2; ++n) {
