@@ -651,11 +651,11 @@ __device__ __forceinline__ int32_t wave_allreduce(int32_t v, OP op) {
 //  - the bias of the workgroup's heads lies in LDS as the words the lanes need;
 //  - the 49th query, which would have a tile of its own, has its 49 scores one to a lane: a third of a tile's instructions.
 // Bound by the vector ALU and the addresses of the loads, about equally (a wavefront per query tile against this, without and with
-// a mask: 8192 windows x 3 heads 55.3 -> 45.1 and 66.0 -> 55.7 us, 2048 x 6 30.0 -> 23.9 and 38.5 -> 30.3, 512 x 12 17.9 -> 16.0 and
-// 22.5 -> 21.0).
-constexpr int WIN_T = 49, WIN_WAVES = 8;
+// a mask: 8192 windows x 3 heads 55.3 -> 43.2 and 66.0 -> 54.5 us, 2048 x 6 30.0 -> 24.0 and 38.5 -> 30.6, 512 x 12 17.9 -> 14.9 and
+// 22.5 -> 19.5).
+constexpr int WIN_T = 49, WIN_WAVES = 4;
 template <int HEADS, bool MASK>
-__global__ __launch_bounds__(64 * WIN_WAVES, HEADS == 1 && !MASK ? 6 : 4) void window_attention_kernel(
+__global__ __launch_bounds__(64 * WIN_WAVES, HEADS == 1 ? (MASK ? 5 : 7) : MASK ? 4 : 5) void window_attention_kernel(
     const int8_t* __restrict__ qkv, const int8_t* __restrict__ rel_bias, const int8_t* __restrict__ mask, FastDiv n_mask,
     const int32_t* __restrict__ tok_index, FastDiv n_win, int8_t* __restrict__ o, int B, int C, FastDiv groups, ShiftParams sm,
     Narrow nqk, Narrow npv) {
@@ -858,8 +858,9 @@ static bool window_takes(const AttentionArgs& a) {
 
 static void launch_window(hipStream_t s, const AttentionArgs& a, Narrow nqk, Narrow npv) {
     const int heads = a.H & 1 ? 1 : 2, groups = a.H / heads;
-    // as many passes as three workgroups per CU need (fewer: 8192 x 3 takes 49 us with two), and no more than share the windows evenly
-    const int64_t most = std::max<int64_t>(1, 3 * (int64_t)num_cus() / groups);
+    // as many passes as six workgroups per CU need (8192 x 3 takes 47.6 us with four, 43.8 with five, 43.2 with six), and no more
+    // workgroups than share the windows evenly.  (Of eight wavefronts, three per CU: 45.1 us, 512 x 12 16.0 against 14.9.)
+    const int64_t most = std::max<int64_t>(1, 6 * (int64_t)num_cus() / groups);
     const int64_t passes = (a.B + WIN_WAVES * most - 1) / (WIN_WAVES * most);
     const int grid = groups * (int)((a.B + WIN_WAVES * passes - 1) / (WIN_WAVES * passes));
 #define IVIT_WIN(HEADS_, MASK_)                                                                                                          \
