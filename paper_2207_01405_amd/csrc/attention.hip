@@ -640,40 +640,35 @@ __device__ __forceinline__ int32_t wave_allreduce(int32_t v, OP op) {
     return rows_allreduce(v, op);
 }
 
-// Windows of 7 x 7 tokens, 32 features a head, 24-bit form, when there are many (window, head) pairs: one wavefront takes HEADS
-// neighbouring heads of a window (two, or one when the heads are odd in number), so that
+// Windows of 7 x 7 tokens, 32 features a head, 24-bit form, when there are many (window, head) pairs: one wavefront per pair, so that
 //  - nothing but the start needs a barrier;
-//  - K and Q come from memory in the layout the matrix instruction reads, once and not once per query tile: a lane's 16 bytes of a
-//    row, lane blocks 0 and 1 those of the first head, 2 and 3 those of the second, a head's scores being the product over both with
-//    the other head's part of Q cleared (one head: a lane's 8 bytes).  A load that touches 16 rows costs about 27 cycles
-//    whatever its width, so two heads halve that;
-//  - V passes through the wavefront's own corner of LDS for the transposing read, once per window;
-//  - the bias of the workgroup's heads lies in LDS as the words the lanes need;
+//  - K and Q come from memory in the layout the matrix instruction reads (a lane's 8 bytes of a row), once and not once per query tile;
+//  - V passes through the wavefront's own corner of LDS for the transposing read, once;
+//  - the bias of the workgroup's head lies in LDS as the words the lanes need;
 //  - the 49th query, which would have a tile of its own, has its 49 scores one to a lane: a third of a tile's instructions.
-// Bound by the vector ALU and the addresses of the loads, about equally (a wavefront per query tile against this, without and with
-// a mask: 8192 windows x 3 heads 55.3 -> 43.2 and 66.0 -> 54.5 us, 2048 x 6 30.0 -> 24.0 and 38.5 -> 30.6, 512 x 12 17.9 -> 14.9 and
-// 22.5 -> 19.5).
+// Bound by the vector ALU and the addresses of the loads (one that touches 16 rows costs about 27 cycles whatever its width), about
+// equally.  (Two neighbouring heads to a wavefront, 16 bytes a lane and a load, halve the loads but leave fewer wavefronts: 2048
+// windows x 6 heads 24.0 us, 512 x 12 14.9.)  A wavefront per query tile against this, without and with a mask: 8192 x 3 55.3 -> 42.4
+// and 66.0 -> 54.9 us, 2048 x 6 30.0 -> 23.2 and 38.5 -> 32.1, 512 x 12 17.9 -> 14.2 and 22.5 -> 19.8.
 constexpr int WIN_T = 49, WIN_WAVES = 4;
-template <int HEADS, bool MASK>
-__global__ __launch_bounds__(64 * WIN_WAVES, HEADS == 1 ? (MASK ? 5 : 7) : MASK ? 4 : 5) void window_attention_kernel(
+template <bool MASK>
+__global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention_kernel(
     const int8_t* __restrict__ qkv, const int8_t* __restrict__ rel_bias, const int8_t* __restrict__ mask, FastDiv n_mask,
-    const int32_t* __restrict__ tok_index, FastDiv n_win, int8_t* __restrict__ o, int B, int C, FastDiv groups, ShiftParams sm,
+    const int32_t* __restrict__ tok_index, FastDiv n_win, int8_t* __restrict__ o, int B, int C, FastDiv H, ShiftParams sm,
     Narrow nqk, Narrow npv) {
-    constexpr int T = WIN_T, D = 32, NT = 4, NQ = T / 16, LAST = T - 1, VP = HEADS == 2 ? 72 : 40, NLUT = MASK ? 1024 : 512;
+    constexpr int T = WIN_T, D = 32, NT = 4, NQ = T / 16, LAST = T - 1, VP = 40, NLUT = MASK ? 1024 : 512;
     static_assert(T == 16 * NQ + 1 && NQ + 1 == NT);
     __shared__ __align__(16) int8_t Vall[WIN_WAVES][NT * 16 * VP];
-    __shared__ __align__(16) uint32_t bias_words[HEADS][NQ][64][NT];
-    __shared__ __align__(16) int8_t last_bias[HEADS][64], last_p[WIN_WAVES][64];
+    __shared__ __align__(16) uint32_t bias_words[NQ][64][NT];
+    __shared__ __align__(16) int8_t last_bias[64], last_p[WIN_WAVES][64];
     __shared__ uint16_t lut[NLUT];
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lg = lane >> 4;
 
-    typedef std::conditional_t<HEADS == 2, v4i, long> Frag;   // a lane's bytes of a row
-
     // (the workgroups of one XCD are consecutive: the heads of a window share the lines of qkv)
     const int G = gridDim.x, xcd = blockIdx.x % 8;
-    uint32_t group;                                // of HEADS heads, the workgroup's
-    const int slot = (int)groups.divide((uint32_t)(xcd * (G / 8) + min(xcd, G % 8) + blockIdx.x / 8), group);
-    const int h0 = (int)group * HEADS, stride = G / (int)groups.d * WIN_WAVES;  // windows of one pass of all workgroups
+    uint32_t h;                                    // the workgroup's head
+    const int slot = (int)H.divide((uint32_t)(xcd * (G / 8) + min(xcd, G % 8) + blockIdx.x / 8), h);
+    const int stride = G / (int)H.d * WIN_WAVES;   // windows of one pass of all workgroups
     // four consecutive bytes of row `tok` of a T x T table; the last word of the row, moved down, for the last tile
     auto word = [&](const int8_t* table, uint32_t tok, int t, int block) __attribute__((always_inline)) {
         const int key = 16 * t + 4 * block, from = 16 * t + 16 <= T ? key : min(key, T - 4);
@@ -682,15 +677,15 @@ __global__ __launch_bounds__(64 * WIN_WAVES, HEADS == 1 ? (MASK ? 5 : 7) : MASK 
         return 16 * t + 16 <= T ? v : (uint32_t)((uint64_t)v >> min(8 * (key - from), 32));
     };
     for (int i = tid; i < NLUT; i += 64 * WIN_WAVES) lut[i] = MASK && i == NLUT - 1 ? (uint16_t)0 : (uint16_t)shiftexp(-i, sm.i0, sm.n_shift);
-    for (int i = tid; i < HEADS * NT * 64; i += 64 * WIN_WAVES) {
-        const int hh = i / (NT * 64), q = i / 64 % NT, l = i & 63;
-        const int8_t* table = rel_bias + (int64_t)(h0 + hh) * T * T;
+    for (int i = tid; i < NT * 64; i += 64 * WIN_WAVES) {
+        const int q = i / 64, l = i & 63;
+        const int8_t* table = rel_bias + (int64_t)h * T * T;
         const bool any = !MASK || rel_bias;
         if (q < NQ) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) bias_words[hh][q][l][t] = any ? word(table, 16 * q + (l & 15), t, l >> 4) : 0u;
+            for (int t = 0; t < NT; ++t) bias_words[q][l][t] = any ? word(table, 16 * q + (l & 15), t, l >> 4) : 0u;
         } else {
-            last_bias[hh][l] = any ? table[LAST * T + min(l, LAST)] : (int8_t)0;
+            last_bias[l] = any ? table[LAST * T + min(l, LAST)] : (int8_t)0;
         }
     }
     __syncthreads();
@@ -715,17 +710,17 @@ __global__ __launch_bounds__(64 * WIN_WAVES, HEADS == 1 ? (MASK ? 5 : 7) : MASK 
     uint32_t image = b < B ? fetch_rows(b) : 0;
     while (b < B) {
         const uint64_t row0 = (uint64_t)image * (gather ? tpi : (uint32_t)T);
-        const int8_t* base = qkv + row0 * C3 + h0 * D;
-        int8_t* obase = o + row0 * (uint32_t)C + h0 * D;
+        const int8_t* base = qkv + row0 * C3 + (int)h * D;
+        int8_t* obase = o + row0 * (uint32_t)C + (int)h * D;
         uint32_t row[NT];
-        Frag kf[NT], vr[NT], qf[NT];
+        long kf[NT], vr[NT], qf[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             row[t] = gather ? min(raw[t], tpi - 1) : (uint32_t)min(16 * t + li, LAST);
-            const uint32_t at = row[t] * C3 + (uint32_t)sizeof(Frag) * lg;
-            vr[t] = *reinterpret_cast<const Frag*>(base + 2 * C + at);
-            kf[t] = *reinterpret_cast<const Frag*>(base + C + at);
-            qf[t] = *reinterpret_cast<const Frag*>(base + at);
+            const uint32_t at = row[t] * C3 + 8 * lg;
+            vr[t] = *reinterpret_cast<const long*>(base + 2 * C + at);
+            kf[t] = *reinterpret_cast<const long*>(base + C + at);
+            qf[t] = *reinterpret_cast<const long*>(base + at);
         }
         uint32_t mw[NQ][NT];
         int32_t last_mask = 0;
@@ -742,97 +737,76 @@ __global__ __launch_bounds__(64 * WIN_WAVES, HEADS == 1 ? (MASK ? 5 : 7) : MASK 
         b += stride;
         if (b < B) image = fetch_rows(b);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            int8_t* vdst = Vs + (16 * t + li) * VP + sizeof(Frag) * lg;       // (rows are 8-byte aligned)
-            if constexpr (HEADS == 2) {
-                reinterpret_cast<v2i_att*>(vdst)[0] = v2i_att{vr[t][0], vr[t][1]};
-                reinterpret_cast<v2i_att*>(vdst)[1] = v2i_att{vr[t][2], vr[t][3]};
-            } else {
-                *reinterpret_cast<long*>(vdst) = vr[t];
-            }
+        for (int t = 0; t < NT; ++t) *reinterpret_cast<long*>(Vs + (16 * t + li) * VP + 8 * lg) = vr[t];
+        typedef v2i_att __attribute__((address_space(3))) * lds_v2i;
+        v4i vf[2];
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const v2i_att v0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i)(vbase + 8 * n));
+            const v2i_att v1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i)(vbase + 32 * VP + 8 * n));
+            vf[n] = v4i{v0[0], v0[1], v1[0], v1[1]};
         }
-#pragma unroll 1
-        for (int hh = 0; hh < HEADS; ++hh) {
-            typedef v2i_att __attribute__((address_space(3))) * lds_v2i;
-            v4i vf[2];
 #pragma unroll
-            for (int n = 0; n < 2; ++n) {
-                const v2i_att v0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i)(vbase + D * hh + 8 * n));
-                const v2i_att v1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i)(vbase + D * hh + 32 * VP + 8 * n));
-                vf[n] = v4i{v0[0], v0[1], v1[0], v1[1]};
-            }
-            // a head's part of a fragment of Q; the product of two fragments over the features
-            auto of_head = [&](const Frag& q) __attribute__((always_inline)) {
-                if constexpr (HEADS == 2) return (lg >> 1) == hh ? q : v4i{0, 0, 0, 0}; else return q;
-            };
-            auto product = [&](const Frag& x, const Frag& y) __attribute__((always_inline)) {
-                if constexpr (HEADS == 2) return __builtin_amdgcn_mfma_i32_16x16x64_i8(x, y, v4i{0, 0, 0, 0}, 0, 0, 0);
-                else return __builtin_amdgcn_mfma_i32_16x16x32_i8(x, y, v4i{0, 0, 0, 0}, 0, 0, 0);
-            };
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                int32_t sc[NT][4];
-                const Frag qh = of_head(qf[q]);
-                const v4i words = *reinterpret_cast<const v4i*>(bias_words[hh][q][lane]);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const v4i s = product(kf[t], qh);
-                    sc[t][0] = s[0]; sc[t][1] = s[1]; sc[t][2] = s[2]; sc[t][3] = s[3];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                asm volatile("s_nop 7");           // (asm readers of matrix results, see requant8)
-                asm volatile("s_nop 3");
-                __builtin_amdgcn_sched_barrier(0);
-                const uint32_t bw[NT] = {(uint32_t)words[0], (uint32_t)words[1], (uint32_t)words[2], (uint32_t)words[3]};
-                uint32_t mt[NT];
-#pragma unroll
-                for (int t = 0; t < NT; ++t) mt[t] = MASK ? mw[q][t] : 0u;
-                bool masked;
-                const int32_t mx = biased_scores<MASK>(sc, bw, mt, nqk, mask_add, T, lg, masked);
-                const int32_t sum = MASK && masked ? look_up<true, true>(sc, lut, NLUT, mx, 0u, nqk, T, lg)
-                                                   : look_up<true, false>(sc, lut, NLUT, mx, 0u, nqk, T, lg);
-                uint32_t pk[NT];
-                div_pack4(pk, div_factor(sum, sm), sc[0], sc[1], sc[2], sc[3]);
-                const v4i pf = {(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};
-                v4i oacc[2];
-#pragma unroll
-                for (int n = 0; n < 2; ++n) oacc[n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf[n], pf, v4i{0, 0, 0, 0}, 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                asm volatile("s_nop 7");
-                asm volatile("s_nop 3");
-                __builtin_amdgcn_sched_barrier(0);
-                uint32_t ow[2];
-                narrow_words(ow, oacc, npv);
-                const auto sw = __builtin_amdgcn_permlane16_swap(ow[0], ow[1], false, false);
-                *reinterpret_cast<uint2*>(obase + (uint32_t)(row[q] * (uint32_t)C + D * hh + 8 * lg)) = make_uint2(sw[0], sw[1]);
-            }
-            // ---- the query left over (every row of its tile is that token): S = Q K^T, queries x keys, so that its score with key
-            // 16 t + li is in every lane li of tile t; lane block lg keeps tile lg
-            const Frag qh = of_head(qf[NQ]);
-            int32_t v = 0;
+        for (int q = 0; q < NQ; ++q) {
+            int32_t sc[NT][4];
+            const v4i words = *reinterpret_cast<const v4i*>(bias_words[q][lane]);
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                const v4i s = product(qh, kf[t]);
-                v = lg == t ? s[0] : v;
+                const v4i s = __builtin_amdgcn_mfma_i32_16x16x32_i8(kf[t], qf[q], v4i{0, 0, 0, 0}, 0, 0, 0);
+                sc[t][0] = s[0]; sc[t][1] = s[1]; sc[t][2] = s[2]; sc[t][3] = s[3];
             }
             __builtin_amdgcn_sched_barrier(0);
-            v = (narrow_top(v, nqk) >> 24) + last_bias[hh][lane] + (MASK && last_mask ? mask_add : 0);
-            const int32_t mx = wave_allreduce(lane < T ? v : INT32_MIN, [](int32_t x, int32_t y) { return max(x, y); });
-            int32_t e = (int32_t)lut[lane < T ? min(mx - v, NLUT - 1) : 0];
-            e = lane < T ? e : 0;
-            const uint32_t f = div_factor(wave_allreduce(e, [](int32_t x, int32_t y) { return x + y; }), sm);
-            last_p[wv][lane] = (int8_t)(uint8_t)__umulhi(f, (uint32_t)e);
-            v4i pf;
+            asm volatile("s_nop 7");           // (asm readers of matrix results, see requant8)
+            asm volatile("s_nop 3");
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t bw[NT] = {(uint32_t)words[0], (uint32_t)words[1], (uint32_t)words[2], (uint32_t)words[3]};
+            uint32_t mt[NT];
 #pragma unroll
-            for (int t = 0; t < NT; ++t) pf[t] = *reinterpret_cast<const int*>(&last_p[wv][16 * t + 4 * lg]);
-            // O = P V: a row of features, tile n of them from lane block n
-            const v4i o0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(pf, vf[0], v4i{0, 0, 0, 0}, 0, 0, 0);
-            const v4i o1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(pf, vf[1], v4i{0, 0, 0, 0}, 0, 0, 0);
+            for (int t = 0; t < NT; ++t) mt[t] = MASK ? mw[q][t] : 0u;
+            bool masked;
+            const int32_t mx = biased_scores<MASK>(sc, bw, mt, nqk, mask_add, T, lg, masked);
+            const int32_t sum = MASK && masked ? look_up<true, true>(sc, lut, NLUT, mx, 0u, nqk, T, lg)
+                                               : look_up<true, false>(sc, lut, NLUT, mx, 0u, nqk, T, lg);
+            uint32_t pk[NT];
+            div_pack4(pk, div_factor(sum, sm), sc[0], sc[1], sc[2], sc[3]);
+            const v4i pf = {(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};
+            v4i oacc[2];
+#pragma unroll
+            for (int n = 0; n < 2; ++n) oacc[n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf[n], pf, v4i{0, 0, 0, 0}, 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
-            const int32_t ov = lg & 1 ? o1[0] : o0[0];
+            asm volatile("s_nop 7");
+            asm volatile("s_nop 3");
             __builtin_amdgcn_sched_barrier(0);
-            if (lg < 2) obase[(uint32_t)(row[NQ] * (uint32_t)C + D * hh + 8 * lg + li + (li & 8))] = (int8_t)(narrow_top(ov, npv) >> 24);
+            uint32_t ow[2];
+            narrow_words(ow, oacc, npv);
+            const auto sw = __builtin_amdgcn_permlane16_swap(ow[0], ow[1], false, false);
+            *reinterpret_cast<uint2*>(obase + (uint32_t)(row[q] * (uint32_t)C + 8 * lg)) = make_uint2(sw[0], sw[1]);
         }
+        // ---- the query left over (every row of its tile is that token): S = Q K^T, queries x keys, so that its score with key
+        // 16 t + li is in every lane li of tile t; lane block lg keeps tile lg
+        int32_t v = 0;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const v4i s = __builtin_amdgcn_mfma_i32_16x16x32_i8(qf[NQ], kf[t], v4i{0, 0, 0, 0}, 0, 0, 0);
+            v = lg == t ? s[0] : v;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        v = (narrow_top(v, nqk) >> 24) + last_bias[lane] + (MASK && last_mask ? mask_add : 0);
+        const int32_t mx = wave_allreduce(lane < T ? v : INT32_MIN, [](int32_t x, int32_t y) { return max(x, y); });
+        int32_t e = (int32_t)lut[lane < T ? min(mx - v, NLUT - 1) : 0];
+        e = lane < T ? e : 0;
+        const uint32_t f = div_factor(wave_allreduce(e, [](int32_t x, int32_t y) { return x + y; }), sm);
+        last_p[wv][lane] = (int8_t)(uint8_t)__umulhi(f, (uint32_t)e);
+        v4i pf;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) pf[t] = *reinterpret_cast<const int*>(&last_p[wv][16 * t + 4 * lg]);
+        // O = P V: a row of features, tile n of them from lane block n
+        const v4i o0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(pf, vf[0], v4i{0, 0, 0, 0}, 0, 0, 0);
+        const v4i o1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(pf, vf[1], v4i{0, 0, 0, 0}, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        const int32_t ov = lg & 1 ? o1[0] : o0[0];
+        __builtin_amdgcn_sched_barrier(0);
+        if (lg < 2) obase[(uint32_t)(row[NQ] * (uint32_t)C + 8 * lg + li + (li & 8))] = (int8_t)(narrow_top(ov, npv) >> 24);
     }
 }
 
@@ -848,27 +822,25 @@ static bool narrow_of(Dyadic d, int rnd, Narrow& n) {
     return true;
 }
 
-// The one-wavefront form from 20 (window, head) pairs per CU on: below, a wavefront per query tile finishes a pair sooner (512
-// windows x 3 heads, 6 per CU: 8.2 us against 7.7; 128 x 24, 12 per CU: 10.5 against 10.0; 384 x 12, 18 per CU: 15.3 both; 2048 x 3, 24
-// per CU: 12.6 against 15.7, with a mask 18.1 against 21.0).  The rows of an image are counted in 32 bits there.
+// The one-wavefront form from 9 (window, head) pairs per CU on: below, a wavefront per query tile finishes a pair sooner.  Without
+// and with a mask, us against a wavefront per query tile: 6 per CU 7.4 : 7.4 and 10.2 : 9.4; 9 per CU 8.5 : 9.4; 12 per CU 8.8 : 10.0 and 12.3 :
+// 12.5; 24 per CU 12.9 : 16.4 and 18.4 : 21.2.  The rows of an image are counted in 32 bits there.
 static bool window_takes(const AttentionArgs& a) {
     const int64_t rows = a.tok_index ? (int64_t)a.n_win * WIN_T : WIN_T;
-    return a.T == WIN_T && (int64_t)a.B * a.H >= 20 * (int64_t)num_cus() && rows * 3 * a.C < (int64_t)1 << 31;
+    return a.T == WIN_T && (int64_t)a.B * a.H >= 9 * (int64_t)num_cus() && rows * 3 * a.C < (int64_t)1 << 31;
 }
 
 static void launch_window(hipStream_t s, const AttentionArgs& a, Narrow nqk, Narrow npv) {
-    const int heads = a.H & 1 ? 1 : 2, groups = a.H / heads;
     // as many passes as six workgroups per CU need (8192 x 3 takes 47.6 us with four, 43.8 with five, 43.2 with six), and no more
-    // workgroups than share the windows evenly.  (Of eight wavefronts, three per CU: 45.1 us, 512 x 12 16.0 against 14.9.)
-    const int64_t most = std::max<int64_t>(1, 6 * (int64_t)num_cus() / groups);
+    // workgroups than share the windows evenly.  (Of eight wavefronts, three per CU: 45.1 us.)
+    const int64_t most = std::max<int64_t>(1, 6 * (int64_t)num_cus() / a.H);
     const int64_t passes = (a.B + WIN_WAVES * most - 1) / (WIN_WAVES * most);
-    const int grid = groups * (int)((a.B + WIN_WAVES * passes - 1) / (WIN_WAVES * passes));
-#define IVIT_WIN(HEADS_, MASK_)                                                                                                          \
-    hipLaunchKernelGGL((window_attention_kernel<HEADS_, MASK_>), dim3(grid), dim3(64 * WIN_WAVES), 0, s, a.qkv, a.rel_bias, a.mask,        \
-                       FastDiv(std::max(a.n_mask, 1)), a.tok_index, FastDiv(std::max(a.n_win, 1)), a.o, a.B, a.C, FastDiv(groups),        \
+    const int grid = a.H * (int)((a.B + WIN_WAVES * passes - 1) / (WIN_WAVES * passes));
+#define IVIT_WIN(MASK_)                                                                                                              \
+    hipLaunchKernelGGL((window_attention_kernel<MASK_>), dim3(grid), dim3(64 * WIN_WAVES), 0, s, a.qkv, a.rel_bias, a.mask,            \
+                       FastDiv(std::max(a.n_mask, 1)), a.tok_index, FastDiv(std::max(a.n_win, 1)), a.o, a.B, a.C, FastDiv(a.H),       \
                        a.sm, nqk, npv)
-    if (heads == 2) { if (a.mask) IVIT_WIN(2, true); else IVIT_WIN(2, false); }
-    else { if (a.mask) IVIT_WIN(1, true); else IVIT_WIN(1, false); }
+    if (a.mask) IVIT_WIN(true); else IVIT_WIN(false);
 #undef IVIT_WIN
 }
 

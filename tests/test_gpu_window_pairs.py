@@ -17,7 +17,7 @@ T = 49
 def test_parts_equal_whole(ivit, H, more, kind, i0, sigma):
     import torch
     n_win = 4
-    B = -(-20 * torch.cuda.get_device_properties(0).multi_processor_count // (H * n_win)) * n_win + more * n_win
+    B = -(-9 * torch.cuda.get_device_properties(0).multi_processor_count // (H * n_win)) * n_win + more * n_win
     C, rng = 32 * H, np.random.default_rng(100 * H + more + i0)
     qkv = np.clip(np.rint(rng.normal(0, sigma, size=(B * T, 3 * C))), -128, 127).astype(np.int8)
     qkv[:T, :C] = 100                                            # the first window: key 2 collects everything
