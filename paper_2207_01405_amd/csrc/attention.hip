@@ -15,10 +15,10 @@
 // addresses the lanes name, and V needs no rearranging when it is written.  One exchange between neighbouring
 // lane blocks then gives every lane d/4 consecutive features of its query: one 16-byte (d = 64) store.
 //
-// The kernel is bound by the vector ALU (about a dozen integer operations per score element against
-// 2 d multiply-accumulates on the matrix core), so the per-element path is kept minimal: debug taps, the
-// bias and the 64-bit requantisation are compiled in only when asked for (template flags), and masking
-// of padded keys is done only for key tiles that are not completely valid.
+// The kernel is bound by the vector ALU (five integer operations and a table read per score element in the 24-bit form, about a
+// dozen in the general one, against 2 d multiply-accumulates on the matrix core), so the per-element path is kept minimal:
+// debug taps, the bias and the 64-bit requantisation are compiled in only when asked for (template flags), and masking
+// of padded keys is done only for key tiles that are not completely valid.  Many 7 x 7 windows have a form of their own below.
 #include <algorithm>
 #include <type_traits>
 
