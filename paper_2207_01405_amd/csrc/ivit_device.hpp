@@ -197,8 +197,11 @@ __device__ __forceinline__ uint32_t isqrt10(uint32_t v) {
     s += ((s + 1) * (s + 1) <= v);
     const uint32_t m = s + 1;                                   // v == m^2 - 1 <=> v == s^2 + 2 s
     const bool osc = (v == s * s + 2 * s) & (s >= 1);
-    const uint32_t bit = (T.w[m >> 5 & 7] >> (m & 31)) & 1u;
-    return osc ? s + bit : s;
+    // (the word by seven selections: a load here would be a memory latency in the middle of a row's chain)
+    const bool b0 = m & 32, b1 = m & 64, b2 = m & 128;
+    const uint32_t w01 = b0 ? T.w[1] : T.w[0], w23 = b0 ? T.w[3] : T.w[2], w45 = b0 ? T.w[5] : T.w[4], w67 = b0 ? T.w[7] : T.w[6];
+    const uint32_t w = b2 ? (b1 ? w67 : w45) : (b1 ? w23 : w01);
+    return osc ? s + (w >> (m & 31) & 1u) : s;
 }
 
 // I-LayerNorm of a row of C int8 values (Sec. 3.5, Eq. 19-20) from their sum and sum of squares: mean to nearest and

@@ -97,21 +97,27 @@ __global__ __launch_bounds__(256) void ilayernorm_kernel(const int8_t* __restric
 // of (row, column) offsets (0,0), (1,0), (0,1), (1,1), read where the tokens lie (two passes over the tensor less than gathering
 // first: Swin-T batch 128 1802 -> 1704 us, Swin-S batch 8 851 -> 833 us).
 struct MergeRows { FastDiv image, line; int g; };                  // rows of an image and of a grid line; the token grid's side
+// What a launch of one round of workgroups waits for is the chain launch -> loads -> sums -> statistics -> store, so nothing in it waits
+// twice: the divisions come from the host as multipliers, x, gamma and beta are requested together, and up to eight lanes
+// (2^lanes_log2) share the sums of a row where a workgroup has few.  One after the other before: 50432 x 768 19.4 -> 16.1 us (a copy of
+// the same bytes 16.1), 1576 x 768 5.0 -> 4.3.
+struct RowTile { FastDiv cpr, rp; int lanes_log2; };               // threads a row, rows a pass, lanes that share a row's sums
 template <int J, int GBN = 1024, bool MERGE = false>
 __global__ __launch_bounds__(256) void ilayernorm_tiled_kernel(const int8_t* __restrict__ x,
                                                                const int32_t* __restrict__ gamma_q,
                                                                const int32_t* __restrict__ beta_q,
                                                                int8_t* __restrict__ y, int64_t rows, int C,
-                                                               int f_bits, int c_shift, MergeRows mr) {
+                                                               int f_bits, int c_shift, RowTile rt, MergeRows mr) {
     typedef int v4i __attribute__((ext_vector_type(4)));
     // (sum x, sum x^2) of one 16-byte chunk, laid out [pass][chunk][row of the pass] so that the threads that add up
     // the rows (consecutive rows, the same chunk at a time) read consecutive words: no bank conflicts there
     __shared__ int2 part[J * 256];
     __shared__ int2 stat[J * 64];                  // [row in workgroup]: (mean, f)
     const int tid = threadIdx.x;
-    const int CPR = C >> 4, RP = 256 / CPR, R = RP * J;
+    const int CPR = (int)rt.cpr.d, RP = (int)rt.rp.d, R = RP * J;
     const bool active = tid < RP * CPR;
-    const int rgrp = tid / CPR, cc = tid - rgrp * CPR;
+    uint32_t piece_of_row;
+    const int rgrp = (int)rt.cpr.divide((uint32_t)tid, piece_of_row), cc = (int)piece_of_row;
     const int64_t row0 = (int64_t)blockIdx.x * R;
     const int32_t half = 1 << (c_shift - 1);
 
@@ -120,17 +126,14 @@ __global__ __launch_bounds__(256) void ilayernorm_tiled_kernel(const int8_t* __r
     v4i xv[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-        const int64_t row = row0 + j * RP + rgrp;
-        xv[j] = v4i{0, 0, 0, 0};
-        if (active && row < rows) {
-            const int8_t* src = x + row * C + 16 * cc;
-            if (MERGE) {
-                uint32_t in, xx;
-                const uint32_t b = mr.image.divide((uint32_t)row, in), yy = mr.line.divide(in, xx);
-                src = x + ((((int64_t)b * mr.g + 2 * yy + (quarter & 1)) * mr.g + 2 * xx + (quarter >> 1)) * (C >> 2)) + 16 * piece;
-            }
-            xv[j] = *reinterpret_cast<const v4i*>(src);
+        const int64_t row = min(row0 + j * RP + rgrp, rows - 1);   // (a row past the end repeats the last one and is not stored)
+        const int8_t* src = x + row * C + 16 * cc;
+        if (MERGE) {
+            uint32_t in, xx;
+            const uint32_t b = mr.image.divide((uint32_t)row, in), yy = mr.line.divide(in, xx);
+            src = x + ((((int64_t)b * mr.g + 2 * yy + (quarter & 1)) * mr.g + 2 * xx + (quarter >> 1)) * (C >> 2)) + 16 * piece;
         }
+        xv[j] = *reinterpret_cast<const v4i*>(src);
     }
     // gamma and beta + 2^(c-1) go through LDS: read once per workgroup with coalesced loads instead of 128 bytes per
     // thread; each thread picks up its 16 channels after the first barrier
@@ -138,9 +141,12 @@ __global__ __launch_bounds__(256) void ilayernorm_tiled_kernel(const int8_t* __r
     // time, meet no bank twice)
     constexpr int GBP = GBN / 16 * 20;
     __shared__ __align__(16) int32_t gb[2 * GBP];
-    for (int i = tid; i < C; i += 256) {
-        gb[(i >> 4) * 20 + (i & 15)] = gamma_q[i];
-        gb[GBP + (i >> 4) * 20 + (i & 15)] = (int32_t)((uint32_t)beta_q[i] + (uint32_t)half);
+    v4i gq[GBN / 1024], bq[GBN / 1024];
+#pragma unroll
+    for (int k = 0; k < GBN / 1024; ++k) {
+        const int at = min(4 * tid + 1024 * k, C - 4);
+        gq[k] = *reinterpret_cast<const v4i*>(gamma_q + at);
+        bq[k] = *reinterpret_cast<const v4i*>(beta_q + at);
     }
 #pragma unroll
     for (int j = 0; j < J; ++j) {
@@ -152,14 +158,31 @@ __global__ __launch_bounds__(256) void ilayernorm_tiled_kernel(const int8_t* __r
         }
         if (active) part[j * 256 + cc * RP + rgrp] = make_int2(s, ss);
     }
+#pragma unroll
+    for (int k = 0; k < GBN / 1024; ++k) {
+        const int i = 4 * tid + 1024 * k;
+        if (i < C) {
+            *reinterpret_cast<v4i*>(&gb[(i >> 4) * 20 + (i & 15)]) = gq[k];
+            v4i bh;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bh[e] = (int32_t)((uint32_t)bq[k][e] + (uint32_t)half);
+            *reinterpret_cast<v4i*>(&gb[GBP + (i >> 4) * 20 + (i & 15)]) = bh;
+        }
+    }
     __syncthreads();
-    for (int r = tid; r < R; r += 256) {           // one row per thread: r = j * RP + rgrp
-        const int j = r / RP, rg = r - j * RP;
-        const int2* p = &part[j * 256 + rg];
+    const int r = tid >> rt.lanes_log2, first = tid - (r << rt.lanes_log2);
+    if (r < R) {                                   // r = j * RP + rgrp (R <= 256: launch_tiled)
+        uint32_t rg;
+        const int j = (int)rt.rp.divide((uint32_t)r, rg);
+        const int2* p = &part[j * 256 + (int)rg];
         int32_t s = 0, ss = 0;
-        for (int c = 0; c < CPR; ++c) { s += p[c * RP].x; ss += p[c * RP].y; }
+#pragma unroll 4
+        for (int c = first; c < CPR; c += 1 << rt.lanes_log2) { s += p[c * RP].x; ss += p[c * RP].y; }
+        if (rt.lanes_log2 >= 1) { s += dpp_i32<0xB1>(s); ss += dpp_i32<0xB1>(ss); }
+        if (rt.lanes_log2 >= 2) { s += dpp_i32<0x4E>(s); ss += dpp_i32<0x4E>(ss); }
+        if (rt.lanes_log2 >= 3) { s += dpp_i32<0x141>(s); ss += dpp_i32<0x141>(ss); }
         const LnStat st = ln_stat(s, ss, C, f_bits);
-        stat[r] = make_int2(st.mean, st.f);
+        if (first == 0) stat[r] = make_int2(st.mean, st.f);
     }
     __syncthreads();
     int32_t g[16], bt[16];
@@ -204,8 +227,11 @@ static bool launch_tiled(hipStream_t s, const int8_t* x, const int32_t* gamma_q,
     while (J > 1 && rp * J > 256) J >>= 1;       // at most one row of scalar work per thread (narrow rows: C < 128)
     const int64_t grid = (rows + rp * J - 1) / (rp * J);
     if (grid > 0x7fffffffLL) return false;
+    int lanes_log2 = 0;
+    while (lanes_log2 < 3 && (rp * J) << (lanes_log2 + 1) <= 256) ++lanes_log2;
+    const RowTile rt{FastDiv((uint32_t)(C >> 4)), FastDiv((uint32_t)rp), lanes_log2};
     const dim3 g((unsigned)grid), b(256);
-#define IVIT_LN(J_, GBN_) hipLaunchKernelGGL((ilayernorm_tiled_kernel<J_, GBN_, MERGE>), g, b, 0, s, x, gamma_q, beta_q, y, rows, C, f_bits, c_shift, mr)
+#define IVIT_LN(J_, GBN_) hipLaunchKernelGGL((ilayernorm_tiled_kernel<J_, GBN_, MERGE>), g, b, 0, s, x, gamma_q, beta_q, y, rows, C, f_bits, c_shift, rt, mr)
     if (C > 1024) {
         switch (J) {
             case 8: IVIT_LN(8, 2048); break;
