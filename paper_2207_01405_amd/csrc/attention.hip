@@ -121,11 +121,11 @@ __device__ __forceinline__ uint32_t div_pack(uint32_t f, const int32_t (&e)[4]) 
 }
 
 // The rows of a 24-bit form with a relative-position bias and / or the shifted-window mask, up to the row maximum.  A masked key
-// gets mask_add.  Returns the maximum; masked: whether anything in the tile's rows is masked.
+// gets mask_add.  Returns the maximum; masked: whether anything in the tile's rows is masked.  nfull: key tiles whose keys all exist;
+// left: keys from this lane's first one on.
 template <bool MASK, int NKT>
 __device__ __forceinline__ int32_t biased_scores(int32_t (&sc)[NKT][4], const uint32_t (&bw)[NKT], const uint32_t (&mw)[NKT], Narrow nqk, int32_t mask_add,
-                                                 int T, int lg, bool& masked) {
-    const int nfull = T >> 4;
+                                                 int nfull, int left, bool& masked) {
     uint32_t any = 0;
     int32_t mx = INT32_MIN;
 #pragma unroll
@@ -150,42 +150,49 @@ __device__ __forceinline__ int32_t biased_scores(int32_t (&sc)[NKT][4], const ui
         }
     }
 #pragma unroll
-    for (int t = 0; t < NKT; ++t)
+    for (int t = 0; t < NKT; ++t) {
+        if (t < nfull) {
+            mx = max(mx, max(max(sc[t][0], sc[t][1]), max(sc[t][2], sc[t][3])));
+        } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) if (t < nfull || 16 * t + 4 * lg + r < T) mx = max(mx, sc[t][r]);
+            for (int r = 0; r < 4; ++r) if (16 * t + r < left) mx = max(mx, sc[t][r]);
+        }
+    }
     return rows_allreduce(mx, [](int32_t a, int32_t b) { return max(a, b); });
 }
 
 // ShiftExp of the scores by table (16-bit entries); returns the row sum.  !BIAS: the score's product is subtracted from `base`.
 // CLAMP: a delta may lie beyond the table, whose last entry stands for it.
 template <bool BIAS, bool CLAMP, int NKT>
-__device__ __forceinline__ int32_t look_up(int32_t (&sc)[NKT][4], const uint16_t* lut, int n_lut, int32_t mx, uint32_t base, Narrow nqk, int T, int lg) {
-    const int nfull = T >> 4;
+__device__ __forceinline__ int32_t look_up(int32_t (&sc)[NKT][4], const uint16_t* lut, int n_lut, int32_t mx, uint32_t base, Narrow nqk, int nfull, int left) {
     const char* lut_b = reinterpret_cast<const char*>(lut);
     const int32_t mx2 = 2 * mx;
     int32_t sum = 0;
 #pragma unroll
     for (int t = 0; t < NKT; ++t) {
+        uint32_t at[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            uint32_t at;
             if constexpr (!BIAS) {
-                at = twice_top(base + (uint32_t)__mul24(med3_i32(sc[t][r], nqk.lo, nqk.hi), -nqk.mb));
+                at[r] = twice_top(base + (uint32_t)__mul24(med3_i32(sc[t][r], nqk.lo, nqk.hi), -nqk.mb));
             } else {
-                at = minus_twice(mx2, sc[t][r]);
-                if constexpr (CLAMP) at = min(at, 2u * (uint32_t)(n_lut - 1));
+                at[r] = minus_twice(mx2, sc[t][r]);
+                if constexpr (CLAMP) at[r] = min(at[r], 2u * (uint32_t)(n_lut - 1));
             }
-            int32_t e;
-            if (t < nfull) {
-                e = (int32_t)*reinterpret_cast<const uint16_t*>(lut_b + at);
-            } else {                               // (an absent key may stand above the maximum)
-                const bool there = 16 * t + 4 * lg + r < T;
-                e = (int32_t)*reinterpret_cast<const uint16_t*>(lut_b + (there ? at : 0u));
-                e = there ? e : 0;
-            }
-            sc[t][r] = e;
-            sum += e;
         }
+        if (t < nfull) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sc[t][r] = (int32_t)*reinterpret_cast<const uint16_t*>(lut_b + at[r]);
+        } else {                                   // (an absent key may stand above the maximum)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool there = 16 * t + r < left;
+                const int32_t e = (int32_t)*reinterpret_cast<const uint16_t*>(lut_b + (there ? at[r] : 0u));
+                sc[t][r] = there ? e : 0;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum += sc[t][r];
         if (t & 1) __builtin_amdgcn_sched_barrier(0);
     }
     return rows_allreduce(sum, [](int32_t a, int32_t b) { return a + b; });
@@ -437,27 +444,32 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
                 uint32_t base = 0;                 // without a bias: what a score's product is subtracted from
                 bool masked = false;
                 int32_t mx = INT32_MIN;
+                // keys from this lane's first one on; of an unknown T not known to be the same for the next query tile, so that the
+                // comparisons are not made once for all and kept in more scalar registers than there are
+                int left = T - 4 * lg;
+                if (!TFIX) asm volatile("" : "+v"(left));
                 if constexpr (!BIAS) {
                     // the requantisation is monotonic: the row maximum is that of the accumulators.  With T the maximum's result,
                     // (T | 2^24 - 1) - (m mb + ad), m a limited score, has max - value in its top byte.
 #pragma unroll
-                    for (int t = 0; t < NKT; ++t)
+                    for (int t = 0; t < NKT; ++t) {
+                        if (t >= nfull) {
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            if (t >= nfull && 16 * t + 4 * lg + r >= T) sc[t][r] = INT32_MIN;
-                            mx = max(mx, sc[t][r]);
+                            for (int r = 0; r < 4; ++r) if (16 * t + r >= left) sc[t][r] = INT32_MIN;
                         }
+                        mx = max(mx, max(max(sc[t][0], sc[t][1]), max(sc[t][2], sc[t][3])));
+                    }
                     mx = rows_allreduce(mx, [](int32_t a, int32_t b) { return max(a, b); });
                     base = ((uint32_t)(__mul24(min(max(mx, nqk.lo), nqk.hi), nqk.mb) + nqk.ad) | 0xffffffu) - (uint32_t)nqk.ad;
                 } else {
                     if (!ONE) load_words(qt);
                     move_down(bw);
                     if (MASK) move_down(mw);
-                    mx = biased_scores<MASK>(sc, bw, mw, nqk, mask_add, T, lg, masked);
+                    mx = biased_scores<MASK>(sc, bw, mw, nqk, mask_add, nfull, left, masked);
                 }
                 // ---- ShiftExp by table, row sum, IntDiv
-                const int32_t sum = MASK && masked ? look_up<BIAS, true>(sc, lut, NLUT, mx, base, nqk, T, lg)
-                                                   : look_up<BIAS, false>(sc, lut, NLUT, mx, base, nqk, T, lg);
+                const int32_t sum = MASK && masked ? look_up<BIAS, true>(sc, lut, NLUT, mx, base, nqk, nfull, left)
+                                                   : look_up<BIAS, false>(sc, lut, NLUT, mx, base, nqk, nfull, left);
                 const uint32_t f = div_factor(sum, sm);
 #pragma unroll
                 for (int t = 0; t + 4 <= NKT; t += 4) {
@@ -656,7 +668,7 @@ __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention
     const int8_t* __restrict__ qkv, const int8_t* __restrict__ rel_bias, const int8_t* __restrict__ mask, FastDiv n_mask,
     const int32_t* __restrict__ tok_index, FastDiv n_win, int8_t* __restrict__ o, int B, int C, FastDiv H, ShiftParams sm,
     Narrow nqk, Narrow npv) {
-    constexpr int T = WIN_T, D = 32, NT = 4, NQ = T / 16, LAST = T - 1, VP = 40, NLUT = MASK ? 1024 : 512;
+    constexpr int T = WIN_T, D = 32, NT = 4, NQ = T / 16, LAST = T - 1, nfull = T >> 4, VP = 40, NLUT = MASK ? 1024 : 512;
     static_assert(T == 16 * NQ + 1 && NQ + 1 == NT);
     __shared__ __align__(16) int8_t Vall[WIN_WAVES][NT * 16 * VP];
     __shared__ __align__(16) uint32_t bias_words[NQ][64][NT];
@@ -706,6 +718,7 @@ __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention
     int8_t* Vs = Vall[wv];
     const int8_t* vbase = Vs + (4 * lg + 16 * ((li >> 1) >> 2) + ((li >> 1) & 3)) * VP + ((li & 1) ? D / 2 : 0);
     const int32_t mask_add = -100 * sm.i0;
+    const int left = T - 4 * lg;
     int b = slot * WIN_WAVES + wv;
     uint32_t image = b < B ? fetch_rows(b) : 0;
     while (b < B) {
@@ -764,9 +777,9 @@ __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention
 #pragma unroll
             for (int t = 0; t < NT; ++t) mt[t] = MASK ? mw[q][t] : 0u;
             bool masked;
-            const int32_t mx = biased_scores<MASK>(sc, bw, mt, nqk, mask_add, T, lg, masked);
-            const int32_t sum = MASK && masked ? look_up<true, true>(sc, lut, NLUT, mx, 0u, nqk, T, lg)
-                                               : look_up<true, false>(sc, lut, NLUT, mx, 0u, nqk, T, lg);
+            const int32_t mx = biased_scores<MASK>(sc, bw, mt, nqk, mask_add, nfull, left, masked);
+            const int32_t sum = MASK && masked ? look_up<true, true>(sc, lut, NLUT, mx, 0u, nqk, nfull, left)
+                                               : look_up<true, false>(sc, lut, NLUT, mx, 0u, nqk, nfull, left);
             uint32_t pk[NT];
             div_pack4(pk, div_factor(sum, sm), sc[0], sc[1], sc[2], sc[3]);
             const v4i pf = {(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};

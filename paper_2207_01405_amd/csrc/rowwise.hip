@@ -228,7 +228,7 @@ static bool launch_tiled(hipStream_t s, const int8_t* x, const int32_t* gamma_q,
     const int64_t grid = (rows + rp * J - 1) / (rp * J);
     if (grid > 0x7fffffffLL) return false;
     int lanes_log2 = 0;
-    while (lanes_log2 < 3 && (rp * J) << (lanes_log2 + 1) <= 256) ++lanes_log2;
+    while (lanes_log2 < 3 && (rp * J) << (lanes_log2 + 1) <= 256 && C >> (lanes_log2 + 5) >= 4) ++lanes_log2;   // (at least four sums each)
     const RowTile rt{FastDiv((uint32_t)(C >> 4)), FastDiv((uint32_t)rp), lanes_log2};
     const dim3 g((unsigned)grid), b(256);
 #define IVIT_LN(J_, GBN_) hipLaunchKernelGGL((ilayernorm_tiled_kernel<J_, GBN_, MERGE>), g, b, 0, s, x, gamma_q, beta_q, y, rows, C, f_bits, c_shift, rt, mr)
