@@ -249,7 +249,9 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
     // 24-bit form: 16-bit entries (two to a bank, so that fewer lanes meet in one); with the mask its last entry is 0 whatever
     // the parameters, which is exact: it stands for everything beyond, and at a delta of 1023 itself, which only a masked key
     // reaches and only for I_0 <= 15, ShiftExp is 0
-    constexpr bool N24 = FAST == 2 && !TAPS;
+    // (with a bias it holds a word of it per key tile: beyond 8 tiles that costs a workgroup per CU or spills, and the scores are
+    // taken tile by tile instead, with 24-bit requantisations alone: 1200 pairs of 196 tokens and 32 features 70 us otherwise)
+    constexpr bool N24 = FAST == 2 && !TAPS && !(BIAS && NKT > 8);
     using Entry = std::conditional_t<N24, uint16_t, uint32_t>;
     __shared__ Entry lut[NLUT];
 
@@ -886,11 +888,8 @@ static void launch_flags(hipStream_t s, const AttentionArgs& a, int grid, int sp
         if (masked) { if (narrow) IVIT_ATT(false, true, true, 2, T49); else IVIT_ATT(false, true, true, 1, T49); }
         else { if (narrow) IVIT_ATT(false, true, false, 2, T49); else IVIT_ATT(false, true, false, 1, T49); }
     } else if (!taps && fast) {
-        // with a bias the 24-bit form holds a word of it per key tile: beyond 8 tiles that costs a workgroup per CU or spills
-        // (1200 pairs of 196 tokens and 32 features 53 us in the 32-bit form at first, 70 in the 24-bit one)
-        constexpr int BIASED = NKT <= 8 ? 2 : 1;
-        if (masked) { if (narrow) IVIT_ATT(false, true, true, BIASED, 0); else IVIT_ATT(false, true, true, 1, 0); }
-        else if (bias) { if (narrow) IVIT_ATT(false, true, false, BIASED, 0); else IVIT_ATT(false, true, false, 1, 0); }
+        if (masked) { if (narrow) IVIT_ATT(false, true, true, 2, 0); else IVIT_ATT(false, true, true, 1, 0); }
+        else if (bias) { if (narrow) IVIT_ATT(false, true, false, 2, 0); else IVIT_ATT(false, true, false, 1, 0); }
         else { if (narrow) IVIT_ATT(false, false, false, 2, 0); else IVIT_ATT(false, false, false, 1, 0); }
     } else {
         if (masked) IVIT_ATT(true, true, true, 0, 0);
