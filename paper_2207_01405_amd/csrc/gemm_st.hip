@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
     }
     auto buffer = [](const int8_t* p) __attribute__((always_inline)) {
         const uint64_t a = (uint64_t)p;
-        return v4i{(int)(uint32_t)a, (int)(uint32_t)(a >> 32), 0x7fffffff, 0x00020000};
+        return v4i{(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)kTileBytes, 0x00020000};
     };
     const int stages = (K + BK - 1) / BK, k_last = K - (stages - 1) * BK;      // bytes of K in the last stage: 16 .. 128
     const uint32_t lds0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_offset(lds) + XB + wv * 1024));

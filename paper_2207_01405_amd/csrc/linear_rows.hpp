@@ -6,11 +6,15 @@ namespace ivit {
 
 constexpr int64_t kTileRows = 128;       // the tallest tile of the kernel for any shape (gemm_st.hip)
 
-// That kernel addresses the rows of a tile by 32-bit byte offsets from the tile's first one; they are kept below 2^31,
-// where it does not matter whether anything on the way takes them as signed.  The result is the number of rows, from 1
-// up, that a launch can take for a row stride of ldx >= K bytes; where tiles of full height fit there is no limit.
+// That kernel addresses the rows of a tile by 32-bit byte offsets from the tile's first one; they are kept below kTileBytes =
+// 2^31, where it does not matter whether anything on the way takes them as signed.  kTileBytes is also the size in its buffer
+// descriptors: a row may end there, at its last byte.
+constexpr uint32_t kTileBytes = 0x80000000u;
+
+// The number of rows, from 1 up, that a launch can take for a row stride of ldx >= K bytes; where tiles of full height fit there
+// is no limit.
 constexpr int64_t linear_rows_per_launch(int64_t ldx, int64_t K) {
-    const int64_t reach = (((int64_t)1 << 31) - K) / ldx + 1;
+    const int64_t reach = ((int64_t)kTileBytes - K) / ldx + 1;
     return reach >= kTileRows ? INT64_MAX : reach;
 }
 

@@ -56,3 +56,24 @@ def test_head_over_images_far_apart(ivit, B, T, C, N):
     ivit.ivit_classifier_head(tokens.view(B * T, C), T, dev(w), dev(bias), dev(rq_b), dev(rq_c), room[:B * N].view(B, N))
     got = room.cpu().numpy()
     assert np.array_equal(got[:B * N].reshape(B, N), orc.linear_requant(x, w, bias, rq_b, rq_c)) and (got[B * N:] == 77).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,C", [(2, 16), (2, 1024), (64, 8192)])
+def test_a_launch_that_ends_where_its_offsets_do(ivit, B, C):
+    """The last row ends at byte 2^31 of a tile exactly, and there are more classes than the kernel for few rows takes."""
+    import torch
+    T = (2 ** 31 // C - 1) // (B - 1)
+    assert (B - 1) * T * C + C == 2 ** 31
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    N = 32 * (cus * (1 if C > 768 else 2) // -(-B // 32)) + 40
+    x = synth.make_rows(B + C, B, C, "uniform")
+    x[-1] = np.where(x[-1] == 0, 77, x[-1])
+    w, bias, rq_b, rq_c = synth.make_linear(N, N, C)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    tokens = torch.empty(B * T * C, dtype=torch.int8, device="cuda")
+    tokens.view(B, T * C)[:, :C] = dev(x)
+    room = torch.full((B * N + 64,), 77, dtype=torch.int8, device="cuda")
+    ivit.ivit_classifier_head(tokens.view(B * T, C), T, dev(w), dev(bias), dev(rq_b), dev(rq_c), room[:B * N].view(B, N))
+    got = room.cpu().numpy()
+    assert np.array_equal(got[:B * N].reshape(B, N), orc.linear_requant(x, w, bias, rq_b, rq_c)) and (got[B * N:] == 77).all()
