@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "attention_form.hpp"
 #include "ivit_kernels.hpp"
 
 namespace ivit {
@@ -36,6 +37,10 @@ typedef int v2i_att __attribute__((ext_vector_type(2)));
 // [lo, hi], the first values that give -127 / +127, after which (v b + 2^(c-1)) 2^(24-c) fits 32 bits with the int8
 // result in its top byte.  Valid for c <= 24, b < 2^(c-1) and bounds inside 24 bits (narrow_of() decides).
 struct Narrow { int32_t lo, hi, mb, ad; };
+
+// Constants of the 24-bit IntDiv (intdiv24_up): the scale of the table's entries, 2^(M+up) as a float and modulo 2^32, and the scaled
+// sum of a row in which one key has all of it.
+struct Div24 { int32_t up; float num; uint32_t num32; int32_t alone; };
 
 // FAST: 0 general 64-bit requantisation, 1 pairs that fit 32 bits, 2 the 24-bit form above (and the 24-bit IntDiv).
 template <int FAST>
@@ -198,17 +203,19 @@ __device__ __forceinline__ int32_t look_up(int32_t (&sc)[NKT][4], const uint16_t
     return rows_allreduce(sum, [](int32_t a, int32_t b) { return a + b; });
 }
 
-// IntDiv of the 24-bit form: M - (k_out - 1) = 24 here and inv <= 2^16 (launch_flags sees to it), so (inv 2^8) e has the quotient
-// in its upper word; this is inv 2^8.  2^(k_out-1), which a byte may not become, is the quotient only where one key has
+// IntDiv of the 24-bit form (intdiv24_up): entries and their sum come scaled by 2^up, this is inv 2^(8-up), and the quotient is
+// the upper word of its product with an entry.  2^(k_out-1), which a byte may not become, is the quotient only where one key has
 // the whole sum, ShiftExp(0); taking one from inv there gives 2^(k_out-1) - 1 and leaves every other row
-// alone.  The reciprocal is recip_pow2_small for a sum in its range.
-__device__ __forceinline__ uint32_t div_factor(int32_t sum, ShiftParams sm) {
-    uint32_t inv = (uint32_t)((float)(1u << sm.m_bits) * __builtin_amdgcn_rcpf((float)(uint32_t)sum));
-    const int32_t rem = (int32_t)((1u << sm.m_bits) - inv * (uint32_t)sum);
-    inv += (rem >= sum);
+// alone.  The reciprocal floor(2^M / sum) = floor(2^(M+up) / scaled), below 2^24, from a single-precision quotient with one
+// correction (a power of two times the reciprocal is exact but for the reciprocal's own last bit): to one, which the remainder repairs.
+__device__ __forceinline__ uint32_t div_factor(int32_t scaled, Div24 d) {
+    const float s = (float)(uint32_t)scaled, r = __builtin_amdgcn_rcpf(s), q = d.num * r;
+    uint32_t inv = (uint32_t)__builtin_fmaf(__builtin_fmaf(-q, s, d.num), r, q);
+    const int32_t rem = (int32_t)(d.num32 - inv * (uint32_t)scaled);
+    inv += (rem >= scaled);
     inv -= (rem < 0);
-    inv -= sum == (sm.i0 << sm.n_shift);
-    return inv << 8;
+    inv -= scaled == d.alone;
+    return inv << (8 - d.up);
 }
 
 // The lane's four output tiles requantised (24-bit form) to one word each
@@ -232,7 +239,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
                                                         const int8_t* __restrict__ mask, FastDiv n_mask,
                                                         const int32_t* __restrict__ tok_index, FastDiv n_win,
                                                         int8_t* __restrict__ o, int n_items, FastDiv split_d, int T_arg, int C, FastDiv H,
-                                                        Dyadic qk, ShiftParams sm, Dyadic pv, Narrow nqk, Narrow npv, int rnd,
+                                                        Dyadic qk, ShiftParams sm, Div24 dv, Dyadic pv, Narrow nqk, Narrow npv, int rnd,
                                                         int8_t* __restrict__ tap_s, int8_t* __restrict__ tap_p) {
     const int T = TFIX ? TFIX : T_arg, split = (int)split_d.d;
     constexpr int KROW = D + 16;                  // K row pitch (bytes)
@@ -371,7 +378,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
         };
         if (N24 && BIAS && ONE) load_words(qt0);   // (with K, V and Q: behind the barrier nothing is waited for any more)
         if (work == first) {                       // the table, while the first loads are in flight (visible after the barrier below)
-            for (int i = tid; i < NLUT; i += ATT_THREADS) lut[i] = N24 && MASK && i == NLUT - 1 ? (Entry)0 : (Entry)shiftexp(-i, sm.i0, sm.n_shift);
+            for (int i = tid; i < NLUT; i += ATT_THREADS) lut[i] = N24 && MASK && i == NLUT - 1 ? (Entry)0 : (Entry)(shiftexp(-i, sm.i0, sm.n_shift) << (N24 ? dv.up : 0));
         }
         const uint32_t orow0 = q_row(qt0);         // output row of the first query tile (before the indices move on)
         if (work + G < n_work) {
@@ -472,7 +479,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
                 // ---- ShiftExp by table, row sum, IntDiv
                 const int32_t sum = MASK && masked ? look_up<BIAS, true>(sc, lut, NLUT, mx, base, nqk, nfull, left)
                                                    : look_up<BIAS, false>(sc, lut, NLUT, mx, base, nqk, nfull, left);
-                const uint32_t f = div_factor(sum, sm);
+                const uint32_t f = div_factor(sum, dv);
 #pragma unroll
                 for (int t = 0; t + 4 <= NKT; t += 4) {
                     uint32_t w[4];
@@ -669,7 +676,7 @@ template <bool MASK>
 __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention_kernel(
     const int8_t* __restrict__ qkv, const int8_t* __restrict__ rel_bias, const int8_t* __restrict__ mask, FastDiv n_mask,
     const int32_t* __restrict__ tok_index, FastDiv n_win, int8_t* __restrict__ o, int B, int C, FastDiv H, ShiftParams sm,
-    Narrow nqk, Narrow npv) {
+    Div24 dv, Narrow nqk, Narrow npv) {
     constexpr int T = WIN_T, D = 32, NT = 4, NQ = T / 16, LAST = T - 1, nfull = T >> 4, VP = 40, NLUT = MASK ? 1024 : 512;
     static_assert(T == 16 * NQ + 1 && NQ + 1 == NT);
     __shared__ __align__(16) int8_t Vall[WIN_WAVES][NT * 16 * VP];
@@ -690,7 +697,7 @@ __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention
         __builtin_memcpy(&v, table + (uint32_t)(tok * T + from), 4);
         return 16 * t + 16 <= T ? v : (uint32_t)((uint64_t)v >> min(8 * (key - from), 32));
     };
-    for (int i = tid; i < NLUT; i += 64 * WIN_WAVES) lut[i] = MASK && i == NLUT - 1 ? (uint16_t)0 : (uint16_t)shiftexp(-i, sm.i0, sm.n_shift);
+    for (int i = tid; i < NLUT; i += 64 * WIN_WAVES) lut[i] = MASK && i == NLUT - 1 ? (uint16_t)0 : (uint16_t)(shiftexp(-i, sm.i0, sm.n_shift) << dv.up);
     for (int i = tid; i < NT * 64; i += 64 * WIN_WAVES) {
         const int q = i / 64, l = i & 63;
         const int8_t* table = rel_bias + (int64_t)h * T * T;
@@ -783,7 +790,7 @@ __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention
             const int32_t sum = MASK && masked ? look_up<true, true>(sc, lut, NLUT, mx, 0u, nqk, nfull, left)
                                                : look_up<true, false>(sc, lut, NLUT, mx, 0u, nqk, nfull, left);
             uint32_t pk[NT];
-            div_pack4(pk, div_factor(sum, sm), sc[0], sc[1], sc[2], sc[3]);
+            div_pack4(pk, div_factor(sum, dv), sc[0], sc[1], sc[2], sc[3]);
             const v4i pf = {(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};
             v4i oacc[2];
 #pragma unroll
@@ -810,7 +817,7 @@ __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention
         const int32_t mx = wave_allreduce(lane < T ? v : INT32_MIN, [](int32_t x, int32_t y) { return max(x, y); });
         int32_t e = (int32_t)lut[lane < T ? min(mx - v, NLUT - 1) : 0];
         e = lane < T ? e : 0;
-        const uint32_t f = div_factor(wave_allreduce(e, [](int32_t x, int32_t y) { return x + y; }), sm);
+        const uint32_t f = div_factor(wave_allreduce(e, [](int32_t x, int32_t y) { return x + y; }), dv);
         last_p[wv][lane] = (int8_t)(uint8_t)__umulhi(f, (uint32_t)e);
         v4i pf;
 #pragma unroll
@@ -845,7 +852,7 @@ static bool window_takes(const AttentionArgs& a) {
     return a.T == WIN_T && (int64_t)a.B * a.H >= 9 * (int64_t)num_cus() && rows * 3 * a.C < (int64_t)1 << 31;
 }
 
-static void launch_window(hipStream_t s, const AttentionArgs& a, Narrow nqk, Narrow npv) {
+static void launch_window(hipStream_t s, const AttentionArgs& a, Div24 dv, Narrow nqk, Narrow npv) {
     // as many passes as six workgroups per CU need (8192 x 3 takes 47.6 us with four, 43.8 with five, 43.2 with six), and no more
     // workgroups than share the windows evenly.  (Of eight wavefronts, three per CU: 45.1 us.)
     const int64_t most = std::max<int64_t>(1, 6 * (int64_t)num_cus() / a.H);
@@ -854,7 +861,7 @@ static void launch_window(hipStream_t s, const AttentionArgs& a, Narrow nqk, Nar
 #define IVIT_WIN(MASK_)                                                                                                              \
     hipLaunchKernelGGL((window_attention_kernel<MASK_>), dim3(grid), dim3(64 * WIN_WAVES), 0, s, a.qkv, a.rel_bias, a.mask,            \
                        FastDiv(std::max(a.n_mask, 1)), a.tok_index, FastDiv(std::max(a.n_win, 1)), a.o, a.B, a.C, FastDiv(a.H),       \
-                       a.sm, nqk, npv)
+                       a.sm, dv, nqk, npv)
     if (a.mask) IVIT_WIN(true); else IVIT_WIN(false);
 #undef IVIT_WIN
 }
@@ -863,17 +870,16 @@ template <int D, int NKT>
 static void launch_flags(hipStream_t s, const AttentionArgs& a, int grid, int split, bool taps, bool bias, bool fast) {
     const int n_items = a.B * a.H;
     Narrow nqk{}, npv{};
-    // the 24-bit forms: both requantisations, and IntDiv with its quotient in the top byte of a 24-bit product
-    const int rnd = a.floor_shift ? 0 : 1;
-    // of at most 2^16 (a row's sum is at least ShiftExp(0) = I_0 << N), the reciprocal times 2^8 in 24 bits
-    const int64_t e0 = (int64_t)a.sm.i0 << a.sm.n_shift;
-    const bool narrow = narrow_of(a.qk_rq, rnd, nqk) && narrow_of(a.pv_rq, rnd, npv) && a.sm.m_bits - (a.sm.k_out - 1) == 24 &&
-                        e0 << 16 >= (int64_t)1 << a.sm.m_bits && e0 >= 512;
+    // the 24-bit forms: both requantisations and IntDiv
+    const int rnd = a.floor_shift ? 0 : 1, up = intdiv24_up(a.sm.i0, a.sm.n_shift, a.sm.m_bits, a.sm.k_out);
+    const bool narrow = narrow_of(a.qk_rq, rnd, nqk) && narrow_of(a.pv_rq, rnd, npv) && up >= 0;
+    const uint64_t num = narrow ? (uint64_t)1 << (a.sm.m_bits + up) : 0;
+    const Div24 dv{up, (float)num, (uint32_t)num, narrow ? a.sm.i0 << (a.sm.n_shift + up) : 0};
 #define IVIT_ATT(TAPS_, BIAS_, MASK_, FAST_, TFIX_)                                                                         \
     hipLaunchKernelGGL((attention_kernel<D, NKT, TAPS_, BIAS_, MASK_, FAST_, TFIX_>), dim3(grid), dim3(ATT_THREADS), 0, s,     \
                        a.qkv, a.rel_bias, a.mask, FastDiv(std::max(a.n_mask, 1)), a.tok_index, FastDiv(std::max(a.n_win, 1)), a.o, \
                        n_items, FastDiv(split), a.T, a.C, FastDiv(a.H), a.qk_rq, \
-                       a.sm, a.pv_rq, nqk, npv, rnd, a.tap_scores, a.tap_probs)
+                       a.sm, dv, a.pv_rq, nqk, npv, rnd, a.tap_scores, a.tap_probs)
     // the production paths are <no taps, fast>, with the 24-bit requantisation when both pairs allow it; everything else
     // shares one fully general instantiation per bias / mask combination (a mask is always compiled with the bias code,
     // which tests the bias pointer)
@@ -883,7 +889,7 @@ static void launch_flags(hipStream_t s, const AttentionArgs& a, int grid, int sp
     if (T197 && a.T == 197 && !taps && fast && !bias) {
         if (narrow) IVIT_ATT(false, false, false, 2, T197); else IVIT_ATT(false, false, false, 1, T197);
     } else if (T49 && !taps && fast && bias && narrow && window_takes(a)) {
-        launch_window(s, a, nqk, npv);
+        launch_window(s, a, dv, nqk, npv);
     } else if (T49 && a.T == 49 && !taps && fast && bias) {
         if (masked) { if (narrow) IVIT_ATT(false, true, true, 2, T49); else IVIT_ATT(false, true, true, 1, T49); }
         else { if (narrow) IVIT_ATT(false, true, false, 2, T49); else IVIT_ATT(false, true, false, 1, T49); }

@@ -73,3 +73,22 @@ def test_rows_with_every_key_masked(ivit, i0, T):
 def test_multipliers(ivit, qk, rounding):
     _run(ivit, 1, 197, 2, 64, synth.shift_params(32), qk, pv=qk, sigma=60.0, rounding=rounding)
     _run(ivit, 1, 49, 2, 32, synth.shift_params(32), qk, pv=qk, bias=True, sigma=60.0, rounding=rounding)
+
+
+# ShiftExp(0) over the range whose tables are scaled: ends of every octave, the smallest of each k_out (2^(k_out-1) + 1), odd values
+@pytest.mark.parametrize("e0", [129, 255, 256, 257, 511, 512, 513, 1023, 1024, 4095, 4096, 9999, 16383, 16384, 32767, 32768, 65535])
+@pytest.mark.parametrize("one_key", [False, True])
+def test_exponent_scales(ivit, e0, one_key):
+    sm = dict(i0=e0, n_shift=0, m_bits=31, k_out=8)
+    while sm["i0"] > 40 and sm["i0"] % 2 == 0:
+        sm = dict(sm, i0=sm["i0"] // 2, n_shift=sm["n_shift"] + 1)
+    _run(ivit, 1, 197, 1, 64, sm, (20011, 24), one_key=one_key)
+    _run(ivit, 2, 49, 1, 32, sm, (20011, 23), bias=True, mask="some", one_key=one_key)
+    _run(ivit, 1, 145, 1, 32, sm, (20011, 22), bias=True, one_key=one_key)
+
+
+@pytest.mark.parametrize("k_out", range(2, 8))
+@pytest.mark.parametrize("one_key", [False, True])
+def test_fewer_bits_of_probability(ivit, k_out, one_key):
+    for i0, n in ((2 ** (k_out - 1) + 1, 0), (5, k_out), (33, 10)):
+        _run(ivit, 1, 65, 1, 64, dict(i0=i0, n_shift=n, m_bits=23 + k_out, k_out=k_out), (20011, 24), one_key=one_key)
