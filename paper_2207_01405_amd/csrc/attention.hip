@@ -257,8 +257,9 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
     // the parameters, which is exact: it stands for everything beyond, and at a delta of 1023 itself, which only a masked key
     // reaches and only for I_0 <= 15, ShiftExp is 0
     // (with a bias it holds a word of it per key tile: beyond 8 tiles that costs a workgroup per CU or spills, and the scores are
-    // taken tile by tile instead, with 24-bit requantisations alone: 1200 pairs of 196 tokens and 32 features 70 us otherwise)
-    constexpr bool N24 = FAST == 2 && !TAPS && !(BIAS && NKT > 8);
+    // taken tile by tile instead, between the 24-bit requantisations and IntDiv: 1200 pairs of 196 tokens and 32 features 70 us
+    // otherwise)
+    constexpr bool DIV24 = FAST == 2 && !TAPS, N24 = DIV24 && !(BIAS && NKT > 8);
     using Entry = std::conditional_t<N24, uint16_t, uint32_t>;
     __shared__ Entry lut[NLUT];
 
@@ -378,7 +379,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
         };
         if (N24 && BIAS && ONE) load_words(qt0);   // (with K, V and Q: behind the barrier nothing is waited for any more)
         if (work == first) {                       // the table, while the first loads are in flight (visible after the barrier below)
-            for (int i = tid; i < NLUT; i += ATT_THREADS) lut[i] = N24 && MASK && i == NLUT - 1 ? (Entry)0 : (Entry)(shiftexp(-i, sm.i0, sm.n_shift) << (N24 ? dv.up : 0));
+            for (int i = tid; i < NLUT; i += ATT_THREADS) lut[i] = N24 && MASK && i == NLUT - 1 ? (Entry)0 : (Entry)(shiftexp(-i, sm.i0, sm.n_shift) << (DIV24 ? dv.up : 0));
         }
         const uint32_t orow0 = q_row(qt0);         // output row of the first query tile (before the indices move on)
         if (work + G < n_work) {
@@ -435,6 +436,19 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             uint32_t pk[NKC * 4];
 #pragma unroll
             for (int t = 0; t < NKC * 4; ++t) pk[t] = 0u;
+            // IntDiv of the 24-bit form: the probabilities of the lane's row, four to a word, from the scaled entries and their sum
+            auto div24 = [&](int32_t sum) __attribute__((always_inline)) {
+                const uint32_t f = div_factor(sum, dv);
+#pragma unroll
+                for (int t = 0; t + 4 <= NKT; t += 4) {
+                    uint32_t w[4];
+                    div_pack4(w, f, sc[t], sc[t + 1], sc[t + 2], sc[t + 3]);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) pk[t + k] = w[k];
+                }
+#pragma unroll
+                for (int t = NKT & ~3; t < NKT; ++t) pk[t] = div_pack(f, sc[t]);
+            };
             // ---- requantise, add the bias, row maximum.  Lane (li, lg) holds keys 16 t + 4 lg + r.
             const int64_t tap_row = ((int64_t)item * T + qc) * T;
             // BIAS: a relative-position bias and / or the shifted-window mask.  A masked key gets -100 I_0 (the -100
@@ -479,16 +493,7 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
                 // ---- ShiftExp by table, row sum, IntDiv
                 const int32_t sum = MASK && masked ? look_up<BIAS, true>(sc, lut, NLUT, mx, base, nqk, nfull, left)
                                                    : look_up<BIAS, false>(sc, lut, NLUT, mx, base, nqk, nfull, left);
-                const uint32_t f = div_factor(sum, dv);
-#pragma unroll
-                for (int t = 0; t + 4 <= NKT; t += 4) {
-                    uint32_t w[4];
-                    div_pack4(w, f, sc[t], sc[t + 1], sc[t + 2], sc[t + 3]);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) pk[t + k] = w[k];
-                }
-#pragma unroll
-                for (int t = NKT & ~3; t < NKT; ++t) pk[t] = div_pack(f, sc[t]);
+                div24(sum);
             } else {
             int32_t mx = INT32_MIN;
 #pragma unroll
@@ -566,28 +571,32 @@ __global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t*
             }
             sum = rows_allreduce(sum, [](int32_t a, int32_t b) { return a + b; });
             // ---- IntDiv and packing: the four keys of tile t become one word of the "B" operand
-            const uint32_t inv = (1u << sm.m_bits) / (uint32_t)sum;
-            const uint32_t inv_hi = FAST ? inv << (32 - sh) : 0u;      // FAST: inv < 2^sh, 1 <= sh <= 31
+            if constexpr (DIV24) {
+                div24(sum);
+            } else {
+                const uint32_t inv = (1u << sm.m_bits) / (uint32_t)sum;
+                const uint32_t inv_hi = FAST ? inv << (32 - sh) : 0u;      // FAST: inv < 2^sh, 1 <= sh <= 31
 #pragma unroll
-            for (int t = 0; t < NKT; ++t) {
+                for (int t = 0; t < NKT; ++t) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (TAPS) {
-                        const uint32_t p = FAST ? min(__umulhi(inv_hi, (uint32_t)sc[t][r]), top)
-                                                : min((inv * (uint32_t)sc[t][r]) >> sh, top);
-                        const int key = 16 * t + 4 * lg + r;
-                        if (tap_p && q < T && key < T) tap_p[tap_row + key] = (int8_t)p;
-                        pk[t] |= p << (8 * r);
-                    } else {
-                        // IntDiv gives at most 2^(k_out-1), which fits a byte: clamp the four of a word together below
-                        const uint32_t p = FAST ? __umulhi(inv_hi, (uint32_t)sc[t][r]) : (inv * (uint32_t)sc[t][r]) >> sh;
-                        pk[t] |= p << (8 * r);
+                    for (int r = 0; r < 4; ++r) {
+                        if (TAPS) {
+                            const uint32_t p = FAST ? min(__umulhi(inv_hi, (uint32_t)sc[t][r]), top)
+                                                    : min((inv * (uint32_t)sc[t][r]) >> sh, top);
+                            const int key = 16 * t + 4 * lg + r;
+                            if (tap_p && q < T && key < T) tap_p[tap_row + key] = (int8_t)p;
+                            pk[t] |= p << (8 * r);
+                        } else {
+                            // IntDiv gives at most 2^(k_out-1), which fits a byte: clamp the four of a word together below
+                            const uint32_t p = FAST ? __umulhi(inv_hi, (uint32_t)sc[t][r]) : (inv * (uint32_t)sc[t][r]) >> sh;
+                            pk[t] |= p << (8 * r);
+                        }
                     }
                 }
-            }
-            if (!TAPS) {
+                if (!TAPS) {
 #pragma unroll
-                for (int t = 0; t < NKT; ++t) pk[t] -= (pk[t] >> (sm.k_out - 1)) & 0x01010101u;   // bytewise min(p, 2^(k_out-1) - 1)
+                    for (int t = 0; t < NKT; ++t) pk[t] -= (pk[t] >> (sm.k_out - 1)) & 0x01010101u;   // bytewise min(p, 2^(k_out-1) - 1)
+                }
             }
             }
             // ---- O^T = V^T P^T : "A" = V^T rows (features), "B" = packed probabilities (keys x queries).
