@@ -234,6 +234,7 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(KsParams P) {
     // general 64-bit form for all of its channels.
     int32_t c_lo = 0, c_hi = 0, c_mb = 0, c_ad = 0;
     Residual64 c_r;
+    constexpr uint32_t START = EPI == EPI_RESIDUAL ? kSumStart : 0u;            // of the partial sums that are kept, not of those handed over
     bool chan_24 = true;
     if (EPI == EPI_RESIDUAL) {
         chan_24 = residual64_of(c_r, pb, pc, pbias, P.rnd) && residual_term_24(P.res_rq);
@@ -302,7 +303,7 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(KsParams P) {
         const int32_t b = c_lo, c = c_hi, bias = c_mb;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            int64_t r64 = rnd_shift64(a[4 * d + r] + bias, b, c, P.rnd);
+            int64_t r64 = rnd_shift64(sum_of(a[4 * d + r], bias, START), b, c, P.rnd);
             if (EPI == EPI_RESIDUAL) {
                 const int32_t res = (int32_t)(int8_t)((uint32_t)rw[d >> 1][d & 1] >> (8 * r));
                 r64 += rnd_shift64(res, P.res_rq.b, P.res_rq.c, P.rnd);
@@ -372,8 +373,7 @@ __global__ __launch_bounds__(256) void gemm_ks_kernel(KsParams P) {
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) {
                 if (ks == 0) {
-                    const v16i zero = {};
-                    cur[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[ks % RG], W[cb][ks], zero, 0, 0, 0);
+                    cur[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[ks % RG], W[cb][ks], sums_from(cb == 0 ? START : 0u), 0, 0, 0);
                 } else {
                     cur[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[ks % RG], W[cb][ks], cur[cb], 0, 0, 0);
                 }

@@ -257,6 +257,7 @@ __global__ __launch_bounds__(256 * GR) void gemm_rs_kernel(RsParams P) {
     // workgroup with a channel outside these conditions takes the general 64-bit form for all of its channels.
     int32_t c_lo[NCB], c_hi[NCB], c_mb[NCB], c_ad[NCB];
     Residual64 c_r[NCB];
+    constexpr uint32_t START = EPI == EPI_RESIDUAL ? kSumStart : 0u;
     bool chan_24 = true;
     constexpr int64_t wlim = 127;
     constexpr int sh24 = 24;
@@ -353,7 +354,7 @@ __global__ __launch_bounds__(256 * GR) void gemm_rs_kernel(RsParams P) {
         const int32_t b = c_lo[cb], c = c_hi[cb], bias = c_mb[cb];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            int64_t r64 = rnd_shift64(a[4 * d + r] + bias, b, c, P.rnd);
+            int64_t r64 = rnd_shift64(sum_of(a[4 * d + r], bias, START), b, c, P.rnd);
             if (EPI == EPI_RESIDUAL) {
                 const int32_t res = (int32_t)(int8_t)((uint32_t)rw[cb][d >> 1][d & 1] >> (8 * r));
                 r64 += rnd_shift64(res, P.res_rq.b, P.res_rq.c, P.rnd);
@@ -425,8 +426,7 @@ __global__ __launch_bounds__(256 * GR) void gemm_rs_kernel(RsParams P) {
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) {
                 if (ks == 0) {
-                    const v16i zero = {};
-                    cur[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[ks % RG], W[cb][ks], zero, 0, 0, 0);
+                    cur[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[ks % RG], W[cb][ks], sums_from(START), 0, 0, 0);
                 } else {
                     cur[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[ks % RG], W[cb][ks], cur[cb], 0, 0, 0);
                 }

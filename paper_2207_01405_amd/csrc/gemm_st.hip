@@ -177,9 +177,12 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
         if (stages >= S - 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((S - 1) * DPW) : "memory");
         else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         const int ch = 64 * wv + lane;
+        const int32_t b = qb_s[ch], c = qc_s[ch], bias = bias_s[ch];
         Residual64 q;
-        const bool ok = residual64_of(q, qb_s[ch], qc_s[ch], bias_s[ch], P.rnd);
-        cst[ch] = v4i{ok ? q.b : 0, 0, (int32_t)(uint32_t)q.h, (int32_t)(q.h >> 32) + (EPI == EPI_GELU ? 128 : 0)};
+        bool ok = residual64_of(q, b, c, bias, P.rnd);
+        // (the 128 must not carry a result out of int32: it is at most 2^30 for b < 2^(c-1), and |acc| at most 2^30)
+        if (EPI == EPI_GELU) ok = ok && (b < (1 << ((c - 1) & 31)) || (bias < 0x3fffff00 && bias > -0x3fffff00));
+        cst[ch] = v4i{ok ? (int32_t)q.b : 0, 0, (int32_t)(uint32_t)q.h, (int32_t)((uint32_t)(q.h >> 32) + (EPI == EPI_GELU ? 128u : 0u))};
     }
 
     if constexpr (XS > 0) {
@@ -234,7 +237,11 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
         // (the barrier of the first stage is the one that makes the normalised rows everybody's)
     }
 
-    v16i acc[NT][MT] = {};
+    v16i acc[NT][MT];
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+        for (int tt = 0; tt < MT; ++tt) acc[ct][tt] = sums_from(kSumStart);
     constexpr int KS = BK / 32, AHEAD = MT * NT == 1 ? KS : 2;      // fragments are read AHEAD k-steps before their use
     int fx[KS], fw[KS];                                   // where this lane's fragments of k-step kk lie (buffer 0)
 #pragma unroll
@@ -332,7 +339,7 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const v4i e = cst[ch + r];
-                        q[r] = Residual64{e[0], (int64_t)(((uint64_t)(uint32_t)e[3] << 32) | (uint32_t)e[2])};
+                        q[r] = Residual64{(uint32_t)e[0], ((uint64_t)(uint32_t)e[3] << 32) | (uint32_t)e[2]};
                         asm volatile("" : "+v"(q[r].h));  // (see regst_common.hpp)
                     }
                 } else {
@@ -358,7 +365,7 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
                             else if (EPI == EPI_GELU) v = min(max(v, 1), 255);
                             else v = clamp8(v);
                         } else {
-                            int64_t r64 = rnd_shift64(a32 + bi[r], qb[r], qc[r], P.rnd);
+                            int64_t r64 = rnd_shift64(sum_of(a32, bi[r], kSumStart), qb[r], qc[r], P.rnd);
                             if (EPI == EPI_RESIDUAL) r64 += rnd_shift64(rv, P.res_rq.b, P.res_rq.c, P.rnd);
                             v = clamp8_64(r64) + (EPI == EPI_GELU ? 128 : 0);
                         }

@@ -174,6 +174,7 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
     int p_n0 = 0;                                               // first channel
     int32_t c_lo[2], c_hi[2], c_mb[2], c_ad[2], pb[2], pc[2], pbias[2];
     Residual64 c_r[2];
+    constexpr uint32_t START = EPI == EPI_RESIDUAL ? kSumStart : 0u;
     bool fast24 = false;
     v2i rw[2] = {};                                             // the unit's residual values, as the accumulators lie
     v4i ow = {};                                                // its results, four tokens a register
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
             uint32_t o[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                int64_t r64 = rnd_shift64(prev[mt][cb][4 * d + r] + pbias[cb], pb[cb], pc[cb], P.rnd);
+                int64_t r64 = rnd_shift64(sum_of(prev[mt][cb][4 * d + r], pbias[cb], START), pb[cb], pc[cb], P.rnd);
                 if (EPI == EPI_RESIDUAL) {
                     const int32_t res = (int32_t)(int8_t)((uint32_t)rw[d >> 1][d & 1] >> (8 * r));
                     r64 += rnd_shift64(res, P.res_rq.b, P.res_rq.c, P.rnd);
@@ -415,7 +416,7 @@ __global__ __launch_bounds__(256) void gemm_tl_kernel(TlParams P) {
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = v16i{};
+            for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = sums_from(START);
         int s = 0;
         if (ride) {
             stage(std::integral_constant<int, -1>());

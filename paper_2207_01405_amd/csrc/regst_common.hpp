@@ -58,21 +58,37 @@ __device__ __forceinline__ int32_t med3(int32_t v, int32_t lo, int32_t hi) {
 }
 
 // Residual layers: the first term floor((acc b + h) / 2^c), h = bias b + rounding addend, is the high word of one 64-bit
-// multiply-add by b 2^(32-c).  It needs b < 2^(c-1), so that the factor is an int32; a form with 24-bit multiplies, which has
-// to keep the sum's nine bits above the fraction, ends at c = 23, and layers with long rows need c = 24 (ViT-B's second MLP
-// layer, 50432 rows: 150 us with the general 64-bit form, 131.6 with a multiply-add by b, an addition and a shift; forwards
-// against that one: DeiT-S batch 128 1230 -> 1214 us, ViT-B batch 256 5580 -> 5548).  The addend is one
-// 64-bit register pair that the compiler cannot look into: it would add the two halves one after the other.
-struct Residual64 { int32_t b; int64_t h; };
-__device__ __forceinline__ bool residual64_takes(int32_t b, int32_t c) { return c >= 1 && c <= 31 && b >= 1 && b < (1 << ((c - 1) & 31)); }
+// multiply-add by the factor b 2^(32-c).  It takes every dyadic_fits32 pair, b <= 2^c: the factor and the sum it multiplies are
+// unsigned.  To that end the products of such a layer are added to kSumStart = 2^30 (the bits of 2.0, which a matrix instruction
+// has at hand) and not to 0: |acc| <= 2^14 K <= 2^30, so u = acc + 2^30 is not negative; the addend takes 2^30 times the factor away
+// again.  A form with 24-bit multiplies, which has to keep the sum's nine bits above the fraction, ends at c = 23, and layers
+// with long rows need c = 24 (ViT-B's second MLP layer, 50432 rows: 150 us with the general 64-bit form, 131.6 with a multiply-add
+// by b, an addition and a shift; forwards against that one: DeiT-S batch 128 1230 -> 1214 us, ViT-B batch 256 5580 -> 5548).
+// With a signed factor, which leaves pairs of b >= 2^(c-1) to the general form, two blocks of DeiT-S with such pairs, batch
+// 128, took 260 us instead of 181.  The addend is one 64-bit register pair that the compiler cannot look into: it would add the two
+// halves one after the other.
+constexpr uint32_t kSumStart = 0x40000000u;
+struct Residual64 { uint32_t b; uint64_t h; };
 __device__ __forceinline__ bool residual64_of(Residual64& q, int32_t b, int32_t c, int32_t bias, int32_t rnd) {
     const int up = 32 - (c & 31);
-    q.b = (int32_t)((uint32_t)b << (up & 31));
-    q.h = (int64_t)((uint64_t)((int64_t)bias * b + (int64_t)((uint32_t)rnd << ((c - 1) & 31))) << up);
+    const uint32_t one = 1u << (c & 31);
+    const int64_t h = (int64_t)bias * b + ((int64_t)b * -(int32_t)kSumStart + (int64_t)((uint32_t)rnd << ((c - 1) & 31)));
+    // b = 2^c, a factor of 2^32: u 2^32 + h' has the high word of u (2^32 - 1) + (h' | 2^32 - 1), u being below 2^32
+    const uint32_t whole = (uint32_t)b == one ? 0xffffffffu : 0u;
+    q.b = ((uint32_t)b << (up & 31)) | whole;
+    q.h = (uint64_t)h << up | whole;
     asm volatile("" : "+v"(q.h));
-    return residual64_takes(b, c);
+    return (c >= 1) & (c <= 31) & (b >= 1) & ((uint32_t)b <= one);       // dyadic_fits32, without branches
 }
-__device__ __forceinline__ int32_t residual64_first(int32_t acc, const Residual64& q) { return (int32_t)(((int64_t)acc * q.b + q.h) >> 32); }
+__device__ __forceinline__ int32_t residual64_first(int32_t u, const Residual64& q) { return (int32_t)(((uint64_t)(uint32_t)u * q.b + q.h) >> 32); }
+// acc + bias from sums that exceed acc by `start`, for the general form
+__device__ __forceinline__ int32_t sum_of(int32_t u, int32_t bias, uint32_t start) { return (int32_t)((uint32_t)u + ((uint32_t)bias - start)); }
+__device__ __forceinline__ v16i sums_from(uint32_t start) {
+    v16i v;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[e] = (int)start;
+    return v;
+}
 // The residual term round(b_r r / 2^c_r) takes one 24-bit multiply-add under these conditions.
 __device__ __forceinline__ bool residual_term_24(Dyadic d) { return d.b >= 1 && d.b < (1 << 23) && d.c >= 1 && d.c <= 30; }
 

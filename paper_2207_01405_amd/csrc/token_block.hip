@@ -104,8 +104,8 @@ __global__ __launch_bounds__(256) void table_kernel(TableJobs J) {
         // |acc| <= 2^14 K.  A term of up to 2^30 is asked for here, once per channel, so that its sum with the residual's needs
         // no saturating addition there (the longer instruction costs 0.6 % of a forward: DeiT-S batch 128 1216 -> 1223 us)
         const int64_t sum = (bias < 0 ? -(int64_t)bias : (int64_t)bias) + ((int64_t)J.arg[blockIdx.y] << 14);
-        const bool fits = residual64_takes(b, c) && sum * b < (int64_t)1 << (30 + c);
-        e = v4i{fits ? q.b : 0, 0, (int32_t)(uint32_t)q.h, (int32_t)(q.h >> 32)};
+        const bool fits = dyadic_fits32(b, c) && sum * b < (int64_t)1 << (30 + c);
+        e = v4i{fits ? (int32_t)q.b : 0, 0, (int32_t)(uint32_t)q.h, (int32_t)(q.h >> 32)};
     } else {
         e = v4i{1, 0, 0, 0};
         if (c >= 1 && c <= 24 && b >= 1 && b < (1 << ((c - 1) & 31))) {
@@ -129,8 +129,11 @@ template <bool ACCA, bool AA> __device__ __forceinline__ void mfma(v16i& acc, co
     else if constexpr (AA) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(acc) : "a"(a), "v"(b));
     else asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
-template <bool AA> __device__ __forceinline__ void mfma_first(v16i& acc, const v4i& a, const v4i& b) {      // ... on a zero accumulator
-    if constexpr (AA) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0" : "=&v"(acc) : "a"(a), "v"(b));
+// ... on a zero accumulator, or (RES) on one of kSumStart
+template <bool AA, bool RES = false> __device__ __forceinline__ void mfma_first(v16i& acc, const v4i& a, const v4i& b) {
+    static_assert(kSumStart == 0x40000000u, "2.0 below");
+    if constexpr (AA && RES) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 2.0" : "=&v"(acc) : "a"(a), "v"(b));
+    else if constexpr (AA) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0" : "=&v"(acc) : "a"(a), "v"(b));
     else asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
 }
 
@@ -332,7 +335,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int tok = min(32 * tt + (perm ? 16 * lg + 4 * d : 8 * d + 4 * lg) + r, rows - 1);
-                o[r] = (uint32_t)clamp8_64(rnd_shift64(a[4 * d + r] + bias, b, c) + rnd_shift64(res[(m0 + tok) * C + ch], rr.b, rr.c));
+                o[r] = (uint32_t)clamp8_64(rnd_shift64(sum_of(a[4 * d + r], bias, kSumStart), b, c) + rnd_shift64(res[(m0 + tok) * C + ch], rr.b, rr.c));
             }
             w[d] = pack4(o, std::true_type());
         }
@@ -472,7 +475,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     auto cst_at = [&](int b, int row) __attribute__((always_inline)) -> v4i { return *reinterpret_cast<const v4i*>(set_at(b) + SETW + 16 * row); };
     auto as_rq = [](const v4i& v) __attribute__((always_inline)) -> Rq { return Rq{v[0], v[1], v[2], v[3]}; };
     auto as_rq64 = [](const v4i& v) __attribute__((always_inline)) -> Rq64 {
-        Rq64 q{v[0], (int64_t)(((uint64_t)(uint32_t)v[3] << 32) | (uint32_t)v[2])};
+        Rq64 q{(uint32_t)v[0], ((uint64_t)(uint32_t)v[3] << 32) | (uint32_t)v[2]};
         pin(q.h);
         return q;
     };
@@ -525,7 +528,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
             stream(ic<PT>(), ic<TT>(), set_at(b) + wn * 32 * C, ic<WNG * 32 * C>(), std::bool_constant<!last>(),
                 [&](auto p_c, auto t_c, auto ks_c, const v4i& f) __attribute__((always_inline)) {
                     constexpr int par = (s * PT + decltype(p_c)::value) & 1, t = decltype(t_c)::value, ks = decltype(ks_c)::value;
-                    if constexpr (ks == 0) mfma_first<true>(pa[par][t], ar[t][ks], f); else mfma<false, true>(pa[par][t], ar[t][ks], f);
+                    if constexpr (ks == 0) mfma_first<true, true>(pa[par][t], ar[t][ks], f); else mfma<false, true>(pa[par][t], ar[t][ks], f);
                 },
                 [&](auto m_c) __attribute__((always_inline)) {
                     constexpr int m = decltype(m_c)::value, p = m / NMT, mt = m % NMT, g = s * PT + p;
@@ -576,7 +579,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
 #pragma unroll
         for (int j = 0; j < 3; ++j)
 #pragma unroll
-            for (int t = 0; t < TT; ++t) { acc[j][t] = v16i{}; asm volatile("" : "+a"(acc[j][t])); }
+            for (int t = 0; t < TT; ++t) { acc[j][t] = sums_from(kSumStart); asm volatile("" : "+a"(acc[j][t])); }
         const int8_t* f1w0 = set_at(0) + wn1 * N1 * 32 * C;
         const int8_t* f1w1 = set_at(1) + wn1 * N1 * 32 * C;
         first_frags(f1w1);

@@ -1,4 +1,4 @@
-"""Residual layers at the edges of the 64-bit multiply-add by b 2^(32-c): it takes b < 2^(c-1) and c <= 31, anything else goes
+"""Residual layers at the edges of the 64-bit multiply-add by b 2^(32-c): it takes b <= 2^c and c <= 31, anything else goes
 through general 64-bit arithmetic.  Whole numbers, compared for equality with the oracle."""
 import numpy as np
 import pytest
@@ -12,11 +12,13 @@ PAIRS = [(1, 1), (1, 2), (2 ** 14 - 1, 15), (2 ** 14, 15), (2 ** 15, 15), (2 ** 
          (2 ** 31 - 1, 31), (2 ** 31 - 1, 32), (20011, 46)]
 
 
-def _constants(n, rng):
-    """Every pair on some channels, biases over the whole int32 range."""
+def _constants(n, K, rng):
+    """Every pair on some channels; biases small, up to 2^30, and as far as the sum of the largest products stays an int32."""
     b, c = (np.array([PAIRS[j % len(PAIRS)][k] for j in range(n)], np.int32) for k in (0, 1))
     bias = rng.integers(-2 ** 30, 2 ** 30, size=n).astype(np.int32)
     bias[rng.random(n) < 0.5] >>= 18
+    end = 2 ** 31 - 1 - 2 ** 14 * K
+    bias[0::5], bias[1::5] = end, -end
     return b, c, bias
 
 
@@ -30,7 +32,7 @@ def test_dense(ivit, M, N, K, kernel, rounding, uniform):
     x, w, res = (rng.integers(-128, 128, size=s).astype(np.int8) for s in ((M, K), (N, K), (M, N)))
     rows = np.unique(np.linspace(0, M - 1, 60).astype(int))
     dev = lambda a: torch.from_numpy(a).cuda()
-    b, c, bias = _constants(N, rng)
+    b, c, bias = _constants(N, K, rng)
     for pair in (PAIRS if uniform else PAIRS[:1]):
         if uniform:
             b[:], c[:] = pair
@@ -39,6 +41,47 @@ def test_dense(ivit, M, N, K, kernel, rounding, uniform):
         want = orc.linear_requant(x[rows], w, bias, b, c, residual=res[rows], res_rq=(20011, 15), floor_shift=rounding == "floor")
         got = y.cpu().numpy()[rows]
         assert np.array_equal(got, want), "%s: %d of %d differ" % (pair, (got != want).sum(), got.size)
+
+
+# pairs of the residual itself: the 24-bit form, 64-bit multiply-adds up to b = 2^c and c = 31, general arithmetic
+@pytest.mark.parametrize("res_rq", [(2 ** 23 - 1, 30), (2 ** 23 - 1, 3), (2 ** 23, 24), (2 ** 23, 22), (2 ** 30, 30), (2 ** 31 - 1, 31), (20011, 31), (20011, 33)])
+@pytest.mark.parametrize("M,N,K,kernel", [(130, 130, 144, None), (1200, 600, 144, None), (300, 384, 384, "reg_stationary"), (300, 384, 1536, "reg_stationary"),
+                                          (700, 256, 512, "big_tiles")])
+@pytest.mark.parametrize("rounding", ["nearest", "floor"])
+def test_residual_pairs(ivit, M, N, K, kernel, res_rq, rounding):
+    import torch
+    rng = np.random.default_rng(M + N + K)
+    x, w, res = (rng.integers(-128, 128, size=s).astype(np.int8) for s in ((M, K), (N, K), (M, N)))
+    res[0], res[1] = 127, -128
+    b, c = np.full(N, 20011, np.int32), np.full(N, 26, np.int32)
+    bias = rng.integers(-2 ** 18, 2 ** 18, size=N).astype(np.int32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    y = torch.empty((M, N), dtype=torch.int8, device="cuda")
+    ivit.ivit_linear_requant(dev(x), dev(w), dev(bias), dev(b), dev(c), y, residual=dev(res), res_rq=res_rq, kernel=kernel, rounding=rounding)
+    rows = np.unique(np.r_[1, np.linspace(0, M - 1, 100).astype(int)])
+    want = orc.linear_requant(x[rows], w, bias, b, c, residual=res[rows], res_rq=res_rq, floor_shift=rounding == "floor")
+    got = y.cpu().numpy()[rows]
+    assert np.array_equal(got, want), "%d of %d differ" % ((got != want).sum(), got.size)
+
+
+@pytest.mark.parametrize("M,N,kernel", [(3, 40, None), (1200, 600, None), (300, 128, "big_tiles")])
+@pytest.mark.parametrize("pair", PAIRS)
+def test_longest_rows(ivit, M, N, kernel, pair):
+    """K = 65536: products that sum up to 2^30, the bias beside them to the ends of int32."""
+    import torch
+    K = 65536
+    x, w = torch.full((M, K), -128, dtype=torch.int8), torch.full((N, K), -128, dtype=torch.int8)
+    w[1::2] = 127
+    x[1::3, ::2] = 0
+    total = x[:3].long() @ w[:2].long().T                        # rows of three kinds, channels of two
+    bias = torch.tensor([2 ** 31 - 1 - 2 ** 30, -2 ** 31 + 127 * 128 * K], dtype=torch.int32).repeat(N // 2)
+    b, c = (torch.full((N,), v, dtype=torch.int32) for v in pair)
+    res = torch.arange(M * N, dtype=torch.int32).to(torch.int8).view(M, N)
+    y = torch.empty((M, N), dtype=torch.int8, device="cuda")
+    ivit.ivit_linear_requant(x.cuda(), w.cuda(), bias.cuda(), b.cuda(), c.cuda(), y, residual=res.cuda(), res_rq=(20011, 15), kernel=kernel)
+    v = total.repeat(-(-M // 3), N // 2)[:M] + bias.long()
+    want = ((v * pair[0] + (1 << (pair[1] - 1))) >> pair[1]) + ((res.long() * 20011 + (1 << 14)) >> 15)
+    assert torch.equal(y.cpu().long(), want.clamp(-127, 127))
 
 
 @pytest.mark.parametrize("C,H,F", [(96, 3, 384), (192, 3, 768), (384, 6, 1536)])
