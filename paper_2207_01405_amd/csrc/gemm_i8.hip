@@ -4,6 +4,7 @@
 // fit LDS, and the choice between all Dense kernels (launch_linear, at the end).
 #include "ivit_kernels.hpp"
 #include "linear_rows.hpp"
+#include "residual_pair.hpp"
 #include <algorithm>
 #include <type_traits>
 
@@ -490,6 +491,14 @@ hipError_t launch_linear(hipStream_t s, const LinearArgs& a) {
             if (hipError_t e = launch_linear(s, part)) return e;
         }
         return hipSuccess;
+    }
+    if (a.residual && (a.res_rq.b >= 1 << 23 || a.res_rq.c > 30)) {
+        const ResidualPair p = residual_pair(a.res_rq.b, a.res_rq.c, a.floor_shift ? 0 : 1);
+        if (p.c != a.res_rq.c) {
+            LinearArgs same = a;
+            same.res_rq = Dyadic{p.b, p.c};
+            return launch_linear(s, same);
+        }
     }
     GemmParams P;
     P.x = a.x; P.w = a.w; P.bias = a.bias; P.rq_b = a.rq_b; P.rq_c = a.rq_c;
