@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
         Residual64 q;
         bool ok = residual64_of(q, b, c, bias, P.rnd);
         // (the 128 must not carry a result out of int32: it is at most 2^30 for b < 2^(c-1), and |acc| at most 2^30)
-        if (EPI == EPI_GELU) ok = ok && (b < (1 << ((c - 1) & 31)) || (bias < 0x3fffff00 && bias > -0x3fffff00));
+        if (EPI == EPI_GELU) ok &= (b < (1 << ((c - 1) & 31))) | ((uint32_t)bias + 0x3fffff00u < 0x7ffffe00u);
         cst[ch] = v4i{ok ? (int32_t)q.b : 0, 0, (int32_t)(uint32_t)q.h, (int32_t)((uint32_t)(q.h >> 32) + (EPI == EPI_GELU ? 128u : 0u))};
     }
 
