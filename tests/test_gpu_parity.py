@@ -253,7 +253,7 @@ LIN_SHAPES = [(0, 64, 64), (1, 1, 16), (5, 7, 80), (65, 192, 64), (130, 40, 256)
 
 @pytest.fixture(params=[None, "many_rows"])
 def dense_path(request):
-    """Shapes with few rows take small streamed tiles; "many_rows" (an option of ivit_linear_requant_ex) puts them on the
+    """Shapes with few rows take the kernel for few rows or small streamed tiles; "many_rows" (an option of ivit_linear_requant_ex) puts them on the
     kernel with a weight slab in LDS or, where that does not take them, on the largest streamed tiles, so that the small
     test shapes exercise both.  None calls ivit_linear_requant itself."""
     return request.param

@@ -60,8 +60,8 @@ def _dense_params(rng, N, K, regime):
 
 @pytest.fixture(params=[None, "many_rows"])
 def dense_path(request):
-    """Few-row shapes take small streamed tiles; "many_rows" (an option of ivit_linear_requant_ex) puts them on the kernel
-    with a weight slab in LDS or on the largest streamed tiles, so both see the random shapes."""
+    """Almost all of these shapes take the kernel for few rows; "many_rows" (an option of ivit_linear_requant_ex) puts them on the
+    kernel with a weight slab in LDS or on the largest streamed tiles, so both see the random shapes."""
     return request.param
 
 

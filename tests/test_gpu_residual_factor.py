@@ -23,7 +23,7 @@ def _constants(n, K, rng):
 
 
 @pytest.mark.parametrize("uniform", [True, False])                 # a workgroup with one pair everywhere, or with all of them
-@pytest.mark.parametrize("M,N,K,kernel", [(130, 130, 144, None), (300, 384, 384, "reg_stationary"), (300, 256, 768, "reg_stationary"),
+@pytest.mark.parametrize("M,N,K,kernel", [(130, 130, 144, None), (1200, 600, 144, None), (300, 384, 384, "reg_stationary"), (300, 256, 768, "reg_stationary"),
                                           (300, 384, 1536, "reg_stationary"), (700, 256, 512, "big_tiles"), (40000, 256, 2304, "big_tiles")])
 @pytest.mark.parametrize("rounding", ["nearest", "floor"])
 def test_dense(ivit, M, N, K, kernel, rounding, uniform):

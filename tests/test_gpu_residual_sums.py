@@ -13,9 +13,9 @@ from paper_2207_01405_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# (rows, N, K, kernel): streamed tiles of each size, weight slab, weights in registers, K split, big tiles alone and with
+# (rows, N, K, kernel): few rows, streamed tiles of each size, weight slab, weights in registers, K split, big tiles alone and with
 # the epilogue inside the next tile's k-loop
-LAYERS = [(130, 130, 144, None), (5000, 601, 144, None), (9000, 1017, 144, None), (333, 208, 96, "many_rows"),
+LAYERS = [(130, 130, 144, None), (1200, 600, 144, None), (5000, 601, 144, None), (9000, 1017, 144, None), (333, 208, 96, "many_rows"),
           (300, 384, 384, "reg_stationary"), (300, 256, 768, "reg_stationary"), (300, 384, 1536, "reg_stationary"),
           (700, 256, 512, "big_tiles"), (40000, 256, 2304, "big_tiles")]
 

@@ -1,8 +1,9 @@
 """The Dense kernel for any shape (gemm_st.hip) at the edges of its tiles, stages and stores, against the oracle.
 
-Shapes: one row and one channel up to a few tiles; K from one 16-byte piece over partial stages to more stages than buffers;
-N that is no multiple of 16, 8 or 4 (stores at any alignment, byte stores at the end of a row).  The two larger tiles are
-reached through shapes with enough 64 x 64 tiles that no other kernel takes (N % 16 != 0).  Results are whole numbers.
+Shapes: one row or one channel up to a few tiles; K from one 16-byte piece over partial stages to more stages than buffers;
+N that is no multiple of 16, 8 or 4 (stores at any alignment, byte stores at the end of a row).  The smallest tile is reached with
+more 32 x 32 tiles than the kernel for few rows takes (_smallest_tile looks), the two larger ones through shapes with enough
+64 x 64 tiles that no other kernel takes (N % 16 != 0).  Results are whole numbers.
 """
 import numpy as np
 import pytest
@@ -12,9 +13,25 @@ from paper_2207_01405_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-SMALL = [(1, 1, 16), (63, 7, 32), (64, 64, 48), (65, 72, 112), (129, 15, 128), (130, 130, 144), (67, 24, 256), (200, 1000, 400),
-         (31, 65, 512), (197, 250, 1552), (300, 128, 3072)]
+SMALL = [(16500, 1, 16), (17001, 7, 32), (1, 16500, 48), (63, 9000, 64), (5500, 72, 112), (17000, 15, 128), (4100, 130, 144), (2000, 280, 256),
+         (200, 2500, 400), (1030, 513, 512), (67, 2900, 784), (197, 1200, 1552), (300, 900, 3072)]
 LARGE = [(5000, 601, 144), (2600, 1400, 1040), (13001, 520, 112), (7000, 1017, 528)]
+
+
+def _cus():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def _smallest_tile(M, N, K):
+    """More 32 x 32 tiles than gemm_kq.hip takes, few enough 64 x 64 tiles for the smallest tile of this kernel."""
+    cus = _cus()
+    return -(-M // 32) * -(-N // 32) > cus * (1 if K > 768 else 2) and 2 * (-(-M // 64) * -(-N // 64)) <= 5 * cus
+
+
+def _rows_of(M, step):
+    """Rows the oracle is asked for: the first and last tiles and some between."""
+    return np.unique(np.concatenate([np.arange(min(M, 140)), np.arange(max(M - 140, 0), M), np.arange(0, M, step)]))
 
 
 def _case(M, N, K, epi, regime):
@@ -53,9 +70,35 @@ def _run(ivit, args, kw, M, N, **more):
 @pytest.mark.parametrize("epi", ["plain", "residual", "gelu"])
 @pytest.mark.parametrize("regime,rounding", [("as drawn", "nearest"), ("general", "floor"), ("no bias", "floor")])
 def test_edges(ivit, M, N, K, epi, regime, rounding):
+    assert _smallest_tile(M, N, K)
     host, kw_o, dev, kw_g = _case(M, N, K, epi, regime)
     got = _run(ivit, dev, kw_g, M, N, rounding=rounding)
-    assert np.array_equal(got, orc.linear_requant(*host, floor_shift=(rounding == "floor"), **kw_o))
+    rows = _rows_of(M, 61)
+    if epi == "residual":
+        kw_o["residual"] = kw_o["residual"][rows]
+    assert np.array_equal(got[rows], orc.linear_requant(host[0][rows], *host[1:], floor_shift=(rounding == "floor"), **kw_o))
+
+
+# sums up to the ends of int32 at pairs up to b = 2^c: with ShiftGELU a result is an index of 0 .. 255
+@pytest.mark.parametrize("pair", [(1, 1), (2 ** 19 - 1, 20), (2 ** 19, 20), (2 ** 20, 20), (2 ** 30 - 1, 31), (2 ** 31 - 1, 31), (20011, 40)])
+@pytest.mark.parametrize("epi", ["plain", "gelu"])
+@pytest.mark.parametrize("rounding", ["nearest", "floor"])
+def test_largest_sums(ivit, pair, epi, rounding):
+    import torch
+    M, N, K = 1030, 520, 144
+    assert _smallest_tile(M, N, K)
+    rng = np.random.default_rng(pair[1])
+    x, w = rng.integers(-128, 128, size=(M, K)).astype(np.int8), rng.integers(0, 3, size=(N, K)).astype(np.int8)
+    x[0], x[1] = 127, -128                                   # no negative weight: the extremes of every channel
+    total = w.astype(np.int64).sum(axis=1)
+    bias = np.where(np.arange(N) % 2, 128 * total - 2 ** 31, 2 ** 31 - 1 - 127 * total).astype(np.int32)
+    bias[::3] = rng.integers(-2 ** 12, 2 ** 12, size=len(bias[::3]))
+    bias[1::6], bias[4::6] = 0x3fffff00, -0x3fffff00
+    b, c = np.full(N, pair[0], np.int32), np.full(N, pair[1], np.int32)
+    kw = dict(gelu=synth.shift_params(32), gelu_rq=(24171, 21)) if epi == "gelu" else {}
+    got = _run(ivit, tuple(torch.from_numpy(a).cuda() for a in (x, w, bias, b, c)), kw, M, N, rounding=rounding)
+    rows = _rows_of(M, 7)
+    assert np.array_equal(got[rows], orc.linear_requant(x[rows], w, bias, b, c, floor_shift=rounding == "floor", **kw))
 
 
 @pytest.mark.parametrize("M,N,K", LARGE)
@@ -64,17 +107,19 @@ def test_edges(ivit, M, N, K, epi, regime, rounding):
 def test_larger_tiles(ivit, M, N, K, epi, regime):
     host, kw_o, dev, kw_g = _case(M, N, K, epi, regime)
     got = _run(ivit, dev, kw_g, M, N)
-    # the oracle on the first and last tiles and on rows spread over the rest
-    rows = np.unique(np.concatenate([np.arange(0, 140), np.arange(M - 140, M), np.arange(0, M, 61)]))
+    rows = _rows_of(M, 61)
     if epi == "residual":
         kw_o["residual"] = kw_o["residual"][rows]
     assert np.array_equal(got[rows], orc.linear_requant(host[0][rows], *host[1:], **kw_o))
 
 
-@pytest.mark.parametrize("C,H,F", [(64, 2, 256), (96, 3, 144), (128, 4, 208), (160, 5, 64), (384, 6, 1536), (416, 13, 400), (736, 23, 272), (768, 12, 3072)])
-@pytest.mark.parametrize("B,T", [(1, 1), (3, 21), (5, 13), (2, 65)])
+# QKV, or QKV and the first MLP layer, past the kernel for few rows; widths of both forms (to 384 and to 768 bytes a row)
+@pytest.mark.parametrize("C,H,F,B,T", [(64, 2, 256, 43, 65), (128, 4, 400, 56, 25), (160, 5, 464, 18, 65), (384, 6, 1536, 8, 59), (416, 13, 1232, 7, 65),
+                                       (736, 23, 2000, 4, 65), (768, 12, 3072, 2, 130)])
 def test_layernorm_inside_the_dense_kernel(ivit, C, H, F, B, T):
     """A block whose I-LayerNorms run in the kernels of the QKV and the first MLP layer, against the oracle."""
+    for n in (3 * C, F):
+        assert _smallest_tile(B * T, n, C) and -(-B * T // 64) * -(-n // 64) <= 2 * _cus(), n
     import torch
     d = dict(B=B, T=T, C=C, H=H, F=F)
     p = synth.make_block(dict(T=T, C=C, H=H, F=F, seed=C + F, i0="fixed", rel_bias=False), 0)

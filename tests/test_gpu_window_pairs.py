@@ -1,9 +1,10 @@
-"""7 x 7 windows in numbers that give every wavefront whole windows, against the same windows in parts too small for that form (which
-the other tests hold against the oracle): odd and even heads, windows that leave the last pass partly empty, tables with entries
+"""7 x 7 windows in numbers that give every wavefront whole windows, against the same windows in parts too small for that form and,
+some of them, against the oracle: odd and even heads, windows that leave the last pass partly empty, tables with entries
 outside the image, masks with and without a bias, rows with everything masked, one key that has the whole sum.  Equality."""
 import numpy as np
 import pytest
 
+import oracle as orc
 from paper_2207_01405_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -40,6 +41,14 @@ def test_parts_equal_whole(ivit, H, more, kind, i0, sigma):
             n = min(part, B - at)
             ivit.ivit_window_attention(x[at * T:(at + n) * T], o[at * T:(at + n) * T], dict(B=n, T=T, C=C, H=H, F=C), (20011, 23),
                                        synth.shift_params(i0), (20011, 22), b, ix, mask=m, rounding="floor" if more else "nearest")
+    # the oracle, window by window: those of the first image and of the last, and some between
+    got, last = out[0].cpu().numpy(), n_win * T - 1
+    for w in sorted({0, 1, 2, 3, B - 1, B - 2, B - 3, *range(5, B, max(B // 6, 1))}):
+        rows = np.arange(w * T, (w + 1) * T) if index is None else w // n_win * n_win * T + np.minimum(index[w % n_win].astype(np.int64), last)
+        want = orc.attention(qkv[rows], dict(B=1, T=T, C=C, H=H, F=C), (20011, 23), synth.shift_params(i0), (20011, 22), bias,
+                             mask=None if mask is None else mask[w % n_win:w % n_win + 1], floor_shift=bool(more))
+        sure = rows % (n_win * T) != last if index is not None else np.ones(T, bool)       # (several tokens of a table write the last row)
+        assert np.array_equal(got[rows][sure], want[sure]), "window %d" % w
     if index is not None:                                        # (several tokens write the last row, some rows are written by none)
         rows = [r for r in range(B * T) if r % (n_win * T) not in (n_win * T - 1,)]
         out = [o[rows] for o in out]
