@@ -678,8 +678,8 @@ __device__ __forceinline__ int32_t wave_allreduce(int32_t v, OP op) {
 //  - the 49th query, which would have a tile of its own, has its 49 scores one to a lane: a third of a tile's instructions.
 // Bound by the vector ALU and the addresses of the loads (one that touches 16 rows costs about 27 cycles whatever its width), about
 // equally.  (Two neighbouring heads to a wavefront, 16 bytes a lane and a load, halve the loads but leave fewer wavefronts: 2048
-// windows x 6 heads 24.0 us, 512 x 12 14.9.)  A wavefront per query tile against this, without and with a mask: 8192 x 3 55.3 -> 42.4
-// and 66.0 -> 54.9 us, 2048 x 6 30.0 -> 23.2 and 38.5 -> 32.1, 512 x 12 17.9 -> 14.2 and 22.5 -> 19.8.
+// windows x 6 heads 24.0 against 23.2 us, 512 x 12 14.9 against 14.2.)  A wavefront per query tile against this, without and with a mask: 2048
+// x 3 13.7 -> 11.1 and 18.3 -> 16.3 us, 1024 x 6 13.9 -> 11.7 and 18.9 -> 17.0, 512 x 12 15.1 -> 13.2 and 19.8 -> 18.4.
 constexpr int WIN_T = 49, WIN_WAVES = 4;
 template <bool MASK>
 __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention_kernel(
@@ -854,16 +854,19 @@ static bool narrow_of(Dyadic d, int rnd, Narrow& n) {
 }
 
 // The one-wavefront form from 9 (window, head) pairs per CU on: below, a wavefront per query tile finishes a pair sooner.  Without
-// and with a mask, us against a wavefront per query tile: 6 per CU 7.4 : 7.4 and 10.2 : 9.4; 9 per CU 8.5 : 9.4; 12 per CU 8.8 : 10.0 and 12.3 :
-// 12.5; 24 per CU 12.9 : 16.4 and 18.4 : 21.2.  The rows of an image are counted in 32 bits there.
+// and with a mask, us against a wavefront per query tile, 3 heads and 12: 4 per CU 5.7 : 4.4 and 8.1 : 5.7, 6.6 : 4.4 and 8.8 : 5.7;
+// 7.5 per CU 6.1 : 6.4 and 8.3 : 8.0, 6.8 : 6.5 and 9.0 : 8.1; 9 per CU 7.0 : 8.4 and 9.7 : 10.6, 8.0 : 8.7 and 10.7 : 10.9; 12 per CU
+// 7.3 : 8.5 and 10.0 : 10.7, 8.3 : 8.8 and 10.9 : 11.0; 24 per CU 11.1 : 13.7 and 16.3 : 18.3, 13.2 : 15.1 and 18.4 : 19.8.  The rows of
+// an image are counted in 32 bits there.
 static bool window_takes(const AttentionArgs& a) {
     const int64_t rows = a.tok_index ? (int64_t)a.n_win * WIN_T : WIN_T;
     return a.T == WIN_T && (int64_t)a.B * a.H >= 9 * (int64_t)num_cus() && rows * 3 * a.C < (int64_t)1 << 31;
 }
 
 static void launch_window(hipStream_t s, const AttentionArgs& a, Div24 dv, Narrow nqk, Narrow npv) {
-    // as many passes as six workgroups per CU need (8192 x 3 takes 47.6 us with four, 43.8 with five, 43.2 with six), and no more
-    // workgroups than share the windows evenly.  (Of eight wavefronts, three per CU: 45.1 us.)
+    // As many passes as six workgroups per CU need, and no more workgroups than share the windows evenly.  With five and with six,
+    // without and with a mask (with one, five are resident at a time): 8192 x 3 34.4 -> 33.7 and 48.9 -> 47.9 us, 2048 x 6 22.5 -> 20.9
+    // and 33.2 -> 28.5, 512 x 12 13.6 -> 13.2 and 19.2 -> 18.5; others the same.  (Of eight wavefronts, three per CU, were slower.)
     const int64_t most = std::max<int64_t>(1, 6 * (int64_t)num_cus() / a.H);
     const int64_t passes = (a.B + WIN_WAVES * most - 1) / (WIN_WAVES * most);
     const int grid = a.H * (int)((a.B + WIN_WAVES * passes - 1) / (WIN_WAVES * passes));

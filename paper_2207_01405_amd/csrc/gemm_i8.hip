@@ -509,13 +509,14 @@ hipError_t launch_linear(hipStream_t s, const LinearArgs& a) {
     if (a.kernel == LINEAR_AUTO && linear_kq_takes(a)) return launch_linear_kq(s, a);
     if (a.ln_g) return launch_linear_st(s, a);
     if (a.kernel == LINEAR_AUTO) {
-        // Up to a few 64 x 64 tiles per CU, and more than gemm_kq.hip takes: streamed tiles (gemm_st.hip).  The kernels below keep weights in registers or LDS
-        // or use large tiles, which pays once a workgroup has many rows to apply them to.  Measured with 256 CUs, time with
-        // streamed tiles against the kernel it replaces: rows x N = 1576 x 2304 (900 tiles), K = 768: 7.4 against 9.5 us;
-        // 6000 x 768 (1128): 8.8 against 10.5; 4100 x 2304 (2340): 15.2 against 14.0.  With a residual 4100 x 768 (780),
-        // K = 768: 9.1 against 10.5; 6272 x 768 (1176): 14.0 against 12.2; K = 3072, 1576 rows (300): 10.4 against 25.0,
-        // 6000 rows (1128): 27.1 against 27.7, 25216 rows (4728): 80.6 against 77.6.  K = 192 without one, 4100 x 768 (780):
-        // 5.8 against 6.3; 12544 x 576 (1764): 8.6 against 8.1.
+        // Up to a few 64 x 64 tiles per CU, and more than gemm_kq.hip takes: streamed tiles (gemm_st.hip).  The kernels below
+        // keep weights in registers or LDS or use large tiles, which pays once a workgroup has many rows to apply them to.
+        // Measured with 256 CUs, time with streamed tiles of the size that the rule there chooses against the kernel they
+        // replace: rows x N = 1576 x 2304 (900 tiles), K = 768: 6.0 against 8.6 us; 6000 x 768 (1128): 7.7 against 9.5;
+        // 9472 x 768 (1776): 9.0 against 10.7; 4100 x 2304 (2340): 14.2 against 12.1; K = 384, 6304 x 1152 (1782): 7.1 against 8.0;
+        // 9000 x 1152 (2538): 10.8 against 9.4.  With a residual, K = 768, 5376 x 768 (1008): 7.7 against 9.4; 6272 x 768 (1176):
+        // 12.0 against 10.7; K = 3072, 6000 rows (1128): 23.8 against 24.9, 25216 rows (4728): 73.5 against 70.8.  K = 192
+        // without one, 4100 x 768 (780): 4.4 against 5.3; 12544 x 576 (1764): 6.2 against 7.3 (with 128 x 64 tiles 7.2).
         const int64_t limit = !a.residual && a.K >= 384 && a.K < 1536 ? 7 : 4;
         if (((a.M + 63) / 64) * ((a.N + 63) / 64) <= limit * num_cus()) return launch_linear_st(s, a);
     }

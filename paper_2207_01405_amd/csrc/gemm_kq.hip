@@ -11,8 +11,8 @@
 //
 // What bounds it is the chain of latencies of a launch with one or two workgroups per CU; a kernel that only stores takes
 // 2.3 us in the same loop.  Against 64 x 64 tiles whose wavefronts meet at every 128 bytes of K and finish 16 results a lane:
-// 197 x 384 x 384 with a residual 3.6 -> 2.6 us, 197 x 384 x 1536 5.4 -> 3.2, 197 x 768 x 3072 8.0 -> 4.2; forwards: DeiT-S batch 1 357 ->
-// 292 us.
+// 197 x 384 x 384 with a residual 3.9 -> 2.9 us, 197 x 384 x 1536 5.4 -> 3.5, 197 x 768 x 3072 7.7 -> 4.4 (launches of a graph); forwards:
+// DeiT-S batch 1 357 -> 292 us.
 #include "linear_rows.hpp"
 #include "regst_common.hpp"
 
@@ -280,10 +280,11 @@ hipError_t launch_k(hipStream_t s, KqParams& P) {
 
 // Up to two tiles per CU; one where the rows are so long that a workgroup's operands fill a CU's LDS.  Beyond that the larger
 // tiles of gemm_st.hip, which move half the bytes per product, are faster.  us with this kernel against those (rows x N,
-// tiles in brackets, 256 CUs, launches back to back): K = 384 with a residual 197 x 384 (84) 2.6 against 3.6, 1568 x 384 (588) 3.5
-// against 3.7, 3737 x 384 (1404) 5.1 against 4.3; 394 x 1152 (468) 3.1 against 3.1, 788 x 1152 (900) 3.8 against 3.3; K = 768
-// 197 x 2304 (504) 3.5 against 3.8, 392 x 3072 (1248) 6.7 against 4.8; K = 1536 197 x 384 (84) 3.2 against 5.2, 788 x 384 (300) 5.5
-// against 5.2; K = 3072 197 x 768 (168) 4.2 against 7.6, 788 x 768 (600) 10.5 against 8.0.
+// tiles in brackets, 256 CUs, launches of a graph): K = 384 with a residual 197 x 384 (84) 2.9 against 3.9, 1568 x 384 (588) 3.8
+// against 4.0, 3737 x 384 (1404) 5.5 against 4.6; without 512 x 1024 (512) 3.3 against 3.4, 788 x 1152 (900) 4.0 against 3.6; K = 768
+// 197 x 2304 (504) 3.8 against 4.0, 394 x 1280 (520) 4.2 against 4.0, 392 x 3072 (1248) 6.6 against 4.7; K = 1536 197 x 384 (84) 3.5
+// against 5.4, 500 x 512 (256) 3.8 against 5.5, 788 x 384 (300) 5.7 against 5.5; K = 3072 197 x 768 (168) 4.4 against 7.7, 320 x 768
+// (240) 4.6 against 7.7, 788 x 768 (600) 10.4 against 7.9.
 bool linear_kq_takes(const LinearArgs& a) {
     if ((a.K & 15) || a.M < 1 || a.M > (1 << 24) || (a.ln_g && (a.residual || a.K > 768))) return false;
     return ((a.M + TILE - 1) / TILE) * ((a.N + TILE - 1) / TILE) <= (a.K > 768 ? 1 : 2) * num_cus();

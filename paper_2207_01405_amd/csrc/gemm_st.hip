@@ -422,10 +422,12 @@ hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
 
 }  // namespace
 
-// Up to two of these tiles per CU the repeated normalisation takes less than the launch it saves, beyond that more.  Forwards
-// with it against without: DeiT-S batch 1 357 against 386 us, batch 4 374 against 396, ViT-B batch 1 455 against 473, Swin-S
-// batch 2 760 against 807, batch 8 873 against 881; with up to four tiles per CU ViT-B batch 4 560 against 518, Swin-S batch 8
-// 917 against 881.  With 64 x 64 tiles, twice the rows to normalise: DeiT-S batch 1 390, ViT-B batch 1 515 us.
+// Up to two of these tiles per CU the repeated normalisation takes less than the launch it saves, beyond that more (fewer rows than
+// that take the form inside gemm_kq.hip).  Forwards with it, without it and with it up to four tiles per CU: DeiT-S batch 2 266, 276 and
+// 267 us, batch 4 331, 338 and 327, batch 8 372, 374 and 409, Swin-S batch 2 627, 644 and 628, batch 4 721, 736 and 721, batch 8 801,
+// 795 and 856.  Rows of 768 bytes have lost by it since the separate layers became faster: ViT-B batch 1 340, 336 and 340, batch 2
+// 450, 419 and 450, batch 4 464, 460 and 537.  (With 64 x 64 tiles, twice the rows to normalise, it was slower: batch 1 of DeiT-S by
+// 9 %, of ViT-B by 13 %.)
 bool linear_ln_takes(const LinearArgs& a) {
     if (!a.residual && a.K <= 768 && linear_kq_takes(a)) return true;
     using TL = StTile<1, 1, 6>;
@@ -437,11 +439,11 @@ hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
     if (a.ln_g) return a.K <= 384 ? launch_tile<1, 1, 3, 3>(s, a) : launch_tile<1, 1, 3, 6>(s, a);
     // The tile grows with the number of 64 x 64 tiles: larger ones load less per multiply, smaller ones leave no CU idle and
     // have shorter chains.  Measured with 256 CUs (times with 64 x 64, 128 x 64 and 128 x 128): 1576 x 768 x 3072 (300 tiles)
-    // 10.4, 15.9 and 20.1 us; 3137 x 768 x 768 (600) 6.5, 6.6 and 7.3; 1576 x 2304 x 768 (900) 8.8, 7.4 and 7.9;
-    // 6000 x 1000 x 768 (1504) 11.7, 10.3 and 10.9; 25216 x 1000 x 768 (6304) 44, 36 and 34; with longer rows the largest
-    // tile pays earlier: 6000 x 768 x 3072 (1128) 27.2, 38.6 and 27.1, 3137 x 1000 x 3072 (800) 24.7, 24.5 and 29.3.
-    // Stages: two workgroups of 128 x 128 share a CU with two stages, one with four: 6000 x 1000 x 768 10.8 against 15.3 us;
-    // 64 x 64 with three stages against four (three workgroups per CU against two): 11.7 against 13.6 us.
+    // 10.1, 14.8 and 18.0 us; 3137 x 768 x 768 (600) 6.7, 7.2 and 9.0; 1576 x 2304 x 768 (900) 7.7, 5.9 and 7.1;
+    // 6000 x 1000 x 768 (1504) 10.2, 9.4 and 9.6; 25216 x 1000 x 768 (6304) 37, 31 and 31; with longer rows the largest
+    // tile pays earlier: 6000 x 768 x 3072 (1128) 24.8, 33.3 and 23.4 (but 3137 x 1000 x 3072 (800) 19.3, 17.7 and 20.8).
+    // Stages: two workgroups of 128 x 128 share a CU with two stages, one with four: 6000 x 1000 x 768 9.6 against 14.6 us;
+    // 64 x 64 with three stages against four (three workgroups per CU against two): 10.2 against 12.4 us.
     if (a.kernel == LINEAR_MANY_ROWS) return launch_tile<2, 2, 2, 0>(s, a);
     const int64_t tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64), cus = num_cus();
     if (2 * tiles <= 5 * cus) return launch_tile<1, 1, 3, 0>(s, a);
