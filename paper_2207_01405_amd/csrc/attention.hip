@@ -39,10 +39,14 @@ typedef int v2i_att __attribute__((ext_vector_type(2)));
 struct Narrow { int32_t lo, hi, mb, ad; };
 
 // Constants of the 24-bit IntDiv (intdiv24_up): the scale of the table's entries, 2^(M+up) as a float and modulo 2^32, and the scaled
-// sum of a row in which one key has all of it.  Formed here from `up`: as four arguments of a kernel they parted the loads of the
-// others, which a workgroup with one item waits for (100 images x 8 heads of 81 tokens with a bias 11.1 -> 11.8 us).
+// sum of a row in which one key has all of it.  Formed here, for every row, from `up`, which stands in the place of k_out in the
+// kernels' arguments (k_out is M - 23 in that form): more arguments part the loads of the others, which a workgroup with one item
+// waits for (100 images x 8 heads of 81 tokens with a bias 11.1 -> 11.8 us with four), and the constants kept take scalar registers
+// that the forms with a bias do not have.
 struct Div24 { int32_t up; float num; uint32_t num32; int32_t alone; };
-__device__ __forceinline__ Div24 div24_of(ShiftParams sm, int up) {
+__device__ __forceinline__ Div24 div24_of(ShiftParams sm) {
+    int up = sm.k_out;
+    asm volatile("" : "+s"(up));
     const int bits = sm.m_bits + up;
     return Div24{up, __uint_as_float((uint32_t)(127 + bits) << 23), (uint32_t)((uint64_t)1 << bits), sm.i0 << (sm.n_shift + up)};
 }
@@ -238,15 +242,13 @@ template <int ND> __device__ __forceinline__ void narrow_words(uint32_t (&ow)[ND
 // exceeds 2^(k_out-1), so that IntDiv is one multiply-high by the pre-shifted reciprocal.
 // TFIX: 0, or the token count known at compile time (49, the 7 x 7 windows; 197, the 14 x 14 patches with a class token):
 // every test of a key or query against T then folds, and the absent keys of the last key tile cost nothing.
-// Four workgroups per CU for masked windows of 65 to 128 tokens and 32 features: their 128 registers allow it, and a few more would
-// leave three (1200 pairs of 100 tokens 27.2 us, 34.5 with 132 registers).
 template <int D, int NKT, bool TAPS, bool BIAS, bool MASK, int FAST, int TFIX = 0>
-__global__ __launch_bounds__(ATT_THREADS, D == 32 && NKT == 8 && MASK && FAST == 2 ? 4 : 3) void attention_kernel(const int8_t* __restrict__ qkv,
+__global__ __launch_bounds__(ATT_THREADS, 3) void attention_kernel(const int8_t* __restrict__ qkv,
                                                         const int8_t* __restrict__ rel_bias,
                                                         const int8_t* __restrict__ mask, FastDiv n_mask,
                                                         const int32_t* __restrict__ tok_index, FastDiv n_win,
                                                         int8_t* __restrict__ o, int n_items, FastDiv split_d, int T_arg, int C, FastDiv H,
-                                                        Dyadic qk, ShiftParams sm, Dyadic pv, Narrow nqk, Narrow npv, int rnd, int up,
+                                                        Dyadic qk, ShiftParams sm, Dyadic pv, Narrow nqk, Narrow npv, int rnd,
                                                         int8_t* __restrict__ tap_s, int8_t* __restrict__ tap_p) {
     const int T = TFIX ? TFIX : T_arg, split = (int)split_d.d;
     constexpr int KROW = D + 16;                  // K row pitch (bytes)
@@ -266,7 +268,8 @@ __global__ __launch_bounds__(ATT_THREADS, D == 32 && NKT == 8 && MASK && FAST ==
     // (with a bias it holds a word of it per key tile: beyond 8 tiles that costs a workgroup per CU or spills, and the scores are
     // taken tile by tile instead, between the 24-bit requantisations and IntDiv: 1200 pairs of 196 tokens and 32 features 70 us
     // otherwise)
-    constexpr bool DIV24 = FAST == 2 && !TAPS, N24 = DIV24 && !(BIAS && NKT > 8);
+    // (and with a mask, 64 features and more than 208 tokens without that IntDiv: 1200 pairs of 256 tokens 190 us with it, 180 without)
+    constexpr bool DIV24 = FAST == 2 && !TAPS && !(MASK && D == 64 && NKT == 16), N24 = DIV24 && !(BIAS && NKT > 8);
     using Entry = std::conditional_t<N24, uint16_t, uint32_t>;
     __shared__ Entry lut[NLUT];
 
@@ -277,8 +280,9 @@ __global__ __launch_bounds__(ATT_THREADS, D == 32 && NKT == 8 && MASK && FAST ==
     // clear their rows once so that no uninitialised LDS is ever read
     for (int i = NKT * 16 * VP / 4 + tid; i < NKC * 64 * VP / 4; i += ATT_THREADS) reinterpret_cast<uint32_t*>(Vs)[i] = 0u;
 
-    const int sh = sm.m_bits - (sm.k_out - 1);
-    const uint32_t top = (1u << (sm.k_out - 1)) - 1u;
+    const int k_out = FAST == 2 ? sm.m_bits - 23 : sm.k_out;                   // (see Div24)
+    const int sh = sm.m_bits - (k_out - 1);
+    const uint32_t top = (1u << (k_out - 1)) - 1u;
     const int nqt = (T + 15) >> 4;
     const int nfull = T >> 4;                      // key tiles whose 16 keys all exist
 
@@ -386,7 +390,7 @@ __global__ __launch_bounds__(ATT_THREADS, D == 32 && NKT == 8 && MASK && FAST ==
         };
         if (N24 && BIAS && ONE) load_words(qt0);   // (with K, V and Q: behind the barrier nothing is waited for any more)
         if (work == first) {                       // the table, while the first loads are in flight (visible after the barrier below)
-            for (int i = tid; i < NLUT; i += ATT_THREADS) lut[i] = N24 && MASK && i == NLUT - 1 ? (Entry)0 : (Entry)(shiftexp(-i, sm.i0, sm.n_shift) << (DIV24 ? up : 0));
+            for (int i = tid; i < NLUT; i += ATT_THREADS) lut[i] = N24 && MASK && i == NLUT - 1 ? (Entry)0 : (Entry)(shiftexp(-i, sm.i0, sm.n_shift) << (DIV24 ? sm.k_out : 0));
         }
         const uint32_t orow0 = q_row(qt0);         // output row of the first query tile (before the indices move on)
         if (work + G < n_work) {
@@ -443,19 +447,7 @@ __global__ __launch_bounds__(ATT_THREADS, D == 32 && NKT == 8 && MASK && FAST ==
             uint32_t pk[NKC * 4];
 #pragma unroll
             for (int t = 0; t < NKC * 4; ++t) pk[t] = 0u;
-            // IntDiv of the 24-bit form: the probabilities of the lane's row, four to a word, from the scaled entries and their sum
-            auto div24 = [&](int32_t sum) __attribute__((always_inline)) {
-                const uint32_t f = div_factor(sum, div24_of(sm, up));
-#pragma unroll
-                for (int t = 0; t + 4 <= NKT; t += 4) {
-                    uint32_t w[4];
-                    div_pack4(w, f, sc[t], sc[t + 1], sc[t + 2], sc[t + 3]);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) pk[t + k] = w[k];
-                }
-#pragma unroll
-                for (int t = NKT & ~3; t < NKT; ++t) pk[t] = div_pack(f, sc[t]);
-            };
+            int32_t sum;                                   // ShiftExp over the row
             // ---- requantise, add the bias, row maximum.  Lane (li, lg) holds keys 16 t + 4 lg + r.
             const int64_t tap_row = ((int64_t)item * T + qc) * T;
             // BIAS: a relative-position bias and / or the shifted-window mask.  A masked key gets -100 I_0 (the -100
@@ -497,10 +489,9 @@ __global__ __launch_bounds__(ATT_THREADS, D == 32 && NKT == 8 && MASK && FAST ==
                     if (MASK) move_down(mw);
                     mx = biased_scores<MASK>(sc, bw, mw, nqk, mask_add, nfull, left, masked);
                 }
-                // ---- ShiftExp by table, row sum, IntDiv
-                const int32_t sum = MASK && masked ? look_up<BIAS, true>(sc, lut, NLUT, mx, base, nqk, nfull, left)
-                                                   : look_up<BIAS, false>(sc, lut, NLUT, mx, base, nqk, nfull, left);
-                div24(sum);
+                // ---- ShiftExp by table, row sum
+                sum = MASK && masked ? look_up<BIAS, true>(sc, lut, NLUT, mx, base, nqk, nfull, left)
+                                     : look_up<BIAS, false>(sc, lut, NLUT, mx, base, nqk, nfull, left);
             } else {
             int32_t mx = INT32_MIN;
 #pragma unroll
@@ -541,7 +532,7 @@ __global__ __launch_bounds__(ATT_THREADS, D == 32 && NKT == 8 && MASK && FAST ==
             }
             mx = rows_allreduce(mx, [](int32_t a, int32_t b) { return max(a, b); });
             // ---- ShiftExp by table, row sum.  The byte offset 4 (max - a) of the table entry is one 24-bit multiply-add.
-            int32_t sum = 0;
+            sum = 0;
             const int32_t mx4 = 4 * mx;
             const char* lut_b = reinterpret_cast<const char*>(lut);
 #pragma unroll
@@ -577,9 +568,19 @@ __global__ __launch_bounds__(ATT_THREADS, D == 32 && NKT == 8 && MASK && FAST ==
                 if (t & 1) __builtin_amdgcn_sched_barrier(0);
             }
             sum = rows_allreduce(sum, [](int32_t a, int32_t b) { return a + b; });
+            }
             // ---- IntDiv and packing: the four keys of tile t become one word of the "B" operand
             if constexpr (DIV24) {
-                div24(sum);
+                const uint32_t f = div_factor(sum, div24_of(sm));
+#pragma unroll
+                for (int t = 0; t + 4 <= NKT; t += 4) {
+                    uint32_t w[4];
+                    div_pack4(w, f, sc[t], sc[t + 1], sc[t + 2], sc[t + 3]);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) pk[t + k] = w[k];
+                }
+#pragma unroll
+                for (int t = NKT & ~3; t < NKT; ++t) pk[t] = div_pack(f, sc[t]);
             } else {
                 const uint32_t inv = (1u << sm.m_bits) / (uint32_t)sum;
                 const uint32_t inv_hi = FAST ? inv << (32 - sh) : 0u;      // FAST: inv < 2^sh, 1 <= sh <= 31
@@ -602,9 +603,8 @@ __global__ __launch_bounds__(ATT_THREADS, D == 32 && NKT == 8 && MASK && FAST ==
                 }
                 if (!TAPS) {
 #pragma unroll
-                    for (int t = 0; t < NKT; ++t) pk[t] -= (pk[t] >> (sm.k_out - 1)) & 0x01010101u;   // bytewise min(p, 2^(k_out-1) - 1)
+                    for (int t = 0; t < NKT; ++t) pk[t] -= (pk[t] >> (k_out - 1)) & 0x01010101u;   // bytewise min(p, 2^(k_out-1) - 1)
                 }
-            }
             }
             // ---- O^T = V^T P^T : "A" = V^T rows (features), "B" = packed probabilities (keys x queries).
             // Contraction position 16 lg + 4 j + r of chunk c is key 64 c + 16 j + 4 lg + r (the layout of pk).  A
@@ -692,7 +692,7 @@ template <bool MASK>
 __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention_kernel(
     const int8_t* __restrict__ qkv, const int8_t* __restrict__ rel_bias, const int8_t* __restrict__ mask, FastDiv n_mask,
     const int32_t* __restrict__ tok_index, FastDiv n_win, int8_t* __restrict__ o, int B, int C, FastDiv H, ShiftParams sm,
-    int up, Narrow nqk, Narrow npv) {
+    Narrow nqk, Narrow npv) {
     constexpr int T = WIN_T, D = 32, NT = 4, NQ = T / 16, LAST = T - 1, nfull = T >> 4, VP = 40, NLUT = MASK ? 1024 : 512;
     static_assert(T == 16 * NQ + 1 && NQ + 1 == NT);
     __shared__ __align__(16) int8_t Vall[WIN_WAVES][NT * 16 * VP];
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention
         __builtin_memcpy(&v, table + (uint32_t)(tok * T + from), 4);
         return 16 * t + 16 <= T ? v : (uint32_t)((uint64_t)v >> min(8 * (key - from), 32));
     };
-    for (int i = tid; i < NLUT; i += 64 * WIN_WAVES) lut[i] = MASK && i == NLUT - 1 ? (uint16_t)0 : (uint16_t)(shiftexp(-i, sm.i0, sm.n_shift) << up);
+    for (int i = tid; i < NLUT; i += 64 * WIN_WAVES) lut[i] = MASK && i == NLUT - 1 ? (uint16_t)0 : (uint16_t)(shiftexp(-i, sm.i0, sm.n_shift) << sm.k_out);
     for (int i = tid; i < NT * 64; i += 64 * WIN_WAVES) {
         const int q = i / 64, l = i & 63;
         const int8_t* table = rel_bias + (int64_t)h * T * T;
@@ -806,7 +806,7 @@ __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention
             const int32_t sum = MASK && masked ? look_up<true, true>(sc, lut, NLUT, mx, 0u, nqk, nfull, left)
                                                : look_up<true, false>(sc, lut, NLUT, mx, 0u, nqk, nfull, left);
             uint32_t pk[NT];
-            div_pack4(pk, div_factor(sum, div24_of(sm, up)), sc[0], sc[1], sc[2], sc[3]);
+            div_pack4(pk, div_factor(sum, div24_of(sm)), sc[0], sc[1], sc[2], sc[3]);
             const v4i pf = {(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3]};
             v4i oacc[2];
 #pragma unroll
@@ -833,7 +833,7 @@ __global__ __launch_bounds__(64 * WIN_WAVES, MASK ? 5 : 7) void window_attention
         const int32_t mx = wave_allreduce(lane < T ? v : INT32_MIN, [](int32_t x, int32_t y) { return max(x, y); });
         int32_t e = (int32_t)lut[lane < T ? min(mx - v, NLUT - 1) : 0];
         e = lane < T ? e : 0;
-        const uint32_t f = div_factor(wave_allreduce(e, [](int32_t x, int32_t y) { return x + y; }), div24_of(sm, up));
+        const uint32_t f = div_factor(wave_allreduce(e, [](int32_t x, int32_t y) { return x + y; }), div24_of(sm));
         last_p[wv][lane] = (int8_t)(uint8_t)__umulhi(f, (uint32_t)e);
         v4i pf;
 #pragma unroll
@@ -870,7 +870,7 @@ static bool window_takes(const AttentionArgs& a) {
     return a.T == WIN_T && (int64_t)a.B * a.H >= 9 * (int64_t)num_cus() && rows * 3 * a.C < (int64_t)1 << 31;
 }
 
-static void launch_window(hipStream_t s, const AttentionArgs& a, int up, Narrow nqk, Narrow npv) {
+static void launch_window(hipStream_t s, const AttentionArgs& a, ShiftParams sm, Narrow nqk, Narrow npv) {
     // As many passes as six workgroups per CU need, and no more workgroups than share the windows evenly.  With five and with six,
     // without and with a mask (with one, five are resident at a time): 8192 x 3 34.4 -> 33.7 and 48.9 -> 47.9 us, 2048 x 6 22.5 -> 20.9
     // and 33.2 -> 28.5, 512 x 12 13.6 -> 13.2 and 19.2 -> 18.5; others the same.  (Of eight wavefronts, three per CU, were slower.)
@@ -880,7 +880,7 @@ static void launch_window(hipStream_t s, const AttentionArgs& a, int up, Narrow 
 #define IVIT_WIN(MASK_)                                                                                                              \
     hipLaunchKernelGGL((window_attention_kernel<MASK_>), dim3(grid), dim3(64 * WIN_WAVES), 0, s, a.qkv, a.rel_bias, a.mask,            \
                        FastDiv(std::max(a.n_mask, 1)), a.tok_index, FastDiv(std::max(a.n_win, 1)), a.o, a.B, a.C, FastDiv(a.H),       \
-                       a.sm, up, nqk, npv)
+                       sm, nqk, npv)
     if (a.mask) IVIT_WIN(true); else IVIT_WIN(false);
 #undef IVIT_WIN
 }
@@ -892,11 +892,12 @@ static void launch_flags(hipStream_t s, const AttentionArgs& a, int grid, int sp
     // the 24-bit forms: both requantisations and IntDiv
     const int rnd = a.floor_shift ? 0 : 1, up = intdiv24_up(a.sm.i0, a.sm.n_shift, a.sm.m_bits, a.sm.k_out);
     const bool narrow = narrow_of(a.qk_rq, rnd, nqk) && narrow_of(a.pv_rq, rnd, npv) && up >= 0;
+    const ShiftParams sm24{a.sm.i0, a.sm.n_shift, a.sm.m_bits, up};           // (see Div24)
 #define IVIT_ATT(TAPS_, BIAS_, MASK_, FAST_, TFIX_)                                                                         \
     hipLaunchKernelGGL((attention_kernel<D, NKT, TAPS_, BIAS_, MASK_, FAST_, TFIX_>), dim3(grid), dim3(ATT_THREADS), 0, s,     \
                        a.qkv, a.rel_bias, a.mask, FastDiv(std::max(a.n_mask, 1)), a.tok_index, FastDiv(std::max(a.n_win, 1)), a.o, \
                        n_items, FastDiv(split), a.T, a.C, FastDiv(a.H), a.qk_rq, \
-                       a.sm, a.pv_rq, nqk, npv, rnd, up, a.tap_scores, a.tap_probs)
+                       FAST_ == 2 ? sm24 : a.sm, a.pv_rq, nqk, npv, rnd, a.tap_scores, a.tap_probs)
     // the production paths are <no taps, fast>, with the 24-bit requantisation when both pairs allow it; everything else
     // shares one fully general instantiation per bias / mask combination (a mask is always compiled with the bias code,
     // which tests the bias pointer)
@@ -906,7 +907,7 @@ static void launch_flags(hipStream_t s, const AttentionArgs& a, int grid, int sp
     if (T197 && a.T == 197 && !taps && fast && !bias) {
         if (narrow) IVIT_ATT(false, false, false, 2, T197); else IVIT_ATT(false, false, false, 1, T197);
     } else if (T49 && !taps && fast && bias && narrow && window_takes(a)) {
-        launch_window(s, a, up, nqk, npv);
+        launch_window(s, a, sm24, nqk, npv);
     } else if (T49 && a.T == 49 && !taps && fast && bias) {
         if (masked) { if (narrow) IVIT_ATT(false, true, true, 2, T49); else IVIT_ATT(false, true, true, 1, T49); }
         else { if (narrow) IVIT_ATT(false, true, false, 2, T49); else IVIT_ATT(false, true, false, 1, T49); }

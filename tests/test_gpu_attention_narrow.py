@@ -61,6 +61,16 @@ def test_exponent_parameters(ivit, i0, n, c, one_key):
         _run(ivit, 2, 49, 1, 32, sm, (20011, c), bias=True, one_key=one_key, rounding="floor")
 
 
+# more than 208 tokens and 64 features take the 24-bit requantisations with the 32-bit IntDiv where there is a mask
+@pytest.mark.parametrize("i0,n", [(32, 10), (32, 9), (7, 3)])
+@pytest.mark.parametrize("k_out", [8, 4])
+@pytest.mark.parametrize("extra", ["bias", "mask", "bias and mask"])
+def test_exponent_parameters_of_long_rows(ivit, i0, n, k_out, extra):
+    sm = dict(i0=i0, n_shift=n, m_bits=24 + k_out - 1, k_out=k_out)
+    for d_head, T in ((64, 250), (32, 250), (64, 200)):
+        _run(ivit, 1, T, 1, d_head, sm, (20011, 24), bias="bias" in extra, mask="some" if "mask" in extra else None)
+
+
 @pytest.mark.parametrize("i0", [1, 6, 7, 15, 16, 64])
 @pytest.mark.parametrize("T", [49, 65])
 def test_rows_with_every_key_masked(ivit, i0, T):
