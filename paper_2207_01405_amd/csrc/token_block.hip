@@ -6,7 +6,7 @@
 // too until it has been normalised; its LDS then goes to the hidden layer, so it is written out once (to the workspace,
 // from where the L2 has it) and comes back as the residual of the last layer, during that layer's last products.
 //
-// A workgroup of four wavefronts (one per SIMD) takes M tokens through all layers.  Weights stream through two LDS
+// A workgroup of four or eight wavefronts (one or two per SIMD) takes M tokens through all layers.  Weights stream through two LDS
 // buffers in sets (128 to 192 rows of proj / fc1 / qkv, or 128 bytes of every row of fc2), each requested while its
 // predecessor is multiplied; every compute unit reads the same sets at about the same time, from its L2.  Activations
 // stand: those of proj, fc1 and qkv in registers as the "A" operand for all k-steps, the hidden layer in chunks of 128
@@ -14,9 +14,12 @@
 // channel and 16 tokens of a product, so requantisation constants are registers; results turn into token rows through
 // wavefront-private LDS with the transposing LDS read.  The LayerNorms work on the token tile in LDS.
 //
-// What bounds it is the rate at which one wavefront per SIMD issues instructions (one per 4 to 4.5 cycles): a matrix
-// instruction of 32 cycles hides about seven others, and every further one adds its own time.  So the results of a
-// channel tile are requantised between the products of the next one, spread evenly, and loads are three instructions.
+// What bounds it is the rate at which a wavefront issues instructions (one per 4.5 to 5.5 cycles; a second wavefront on the SIMD
+// runs beside it at the same rate: a step of one product, 12 vector, 2 LDS and 4 scalar instructions takes 160 cycles with one
+// wavefront and 164 with two).  So the results of a channel tile are requantised between the products of the next one, spread
+// evenly, loads are three instructions, and where the tokens of a workgroup divide among eight wavefronts there are eight, which
+// leaves 128 registers beside 128 accumulation registers to each: forwards of 197 tokens, four wavefronts against eight, DeiT-S
+// batch 64 720 -> 669 us and batch 128 1041 -> 984, DeiT-T batch 128 583 -> 522 and batch 256 978 -> 882.
 #include "regst_common.hpp"
 #include <algorithm>
 #include <type_traits>
@@ -39,12 +42,13 @@ __host__ __device__ constexpr int TB_FC2(int C) { return 32 * C; }
 __host__ __device__ constexpr int TB_FC1(int C) { return 48 * C; }
 __host__ __device__ constexpr int TB_QKV(int C, int F) { return 48 * C + 16 * F; }
 
-template <int C, int MT>
+// M = 32 MT tokens, NW wavefronts
+template <int C, int MT, int NW>
 struct TbLayout {
     static constexpr int KS = C / 32, P = C / 16;                  // k-steps and 16-byte pieces of a row of C bytes
     static constexpr int M = 32 * MT;                              // tokens of a workgroup
-    static constexpr int WNG = C / 96, WMG = 4 / WNG, TT = MT / WMG;      // wavefront grid of proj / fc2 / qkv, token tiles of a wavefront
-    static constexpr int WM1 = WNG == 4 ? (MT < 2 ? MT : 2) : WMG, WN1 = 4 / WM1;      // ... of fc1
+    static constexpr int WNG = C / 96, WMG = NW / WNG, TT = MT / WMG;     // wavefront grid of proj / fc2 / qkv, token tiles of a wavefront
+    static constexpr int WM1 = WNG != 4 ? WMG : NW == 8 ? MT : MT < 2 ? MT : 2, WN1 = NW / WM1;      // ... of fc1
     static constexpr int T1 = MT / WM1, N1 = 4 / WN1;
     static constexpr int PT = WNG == 4 ? 1 : 3;                    // channel tiles of a wavefront per weight set of proj / qkv
     static constexpr int RS = PT * WNG * 32;                       // weight rows of such a set
@@ -52,15 +56,16 @@ struct TbLayout {
     static constexpr int G16 = (P & 15) == 0 ? 16 : (P & 7) == 0 ? 8 : (P & 3) == 0 ? 4 : (P & 1) == 0 ? 2 : 1;     // gcd(P, 16)
     static constexpr int SETR = RS * C, SET1 = FC * C;             // bytes of a set of proj / qkv, of fc1 and fc2
     static constexpr int SETW = SETR > SET1 ? SETR : SET1;
-    static constexpr int SETB = SETW + 3072;                       // weights, then the constants of up to 192 rows
+    static constexpr int CW = (RS > FC ? RS + 63 : FC + 63) / 64;  // wavefronts that fetch the constants of a set's rows, 64 each
+    static constexpr int SETB = SETW + 1024 * CW;                  // weights, then those constants
     static constexpr int HP = M + 16, HB = FC * HP;                // hidden chunk [channel][token]
     static constexpr int LUT = 0, SET = 256;                       // the ShiftGELU table lies at address 0: an index is its address
     static constexpr int ACT = SET + 2 * SETB;                     // token tile [row][C], or the two hidden chunks
     static constexpr int ACTB = M * C > 2 * HB ? M * C : 2 * HB;
-    static constexpr int LN = ACT + ACTB;                          // gamma (2 KB), beta (2 KB)
-    static constexpr int STG = LN + 4096, STGB = 32 * 40;          // staging tile of a wavefront: [32 channels][40]
-    static constexpr int TOTAL = STG + 4 * STGB;
-    static_assert(C % 96 == 0 && 4 % WNG == 0 && MT % WMG == 0 && TT >= 1, "shape");
+    static constexpr int LN = ACT + ACTB;                          // gamma, beta
+    static constexpr int STG = LN + (8 * C + 1023) / 1024 * 1024, STGB = 32 * 32;      // staging tile of a wavefront: [32 channels][32 tokens]
+    static constexpr int TOTAL = STG + NW * STGB;
+    static_assert(C % 96 == 0 && NW % WNG == 0 && MT % WMG == 0 && TT >= 1 && MT % WM1 == 0 && 4 % WN1 == 0, "shape");
     static_assert(C % RS == 0 && SETW >= M * C && (NPROJ == 1 || NPROJ == 3) && NQKV % 2 == 1, "sets");
     static_assert(TOTAL <= 160 * 1024, "LDS");
 };
@@ -144,14 +149,14 @@ constexpr int spread_slot(int i, int n, int from, int to) {
     return to;
 }
 
-template <int C, int MT>
-__global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
-    using LY = TbLayout<C, MT>;
+template <int C, int MT, int NW>
+__global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) {
+    using LY = TbLayout<C, MT, NW>;
     constexpr int KS = LY::KS, PP = LY::P, M = LY::M, TT = LY::TT, T1 = LY::T1, N1 = LY::N1, PT = LY::PT, RS = LY::RS;
     constexpr int WNG = LY::WNG, WN1 = LY::WN1, G16 = LY::G16, SETW = LY::SETW, HP = LY::HP;
     constexpr int NX = G16 / 2 > 0 ? G16 / 2 : 1;
     constexpr int LPR = PP / 3;                                    // lanes of a row in the LayerNorm passes, three pieces each
-    constexpr int RD = KS == 12 ? 4 : 3;                           // ring of weight fragments: requested RD - 1 k-steps ahead
+    constexpr int RD = KS == 12 && NW == 4 ? 4 : 3;                           // ring of weight fragments: requested RD - 1 k-steps ahead
     static_assert((KS % RD) == 0 || ((PT * KS) % RD == 0 && (N1 * KS) % RD == 0), "the ring must align with a set");
 
     extern __shared__ __align__(1024) int8_t lds[];
@@ -159,7 +164,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wv % WNG, wm = wv / WNG, wn1 = wv % WN1, wm1 = wv / WN1;
-    const int lj = lane & 31, lg = lane >> 5, lb = lane >> 4;
+    const int lj = lane & 31, lg = lane >> 5;
     int8_t* stg = lds + LY::STG + wv * LY::STGB;
     const int64_t m0 = (int64_t)blockIdx.x * M;
     const int rows = __builtin_amdgcn_readfirstlane((int)min64(P.R - m0, M));
@@ -178,11 +183,11 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
 
     // ---- loads into LDS.  A set of rows (proj, fc1, qkv) is contiguous in memory, a set of fc2 is 128 bytes of every row,
     // a token tile has its rows permuted (LDS row i holds token 32 (i / 32) + token_of_row(i % 32)).  Load instruction
-    // n = 4 i + wavefront covers 16-byte slots 64 n .. 64 n + 63; what differs from piece i to i + 3 is a constant step.
+    // n = NW i + wavefront covers 16-byte slots 64 n .. 64 n + 63; what differs from piece i to i + 3 is a constant step.
     uint32_t vr[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        const int s = 64 * (4 * i + wv) + lane, r = s / PP, p = s % PP;
+        const int s = 64 * (NW * i + wv) + lane, r = s / PP, p = s % PP;
         vr[i] = (uint32_t)(r * C + 16 * (p ^ swz<G16>(r)));
     }
     const int r2 = 8 * wv + (lane >> 3);
@@ -196,23 +201,24 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         return (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + LY::SET + b * LY::SETB + wv * 1024));
     };
     auto load_rows = [&](const int8_t* w, const int8_t* cst, int row0, int b) __attribute__((always_inline)) -> Load {
-        return Load{buffer(w + row0 * C, 0x7fffffffu), 0u - 12288u, 0, 12288, {vr[0], vr[1], vr[2]}, set_dst(b), uniform_ptr(cst + row0 * 16)};
+        return Load{buffer(w + row0 * C, 0x7fffffffu), 0u - 3072u * NW, 0, 3072 * NW, {vr[0], vr[1], vr[2]}, set_dst(b), uniform_ptr(cst + row0 * 16)};
     };
     auto load_f2 = [&](int chunk, int b) __attribute__((always_inline)) -> Load {
-        return Load{buffer(P.fc2.w + chunk * FC, 0x7fffffffu), 0u - 32u * (uint32_t)F, 32u * (uint32_t)F, 32u * (uint32_t)F, {v2, v2, v2}, set_dst(b),
+        return Load{buffer(P.fc2.w + chunk * FC, 0x7fffffffu), 0u - 8u * NW * (uint32_t)F, 8u * NW * (uint32_t)F, 8u * NW * (uint32_t)F, {v2, v2, v2}, set_dst(b),
                     uniform_ptr(P.fc2.w)};
     };
-    // piece i of a set of `bytes`; the last piece brings the constants of the set's rows (64 rows a wavefront, the fourth repeats
-    // the third; a set of fc2 has none and fetches some bytes that nobody reads instead, so that nothing branches here)
+    // piece i of a set of `bytes`; the last piece brings the constants of the set's rows (64 rows a wavefront, the last ones repeat
+    // each other; a set of fc2 has none and fetches some bytes that nobody reads instead, so that nothing branches here)
     auto load_piece = [&](Load& l, auto i_c, auto bytes_c) __attribute__((always_inline)) {
-        constexpr int i = decltype(i_c)::value, NI = decltype(bytes_c)::value / 1024, NP = (NI + 3) / 4, nr = decltype(bytes_c)::value / C;
+        constexpr int i = decltype(i_c)::value, NI = decltype(bytes_c)::value / 1024, NP = (NI + NW - 1) / NW, nr = decltype(bytes_c)::value / C;
         if constexpr (i < NP) {
             // (the addition between the write of m0 and the load is the wait state that pair needs)
-            if (4 * i + 3 < NI || 4 * i + wv < NI)
+            if (NW * i + NW - 1 < NI || NW * i + wv < NI)
                 asm volatile("s_add_u32 m0, %1, %5\n\ts_add_u32 %0, %0, %2\n\tbuffer_load_dwordx4 %3, %4, %0 offen lds"
-                             : "+s"(l.so) : "s"(l.dst), "s"(i % 3 == 0 ? l.d3 : l.d1), "v"(l.v[i % 3]), "s"(l.rsrc), "i"(i * 4096) : "memory", "m0", "scc");
+                             : "+s"(l.so) : "s"(l.dst), "s"(i % 3 == 0 ? l.d3 : l.d1), "v"(l.v[i % 3]), "s"(l.rsrc), "i"(i * NW * 1024) : "memory", "m0", "scc");
         } else {
-            dma16(l.cst, (uint32_t)(16 * min(64 * min(wv, 2) + lane, nr - 1)), l.dst + SETW - (wv == 3 ? 1024 : 0));
+            const int w = min(wv, LY::CW - 1);
+            dma16(l.cst, (uint32_t)(16 * min(64 * w + lane, nr - 1)), l.dst + SETW - 1024 * (wv - w));
         }
     };
     auto load_range = [&](Load& l, auto lo_c, auto hi_c, auto bytes_c) __attribute__((always_inline)) {
@@ -221,16 +227,16 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         });
     };
     using BR = ic<LY::SETR>; using B1 = ic<LY::SET1>;
-    constexpr int NPR = (LY::SETR / 1024 + 3) / 4 + 1, NP1 = (LY::SET1 / 1024 + 3) / 4 + 1;      // pieces of a set
+    constexpr int NPR = (LY::SETR / 1024 + NW - 1) / NW + 1, NP1 = (LY::SET1 / 1024 + NW - 1) / NW + 1;      // pieces of a set
     // a token tile: rows past the matrix read as zero (the buffer ends there)
-    constexpr int NPA = (M * PP / 64 + 3) / 4;
+    constexpr int NPA = (M * PP / 64 + NW - 1) / NW;
     auto act_piece = [&](const v4i& rsrc, uint32_t dst, auto i_c) __attribute__((always_inline)) {
         constexpr int i = decltype(i_c)::value, NI = M * PP / 64;
-        const int s = 64 * (4 * (i % 3) + wv) + lane, r = s / PP, p = s % PP;
+        const int s = 64 * (NW * (i % 3) + wv) + lane, r = s / PP, p = s % PP;
         const uint32_t v = (uint32_t)(((r & ~31) + token_of_row(r & 31)) * C + 16 * (p ^ swz<G16>(r)));
-        if (4 * i + 3 < NI || 4 * i + wv < NI)
+        if (NW * i + NW - 1 < NI || NW * i + wv < NI)
             asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                         : : "s"(dst), "v"(v + (i / 3) * 12288), "s"(rsrc), "i"(i * 4096) : "memory", "m0", "scc");
+                         : : "s"(dst), "v"(v + (i / 3) * 3072 * NW), "s"(rsrc), "i"(i * NW * 1024) : "memory", "m0", "scc");
     };
     auto tile_buffer = [&](const int8_t* src) __attribute__((always_inline)) -> v4i { return buffer(src + m0 * C, (uint32_t)(rows * C)); };
     auto tile_dst = [&](int off) __attribute__((always_inline)) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + off + wv * 1024)); };
@@ -243,6 +249,9 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         const int at = 1024 * wv + 16 * lane;
         if (1024 * wv < 8 * C) dma16(uniform_ptr(src), (uint32_t)min(at, 8 * C - 16), lds0 + LY::LN + wv * 1024);
     };
+    // (What a phase derives from the lane it derives anew, from a copy that the compiler cannot trace to the lane: kept from one
+    // phase to the next these addresses are 20 of the 128 registers that a wavefront has beside its accumulation registers.)
+    auto fresh_lane = [&]() __attribute__((always_inline)) -> int { int l = lane; pin(l); return l; };
     // ---- fragments.  Lane (lj, lg) of k-step ks: piece 2 ks + lg of row lj of a tile.
     int xr[NX];                                                     // tiles of rows of C bytes
 #pragma unroll
@@ -250,17 +259,28 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     auto frag = [&](const int8_t* tile, int ks) __attribute__((always_inline)) -> v4i {
         return *reinterpret_cast<const v4i*>(tile + xr[ks % NX] + 16 * G16 * (ks / NX));
     };
-    int x2[4];                                                      // tiles of rows of 128 bytes
-#pragma unroll
-    for (int i = 0; i < 4; ++i) x2[i] = lj * FC + 16 * ((2 * i + lg) ^ swz<8>(lj));
+    int x2[4] = {};                                                 // tiles of rows of 128 bytes
 
     // ---- residual and staging addresses (see gemm_rs.hip for the transposing reads)
-    const int jb = (lane & 15) >> 1, jo = lane & 1;                 // source side of a transposing read
-    const int dj = lane & 7, d_o = (lane >> 3) & 1;                 // destination side
-    const int res_row_p = 8 * (jb >> 2) + 4 * lg + (jb & 3);        // + 16 h: row of the token of result 8 h + jb, A rows in permuted order
-    const int res_row_i = 16 * (jb >> 2) + 8 * lg + (jb & 3);       // + 4 h: ... A rows in natural order
-    const int out_row = 16 * (lb & 1) + 8 * (dj >> 2) + 4 * (lb >> 1) + (dj & 3);      // row of token 8 lb + dj
-    const int out_xor = swz<G16>(out_row);
+    int jb, jo;                                                     // source side of a transposing read
+    int dj, d_o, lb;                                                // destination side
+    int res_row_p;                                                  // + 16 h: row of the token of result 8 h + jb, A rows in permuted order
+    int res_row_i;                                                  // + 4 h: ... A rows in natural order
+    int out_row, out_xor;                                           // row of token 8 lb + dj
+    // (8-byte unit u of row r of the staging tile lies at u ^ ((r / 4) % 4), so that no bank is met twice)
+    int stg_src, stg_src8, stg_dst, stg_x;
+    auto row_addresses = [&]() __attribute__((always_inline)) {
+        const int l = fresh_lane(), g = l >> 5;
+        jb = (l & 15) >> 1; jo = l & 1; dj = l & 7; d_o = (l >> 3) & 1; lb = l >> 4;
+        res_row_p = 8 * (jb >> 2) + 4 * g + (jb & 3);
+        res_row_i = 16 * (jb >> 2) + 8 * g + (jb & 3);
+        out_row = 16 * (lb & 1) + 8 * (dj >> 2) + 4 * (lb >> 1) + (dj & 3);
+        out_xor = swz<G16>(out_row);
+        stg_src = (16 * jo + jb) * 32 + 8 * (lb ^ (jb >> 2));
+        stg_src8 = (16 * jo + jb + 8) * 32 + 8 * (lb ^ (jb >> 2) ^ 2);
+        stg_dst = (l & 31) * 32;
+        stg_x = (l >> 2) & 3;
+    };
     auto res_read = [&](const int8_t* tile, int ct, auto perm_c, v2i (&rw)[2]) __attribute__((always_inline)) {
         constexpr bool perm = decltype(perm_c)::value;
 #pragma unroll
@@ -270,20 +290,20 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
             rw[h] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3)))*)(a));
         }
     };
-    const int stg_src = (16 * jo + jb) * 40 + 8 * lb;
     auto stg_put = [&](const v4i& w, auto perm_c) __attribute__((always_inline)) {
         constexpr bool perm = decltype(perm_c)::value;
         if (perm) {
-            v2i* d = reinterpret_cast<v2i*>(stg + lj * 40 + 16 * lg);
-            d[0] = v2i{w[0], w[1]}; d[1] = v2i{w[2], w[3]};
+            v2i* d = reinterpret_cast<v2i*>(stg + stg_dst);
+            d[(2 * lg) ^ stg_x] = v2i{w[0], w[1]}; d[(2 * lg + 1) ^ stg_x] = v2i{w[2], w[3]};
         } else {
-            int* d = reinterpret_cast<int*>(stg + lj * 40 + 4 * lg);
-            d[0] = w[0]; d[2] = w[1]; d[4] = w[2]; d[6] = w[3];
+            int* d = reinterpret_cast<int*>(stg + stg_dst + 4 * lg);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) d[2 * (u ^ stg_x)] = w[u];
         }
     };
     auto stg_get = [&]() __attribute__((always_inline)) -> v4i {
         const v2i a = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3)))*)(stg + stg_src));
-        const v2i b = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3)))*)(stg + stg_src + 8 * 40));
+        const v2i b = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3)))*)(stg + stg_src8));
         return v4i{a[0], a[1], b[0], b[1]};
     };
     auto act_put = [&](int tt, int ct, const v4i& w) __attribute__((always_inline)) {      // results of (token tile, channel tile) into the token tile
@@ -344,28 +364,15 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
 
     // ---- I-LayerNorm of the token tile, in place; `st`: the rows before normalisation also go to global memory, `dst`:
     // the normalised ones do
-    int32_t g[48], b[48];
-    const int q = lane % LPR, rl = lane / LPR;
-    auto ln_params = [&]() __attribute__((always_inline)) {
-        const int32_t* gt = reinterpret_cast<const int32_t*>(lds + LY::LN);
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const v4i gv = *reinterpret_cast<const v4i*>(gt + 16 * (q + LPR * j) + 4 * e);
-                const v4i bv = *reinterpret_cast<const v4i*>(gt + C + 16 * (q + LPR * j) + 4 * e);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) { g[16 * j + 4 * e + r] = gv[r]; b[16 * j + 4 * e + r] = bv[r]; }
-            }
-    };
     auto layernorm = [&](int f_bits, int c_shift, int8_t* st, int8_t* dst) __attribute__((always_inline)) {
-        constexpr int RPP = 64 / LPR, RW = M / 4;                   // rows per pass, rows of a wavefront
+        constexpr int RPP = 64 / LPR, RW = M / NW;                   // rows per pass, rows of a wavefront
         const __amdgpu_buffer_rsrc_t sb = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(st + m0 * C)), 0, st ? rows * C : 0, 0x00020000);
         const __amdgpu_buffer_rsrc_t db = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(dst + m0 * C)), 0, dst ? rows * C : 0, 0x00020000);
         constexpr int NPASS = RW / RPP;
         static_assert(RW % RPP == 0 && NPASS <= LPR, "rows of a wavefront");
         v4i v[NPASS][3];
         int32_t sm[NPASS], sq[NPASS];
+        const int ll = fresh_lane(), q = ll % LPR, rl = ll / LPR;
         const int i0 = wv * RW + rl;                                // row of pass k: i0 + k RPP
 #pragma unroll
         for (int k = 0; k < NPASS; ++k) {
@@ -396,13 +403,25 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
 #pragma unroll
         for (int k = 1; k < NPASS; ++k) { s = q == k ? sm[k] : s; ss = q == k ? sq[k] : ss; }
         const LnStat own = ln_stat(s, ss, C, f_bits);
+        LnStat row[NPASS];
 #pragma unroll
         for (int k = 0; k < NPASS; ++k) {
-            const int i = i0 + k * RPP, tok = (i & ~31) + token_of_row(i & 31);
-            const int from = 4 * ((lane & ~(LPR - 1)) + k);
-            const LnStat row{__builtin_amdgcn_ds_bpermute(from, own.mean), __builtin_amdgcn_ds_bpermute(from, own.f)};
+            const int from = 4 * ((ll & ~(LPR - 1)) + k);
+            row[k] = LnStat{__builtin_amdgcn_ds_bpermute(from, own.mean), __builtin_amdgcn_ds_bpermute(from, own.f)};
+        }
+        // (gamma and beta of one piece at a time: all three would be 96 registers)
+        const int32_t* gt = reinterpret_cast<const int32_t*>(lds + LY::LN);
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
+        for (int j = 0; j < 3; ++j) {
+            v4i g[4], b[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                g[e] = *reinterpret_cast<const v4i*>(gt + 16 * (q + LPR * j) + 4 * e);
+                b[e] = *reinterpret_cast<const v4i*>(gt + C + 16 * (q + LPR * j) + 4 * e);
+            }
+#pragma unroll
+            for (int k = 0; k < NPASS; ++k) {
+                const int i = i0 + k * RPP, tok = (i & ~31) + token_of_row(i & 31);
                 v4i w;
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
@@ -410,7 +429,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int32_t xe = (int32_t)(int8_t)((uint32_t)v[k][j][d] >> (8 * r));
-                        o[r] = (uint32_t)ln_value(xe, row, g[16 * j + 4 * d + r], b[16 * j + 4 * d + r], c_shift);
+                        o[r] = (uint32_t)ln_value(xe, row[k], g[d][r], b[d][r], c_shift);
                     }
                     w[d] = pack4(o, std::true_type());
                 }
@@ -458,10 +477,11 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
 #pragma unroll
         for (int t = 0; t < TT; ++t)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                ar[t][ks] = frag(act + 32 * (wm * TT + t) * C, ks);
-                asm volatile("" : "+a"(ar[t][ks]));
-            }
+            for (int ks = 0; ks < KS; ++ks) ar[t][ks] = frag(act + 32 * (wm * TT + t) * C, ks);
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(ar[t][ks]));
     };
 
     // ---- proj and qkv: tile g of a wavefront goes to accumulators g % 2 and is requantised while tile g + 1 is multiplied
@@ -487,13 +507,14 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         load_ln(tab);
         load_range(L0, ic<0>(), ic<NPR>(), BR());
         if constexpr (LY::NPROJ > 1) load_range(L1, ic<0>(), ic<NPR>(), BR()); else load_range(L1, ic<0>(), ic<NP1>(), B1());
-        lds[LY::LUT + tid] = (int8_t)requant64(shiftgelu_raw((int32_t)(int8_t)tid, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c);
+        lds[LY::LUT + (tid & 255)] = (int8_t)requant64(shiftgelu_raw((int32_t)(int8_t)tid, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c);
         const ResRq rr1 = make_res(P.res1);
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(LY::NPROJ > 1 && LY::SETR % 4096 == 0 ? NPR : 0) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(LY::NPROJ > 1 && LY::SETR % (1024 * NW) == 0 ? NPR : 0) : "memory");
         load_ar();
         first_frags(set_at(0) + wn * 32 * C);
         sync_lds();
         load_act(P.x, LY::ACT);
+        row_addresses();
         // ---- proj.  Sets 0 .. NPROJ - 1, then fc1's first two, alternate between the two buffers.
         Rq64 pq = {};
         v4i pqn = {};
@@ -552,7 +573,6 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
             static_for<NOT + 2>([&](auto i) __attribute__((always_inline)) { proj_out(g, ic<g & 1>(), i); });
             proj_slow(g, ic<g & 1>());
         }
-        ln_params();
         sync_lds();
         // ---- LN2
         Load L = load_rows(P.fc1.w, tab + TB_FC1(C), FC, 0);
@@ -564,17 +584,21 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         // buffer 1, from then on F1 sets are in buffer 0, F2 sets in buffer 1 (the last one, having no F1 set after its
         // predecessor, in buffer 0).  Results of fc1: channel tile n is requantised while tile n + 1 is multiplied, the last
         // one during the next F2.
-        constexpr int NM1 = KS * T1, NO1 = T1 * 16, NM2 = 12 * TT, LAG = 8;
+        constexpr int NM1 = KS * T1, NO1 = T1 * 16, NM2 = 12 * TT, LAG = NW == 8 ? 4 : 8;     // results between a table read and its use
         constexpr int EF1 = NM1 > 3 ? 3 : NM1 - 1;
         constexpr int TP = NP1 / 3;                                 // pieces of a set requested before the end of the set before its predecessor
-        constexpr auto vv_acc = [](int t, int ks) constexpr { return 3 * TT * 16 + 4 * (t * KS + ks + 1) <= 256; };      // fits beside fc2's accumulators
+        constexpr auto vv_acc = [](int t, int ks) constexpr { return 3 * TT * 16 + 4 * (t * KS + ks + 1) <= 1024 / NW; };      // fits beside fc2's accumulators (half of the registers)
         v4i vv[T1][KS];
         static_for<T1>([&](auto t) __attribute__((always_inline)) {
             static_for<KS>([&](auto ks) __attribute__((always_inline)) {
                 vv[t][ks] = frag(act + 32 * (wm1 * T1 + decltype(t)::value) * C, ks);
-                if constexpr (vv_acc(decltype(t)::value, decltype(ks)::value)) asm volatile("" : "+a"(vv[t][ks]));
             });
         });
+#pragma unroll
+        for (int t = 0; t < T1; ++t)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                if (vv_acc(t, ks)) asm volatile("" : "+a"(vv[t][ks]));
         v16i acc[3][TT], ha[N1][T1];
 #pragma unroll
         for (int j = 0; j < 3; ++j)
@@ -613,8 +637,12 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                 *reinterpret_cast<v4i*>(h_at(hbuf, u)) = unit_slow(ha[u / T1][u % T1], P.fc1, chunk * FC + (wn1 * N1 + u / T1) * 32 + lj, true);
             });
         };
-        const int8_t* h0 = act + (16 * lg + jb) * HP + 32 * wm * TT + 16 * (lb & 1) + 8 * jo;
-        v4i af[2][TT], b2[4];
+        const int hl = fresh_lane();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x2[i] = (hl & 31) * FC + 16 * ((2 * i + (hl >> 5)) ^ swz<8>(hl & 31));
+        const int8_t* h0 = act + (16 * (hl >> 5) + ((hl & 15) >> 1)) * HP + 32 * wm * TT + (hl & 16) + 8 * (hl & 1);
+        constexpr int RB = RD;                                      // ring of weight fragments of fc2
+        v4i af[2][TT], b2[RB];
         auto read_a = [&](int hbuf, auto kk_c) __attribute__((always_inline)) {
             constexpr int kk = decltype(kk_c)::value;
 #pragma unroll
@@ -627,13 +655,12 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         };
         auto read_b = [&](int b, auto st_c) __attribute__((always_inline)) {
             constexpr int st = decltype(st_c)::value;
-            b2[st & 3] = *reinterpret_cast<const v4i*>(set_at(b) + wn * 32 * FC + (st % 3) * WNG * 32 * FC + x2[st / 3]);
+            b2[st % RB] = *reinterpret_cast<const v4i*>(set_at(b) + wn * 32 * FC + (st % 3) * WNG * 32 * FC + x2[st / 3]);
         };
         auto f2_first = [&](int b, int hbuf, auto k_c) __attribute__((always_inline)) {      // piece k of RD - 1 of an F2's first fragments
             constexpr int k = decltype(k_c)::value;
             if constexpr (k == 0) read_a(hbuf, ic<0>());
-            if constexpr (k == 0 && RD == 3) { read_b(b, ic<0>()); read_b(b, ic<1>()); }
-            if constexpr (RD == 4) read_b(b, k_c); else if constexpr (k == 1) read_b(b, ic<2>());
+            read_b(b, k_c);
         };
         // body(m): the loads and whatever else goes with product m; after(): loads to start once this set's memory is free
         auto f1 = [&](const int8_t* w0, int b, int hbuf, auto body, auto after, auto next) __attribute__((always_inline)) {
@@ -665,7 +692,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
             static_for<12>([&](auto st_c) __attribute__((always_inline)) {
                 constexpr int st = decltype(st_c)::value, kk = st / 3, j = st % 3;
                 if constexpr (decltype(tail_c)::value && st == 10) { sync(); after(); }
-                if constexpr (st + 3 < 12) read_b(b, ic<st + 3>());
+                if constexpr (st + RB - 1 < 12) read_b(b, ic<st + RB - 1>());
                 if constexpr (j == 1 && kk < 3) read_a(hbuf, ic<kk + 1>());
                 if constexpr (decltype(tail_c)::value && st >= 10) {
                     next(ic<2 * (st - 10)>());
@@ -673,7 +700,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                 }
                 static_for<TT>([&](auto t_c) __attribute__((always_inline)) {
                     constexpr int t = decltype(t_c)::value;
-                    mfma<true, false>(acc[j][t], af[kk & 1][t], b2[st & 3]);
+                    mfma<true, false>(acc[j][t], af[kk & 1][t], b2[st % RB]);
                     body(ic<st * TT + t>());
                     __builtin_amdgcn_sched_barrier(0);
                 });
@@ -746,6 +773,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
             res_read(set_at(1) + 32 * (wm * TT + u % TT) * C, (u / TT) * WNG + wn, std::false_type(), rwn);
         };
         auto f2_put = [&](int u, const v4i& w) __attribute__((always_inline)) { act_put(wm * TT + u % TT, (u / TT) * WNG + wn, w); };
+        row_addresses();
         f2_res(0);
         static_for<3 * TT>([&](auto u_c) __attribute__((always_inline)) {
             constexpr int u = decltype(u_c)::value;
@@ -767,7 +795,6 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
                 stg_put(unit_slow_res(acc[u / TT][u % TT], P.fc2, rr2, P.xhat, wm * TT + u % TT, (u / TT) * WNG + wn, std::false_type()), std::false_type());
                 f2_put(u, stg_get());
             });
-        ln_params();
         sync_lds();
     } else {
         Load L = load_rows(P.qkv_w.w, tab + TB_QKV(C, F), 0, 0);
@@ -775,14 +802,13 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
         load_ln(tab + TB_LN1(C));
         load_range(L, ic<0>(), ic<NPR>(), BR());
         sync();
-        ln_params();
     }
     if (!P.next) {                                                  // only the block's output leaves
         constexpr int NI = M * PP / 64;
         const __amdgpu_buffer_rsrc_t yb = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(P.y + m0 * C)), 0, rows * C, 0x00020000);
 #pragma unroll
-        for (int i = 0; i < (NI + 3) / 4; ++i) {
-            const int s = 64 * (4 * i + wv) + lane, r = s / PP, p = s % PP;
+        for (int i = 0; i < (NI + NW - 1) / NW; ++i) {
+            const int s = 64 * (NW * i + wv) + lane, r = s / PP, p = s % PP;
             if (s < M * PP) __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const v4i*>(act + r * C + 16 * (p ^ swz<G16>(r))), yb,
                                                                   ((r & ~31) + token_of_row(r & 31)) * C + 16 * p, 0, 0);
         }
@@ -798,6 +824,7 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     const int N3 = 3 * C;
     // rows of qkv from this workgroup's first one on, as a buffer that ends with the matrix
     const uint64_t q_base = (uint64_t)uniform_ptr(P.out + m0 * N3);
+    row_addresses();
     uint32_t q_off[TT];
 #pragma unroll
     for (int t = 0; t < TT; ++t) q_off[t] = (uint32_t)((32 * (wm * TT + t) + 8 * lb + dj) * N3 + 16 * d_o);
@@ -820,7 +847,9 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     constexpr int NSA = stores_after_loads();
     auto qkv_put = [&](int g, int t, const v4i& w, bool real) __attribute__((always_inline)) {
         const __amdgpu_buffer_rsrc_t ob = __builtin_amdgcn_make_buffer_rsrc((int8_t*)q_base, 0, real ? rows * N3 : 0, 0x00020000);
-        __builtin_amdgcn_raw_buffer_store_b128(w, ob, (int)q_off[t], (g * WNG + wn) * 32, 0);
+        // (The offset all in a vector register: behind a 16-byte store with a scalar offset the compiler leaves out the wait state
+        // before the next write of its data registers, and with a second wavefront on the SIMD some lanes then stored the new value.)
+        __builtin_amdgcn_raw_buffer_store_b128(w, ob, (int)q_off[t] + (g * WNG + wn) * 32, 0, 0);
     };
     auto qkv_out = [&](int g, auto par_c, auto i_c) __attribute__((always_inline)) {
         constexpr int i = decltype(i_c)::value, t = i / 16, e = i % 16, par = decltype(par_c)::value;
@@ -880,10 +909,11 @@ __global__ __launch_bounds__(256) void token_block_kernel(TokenBlockArgs P) {
     qkv_slow(LY::NQKV * PT - 1, ic<(PT + 1) & 1>());
 }
 
-template <int C, int MT>
+template <int C, int MT, int NW>
 hipError_t launch_tb(hipStream_t s, const TokenBlockArgs& a) {
-    const int64_t grid = (a.R + TbLayout<C, MT>::M - 1) / TbLayout<C, MT>::M;
-    hipLaunchKernelGGL((token_block_kernel<C, MT>), dim3((unsigned)grid), dim3(256), (TbLayout<C, MT>::TOTAL), s, a);
+    using LY = TbLayout<C, MT, NW>;
+    const int64_t grid = (a.R + LY::M - 1) / LY::M;
+    hipLaunchKernelGGL((token_block_kernel<C, MT, NW>), dim3((unsigned)grid), dim3(64 * NW), LY::TOTAL, s, a);
     return hipGetLastError();
 }
 
@@ -948,12 +978,12 @@ hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a) {
     auto tile = [&](const TokenBlockArgs& t) -> hipError_t {
         TraceScope trace(s, KIND_TOKEN_BLOCK, 2 * t.R * per_row, per_row + t.R * row_bytes);
         if (t.C == 384) {
-            if (t.R <= 32 * cus) return launch_tb<384, 1>(s, t);
-            if (t.R <= 64 * cus) return launch_tb<384, 2>(s, t);
-            return launch_tb<384, 4>(s, t);
+            if (t.R <= 32 * cus) return launch_tb<384, 1, 4>(s, t);
+            if (t.R <= 64 * cus) return launch_tb<384, 2, 8>(s, t);
+            return launch_tb<384, 4, 8>(s, t);
         }
-        if (t.C == 192) return t.R <= 64 * cus ? launch_tb<192, 2>(s, t) : launch_tb<192, 4>(s, t);
-        return launch_tb<96, 4>(s, t);
+        if (t.C == 192) return t.R <= 64 * cus ? launch_tb<192, 2, 4>(s, t) : launch_tb<192, 4, 8>(s, t);
+        return launch_tb<96, 4, 4>(s, t);
     };
     // One workgroup fits a CU (C = 192, 384), so the last round of 128-row tiles takes as long as a full one however few rows
     // it has: what is left beyond full rounds goes to a launch with tiles of its own size (forwards: DeiT-S batch 192 2220 ->

@@ -129,3 +129,23 @@ def test_deep_stacks(ivit, R, n):
     for final_ln in (None, synth.make_final_ln(cfg)):
         got, want = _run(ivit, dict(B=R, T=1, C=C, H=H, F=F), x, blocks, final_ln)
         assert np.array_equal(got, want), "%d of %d differ" % ((got != want).sum(), got.size)
+
+
+@pytest.mark.parametrize("C,H,F,R", [(384, 6, 1536, 8193), (384, 6, 1536, 16384), (384, 6, 1536, 25216), (384, 12, 256, 12608),
+                                     (192, 3, 768, 16385), (192, 3, 768, 32768)])
+def test_two_wavefronts_on_a_simd_store_what_they_computed(ivit, C, H, F, R):
+    """Launches with eight wavefronts, again and again: a 16-byte store whose data registers are overwritten at once went out
+    with the new value in some lanes when a second wavefront shared the SIMD, in some workgroups of some launches."""
+    import torch
+    d = dict(B=R, T=1, C=C, H=H, F=F)
+    cfg, blocks = _blocks(C, H, F, 1, 2, "as drawn")
+    x = synth.make_rows(5 + R, R, C)
+    got, want = _run(ivit, d, x, blocks, None)
+    assert np.array_equal(got, want)
+    xd, y = torch.from_numpy(x).cuda(), torch.empty((R, C), dtype=torch.int8, device="cuda")
+    ws = torch.empty(ivit.ivit_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    bl, wd = [ivit.to_device(p) for p in blocks], torch.from_numpy(want).cuda()
+    for _ in range(8):
+        y.zero_()
+        ivit.ivit_forward(xd, y, bl, d, ws)
+        assert torch.equal(y, wd)
