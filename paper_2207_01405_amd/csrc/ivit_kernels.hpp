@@ -74,6 +74,8 @@ constexpr int kTableLaunches = 15;       // launches whose constants one table l
 hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n);      // n <= kTableLaunches
 bool token_block_takes(int C, int F, int64_t R);
 hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a);
+bool token_stream_takes(int C, int F, int64_t R);       // the form of launch_token_block for few rows (token_stream.hip)
+hipError_t launch_token_stream(hipStream_t s, const TokenBlockArgs& a);
 
 hipError_t launch_embed_tokens(hipStream_t s, const int8_t* patch_tok, const int8_t* cls, const int8_t* pos, Dyadic tok_rq,
                                Dyadic pos_rq, int8_t* tokens, int B, int P, int C);
@@ -98,7 +100,8 @@ int num_cus();
 // Kinds of launches reported by the trace (ivit_trace_end); values are part of the C ABI.
 enum LaunchKind { KIND_ILAYERNORM = 1, KIND_GEMM = 2, KIND_GEMM_RESIDUAL = 3, KIND_GEMM_GELU = 4,
                   KIND_ATTENTION = 5, KIND_SHIFTMAX = 6, KIND_SHIFTGELU = 7, KIND_EMBED = 8, KIND_PATCH_MERGE = 9, KIND_MEAN_POOL = 10,
-                  KIND_TOKEN_BLOCK = 11, KIND_TOKEN_TABLES = 12 };
+                  KIND_TOKEN_BLOCK = 11, KIND_TOKEN_TABLES = 12,
+                  KIND_TOKEN_FEW = 13 };     // KIND_TOKEN_BLOCK of width 384 and fewer than 20 rows per CU: as long as its weights take to fetch
 
 // Brackets one kernel launch with two HIP events on its stream while a trace is active; otherwise a no-op.
 // ops = algorithmic integer operations (2 per int8 multiply-accumulate), bytes = algorithmic HBM bytes.

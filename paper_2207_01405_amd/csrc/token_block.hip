@@ -20,7 +20,7 @@
 // evenly, loads are three instructions, and where the tokens of a workgroup divide among eight wavefronts there are eight, which
 // leaves 128 registers beside 128 accumulation registers to each: forwards of 197 tokens, four wavefronts against eight, DeiT-S
 // batch 64 720 -> 669 us and batch 128 1041 -> 984, DeiT-T batch 128 583 -> 522 and batch 256 978 -> 882.
-#include "regst_common.hpp"
+#include "token_block_common.hpp"
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -29,18 +29,9 @@ namespace ivit {
 
 namespace {
 
-using namespace regst;
-
-template <int I> using ic = std::integral_constant<int, I>;
+using namespace tokblk;
 
 constexpr int FC = 128;                          // hidden channels per chunk of the MLP
-
-// Offsets in the table of one launch: LN2 (gamma, beta), LN1 or the final LN, then 16 bytes per channel of proj, fc2, fc1, qkv.
-__host__ __device__ constexpr int TB_LN1(int C) { return 8 * C; }
-__host__ __device__ constexpr int TB_PROJ(int C) { return 16 * C; }
-__host__ __device__ constexpr int TB_FC2(int C) { return 32 * C; }
-__host__ __device__ constexpr int TB_FC1(int C) { return 48 * C; }
-__host__ __device__ constexpr int TB_QKV(int C, int F) { return 48 * C + 16 * F; }
 
 // M = 32 MT tokens, NW wavefronts
 template <int C, int MT, int NW>
@@ -53,7 +44,7 @@ struct TbLayout {
     static constexpr int PT = WNG == 4 ? 1 : 3;                    // channel tiles of a wavefront per weight set of proj / qkv
     static constexpr int RS = PT * WNG * 32;                       // weight rows of such a set
     static constexpr int NPROJ = C / RS, NQKV = 3 * C / RS;
-    static constexpr int G16 = (P & 15) == 0 ? 16 : (P & 7) == 0 ? 8 : (P & 3) == 0 ? 4 : (P & 1) == 0 ? 2 : 1;     // gcd(P, 16)
+    static constexpr int G16 = gcd16(P);
     static constexpr int SETR = RS * C, SET1 = FC * C;             // bytes of a set of proj / qkv, of fc1 and fc2
     static constexpr int SETW = SETR > SET1 ? SETR : SET1;
     static constexpr int CW = (RS > FC ? RS + 63 : FC + 63) / 64;  // wavefronts that fetch the constants of a set's rows, 64 each
@@ -70,21 +61,6 @@ struct TbLayout {
     static_assert(C % RS == 0 && SETW >= M * C && (NPROJ == 1 || NPROJ == 3) && NQKV % 2 == 1, "sets");
     static_assert(TOTAL <= 160 * 1024, "LDS");
 };
-
-// XOR applied to the piece number of row r of a tile of P 16-byte pieces per row, so that the same piece of 16 consecutive
-// rows meets every bank group once.
-template <int G16> __device__ __forceinline__ int swz(int r) { return (r / (16 / G16)) & (G16 - 1); }
-
-// Requantisation constants of a channel, 16 bytes in the tables that table_kernel prepares.
-//   Rq     24-bit form (derivation in gemm_rs.hip); lo > hi: the channel needs the general form
-//   Rq64   residual layers: b and h of Residual64 (regst_common.hpp), the first term at most 2^30; b = 0: the channel needs
-//          the general form.  Bytes 4 .. 7 of the entry are unused.
-struct Rq { int32_t lo, hi, mb, ad; };
-using Rq64 = Residual64;
-
-// median of three as the pattern the compiler turns into one v_med3_i32
-__device__ __forceinline__ int32_t med3c(int32_t v, int32_t lo, int32_t hi) { return max(min(v, lo), min(max(v, lo), hi)); }
-template <class T> __device__ __forceinline__ void pin(T& v) { asm volatile("" : "+v"(v)); }      // keeps a value's computation in its place
 
 // The constants of up to MAXJ layers: one thread per channel, one row of workgroups per layer.  Prepared by a launch of
 // its own because the two divisions per channel, done by every workgroup for every channel, cost the block kernel more
@@ -261,7 +237,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     // 1653 -> 1506; requested all at once at the start, where the first barrier waits for it, DeiT-T batch 128 544 instead of 522.
     const uint32_t warm_n = min(max(gridDim.x / 8, 1u), 32u), warm_i = blockIdx.x / 8;
     auto warm = [&](const int8_t* p, uint32_t bytes) __attribute__((always_inline)) {
-        if (warm_i < warm_n)
+        if (warm_n >= 4 && warm_i < warm_n)
             for (uint32_t at = (warm_i * 64 * NW + 64 * wv + fresh_lane()) * 128; at < bytes; at += warm_n * 64 * NW * 128)
                 dma4(uniform_ptr(p), at, lds0 + LY::SINK);
     };
@@ -323,23 +299,6 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
         *reinterpret_cast<v4i*>(act + (32 * tt + out_row) * C + 16 * ((2 * ct + d_o) ^ out_xor)) = w;
     };
 
-    struct ResRq { int32_t b, c, h; bool ok; };
-    auto make_res = [](Dyadic d) __attribute__((always_inline)) -> ResRq {
-        return ResRq{d.b, d.c, 1 << ((d.c - 1) & 31), d.b >= 1 && d.b < (1 << 23) && d.c >= 1 && d.c <= 30};
-    };
-    auto pack4 = [](const uint32_t (&o)[4], auto low_c) __attribute__((always_inline)) -> int {
-        constexpr bool low = decltype(low_c)::value;
-        const uint32_t p01 = __builtin_amdgcn_perm(o[1], o[0], low ? 0x0c0c0400u : 0x0c0c0703u);
-        const uint32_t p23 = __builtin_amdgcn_perm(o[3], o[2], low ? 0x04000c0cu : 0x07030c0cu);
-        return (int)(p01 | p23);
-    };
-    // one result, 24-bit form
-    auto out_top = [](int32_t a, const Rq& q) __attribute__((always_inline)) -> uint32_t { return (uint32_t)(__mul24(med3c(a, q.lo, q.hi), q.mb) + q.ad); };
-    // one result of a residual layer: one 64-bit multiply-add, the residual term, the sum limited (it fits
-    // 32 bits: at most 2^30 from channels with a 32-bit form, see table_kernel, and 2^29 from the residual)
-    auto out_res = [](int32_t a, const Rq64& q, const ResRq& rr, int32_t res) __attribute__((always_inline)) -> uint32_t {
-        return (uint32_t)clamp8(residual64_first(a, q) + ((__mul24(res, rr.b) + rr.h) >> rr.c));
-    };
     // a lane's 16 results of a tile in 64-bit arithmetic, channel ch of W; results in the low byte
     auto unit_slow = [&](const v16i& a, const DenseW& W, int ch, bool gelu) __attribute__((always_inline)) -> v4i {
         const int32_t b = W.rq_b[ch], c = W.rq_c[ch], bias = W.bias ? W.bias[ch] : 0;
@@ -352,7 +311,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
                 o[r] = (uint32_t)clamp8_64(rnd_shift64(a[4 * d + r] + bias, b, c));
                 if (gelu) o[r] = (uint32_t)(uint8_t)lds[LY::LUT + (o[r] & 0xffu)];
             }
-            w[d] = pack4(o, std::true_type());
+            w[d] = pack4<true>(o);
         }
         return w;
     };
@@ -370,7 +329,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
                 const int tok = min(32 * tt + (perm ? 16 * lg + 4 * d : 8 * d + 4 * lg) + r, rows - 1);
                 o[r] = (uint32_t)clamp8_64(rnd_shift64(sum_of(a[4 * d + r], bias, kSumStart), b, c) + rnd_shift64(res[(m0 + tok) * C + ch], rr.b, rr.c));
             }
-            w[d] = pack4(o, std::true_type());
+            w[d] = pack4<true>(o);
         }
         return w;
     };
@@ -444,7 +403,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
                         const int32_t xe = (int32_t)(int8_t)((uint32_t)v[k][j][d] >> (8 * r));
                         o[r] = (uint32_t)ln_value(xe, row[k], g[d][r], b[d][r], c_shift);
                     }
-                    w[d] = pack4(o, std::true_type());
+                    w[d] = pack4<true>(o);
                 }
                 if (dst) __builtin_amdgcn_raw_buffer_store_b128(w, db, tok * C + 16 * (q + LPR * j), 0, 0);
                 *reinterpret_cast<v4i*>(act + i * C + 16 * ((q + LPR * j) ^ swz<G16>(i))) = w;
@@ -506,12 +465,6 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     v2i rw[2] = {}, rwn[2] = {};
     bool fast = false;
     auto cst_at = [&](int b, int row) __attribute__((always_inline)) -> v4i { return *reinterpret_cast<const v4i*>(set_at(b) + SETW + 16 * row); };
-    auto as_rq = [](const v4i& v) __attribute__((always_inline)) -> Rq { return Rq{v[0], v[1], v[2], v[3]}; };
-    auto as_rq64 = [](const v4i& v) __attribute__((always_inline)) -> Rq64 {
-        Rq64 q{(uint32_t)v[0], ((uint64_t)(uint32_t)v[3] << 32) | (uint32_t)v[2]};
-        pin(q.h);
-        return q;
-    };
     const int8_t* const tab = P.table;
 
     if (front) {
@@ -540,7 +493,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
             else {
                 if constexpr (e == 0) { rw[0] = rwn[0]; rw[1] = rwn[1]; }
                 eo[e & 3] = out_res(pa[par][t][e], pq, rr1, (int32_t)(int8_t)((uint32_t)rw[e >> 3][(e >> 2) & 1] >> (8 * (e & 3))));
-                if constexpr ((e & 3) == 3) { int w = pack4(eo, std::true_type()); pin(w); ew[e >> 2] = w; }
+                if constexpr ((e & 3) == 3) { int w = pack4<true>(eo); pin(w); ew[e >> 2] = w; }
                 if constexpr (e == 8 && t + 1 < TT) proj_res(g, t + 1);
                 if constexpr (e == 3 && t > 0) es = stg_get();
                 if constexpr (e == 11 && t > 0) act_put(wm * TT + t - 1, ct_of(g), es);
@@ -572,7 +525,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
                         if constexpr (LY::NPROJ == 1 || s == 0) warm(P.fc1.w, F * C);
                         if constexpr (LY::NPROJ == 1 || s == 1) warm(P.fc2.w, F * C);
                         if constexpr (s + 1 == LY::NPROJ) {
-                            warm(P.table, TB_QKV(C, F) + 48 * C);
+                            warm(P.table, TB_BYTES(C, F));
                             if (P.next == 2) warm(P.qkv_w.w, 3 * C * C);
                         }
                     }
@@ -640,7 +593,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
             constexpr int i = decltype(i_c)::value, j = i - LAG, u0 = decltype(u0_c)::value;
             if constexpr (j >= 0 && (j & 3) == 3) {
                 const uint32_t o[4] = {gl[(j - 3) % (LAG + 4)], gl[(j - 2) % (LAG + 4)], gl[(j - 1) % (LAG + 4)], gl[j % (LAG + 4)]};
-                int w = pack4(o, std::true_type());
+                int w = pack4<true>(o);
                 pin(w);
                 ew[(j >> 2) & 3] = w;
                 if constexpr ((j & 15) == 15) *reinterpret_cast<v4i*>(h_at(hbuf, u0 + j / 16)) = ew;
@@ -804,7 +757,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
             static_for<16>([&](auto e_c) __attribute__((always_inline)) {
                 constexpr int e = decltype(e_c)::value;
                 eo[e & 3] = out_res(acc[u / TT][u % TT][e], fq[u / TT], rr2, (int32_t)(int8_t)((uint32_t)rw[e >> 3][(e >> 2) & 1] >> (8 * (e & 3))));
-                if constexpr ((e & 3) == 3) ew[e >> 2] = pack4(eo, std::true_type());
+                if constexpr ((e & 3) == 3) ew[e >> 2] = pack4<true>(eo);
             });
             if constexpr (u > 0) f2_put(u - 1, es);
             stg_put(ew, std::false_type());
@@ -824,7 +777,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
         load_range(L, ic<0>(), ic<NPR>(), BR());
         sync();
         warm(P.qkv_w.w, 3 * C * C);
-        warm(P.table, TB_QKV(C, F) + 48 * C);
+        warm(P.table, TB_BYTES(C, F));
     }
     if (!P.next) {                                                  // only the block's output leaves
         constexpr int NI = M * PP / 64;
@@ -880,7 +833,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
         else if constexpr (i == NOT + 1) qkv_put(g, TT - 1, es, fast);
         else {
             eo[e & 3] = out_top(pa[par][t][e], rq);
-            if constexpr ((e & 3) == 3) { int w = pack4(eo, std::false_type()); pin(w); ew[e >> 2] = w; }
+            if constexpr ((e & 3) == 3) { int w = pack4<false>(eo); pin(w); ew[e >> 2] = w; }
             if constexpr (e == 3 && t > 0) es = stg_get();
             if constexpr (e == 11 && t > 0) qkv_put(g, t - 1, es, fast);
             if constexpr (e == 15) stg_put(ew, std::true_type());
@@ -944,10 +897,11 @@ hipError_t launch_tb(hipStream_t s, const TokenBlockArgs& a) {
 
 bool token_block_takes(int C, int F, int64_t R) {
     // C = 384: with few tiles a CU spends its time on fetching the layers' 1.7 MB of weights through one workgroup; the
-    // separate kernels spread each layer over the chip.  Whole forwards, fused against separate: DeiT-S batch 1 533 against
-    // 421 us, 16 (3152 rows) 538 against 509, 24 (4728 rows) 570 against 556, 32 (6304 rows) 591 against 661.
-    // A little more than one full round of workgroups (see launch_token_block) is where the separate kernels win once more:
-    // DeiT-S batch 168 (33096 rows) 1737 against 1642 us, 184 (36248) 1861 against 1858, 192 (37824) 1930 against 1988.
+    // separate kernels spread each layer over the chip.  Whole forwards, fused against separate, F = 4 C (token_stream.hip): DeiT-S
+    // batch 4 378 against 350 us, 6 (1182 rows) 368 against 372, 8 (1576) 367 against 382, 16 382 against 452, 25 413 against 542.
+    // Other F: DeiT-S's sizes in the form with shared sets, batch 24 (4728 rows) 570 against 556, 32 (6304) 591 against 661.
+    // What is left beyond full rounds of tiles is cheap in the form for few rows: batch 168 (33096 rows, 328 of them beyond) 1481
+    // against 1567 us with separate kernels, 184 (36248) 1567 against 1731.
     // A workgroup walks the F / 128 chunks of the MLP one after the other, where a separate layer spreads them over the chip,
     // so a long MLP needs rows.  us a block, fused against separate: up to F = 4 C + 128 any number of rows (C = 96, F = 384,
     // 197 rows 24.2 against 24.4, F = 512 25.3 against 27.1; C = 192, F = 768 25.4 against 26.1, F = 896 28.3 against 30.1);
@@ -960,12 +914,11 @@ bool token_block_takes(int C, int F, int64_t R) {
         const int64_t need = (C == 96 ? 3 : 2) * (int64_t)F;
         if (R < (C == 384 ? need : std::min(need, 64 * (int64_t)num_cus()))) return false;
     }
-    const int64_t round = 128 * (int64_t)num_cus();
-    if (C == 384 && (R < 5120 || (R > round && R < round + round / 9))) return false;
+    if (C == 384 && R < (F == 4 * C ? 1300 : 5120)) return false;
     return (C == 96 || C == 192 || C == 384) && F >= 2 * FC && F % FC == 0 && R >= 1 && R < (1 << 30) && (int64_t)F * C < (1 << 30);
 }
 
-size_t token_block_table_bytes(int C, int F) { return (size_t)TB_QKV(C, F) + 48 * (size_t)C; }
+size_t token_block_table_bytes(int C, int F) { return (size_t)TB_BYTES(C, F); }
 
 hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n) {
     TableJobs J;
@@ -999,7 +952,10 @@ hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a) {
     const int64_t per_row = (a.o ? (int64_t)a.C * a.C + 2LL * a.C * a.F : 0) + (a.next == 2 ? 3LL * a.C * a.C : 0);
     const int64_t row_bytes = (int64_t)a.C * ((a.o ? 3 : 1) + (a.next == 2 ? 3 : a.next == 1 ? 1 : 0));
     auto tile = [&](const TokenBlockArgs& t) -> hipError_t {
-        TraceScope trace(s, KIND_TOKEN_BLOCK, 2 * t.R * per_row, per_row + t.R * row_bytes);
+        TraceScope trace(s, t.C == 384 && t.R < 20 * cus ? KIND_TOKEN_FEW : KIND_TOKEN_BLOCK, 2 * t.R * per_row, per_row + t.R * row_bytes);
+        // (us a launch, form with shared sets against the one for few rows: C = 384, 5122 rows 34.3 against 27.9, 8077 rows 38.0
+        // against 32.8; C = 192, forwards of DeiT-T, batch 8 298 against 202, 40 330 against 237, 64 376 against 349, 83 396 against 366)
+        if (token_stream_takes(t.C, t.F, t.R)) return launch_token_stream(s, t);
         if (t.C == 384) {
             if (t.R <= 32 * cus) return launch_tb<384, 1, 4>(s, t);
             if (t.R <= 64 * cus) return launch_tb<384, 2, 8>(s, t);

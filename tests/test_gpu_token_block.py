@@ -149,3 +149,22 @@ def test_two_wavefronts_on_a_simd_store_what_they_computed(ivit, C, H, F, R):
         y.zero_()
         ivit.ivit_forward(xd, y, bl, d, ws)
         assert torch.equal(y, wd)
+
+
+@pytest.mark.parametrize("C,H,R", [(384, 6, 1299), (384, 6, 1300), (384, 12, 1343), (384, 6, 8192), (192, 3, 31), (192, 6, 8160),
+                                   (192, 3, 8191), (192, 3, 8225), (192, 3, 16383), (192, 3, 16384)])
+@pytest.mark.parametrize("regime", ["as drawn", "general", "mixed", "no_bias"])
+def test_few_rows(ivit, C, H, R, regime):
+    """token_stream.hip at the edges of its range and of its tiles (32 tokens, 64 beyond 32 a CU), all requantisation forms."""
+    d = dict(B=R, T=1, C=C, H=H, F=4 * C)
+    cfg, blocks = _blocks(C, H, 4 * C, 1, 2, regime)
+    got, want = _run(ivit, d, synth.make_rows(9 + R, R, C), blocks, synth.make_final_ln(cfg) if R % 2 else None)
+    assert np.array_equal(got, want)
+
+
+def test_few_rows_against_the_oracle(ivit):
+    C, H, T, B = 192, 3, 65, 2
+    cfg, blocks = _blocks(C, H, 4 * C, T, 1, "as drawn")
+    x = synth.make_rows(4, B * T, C)
+    got, _ = _run(ivit, dict(B=B, T=T, C=C, H=H, F=4 * C), x, blocks, None)
+    assert np.array_equal(got, orc.forward(x, blocks, dict(B=B, T=T, C=C, H=H, F=4 * C)))
