@@ -2,7 +2,7 @@
 // 2207.01405, Sec. 3.2, Eq. 7-10) fused into the epilogue, optionally with the residual add of Eq. 1-2 or with ShiftGELU
 // (Sec. 3.4, Algorithm 2) and its rescale: the form for any K % 16 == 0, any N and any number of rows.
 //
-// A workgroup (256 threads = 2 x 2 wavefronts) computes one tile of 64 MT tokens x 64 NT channels.  Both operands stream
+// A workgroup of GM x GN wavefronts (2 x 2 or eight) computes one tile of 32 MT GM tokens x 32 NT GN channels.  Both operands stream
 // through S LDS stages of 128 bytes of K, filled by LDS-direct loads S - 1 stages ahead (no register pass, one barrier
 // per stage); 16-byte pieces of a row are permuted by an XOR with bits of the row number, which costs the loads nothing
 // and spreads the fragment reads over the banks.  Several workgroups share a compute unit, so one's prologue and
@@ -47,15 +47,16 @@ template <int N> __device__ __forceinline__ void arrive() {
 // XS > 0: the rows of x are normalised first (I-LayerNorm, Sec. 3.5, Eq. 19-20).  The token rows of the tile, all of K
 // (K <= 128 XS), are fetched at once and stay in LDS, where they are normalised in place; only the weights stream.  Every
 // workgroup of a row of tiles repeats that work, so the four wavefronts stand side by side: 32 tokens x 128 channels.
-template <int MT, int NT, int XS> struct StTile {
-    static constexpr int WGM = XS > 0 ? 1 : 2, WGN = 4 / WGM, TM = 32 * MT * WGM, TN = 32 * NT * WGN;
+template <int MT, int NT, int XS, int GM = 2, int GN = 2> struct StTile {
+    static constexpr int WGM = XS > 0 ? 1 : GM, WGN = XS > 0 ? 4 : GN, W = WGM * WGN, TM = 32 * MT * WGM, TN = 32 * NT * WGN;
+    static_assert(TM % (8 * W) == 0 && TN % (8 * W) == 0 && W % 2 == 0, "a load instruction of all wavefronts fills rows of one operand");
 };
 
-template <int EPI, int MT, int NT, int S, int XS>
-__global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
-    using TL = StTile<MT, NT, XS>;
-    constexpr int TM = TL::TM, TN = TL::TN, XI = TM / 32;
-    constexpr int DPX = XS > 0 ? 0 : XI, DPW = DPX + TN / 32;           // load instructions of a wavefront and streamed stage: of x, in all
+template <int EPI, int MT, int NT, int S, int XS, int GM, int GN>
+__global__ __launch_bounds__((64 * StTile<MT, NT, XS, GM, GN>::W), 2) void gemm_st_kernel(StParams P) {
+    using TL = StTile<MT, NT, XS, GM, GN>;
+    constexpr int W = TL::W, TM = TL::TM, TN = TL::TN, XI = XS > 0 ? TM / 32 : TM / (8 * W), WI = TN / (8 * W);
+    constexpr int DPX = XS > 0 ? 0 : XI, DPW = DPX + WI;           // load instructions of a wavefront and streamed stage: of x, in all
     constexpr int XB = XS * TM * BK, WR = XS > 0 ? 0 : TM, STG = (WR + TN) * BK;    // resident bytes of x; rows of x in a streamed stage
     __shared__ __align__(16) int8_t lds[XB + S * STG];
     __shared__ __align__(16) int32_t qb_s[TN], qc_s[TN], bias_s[TN];
@@ -110,21 +111,21 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
     }
 
     // (32-bit offsets from the tile's first row: linear_rows_per_launch sees to it that they are enough)
-    // Load instruction i of a wavefront fills LDS rows 32 i + r, r = 8 wavefront + lane / 8, eight lanes a row; the lane
+    // Load instruction i of a wavefront fills LDS rows 8 W i + r, r = 8 wavefront + lane / 8, eight lanes a row; the lane
     // lands in physical piece lane % 8 and fetches piece (lane % 8) ^ ((r / 2) % 8).  Rows past the last token or channel
     // repeat it (never stored), pieces past the end of a row its last piece (never multiplied, see below).
     const int ld_r = 8 * wv + (lane >> 3), ld_col = 16 * ((lane & 7) ^ ((ld_r >> 1) & 7));
     const int8_t* xg = uniform_ptr(P.x + m0 * P.ldx);
     const int8_t* wg = uniform_ptr(P.w + (int64_t)n0 * K);
-    uint32_t off[XI + TN / 32];
+    uint32_t off[XI + WI];
 #pragma unroll
-    for (int i = 0; i < XI + TN / 32; ++i) {
+    for (int i = 0; i < XI + WI; ++i) {
         if (i < XI) {
-            off[i] = (uint32_t)min(32 * i + ld_r, rows - 1) * (uint32_t)P.ldx + ld_col;
+            off[i] = (uint32_t)min(8 * W * i + ld_r, rows - 1) * (uint32_t)P.ldx + ld_col;
         } else {
             // row 8 q + 4 g + r of MFMA tile ct holds channel 16 NT g + 16 ct + 4 q + r of the wavefront's 32 NT: that is
             // accumulator register 4 q + r of lane group g
-            const int R = 32 * (i - XI) + ld_r, ct = (R >> 5) % NT, rr = R & 31;
+            const int R = 8 * W * (i - XI) + ld_r, ct = (R >> 5) % NT, rr = R & 31;
             const int ch = (R / (32 * NT)) * 32 * NT + 16 * NT * ((rr >> 2) & 1) + 16 * ct + 4 * (rr >> 3) + (rr & 3);
             off[i] = (uint32_t)min(ch, N - 1 - n0) * (uint32_t)K + ld_col;
         }
@@ -151,12 +152,12 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
     uint32_t k_off = 0;
     auto issue_one = [&](auto i_c, auto buf_c) __attribute__((always_inline)) {
         constexpr int i = decltype(i_c)::value;
-        load_lds<decltype(buf_c)::value * STG + i * 4096>(i < DPX ? x_buf : w_buf, off[XI - DPX + i], k_off, lds0);
+        load_lds<decltype(buf_c)::value * STG + i * W * 1024>(i < DPX ? x_buf : w_buf, off[XI - DPX + i], k_off, lds0);
     };
     auto issue_begin = [&]() __attribute__((always_inline)) {
         if (is == moves) {
 #pragma unroll
-            for (int i = XI - DPX; i < XI + TN / 32; ++i) off[i] -= back;
+            for (int i = XI - DPX; i < XI + WI; ++i) off[i] -= back;
         }
     };
     auto issue_done = [&]() __attribute__((always_inline)) { ++is; k_off += BK; };
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
             issue_done();
         }
     });
-    if (EPI == EPI_GELU) {
+    if (EPI == EPI_GELU && tid < 256) {
         const int32_t I = (int32_t)(int8_t)tid;
         gelu_lut[(uint8_t)(I + 128)] = (int8_t)requant64(shiftgelu_raw(I, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c, P.rnd);
     }
@@ -394,29 +395,30 @@ __global__ __launch_bounds__(256, 2) void gemm_st_kernel(StParams P) {
     if (fast) finish(std::true_type()); else finish(std::false_type());
 }
 
-template <int MT, int NT, int S, int XS>
+template <int MT, int NT, int S, int XS, int GM = 2, int GN = 2>
 hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
     StParams P;
     P.x = a.x; P.w = a.w; P.bias = a.bias; P.rq_b = a.rq_b; P.rq_c = a.rq_c;
     P.residual = a.residual; P.res_rq = a.res_rq; P.gelu_p = a.gelu_p; P.gelu_rq = a.gelu_rq;
     P.y = a.y; P.M = a.M; P.N = a.N; P.K = a.K; P.ldx = a.ldx ? a.ldx : a.K; P.rnd = a.floor_shift ? 0 : 1;
     P.ln_g = a.ln_g; P.ln_b = a.ln_b; P.ln_f = a.ln_f; P.ln_c = a.ln_c;
-    constexpr int TM = StTile<MT, NT, XS>::TM, TN = StTile<MT, NT, XS>::TN;
+    using TL = StTile<MT, NT, XS, GM, GN>;
+    constexpr int TM = TL::TM, TN = TL::TN;
     static_assert(TM <= kTileRows, "row offsets");
     const int64_t tm = (a.M + TM - 1) / TM, tn = (a.N + TN - 1) / TN, grid = (tm * tn + NXCD - 1) / NXCD * NXCD;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     P.m_fast = a.M < a.N;
     P.inner = FastDiv((uint32_t)(P.m_fast ? tm : tn));
     P.tiles = (uint32_t)(tm * tn); P.per_xcd = (uint32_t)(grid / NXCD);
-    const dim3 g((unsigned)grid), b(256);
+    const dim3 g((unsigned)grid), b(64 * TL::W);
     if constexpr (XS == 0) {
         if (a.residual) {
-            hipLaunchKernelGGL((gemm_st_kernel<EPI_RESIDUAL, MT, NT, S, XS>), g, b, 0, s, P);
+            hipLaunchKernelGGL((gemm_st_kernel<EPI_RESIDUAL, MT, NT, S, XS, GM, GN>), g, b, 0, s, P);
             return hipGetLastError();
         }
     }
-    if (a.gelu) hipLaunchKernelGGL((gemm_st_kernel<EPI_GELU, MT, NT, S, XS>), g, b, 0, s, P);
-    else hipLaunchKernelGGL((gemm_st_kernel<EPI_PLAIN, MT, NT, S, XS>), g, b, 0, s, P);
+    if (a.gelu) hipLaunchKernelGGL((gemm_st_kernel<EPI_GELU, MT, NT, S, XS, GM, GN>), g, b, 0, s, P);
+    else hipLaunchKernelGGL((gemm_st_kernel<EPI_PLAIN, MT, NT, S, XS, GM, GN>), g, b, 0, s, P);
     return hipGetLastError();
 }
 
@@ -446,6 +448,19 @@ hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
     // 64 x 64 with three stages against four (three workgroups per CU against two): 10.2 against 12.4 us.
     if (a.kernel == LINEAR_MANY_ROWS) return launch_tile<2, 2, 2, 0>(s, a);
     const int64_t tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64), cus = num_cus();
+    // Rows of 768 bytes and more: where some tile gives every CU at most one workgroup, the smallest such tile, with the stages that
+    // fit and eight wavefronts for the larger ones (a SIMD issues twice as much from two).  Inputs in turn, us, the rule below against
+    // this one: 64 x 64 with four stages for three 394 x 768 x 3072 9.4 and 8.2, 788 x 384 x 1536 6.4 and 6.0, 788 x 768 x 768 5.1
+    // and 5.0 (six stages 5.2; 1568 x 384 x 384 3.9 and 4.0); 128 x 64 1576 x 768 x 3072 12.0 and 10.9, 2364 x 768 x 3072 13.3 and
+    // 11.3, 788 x 2304 x 768 5.5 and 5.3 (1568 x 1152 x 384 4.35 and 4.42); 128 x 128 1576 x 2304 x 768 7.9 and 7.0, 4000 x 768 x
+    // 3072 18.5 and 15.5 (1568 x 1536 x 384 5.3 and 5.7).  Beyond one workgroup a CU they lose: 3152 x 768 x 3072 with 128 x 64 19.3
+    // against 16.4, 1576 x 3072 x 768 with 128 x 128 12.1 against 9.1.
+    if (a.K >= 768) {
+        const int64_t tm = (a.M + 127) / 128, tn = (a.N + 63) / 64;
+        if (tiles <= cus) return launch_tile<1, 1, 4, 0>(s, a);
+        if (tm * tn <= cus) return launch_tile<1, 1, 4, 0, 4, 2>(s, a);
+        if (tm * ((tn + 1) / 2) <= cus) return launch_tile<2, 1, 3, 0, 2, 4>(s, a);
+    }
     if (2 * tiles <= 5 * cus) return launch_tile<1, 1, 3, 0>(s, a);
     if (tiles * (a.K > 1024 ? 2 : 1) <= 6 * cus) return launch_tile<2, 1, 2, 0>(s, a);
     return launch_tile<2, 2, 2, 0>(s, a);

@@ -113,6 +113,24 @@ def test_larger_tiles(ivit, M, N, K, epi, regime):
     assert np.array_equal(got[rows], orc.linear_requant(host[0][rows], *host[1:], **kw_o))
 
 
+# Rows of 768 bytes and more and at most one tile a CU: 64 x 64 (more 32 x 32 tiles than gemm_kq.hip takes), 128 x 64, 128 x 128; last
+# stages of 16 to 128 bytes, fewer stages than buffers cannot be
+@pytest.mark.parametrize("M,N,K,tile", [(500, 1000, 784, (64, 64)), (449, 1009, 3072, (64, 64)), (1500, 760, 896, (128, 64)), (1665, 701, 1552, (128, 64)),
+                                        (129, 7300, 768, (128, 64)), (1500, 2290, 784, (128, 128)), (1409, 2177, 1024, (128, 128))])
+@pytest.mark.parametrize("epi", ["plain", "residual", "gelu"])
+@pytest.mark.parametrize("regime", ["as drawn", "general"])
+def test_one_tile_a_compute_unit(ivit, M, N, K, tile, epi, regime):
+    fits = [t for t in ((64, 64), (128, 64), (128, 128)) if -(-M // t[0]) * -(-N // t[1]) <= _cus()]
+    if _cus() == 256:
+        assert fits[0] == tile and -(-M // 32) * -(-N // 32) > (256 if K > 768 else 512)
+    host, kw_o, dev, kw_g = _case(M, N, K, epi, regime)
+    got = _run(ivit, dev, kw_g, M, N)
+    rows = _rows_of(M, 61)
+    if epi == "residual":
+        kw_o["residual"] = kw_o["residual"][rows]
+    assert np.array_equal(got[rows], orc.linear_requant(host[0][rows], *host[1:], **kw_o))
+
+
 # QKV, or QKV and the first MLP layer, past the kernel for few rows; widths of both forms (to 384 and to 768 bytes a row)
 @pytest.mark.parametrize("C,H,F,B,T", [(64, 2, 256, 43, 65), (128, 4, 400, 56, 25), (160, 5, 464, 18, 65), (384, 6, 1536, 8, 59), (416, 13, 1232, 7, 65),
                                        (736, 23, 2000, 4, 65), (768, 12, 3072, 2, 130)])
