@@ -395,6 +395,8 @@ __global__ __launch_bounds__((64 * StTile<MT, NT, XS, GM, GN>::W), 2) void gemm_
     if (fast) finish(std::true_type()); else finish(std::false_type());
 }
 
+constexpr int64_t kBigRows = 256;              // rows of the tallest tile of all, taken only where its offsets fit (big_tiles)
+
 template <int MT, int NT, int S, int XS, int GM = 2, int GN = 2>
 hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
     StParams P;
@@ -404,14 +406,15 @@ hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
     P.ln_g = a.ln_g; P.ln_b = a.ln_b; P.ln_f = a.ln_f; P.ln_c = a.ln_c;
     using TL = StTile<MT, NT, XS, GM, GN>;
     constexpr int TM = TL::TM, TN = TL::TN;
-    static_assert(TM <= kTileRows, "row offsets");
+    constexpr bool BIG = MT * NT == 8;         // (no registers for a residual: 300 bytes a lane would be spilled)
+    static_assert(TM <= (BIG ? kBigRows : kTileRows), "row offsets");
     const int64_t tm = (a.M + TM - 1) / TM, tn = (a.N + TN - 1) / TN, grid = (tm * tn + NXCD - 1) / NXCD * NXCD;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     P.m_fast = a.M < a.N;
     P.inner = FastDiv((uint32_t)(P.m_fast ? tm : tn));
     P.tiles = (uint32_t)(tm * tn); P.per_xcd = (uint32_t)(grid / NXCD);
     const dim3 g((unsigned)grid), b(64 * TL::W);
-    if constexpr (XS == 0) {
+    if constexpr (XS == 0 && !BIG) {
         if (a.residual) {
             hipLaunchKernelGGL((gemm_st_kernel<EPI_RESIDUAL, MT, NT, S, XS, GM, GN>), g, b, 0, s, P);
             return hipGetLastError();
@@ -435,6 +438,20 @@ bool linear_ln_takes(const LinearArgs& a) {
     using TL = StTile<1, 1, 6>;
     return !a.residual && (a.K & 15) == 0 && a.K >= 64 && a.K <= 768 &&
            ((a.M + TL::TM - 1) / TL::TM) * ((a.N + TL::TN - 1) / TL::TN) <= 2 * num_cus();
+}
+
+// 256 x 256 tiles, eight wavefronts of 128 x 64, one workgroup a CU, against 128 x 128 tiles, two workgroups of four wavefronts a CU: six
+// fragments from LDS for eight products instead of four for four, and half the loads.  A round of the larger ones is twice the
+// work of a round of the smaller, so what decides is how many rounds either takes; up to 6 : 5 against them the larger ones win, from
+// 4 : 3 on they lose.  us, 128 x 128 and 256 x 256, rounds in units of the smaller: 10 : 10 40000 x 2000 x 896 108 and 93, 8000 x 2000 x
+// 640 15.8 and 15.0, 12000 x 1040 x 400 14.3 and 12.3; 13 : 14 50000 x 2056 x 560 113 and 100; 7 : 8 50000 x 1000 x 1200 97 and 96; 5 : 6 20000 x
+// 2000 x 2000 121 and 100, 12000 x 3000 x 2800 with ShiftGELU 146 and 123, 40000 x 1024 x 448 34.2 and 32.9; 3 : 4 12000 x 2000 x
+// 448 23.1 and 24.0, 40000 x 512 x 576 21.5 and 24.2.  Not for one stage (30000 x 1000 x 96 19.8 and 21.2).
+static bool big_tiles(const LinearArgs& a) {
+    if (a.residual || a.K <= BK || (kBigRows - 1) * (a.ldx ? a.ldx : (int64_t)a.K) + a.K > (int64_t)kTileBytes) return false;
+    const int64_t cus = num_cus();
+    auto rounds = [&](int64_t t, int64_t per_cu) { return (((a.M + t - 1) / t) * ((a.N + t - 1) / t) + per_cu * cus - 1) / (per_cu * cus); };
+    return 10 * rounds(kBigRows, 1) <= 6 * rounds(128, 2);
 }
 
 hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
@@ -463,6 +480,7 @@ hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
     }
     if (2 * tiles <= 5 * cus) return launch_tile<1, 1, 3, 0>(s, a);
     if (tiles * (a.K > 1024 ? 2 : 1) <= 6 * cus) return launch_tile<2, 1, 2, 0>(s, a);
+    if (big_tiles(a)) return launch_tile<4, 2, 2, 0, 2, 4>(s, a);
     return launch_tile<2, 2, 2, 0>(s, a);
 }
 

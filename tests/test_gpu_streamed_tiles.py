@@ -113,6 +113,24 @@ def test_larger_tiles(ivit, M, N, K, epi, regime):
     assert np.array_equal(got[rows], orc.linear_requant(host[0][rows], *host[1:], **kw_o))
 
 
+# 256 x 256 tiles: a row or a channel beyond a tile, N at any alignment, last stages of 16 bytes to whole ones, more channels than rows, more
+# tiles than CUs.  Every result against the 128 x 128 tiles or the weight slab, which take the shape when asked to.
+@pytest.mark.parametrize("M,N,K", [(7937, 1793, 144), (8191, 2047, 272), (8000, 2000, 640), (49999, 200, 400), (24001, 391, 304), (1793, 7937, 160),
+                                   (40000, 1001, 336), (12000, 1040, 400), (16000, 1600, 1008)])
+@pytest.mark.parametrize("epi", ["plain", "gelu"])
+@pytest.mark.parametrize("regime,rounding", [("as drawn", "nearest"), ("general", "floor"), ("no bias", "nearest")])
+def test_largest_tiles(ivit, M, N, K, epi, regime, rounding):
+    cus = _cus()
+    rounds = lambda t, per_cu: -(-(-(-M // t) * -(-N // t)) // (per_cu * cus))
+    if cus == 256:
+        assert 10 * rounds(256, 1) <= 6 * rounds(128, 2) and -(-M // 64) * -(-N // 64) > 7 * cus
+    host, kw_o, dev, kw_g = _case(M, N, K, epi, regime)
+    got = _run(ivit, dev, kw_g, M, N, rounding=rounding)
+    assert np.array_equal(got, _run(ivit, dev, kw_g, M, N, rounding=rounding, kernel="many_rows"))
+    rows = np.unique(np.concatenate([np.arange(0, 256, 5), np.arange(M - 40, M), np.arange(0, M, 251)]))
+    assert np.array_equal(got[rows], orc.linear_requant(host[0][rows], *host[1:], floor_shift=rounding == "floor", **kw_o))
+
+
 # Rows of 768 bytes and more and at most one tile a CU: 64 x 64 (more 32 x 32 tiles than gemm_kq.hip takes), 128 x 64, 128 x 128; last
 # stages of 16 to 128 bytes, fewer stages than buffers cannot be
 @pytest.mark.parametrize("M,N,K,tile", [(500, 1000, 784, (64, 64)), (449, 1009, 3072, (64, 64)), (1500, 760, 896, (128, 64)), (1665, 701, 1552, (128, 64)),
