@@ -519,6 +519,7 @@ hipError_t launch_linear(hipStream_t s, const LinearArgs& a) {
         // without one, 4100 x 768 (780): 4.4 against 5.3; 12544 x 576 (1764): 6.2 against 7.3 (with 128 x 64 tiles 7.2).
         const int64_t limit = !a.residual && a.K >= 384 && a.K < 1536 ? 7 : 4;
         if (((a.M + 63) / 64) * ((a.N + 63) / 64) <= limit * num_cus()) return launch_linear_st(s, a);
+        if (linear_st_one_round(a)) return launch_linear_st(s, a);
     }
     // weights in registers: K = 192 / 384 / 768 (K = 192, 100352 rows: QKV 39.4 -> 28.1 us, fc1 51.1 -> 36.0 us);
     // measured against the kernels below on the DeiT-S and ViT-B shapes it wins on the layers without a residual (QKV 27.1 -> 21.6 us,
@@ -534,13 +535,11 @@ hipError_t launch_linear(hipStream_t s, const LinearArgs& a) {
         return launch_linear_ks(s, a);
     int ncb, unit, nunits, pitch; size_t lds_bytes;
     const bool ws = ws_plan(a, ncb, unit, nunits, pitch, lds_bytes);
-    // rows too long for the weight-stationary kernels: 256 x 128 tiles with both operands streamed (gemm_tl.hip), when
-    // there are tiles for half the compute units at least (6272 x 768 x 3072, 150 tiles: 37.8 -> 31.2 us; with fewer
-    // tiles a launch is one tile's latency either way).  Its cost per tile outside the k-loop only pays off for long
-    // rows: on the 768-wide model it takes the second MLP layer (K = 3072) from 212 to 148 us and loses at K = 768 (QKV
-    // 174 against 124 us with 128 x 128 tiles, one per workgroup)
-    if (linear_tl_takes(a) && (a.kernel == LINEAR_BIG_TILES ||
-                               (a.kernel == LINEAR_AUTO && !ws && a.K >= 2048 && (a.M + 255) / 256 * (a.N / 128) >= num_cus() / 2)))
+    // rows too long for the weight-stationary kernels, and more of them than one round of 192 x 128 tiles takes: 256 x 128 tiles with both
+    // operands streamed (gemm_tl.hip).  Its cost per tile outside the k-loop only pays off for long rows: on the 768-wide model it
+    // takes the second MLP layer (K = 3072) from 212 to 148 us and loses at K = 768 (QKV 174 against 124 us with 128 x 128 tiles,
+    // one per workgroup)
+    if (linear_tl_takes(a) && (a.kernel == LINEAR_BIG_TILES || (a.kernel == LINEAR_AUTO && !ws && a.K >= 2048)))
         return launch_linear_tl(s, a);
     // Without a residual and with rows of more than 384 bytes, streamed tiles of 128 x 128 or 256 x 256 have overtaken the weight slab, which
     // reads activations once per slab and pads rows to 128 bytes.  us, slab and tiles: 12000 x 1040 x 400 16.9 and 12.3, 50000 x 208 x 432

@@ -395,7 +395,7 @@ __global__ __launch_bounds__((64 * StTile<MT, NT, XS, GM, GN>::W), 2) void gemm_
     if (fast) finish(std::true_type()); else finish(std::false_type());
 }
 
-constexpr int64_t kBigRows = 256;              // rows of the tallest tile of all, taken only where its offsets fit (big_tiles)
+constexpr int64_t kBigRows = 256;              // rows of the tallest tile of all, taken, as that of 192, only where its offsets fit
 
 template <int MT, int NT, int S, int XS, int GM = 2, int GN = 2>
 hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
@@ -407,7 +407,7 @@ hipError_t launch_tile(hipStream_t s, const LinearArgs& a) {
     using TL = StTile<MT, NT, XS, GM, GN>;
     constexpr int TM = TL::TM, TN = TL::TN;
     constexpr bool BIG = MT * NT == 8;         // (no registers for a residual: 300 bytes a lane would be spilled)
-    static_assert(TM <= (BIG ? kBigRows : kTileRows), "row offsets");
+    static_assert(TM <= (BIG ? kBigRows : MT == 3 ? 192 : kTileRows), "row offsets");
     const int64_t tm = (a.M + TM - 1) / TM, tn = (a.N + TN - 1) / TN, grid = (tm * tn + NXCD - 1) / NXCD * NXCD;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     P.m_fast = a.M < a.N;
@@ -454,6 +454,16 @@ static bool big_tiles(const LinearArgs& a) {
     return 10 * rounds(kBigRows, 1) <= 6 * rounds(128, 2);
 }
 
+// Rows of 1024 bytes and more, more 128 x 128 tiles than CUs and at most one of 192 x 128 a CU: eight wavefronts of 96 x 32, one workgroup a
+// CU (the last step of the rule in launch_linear_st).  us, what took the shape before and this: 128 x 128 tiles 4000 x 1536 x 1024 11.3
+// and 10.5, 2500 x 2304 x 1024 10.9 and 10.0, 4000 x 1536 x 2048 19.6 and 16.2; 256 x 128 tiles of gemm_tl.hip 6272 x 768 x 3072 26.2 and
+// 22.0, 8000 x 768 x 3072 26.5 and 23.6, 5000 x 1024 x 3072 27.0 and 23.2; the K-split kernel 6272 x 768 x 1536 14.3 and 11.4, 16000 x 384 x
+// 1536 17.4 and 15.4.  Not for shorter rows (1576 x 3072 x 768 9.6 either way, 1970 x 2304 x 768 8.9 and 9.0), and 256 x 128 tiles for
+// the next size up gain nothing (8000 x 1000 x 2048 21.1 and 21.3, 6600 x 900 x 1104 with a residual 17.1 and 18.3).
+bool linear_st_one_round(const LinearArgs& a) {
+    return !a.ln_g && a.K >= 1024 && ((a.M + 191) / 192) * ((a.N + 127) / 128) <= num_cus() && 191 * (a.ldx ? a.ldx : (int64_t)a.K) + a.K <= (int64_t)kTileBytes;
+}
+
 hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
     if (a.ln_g) return a.K <= 384 ? launch_tile<1, 1, 3, 3>(s, a) : launch_tile<1, 1, 3, 6>(s, a);
     // The tile grows with the number of 64 x 64 tiles: larger ones load less per multiply, smaller ones leave no CU idle and
@@ -476,7 +486,8 @@ hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
         const int64_t tm = (a.M + 127) / 128, tn = (a.N + 63) / 64;
         if (tiles <= cus) return launch_tile<1, 1, 4, 0>(s, a);
         if (tm * tn <= cus) return launch_tile<1, 1, 4, 0, 4, 2>(s, a);
-        if (tm * ((tn + 1) / 2) <= cus) return launch_tile<2, 1, 3, 0, 2, 4>(s, a);
+        if (tm * ((a.N + 127) / 128) <= cus) return launch_tile<2, 1, 3, 0, 2, 4>(s, a);
+        if (linear_st_one_round(a)) return launch_tile<3, 1, 3, 0, 2, 4>(s, a);
     }
     if (2 * tiles <= 5 * cus) return launch_tile<1, 1, 3, 0>(s, a);
     if (tiles * (a.K > 1024 ? 2 : 1) <= 6 * cus) return launch_tile<2, 1, 2, 0>(s, a);

@@ -52,6 +52,7 @@ bool linear_kq_takes(const LinearArgs& a);
 hipError_t launch_linear_kq(hipStream_t s, const LinearArgs& a);
 // Any shape, both operands streamed through LDS in small tiles (gemm_st.hip).
 hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a);
+bool linear_st_one_round(const LinearArgs& a);    // long rows and a tile for every CU at most: before the kernels for many rows
 bool linear_ln_takes(const LinearArgs& a);
 
 // The token-wise part of an encoder block in one kernel (token_block.hip).

@@ -149,6 +149,23 @@ def test_one_tile_a_compute_unit(ivit, M, N, K, tile, epi, regime):
     assert np.array_equal(got[rows], orc.linear_requant(host[0][rows], *host[1:], **kw_o))
 
 
+# 192 x 128 tiles: a row or a channel beyond a tile or just a whole one, last stages of 16 to 128 bytes, shapes that gemm_ks.hip and gemm_tl.hip
+# took before
+@pytest.mark.parametrize("M,N,K", [(6145, 801, 1040), (4033, 1281, 1552), (12200, 384, 1536), (2304, 2561, 1024), (24300, 129, 1136), (6272, 768, 3072)])
+@pytest.mark.parametrize("epi", ["plain", "residual", "gelu"])
+@pytest.mark.parametrize("regime", ["as drawn", "general"])
+def test_tiles_of_192_rows(ivit, M, N, K, epi, regime):
+    if _cus() == 256:
+        assert -(-M // 128) * -(-N // 128) > 256 >= -(-M // 192) * -(-N // 128)
+    host, kw_o, dev, kw_g = _case(M, N, K, epi, regime)
+    got = _run(ivit, dev, kw_g, M, N)
+    assert np.array_equal(got, _run(ivit, dev, kw_g, M, N, kernel="many_rows"))
+    rows = np.unique(np.concatenate([np.arange(0, 193, 3), np.arange(M - 40, M), np.arange(0, M, 251)]))
+    if epi == "residual":
+        kw_o["residual"] = kw_o["residual"][rows]
+    assert np.array_equal(got[rows], orc.linear_requant(host[0][rows], *host[1:], **kw_o))
+
+
 # QKV, or QKV and the first MLP layer, past the kernel for few rows; widths of both forms (to 384 and to 768 bytes a row)
 @pytest.mark.parametrize("C,H,F,B,T", [(64, 2, 256, 43, 65), (128, 4, 400, 56, 25), (160, 5, 464, 18, 65), (384, 6, 1536, 8, 59), (416, 13, 1232, 7, 65),
                                        (736, 23, 2000, 4, 65), (768, 12, 3072, 2, 130)])
