@@ -292,8 +292,7 @@ int ivit_window_attention_ex(void* stream, const int8_t* qkv, const int8_t* rel_
  * `capacity` entries) with, per launch in launch order: elapsed milliseconds, kind (1 I-LayerNorm, 2 Dense,
  * 3 Dense + residual, 4 Dense + ShiftGELU, 5 attention, 6 Shiftmax, 7 ShiftGELU, 8 token assembly, 9 patch-merging
  * gather, 10 mean pooling, 11 the token-wise layers of a block in one kernel, 12 the constants of such
- * launches prepared, 13 a launch of kind 11 of width 384 and fewer than 20 rows per compute unit), algorithmic
- * integer operations (2 per int8 multiply-accumulate; 0 for row-wise kernels)
+ * launches prepared), algorithmic integer operations (2 per int8 multiply-accumulate; 0 for row-wise kernels)
  * and algorithmic HBM bytes (each operand read once, each result written once); *count receives the number of
  * launches seen.
  * One trace at a time per process, not thread-safe; launches beyond max_launches make ivit_trace_end

@@ -26,7 +26,7 @@ EXPORTS = ("ivit_strerror", "ivit_build_id", "ivit_linear_requant", "ivit_shiftm
 
 KIND_NAMES = {1: "ilayernorm", 2: "gemm", 3: "gemm_residual", 4: "gemm_gelu", 5: "attention", 6: "shiftmax",
               7: "shiftgelu", 8: "embed_tokens", 9: "patch_merge_gather", 10: "mean_pool",
-              11: "gemm_token_block", 12: "gemm_token_tables", 13: "gemm_token_block_few_rows"}
+              11: "gemm_token_block", 12: "gemm_token_tables"}
 
 
 class ShiftParams(C.Structure):

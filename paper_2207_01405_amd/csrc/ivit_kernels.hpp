@@ -101,8 +101,7 @@ int num_cus();
 // Kinds of launches reported by the trace (ivit_trace_end); values are part of the C ABI.
 enum LaunchKind { KIND_ILAYERNORM = 1, KIND_GEMM = 2, KIND_GEMM_RESIDUAL = 3, KIND_GEMM_GELU = 4,
                   KIND_ATTENTION = 5, KIND_SHIFTMAX = 6, KIND_SHIFTGELU = 7, KIND_EMBED = 8, KIND_PATCH_MERGE = 9, KIND_MEAN_POOL = 10,
-                  KIND_TOKEN_BLOCK = 11, KIND_TOKEN_TABLES = 12,
-                  KIND_TOKEN_FEW = 13 };     // KIND_TOKEN_BLOCK of width 384 and fewer than 20 rows per CU: as long as its weights take to fetch
+                  KIND_TOKEN_BLOCK = 11, KIND_TOKEN_TABLES = 12 };
 
 // Brackets one kernel launch with two HIP events on its stream while a trace is active; otherwise a no-op.
 // ops = algorithmic integer operations (2 per int8 multiply-accumulate), bytes = algorithmic HBM bytes.

@@ -952,7 +952,7 @@ hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a) {
     const int64_t per_row = (a.o ? (int64_t)a.C * a.C + 2LL * a.C * a.F : 0) + (a.next == 2 ? 3LL * a.C * a.C : 0);
     const int64_t row_bytes = (int64_t)a.C * ((a.o ? 3 : 1) + (a.next == 2 ? 3 : a.next == 1 ? 1 : 0));
     auto tile = [&](const TokenBlockArgs& t) -> hipError_t {
-        TraceScope trace(s, t.C == 384 && t.R < 20 * cus ? KIND_TOKEN_FEW : KIND_TOKEN_BLOCK, 2 * t.R * per_row, per_row + t.R * row_bytes);
+        TraceScope trace(s, KIND_TOKEN_BLOCK, 2 * t.R * per_row, per_row + t.R * row_bytes);
         // (us a launch, form with shared sets against the one for few rows: C = 384, 5122 rows 34.3 against 27.9, 8077 rows 38.0
         // against 32.8; C = 192, forwards of DeiT-T, batch 8 298 against 202, 40 330 against 237, 64 376 against 349, 83 396 against 366)
         if (token_stream_takes(t.C, t.F, t.R)) return launch_token_stream(s, t);

@@ -107,8 +107,9 @@ def test_rows_beyond_full_rounds_of_workgroups(ivit, C, H, F, rows_per_cu, more)
 
 @pytest.mark.parametrize("C,H,F,R,fused", [(96, 3, 512, 197, True), (96, 3, 640, 1919, False), (96, 3, 640, 1920, True),
                                            (192, 3, 896, 197, True), (192, 3, 1024, 2047, False), (192, 3, 1024, 2048, True),
-                                           (192, 3, 8192, 197, False), (192, 3, 16384, 16384, True), (96, 3, 8192, 16383, False), (384, 6, 1536, 5119, False),
-                                           (384, 6, 1536, 5120, True), (384, 6, 3072, 6143, False), (384, 6, 3072, 6144, True)])
+                                           (192, 3, 8192, 197, False), (192, 3, 16384, 16384, True), (96, 3, 8192, 16383, False), (384, 6, 1536, 1299, False),
+                                           (384, 6, 1536, 1300, True), (384, 6, 1536, 5119, True), (384, 6, 1408, 5119, False), (384, 6, 1408, 5120, True),
+                                           (384, 6, 3072, 6143, False), (384, 6, 3072, 6144, True)])
 def test_long_mlps_need_rows(ivit, C, H, F, R, fused):
     """Which side of the line between the block kernel and the separate ones a stack is on, and that both give the same."""
     d = dict(B=R, T=1, C=C, H=H, F=F)
