@@ -915,6 +915,12 @@ bool token_block_takes(int C, int F, int64_t R) {
         if (R < (C == 384 ? need : std::min(need, 64 * (int64_t)num_cus()))) return false;
     }
     if (C == 384 && R < (F == 4 * C ? 1300 : 5120)) return false;
+    // A little more than one full round of workgroups at a longer MLP: the rest is a launch of its own (launch_token_block) that walks the whole
+    // MLP for a few rows in the form with shared sets, which is the longer the larger F is.  Three blocks of 197 tokens, rows beyond the round:
+    // time fused / separate on two boxes: F = 3072 722 1.13 and 1.05, 1510 1.07 and 0.99, 3480 1.03 and 0.96; F = 2048 722 1.07 and 0.97, 1510 1.03
+    // and 0.94; F = 1664 131 1.03, 722 1.01, 1510 0.98; F = 256 to 1280 131 to 5056 0.88 to 0.99; F = 8192 3480 1.10.
+    const int64_t round = 128 * (int64_t)num_cus();
+    if (C == 384 && F > 4 * C && R > round && R - round < std::min(round / 9, 2 * (int64_t)(F - 4 * C))) return false;
     return (C == 96 || C == 192 || C == 384) && F >= 2 * FC && F % FC == 0 && R >= 1 && R < (1 << 30) && (int64_t)F * C < (1 << 30);
 }
 

@@ -109,7 +109,9 @@ def test_rows_beyond_full_rounds_of_workgroups(ivit, C, H, F, rows_per_cu, more)
                                            (192, 3, 896, 197, True), (192, 3, 1024, 2047, False), (192, 3, 1024, 2048, True),
                                            (192, 3, 8192, 197, False), (192, 3, 16384, 16384, True), (96, 3, 8192, 16383, False), (384, 6, 1536, 1299, False),
                                            (384, 6, 1536, 1300, True), (384, 6, 1536, 5119, True), (384, 6, 1408, 5119, False), (384, 6, 1408, 5120, True),
-                                           (384, 6, 3072, 6143, False), (384, 6, 3072, 6144, True)])
+                                           (384, 6, 3072, 6143, False), (384, 6, 3072, 6144, True), (384, 6, 3072, 32768, True),
+                                           (384, 6, 3072, 32769, False), (384, 6, 3072, 35839, False), (384, 6, 3072, 35840, True),
+                                           (384, 6, 8192, 36407, False), (384, 6, 8192, 36408, True), (384, 6, 1408, 32769, True)])
 def test_long_mlps_need_rows(ivit, C, H, F, R, fused):
     """Which side of the line between the block kernel and the separate ones a stack is on, and that both give the same."""
     d = dict(B=R, T=1, C=C, H=H, F=F)
