@@ -1,0 +1,27 @@
+// Which form of the Dense kernels a shape takes where more than one could (host arithmetic only).
+#pragma once
+#include <stdint.h>
+
+namespace ivit {
+
+// Layers without a residual that neither hold weights in registers nor are long enough for gemm_tl.hip: streamed tiles of 128 x 128 or 256 x 256
+// (gemm_st.hip) or the slab of weights in LDS (gemm_i8.hip, slabs of `slab` channels), which reads activations once per slab and pads rows
+// to 128 bytes.  Tiles pad the channels to 128.  us, slab and tiles: 12000 x 1040 x 400 16.9 and 12.3, 4000 x 2000 x 448 13.0 and 9.5,
+// 30000 x 656 x 560 26.8 and 24.7, 12000 x 1024 x 896 22.1 and 15.7, 40000 x 2000 x 896 102 and 93, 4000 x 3008 x 1152 27.5 and 18.3.  The slab keeps
+//   up to 384 bytes a row (50000 x 2000 x 272 75 and 81, 40000 x 400 x 384 17.3 and 19.2),
+//   less than three quarters of a round of 128 x 128 tiles, two a CU (20000 x 208 x 1024 10.4 and 10.9),
+//   64 channels and less, half of a tile (tiles / slab at K = 640, 50000 to 400000 rows: 0.97, 1.00, 1.24, 1.17, 1.15, 1.19),
+//   more than four rounds, where it has the rows to use a slab many times over: N = 256, K = 400, 50000 rows 0.77, 131072 (four rounds) 0.93,
+//   200000 1.22; up to 128 channels two and a half rounds, as one slab reads the rows once (N = 128, K = 400, 131072 rows 0.93, 200000 1.21),
+// except that rows of more than 768 bytes have no such end (K = 1152, 200000 rows, N = 128 0.92, 256 0.95, 400 0.99, 640 1.00) if the tiles pad
+// little beyond the slabs (200000 x 144 x 1152, 256 channels for 192, 1.21; 272, 384 for 288, 1.20) or those are of 64 channels, for
+// longer rows (200000 x 144 x 1664 1.00, 272 0.90).
+constexpr bool tiles_before_slab(int64_t M, int64_t N, int64_t K, int slab, int64_t cus) {
+    if (K <= 384 || N <= 64) return false;
+    const int64_t cols = (N + 127) / 128, tiles = (M + 127) / 128 * cols, slab_cols = (N + slab - 1) / slab * slab;
+    if (2 * tiles < 3 * cus) return false;
+    const bool any_rows = K > 768 && (4 * 128 * cols <= 5 * slab_cols || slab == 64);
+    return any_rows || tiles <= (N > 128 ? 8 : 5) * cus;
+}
+
+}  // namespace ivit

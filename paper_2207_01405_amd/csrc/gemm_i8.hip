@@ -2,6 +2,7 @@
 // I-ViT (arXiv 2207.01405, Sec. 3.2, Eq. 7-10) fused into the epilogue, optionally with the residual
 // add of Eq. 1-2 or with ShiftGELU (Sec. 3.4, Algorithm 2) and its rescale: the weight-stationary kernel for slabs that
 // fit LDS, and the choice between all Dense kernels (launch_linear, at the end).
+#include "dense_form.hpp"
 #include "ivit_kernels.hpp"
 #include "linear_rows.hpp"
 #include "residual_pair.hpp"
@@ -541,17 +542,7 @@ hipError_t launch_linear(hipStream_t s, const LinearArgs& a) {
     // one per workgroup)
     if (linear_tl_takes(a) && (a.kernel == LINEAR_BIG_TILES || (a.kernel == LINEAR_AUTO && !ws && a.K >= 2048)))
         return launch_linear_tl(s, a);
-    // Without a residual and with rows of more than 384 bytes, streamed tiles of 128 x 128 or 256 x 256 have overtaken the weight slab, which
-    // reads activations once per slab and pads rows to 128 bytes.  us, slab and tiles: 12000 x 1040 x 400 16.9 and 12.3, 50000 x 208 x 432
-    // 17.4 and 13.2, 4000 x 2000 x 448 13.0 and 9.5, 30000 x 656 x 560 26.8 and 24.7, 50000 x 432 x 640 31.2 and 27.3, 12000 x 1024 x 896 22.1
-    // and 15.7, 40000 x 2000 x 896 102 and 93, 4000 x 3008 x 1152 27.5 and 18.3.  The slab keeps shorter rows (50000 x 2000 x 272 75
-    // and 81, 50000 x 1008 x 352 43 and 47, 40000 x 400 x 384 17.3 and 19.2), up to 768 bytes more than four rounds of 128 x 128 tiles, two a
-    // CU (50000 x 2000 x 400 80 and 86, 50000 x 1008 x 512 50.4 and 52.6, 24000 x 1392 x 592 37.9 and 38.9), less than three quarters of a
-    // round (20000 x 208 x 1024 10.4 and 10.9), two whole units of three chunks (50000 x 432 x 768 33 and 34.5) and a residual
-    // (30000 x 768 x 640 31 and 33, 40000 x 512 x 1152 42.5 and 45.4).
-    const int64_t tiles = ((a.M + 127) / 128) * ((a.N + 127) / 128), cus = num_cus();
-    if (a.kernel == LINEAR_AUTO && !a.residual && a.K > 384 && a.K != 768 && 2 * tiles >= 3 * cus && (a.K > 768 || tiles <= 8 * cus))
-        return launch_linear_st(s, a);
+    if (a.kernel == LINEAR_AUTO && ws && !a.residual && tiles_before_slab(a.M, a.N, a.K, 32 * ncb, num_cus())) return launch_linear_st(s, a);
     if (ws) {
         WsParams W;
         W.g = P; W.pitch = pitch; W.nunits = nunits;

@@ -1,0 +1,64 @@
+"""Which form of the Dense kernels a shape takes: the rules (host code, compiled here) on both sides of their lines, on the CPU, and on
+the GPU that the forms agree there."""
+import ctypes
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle as orc
+from paper_2207_01405_amd import build, synth
+
+I64, INT = ctypes.c_int64, ctypes.c_int
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("dense")
+    (d / "r.cpp").write_text('#include "dense_form.hpp"\n'
+                             'extern "C" int before_slab(int64_t M, int64_t N, int64_t K, int slab) { return ivit::tiles_before_slab(M, N, K, slab, 256); }\n')
+    subprocess.run(["g++", "-std=c++20", "-shared", "-fPIC", "-I", build.CSRC, str(d / "r.cpp"), "-o", str(d / "r.so")], check=True)
+    lib = ctypes.CDLL(str(d / "r.so"))
+    lib.before_slab.argtypes = [I64, I64, I64, INT]
+    return lib
+
+
+@pytest.mark.parametrize("M,N,K,slab,tiles", [
+    # few channels over very many rows stay on the slab: both sides are measured at the rule
+    (200000, 16, 400, 64, False), (262144, 64, 640, 64, False), (200000, 64, 1152, 64, False), (50000, 64, 896, 64, False),
+    (131072, 96, 640, 96, True), (200000, 96, 400, 96, False), (200000, 128, 400, 128, False), (262144, 96, 896, 96, False), (200000, 128, 1152, 128, True),
+    # channels that tiles pad by a third and slabs do not
+    (50000, 144, 896, 64, True), (131072, 192, 896, 96, True), (200000, 144, 1152, 96, False), (90000, 272, 896, 96, False), (262144, 272, 1152, 96, False),
+    (262144, 272, 1664, 64, True),
+    # rows of up to 768 bytes: four rounds of tiles, 768 itself among them
+    (131072, 256, 400, 128, True), (131073, 256, 400, 128, False), (90000, 640, 640, 128, False), (90000, 400, 896, 96, True), (90000, 208, 768, 128, True),
+    (200000, 208, 768, 128, False), (50000, 528, 768, 96, True), (200000, 272, 768, 96, False),
+    (50000, 1008, 352, 128, False), (20000, 208, 1024, 64, False), (12000, 1040, 400, 128, True), (4000, 3008, 1152, 128, True)])
+def test_tiles_or_the_slab(rules, M, N, K, slab, tiles):
+    assert bool(rules.before_slab(M, N, K, slab)) == tiles
+
+
+def _agree(ivit, M, N, K, epi):
+    """The form of the shape against the kernel for many rows, and some rows against the oracle."""
+    import torch
+    x = synth.make_rows(M + N + K, M, K)
+    w, bias, rq_b, rq_c = synth.make_linear(N + K, N, K)
+    kw_o, kw_g = {}, {}
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    rows = np.unique(np.concatenate([np.arange(0, 200, 3), np.arange(M - 40, M), np.arange(0, M, 997)]))
+    if epi == "residual":
+        res = synth.make_rows(7, M, N)
+        kw_o, kw_g = dict(residual=res[rows], res_rq=(20011, 15)), dict(residual=dev(res), res_rq=(20011, 15))
+    d, out = [dev(a) for a in (x, w, bias, rq_b, rq_c)], []
+    for kernel in ("auto", "many_rows"):
+        y = torch.full((M, N), 55, dtype=torch.int8, device="cuda")
+        ivit.ivit_linear_requant(*d, y, kernel=kernel, **kw_g)
+        out.append(y.cpu().numpy())
+    assert np.array_equal(*out)
+    assert np.array_equal(out[0][rows], orc.linear_requant(x[rows], w, bias, rq_b, rq_c, **kw_o))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(66001, 48, 400), (66001, 64, 1152), (131080, 80, 400), (200001, 96, 400), (66003, 144, 896), (90001, 272, 896), (33001, 208, 768)])
+def test_tiles_and_the_slab_agree(ivit, M, N, K):
+    _agree(ivit, M, N, K, "plain")
