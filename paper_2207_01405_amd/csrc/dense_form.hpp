@@ -24,4 +24,22 @@ constexpr bool tiles_before_slab(int64_t M, int64_t N, int64_t K, int slab, int6
     return any_rows || tiles <= (N > 128 ? 8 : 5) * cus;
 }
 
+// Rows of 1024 bytes and more, more 128 x 128 tiles than CUs and at most one of 192 x 128 a CU: eight wavefronts of 96 x 32, one workgroup a
+// CU (gemm_st.hip; the last step of the rule in launch_linear_st).  us, what took the shape before and this: 128 x 128 tiles 4000 x 1536 x 1024
+// 11.3 and 10.5, 2500 x 2304 x 1024 10.9 and 10.0, 4000 x 1536 x 2048 19.6 and 16.2; 256 x 128 tiles of gemm_tl.hip 6272 x 768 x 3072 26.2 and
+// 22.0, 8000 x 768 x 3072 26.5 and 23.6, 5000 x 1024 x 3072 27.0 and 23.2; the K-split kernel 6272 x 768 x 1536 14.3 and 11.4, 16000 x 384 x
+// 1536 17.4 and 15.4.  Not for shorter rows (1576 x 3072 x 768 9.6 either way, 1970 x 2304 x 768 8.9 and 9.0), and 256 x 128 tiles for
+// the next size up gain nothing (8000 x 1000 x 2048 21.1 and 21.3, 6600 x 900 x 1104 with a residual 17.1 and 18.3).
+// Time with these tiles / without: 64 channels and less fill half of one and lose, K = 1024 1.07 to 1.14, 2048 1.00 to 1.07 (with a residual
+// to 1.24), until rows of 2560 bytes (0.86 to 0.99, but 16 and 32 channels to 1.06; 4096 0.87 to 1.05), with a residual for more than 48
+// channels (64: 0.90 to 1.05; 48: 1.02; 16: 1.09 to 1.17).  At 1024 bytes 128 x 64 tiles, which longer rows do not have then, are faster while
+// two a CU take the shape (20000 x 192 1.09, with a residual 1.14; 24500 x 192 0.97 and 0.70), and from two and a half on at up to 128 channels
+// without a residual (35000 x 128 0.94, 40000 1.00, 49000 1.03 to 1.06; with one 0.71, 0.75, 0.80).
+constexpr bool one_round_of_192(int64_t M, int64_t N, int64_t K, bool residual, int64_t cus) {
+    if (K < 1024 || (M + 191) / 192 * ((N + 127) / 128) > cus) return false;
+    if (N <= 64) return K >= 2560 && (!residual || N > 48);
+    const int64_t tiles = (M + 127) / 128 * ((N + 63) / 64);
+    return K > 1024 || (tiles > 2 * cus && (residual || N > 128 || 2 * tiles <= 5 * cus));
+}
+
 }  // namespace ivit

@@ -11,6 +11,7 @@
 // whatever alignment the row has.
 #include <type_traits>
 
+#include "dense_form.hpp"
 #include "linear_rows.hpp"
 #include "regst_common.hpp"
 
@@ -454,14 +455,8 @@ static bool big_tiles(const LinearArgs& a) {
     return 10 * rounds(kBigRows, 1) <= 6 * rounds(128, 2);
 }
 
-// Rows of 1024 bytes and more, more 128 x 128 tiles than CUs and at most one of 192 x 128 a CU: eight wavefronts of 96 x 32, one workgroup a
-// CU (the last step of the rule in launch_linear_st).  us, what took the shape before and this: 128 x 128 tiles 4000 x 1536 x 1024 11.3
-// and 10.5, 2500 x 2304 x 1024 10.9 and 10.0, 4000 x 1536 x 2048 19.6 and 16.2; 256 x 128 tiles of gemm_tl.hip 6272 x 768 x 3072 26.2 and
-// 22.0, 8000 x 768 x 3072 26.5 and 23.6, 5000 x 1024 x 3072 27.0 and 23.2; the K-split kernel 6272 x 768 x 1536 14.3 and 11.4, 16000 x 384 x
-// 1536 17.4 and 15.4.  Not for shorter rows (1576 x 3072 x 768 9.6 either way, 1970 x 2304 x 768 8.9 and 9.0), and 256 x 128 tiles for
-// the next size up gain nothing (8000 x 1000 x 2048 21.1 and 21.3, 6600 x 900 x 1104 with a residual 17.1 and 18.3).
 bool linear_st_one_round(const LinearArgs& a) {
-    return !a.ln_g && a.K >= 1024 && ((a.M + 191) / 192) * ((a.N + 127) / 128) <= num_cus() && 191 * (a.ldx ? a.ldx : (int64_t)a.K) + a.K <= (int64_t)kTileBytes;
+    return !a.ln_g && one_round_of_192(a.M, a.N, a.K, a.residual, num_cus()) && 191 * (a.ldx ? a.ldx : (int64_t)a.K) + a.K <= (int64_t)kTileBytes;
 }
 
 hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {

@@ -16,10 +16,12 @@ I64, INT = ctypes.c_int64, ctypes.c_int
 def rules(tmp_path_factory):
     d = tmp_path_factory.mktemp("dense")
     (d / "r.cpp").write_text('#include "dense_form.hpp"\n'
-                             'extern "C" int before_slab(int64_t M, int64_t N, int64_t K, int slab) { return ivit::tiles_before_slab(M, N, K, slab, 256); }\n')
+                             'extern "C" int before_slab(int64_t M, int64_t N, int64_t K, int slab) { return ivit::tiles_before_slab(M, N, K, slab, 256); }\n'
+                             'extern "C" int of_192(int64_t M, int64_t N, int64_t K, int residual) { return ivit::one_round_of_192(M, N, K, residual, 256); }\n')
     subprocess.run(["g++", "-std=c++20", "-shared", "-fPIC", "-I", build.CSRC, str(d / "r.cpp"), "-o", str(d / "r.so")], check=True)
     lib = ctypes.CDLL(str(d / "r.so"))
     lib.before_slab.argtypes = [I64, I64, I64, INT]
+    lib.of_192.argtypes = [I64, I64, I64, INT]
     return lib
 
 
@@ -36,6 +38,18 @@ def rules(tmp_path_factory):
     (50000, 1008, 352, 128, False), (20000, 208, 1024, 64, False), (12000, 1040, 400, 128, True), (4000, 3008, 1152, 128, True)])
 def test_tiles_or_the_slab(rules, M, N, K, slab, tiles):
     assert bool(rules.before_slab(M, N, K, slab)) == tiles
+
+
+@pytest.mark.parametrize("M,N,K,residual,taken", [
+    (40000, 16, 1024, False, False), (49000, 64, 1536, False, False), (33000, 64, 2048, False, False), (33000, 64, 3072, False, True), (49000, 48, 2560, False, True),
+    (40000, 16, 3072, True, False), (33000, 64, 2048, True, False), (40000, 48, 3072, True, False), (49000, 64, 2560, True, True),
+    # 1024 bytes a row: two tiles of 128 x 64 a CU are the line, one column of tiles stays off without a residual
+    (20000, 192, 1024, False, False), (20000, 192, 1024, True, False), (24500, 192, 1024, False, True), (24500, 192, 1024, True, True), (20000, 192, 1040, False, True),
+    (12000, 272, 1024, True, False), (14000, 272, 1024, True, True), (40900, 128, 1024, False, True), (41000, 128, 1024, False, False), (49000, 128, 1024, False, False), (49000, 128, 1024, True, True), (49000, 80, 1040, False, True),
+    (7000, 528, 1024, False, False), (8000, 528, 1024, False, True),
+    (4000, 1536, 1024, False, True), (6272, 768, 3072, True, True), (8064, 768, 2048, False, True), (8065, 768, 2048, False, False), (6272, 768, 1008, False, False)])
+def test_one_round_of_192_rows(rules, M, N, K, residual, taken):
+    assert bool(rules.of_192(M, N, K, residual)) == taken
 
 
 def _agree(ivit, M, N, K, epi):
@@ -62,3 +76,10 @@ def _agree(ivit, M, N, K, epi):
 @pytest.mark.parametrize("M,N,K", [(66001, 48, 400), (66001, 64, 1152), (131080, 80, 400), (200001, 96, 400), (66003, 144, 896), (90001, 272, 896), (33001, 208, 768)])
 def test_tiles_and_the_slab_agree(ivit, M, N, K):
     _agree(ivit, M, N, K, "plain")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(33001, 64, 2048), (33001, 64, 2560), (40001, 17, 1040), (20001, 192, 1024), (24501, 192, 1024), (12001, 272, 1024), (49001, 128, 1024)])
+@pytest.mark.parametrize("epi", ["plain", "residual"])
+def test_few_channels_and_long_rows(ivit, M, N, K, epi):
+    _agree(ivit, M, N, K, epi)
