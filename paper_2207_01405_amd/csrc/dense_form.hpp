@@ -24,6 +24,17 @@ constexpr bool tiles_before_slab(int64_t M, int64_t N, int64_t K, int slab, int6
     return any_rows || tiles <= (N > 128 ? 8 : 5) * cus;
 }
 
+// Rows of 768 bytes and more, more 128 x 64 tiles than CUs: at most one of 128 x 128 a CU, eight wavefronts of 64 x 32 (gemm_st.hip, launch_linear_st,
+// where figures are).  Time with these tiles / with 64 x 64: where two of those a CU take the shape, whose last row of tiles is half
+// empty then, K = 1536 and 2048 1.10 to 1.24, with a residual 1.26 to 1.45 (129 x 10736, 257 x 6384, 1341 x 1520; K = 768 0.99 to 1.17); at up
+// to two and a half a CU 0.81 to 1.05 (K = 3072 to 768), with a residual 1.02 to 1.19 at K = 768 and 1024, 0.97 to 1.07 at 2048, 0.86 to 1.00 at 3072;
+// beyond, 0.71 to 1.03 with or without one.
+constexpr bool one_round_of_128(int64_t M, int64_t N, int64_t K, bool residual, int64_t cus) {
+    const int64_t small = (M + 63) / 64 * ((N + 63) / 64);
+    if ((M + 127) / 128 * ((N + 127) / 128) > cus || small <= 2 * cus) return false;
+    return !residual || K >= 2048 || 2 * small > 5 * cus;
+}
+
 // Rows of 1024 bytes and more, more 128 x 128 tiles than CUs and at most one of 192 x 128 a CU: eight wavefronts of 96 x 32, one workgroup a
 // CU (gemm_st.hip; the last step of the rule in launch_linear_st).  us, what took the shape before and this: 128 x 128 tiles 4000 x 1536 x 1024
 // 11.3 and 10.5, 2500 x 2304 x 1024 10.9 and 10.0, 4000 x 1536 x 2048 19.6 and 16.2; 256 x 128 tiles of gemm_tl.hip 6272 x 768 x 3072 26.2 and
@@ -36,7 +47,7 @@ constexpr bool tiles_before_slab(int64_t M, int64_t N, int64_t K, int slab, int6
 // two a CU take the shape (20000 x 192 1.09, with a residual 1.14; 24500 x 192 0.97 and 0.70), and from two and a half on at up to 128 channels
 // without a residual (35000 x 128 0.94, 40000 1.00, 49000 1.03 to 1.06; with one 0.71, 0.75, 0.80).
 constexpr bool one_round_of_192(int64_t M, int64_t N, int64_t K, bool residual, int64_t cus) {
-    if (K < 1024 || (M + 191) / 192 * ((N + 127) / 128) > cus) return false;
+    if (K < 1024 || (M + 127) / 128 * ((N + 127) / 128) <= cus || (M + 191) / 192 * ((N + 127) / 128) > cus) return false;
     if (N <= 64) return K >= 2560 && (!residual || N > 48);
     const int64_t tiles = (M + 127) / 128 * ((N + 63) / 64);
     return K > 1024 || (tiles > 2 * cus && (residual || N > 128 || 2 * tiles <= 5 * cus));

@@ -481,7 +481,7 @@ hipError_t launch_linear_st(hipStream_t s, const LinearArgs& a) {
         const int64_t tm = (a.M + 127) / 128, tn = (a.N + 63) / 64;
         if (tiles <= cus) return launch_tile<1, 1, 4, 0>(s, a);
         if (tm * tn <= cus) return launch_tile<1, 1, 4, 0, 4, 2>(s, a);
-        if (tm * ((a.N + 127) / 128) <= cus) return launch_tile<2, 1, 3, 0, 2, 4>(s, a);
+        if (one_round_of_128(a.M, a.N, a.K, a.residual, cus)) return launch_tile<2, 1, 3, 0, 2, 4>(s, a);
         if (linear_st_one_round(a)) return launch_tile<3, 1, 3, 0, 2, 4>(s, a);
     }
     if (2 * tiles <= 5 * cus) return launch_tile<1, 1, 3, 0>(s, a);

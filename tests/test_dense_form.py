@@ -17,11 +17,12 @@ def rules(tmp_path_factory):
     d = tmp_path_factory.mktemp("dense")
     (d / "r.cpp").write_text('#include "dense_form.hpp"\n'
                              'extern "C" int before_slab(int64_t M, int64_t N, int64_t K, int slab) { return ivit::tiles_before_slab(M, N, K, slab, 256); }\n'
-                             'extern "C" int of_192(int64_t M, int64_t N, int64_t K, int residual) { return ivit::one_round_of_192(M, N, K, residual, 256); }\n')
+                             'extern "C" int of_192(int64_t M, int64_t N, int64_t K, int residual) { return ivit::one_round_of_192(M, N, K, residual, 256); }\n'
+                             'extern "C" int of_128(int64_t M, int64_t N, int64_t K, int residual) { return ivit::one_round_of_128(M, N, K, residual, 256); }\n')
     subprocess.run(["g++", "-std=c++20", "-shared", "-fPIC", "-I", build.CSRC, str(d / "r.cpp"), "-o", str(d / "r.so")], check=True)
     lib = ctypes.CDLL(str(d / "r.so"))
     lib.before_slab.argtypes = [I64, I64, I64, INT]
-    lib.of_192.argtypes = [I64, I64, I64, INT]
+    lib.of_192.argtypes = lib.of_128.argtypes = [I64, I64, I64, INT]
     return lib
 
 
@@ -52,6 +53,17 @@ def test_one_round_of_192_rows(rules, M, N, K, residual, taken):
     assert bool(rules.of_192(M, N, K, residual)) == taken
 
 
+@pytest.mark.parametrize("M,N,K,residual,taken", [
+    # two 64 x 64 tiles a CU; two and a half, with a residual and rows of less than 2048 bytes; one 128 x 128 tile a CU
+    (129, 10736, 1536, False, False), (257, 6384, 2048, True, False), (1341, 1520, 3072, False, False), (1341, 1536, 2048, True, False),
+    (20000, 80, 768, True, False), (20000, 80, 768, False, True), (21245, 80, 768, True, True), (8957, 256, 1024, True, False), (8957, 256, 2048, True, True),
+    (1469, 1536, 768, True, False), (1725, 1536, 768, True, True), (1576, 2304, 768, False, True), (4000, 768, 3072, True, True), (32768, 128, 768, True, True),
+    (32769, 128, 768, True, False)])
+def test_one_round_of_128_rows(rules, M, N, K, residual, taken):
+    assert bool(rules.of_128(M, N, K, residual)) == taken
+    assert not rules.of_192(M, N, K, residual) or M > 32768       # (what is left to smaller tiles is not for the larger ones)
+
+
 def _agree(ivit, M, N, K, epi):
     """The form of the shape against the kernel for many rows, and some rows against the oracle."""
     import torch
@@ -59,7 +71,7 @@ def _agree(ivit, M, N, K, epi):
     w, bias, rq_b, rq_c = synth.make_linear(N + K, N, K)
     kw_o, kw_g = {}, {}
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
-    rows = np.unique(np.concatenate([np.arange(0, 200, 3), np.arange(M - 40, M), np.arange(0, M, 997)]))
+    rows = np.unique(np.concatenate([np.arange(0, min(M, 200), 3), np.arange(M - 40, M), np.arange(0, M, 997)]))
     if epi == "residual":
         res = synth.make_rows(7, M, N)
         kw_o, kw_g = dict(residual=res[rows], res_rq=(20011, 15)), dict(residual=dev(res), res_rq=(20011, 15))
@@ -79,7 +91,8 @@ def test_tiles_and_the_slab_agree(ivit, M, N, K):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K", [(33001, 64, 2048), (33001, 64, 2560), (40001, 17, 1040), (20001, 192, 1024), (24501, 192, 1024), (12001, 272, 1024), (49001, 128, 1024)])
+@pytest.mark.parametrize("M,N,K", [(33001, 64, 2048), (33001, 64, 2560), (40001, 17, 1040), (20001, 192, 1024), (24501, 192, 1024), (12001, 272, 1024), (49001, 128, 1024),
+                                   (129, 8699, 1536), (257, 6384, 784), (20001, 80, 768), (1469, 1537, 1040)])
 @pytest.mark.parametrize("epi", ["plain", "residual"])
 def test_few_channels_and_long_rows(ivit, M, N, K, epi):
     _agree(ivit, M, N, K, epi)
