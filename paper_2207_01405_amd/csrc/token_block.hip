@@ -18,8 +18,10 @@
 // runs beside it at the same rate: a step of one product, 12 vector, 2 LDS and 4 scalar instructions takes 160 cycles with one
 // wavefront and 164 with two).  So the results of a channel tile are requantised between the products of the next one, spread
 // evenly, loads are three instructions, and where the tokens of a workgroup divide among eight wavefronts there are eight, which
-// leaves 128 registers beside 128 accumulation registers to each: forwards of 197 tokens, four wavefronts against eight, DeiT-S
-// batch 64 720 -> 669 us and batch 128 1041 -> 984, DeiT-T batch 128 583 -> 522 and batch 256 978 -> 882.
+// leaves 128 registers beside 128 accumulation registers to each: forwards of 197 tokens, four wavefronts against eight, one model again
+// and again (three models in turn), DeiT-S batch 64 687 -> 652 us (687 -> 652) and batch 128 1035 -> 980 (1047 -> 1000), DeiT-T batch 128
+// 640 -> 576 (640 -> 574) and batch 256 1018 -> 937 (1090 -> 955).  Nothing may be spilled: with 29 registers in scratch memory DeiT-S batch
+// 128 took 1028 (1062), as stores and reloads wait for the weights in flight and go through HBM (91 -> 108 MB a launch).
 #include "token_block_common.hpp"
 #include <algorithm>
 #include <type_traits>
@@ -138,10 +140,8 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
 
     extern __shared__ __align__(1024) int8_t lds[];
     int8_t* act = lds + LY::ACT;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int wn = wv % WNG, wm = wv / WNG, wn1 = wv % WN1, wm1 = wv / WN1;
-    const int lj = lane & 31, lg = lane >> 5;
     int8_t* stg = lds + LY::STG + wv * LY::STGB;
     const int64_t m0 = (int64_t)blockIdx.x * M;
     const int rows = __builtin_amdgcn_readfirstlane((int)min64(P.R - m0, M));
@@ -152,6 +152,14 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
 
     auto sync = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
     auto sync_lds = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    // The lane's number, counted anew at each use: no register holds it, or what a phase derives from it, from one phase to the next
+    // (kept so, these addresses are 20 of the 128 registers that a wavefront of the eight has beside its accumulation registers).
+    auto fresh_lane = []() __attribute__((always_inline)) -> int {
+        int l;
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+        __builtin_assume(l >= 0 && l < 64);
+        return l;
+    };
     auto settle = []() __attribute__((always_inline)) {             // the matrix instructions issued so far have written their results
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
@@ -161,14 +169,18 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     // ---- loads into LDS.  A set of rows (proj, fc1, qkv) is contiguous in memory, a set of fc2 is 128 bytes of every row,
     // a token tile has its rows permuted (LDS row i holds token 32 (i / 32) + token_of_row(i % 32)).  Load instruction
     // n = NW i + wavefront covers 16-byte slots 64 n .. 64 n + 63; what differs from piece i to i + 3 is a constant step.
+    const int lane = fresh_lane(), lj = lane & 31, lg = lane >> 5;
+    // The same for what comes again with every set, channel tile or token tile: counted anew where the MLP's accumulators, activations and
+    // first results leave no register to keep it in, kept otherwise (anew everywhere DeiT-T batch 256 takes 1.5 % longer).
+    constexpr bool TIGHT = 4 * KS * T1 + 16 * (3 * TT + N1 * T1) > 160;
+    auto lane_again = [&]() __attribute__((always_inline)) -> int { if constexpr (TIGHT) return fresh_lane(); else return lane; };
     uint32_t vr[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         const int s = 64 * (NW * i + wv) + lane, r = s / PP, p = s % PP;
         vr[i] = (uint32_t)(r * C + 16 * (p ^ swz<G16>(r)));
     }
-    const int r2 = 8 * wv + (lane >> 3);
-    const uint32_t v2 = (uint32_t)(r2 * F + 16 * ((lane & 7) ^ swz<8>(r2)));
+    uint32_t v2 = 0;                                                // (of fc2, from the MLP on)
     auto buffer = [](const int8_t* p, uint32_t bytes) __attribute__((always_inline)) -> v4i {
         const uint64_t a = (uint64_t)uniform_ptr(p);
         return v4i{(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)bytes, 0x00020000};
@@ -195,7 +207,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
                              : "+s"(l.so) : "s"(l.dst), "s"(i % 3 == 0 ? l.d3 : l.d1), "v"(l.v[i % 3]), "s"(l.rsrc), "i"(i * NW * 1024) : "memory", "m0", "scc");
         } else {
             const int w = min(wv, LY::CW - 1);
-            dma16(l.cst, (uint32_t)(16 * min(64 * w + lane, nr - 1)), l.dst + SETW - 1024 * (wv - w));
+            dma16(l.cst, (uint32_t)(16 * min(64 * w + lane_again(), nr - 1)), l.dst + SETW - 1024 * (wv - w));
         }
     };
     auto load_range = [&](Load& l, auto lo_c, auto hi_c, auto bytes_c) __attribute__((always_inline)) {
@@ -207,28 +219,31 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     constexpr int NPR = (LY::SETR / 1024 + NW - 1) / NW + 1, NP1 = (LY::SET1 / 1024 + NW - 1) / NW + 1;      // pieces of a set
     // a token tile: rows past the matrix read as zero (the buffer ends there)
     constexpr int NPA = (M * PP / 64 + NW - 1) / NW;
-    auto act_piece = [&](const v4i& rsrc, uint32_t dst, auto i_c) __attribute__((always_inline)) {
+    struct Tile { v4i rsrc; uint32_t dst, v[3]; };
+    auto act_piece = [&](const Tile& l, auto i_c) __attribute__((always_inline)) {
         constexpr int i = decltype(i_c)::value, NI = M * PP / 64;
-        const int s = 64 * (NW * (i % 3) + wv) + lane, r = s / PP, p = s % PP;
-        const uint32_t v = (uint32_t)(((r & ~31) + token_of_row(r & 31)) * C + 16 * (p ^ swz<G16>(r)));
         if (NW * i + NW - 1 < NI || NW * i + wv < NI)
             asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                         : : "s"(dst), "v"(v + (i / 3) * 3072 * NW), "s"(rsrc), "i"(i * NW * 1024) : "memory", "m0", "scc");
+                         : : "s"(l.dst), "v"(l.v[i % 3] + (i / 3) * 3072 * NW), "s"(l.rsrc), "i"(i * NW * 1024) : "memory", "m0", "scc");
     };
-    auto tile_buffer = [&](const int8_t* src) __attribute__((always_inline)) -> v4i { return buffer(src + m0 * C, (uint32_t)(rows * C)); };
-    auto tile_dst = [&](int off) __attribute__((always_inline)) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + off + wv * 1024)); };
+    auto act_tile = [&](const int8_t* src, int off) __attribute__((always_inline)) -> Tile {
+        Tile l{buffer(src + m0 * C, (uint32_t)(rows * C)), (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + off + wv * 1024)), {}};
+        const int ll = lane_again();
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int s = 64 * (NW * i + wv) + ll, r = s / PP, p = s % PP;
+            l.v[i] = (uint32_t)(((r & ~31) + token_of_row(r & 31)) * C + 16 * (p ^ swz<G16>(r)));
+        }
+        return l;
+    };
     auto load_act = [&](const int8_t* src, int off) __attribute__((always_inline)) {
-        const v4i r = tile_buffer(src);
-        const uint32_t dst = tile_dst(off);
-        static_for<NPA>([&](auto i) __attribute__((always_inline)) { act_piece(r, dst, i); });
+        const Tile l = act_tile(src, off);
+        static_for<NPA>([&](auto i) __attribute__((always_inline)) { act_piece(l, i); });
     };
     auto load_ln = [&](const int8_t* src) __attribute__((always_inline)) {       // gamma, beta: 8 C bytes, one after the other
-        const int at = 1024 * wv + 16 * lane;
+        const int at = 1024 * wv + 16 * lane_again();
         if (1024 * wv < 8 * C) dma16(uniform_ptr(src), (uint32_t)min(at, 8 * C - 16), lds0 + LY::LN + wv * 1024);
     };
-    // (What a phase derives from the lane it derives anew, from a copy that the compiler cannot trace to the lane: kept from one
-    // phase to the next these addresses are 20 of the 128 registers that a wavefront has beside its accumulation registers.)
-    auto fresh_lane = [&]() __attribute__((always_inline)) -> int { int l = lane; pin(l); return l; };
     // ---- the launch's weights and constants into this XCD's L2, every 128-byte line by one lane of one of its first round of
     // workgroups.  A forward's weights are larger than an L2, so they are not there from the launch before, and a set is
     // requested only about a set's products ahead.
@@ -251,31 +266,35 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     int x2[4] = {};                                                 // tiles of rows of 128 bytes
 
     // ---- residual and staging addresses (see gemm_rs.hip for the transposing reads)
-    int jb, jo;                                                     // source side of a transposing read
-    int dj, d_o, lb;                                                // destination side
-    int res_row_p;                                                  // + 16 h: row of the token of result 8 h + jb, A rows in permuted order
-    int res_row_i;                                                  // + 4 h: ... A rows in natural order
-    int out_row, out_xor;                                           // row of token 8 lb + dj
+    // Byte offsets in a token tile's 32 rows, of the first channel tile of this wavefront (the next one lies 32 WNG bytes on: the
+    // swizzle does not reach beyond the pieces of WNG tiles).
+    int dj, d_o, lb;                                                // destination side of a transposing read: token 8 lb + dj
+    int res_p;                                                      // + 16 h rows: the token of result 8 h + jb, A rows in permuted order
+    int res_i;                                                      // + 4 h rows: ... A rows in natural order
+    int out_at;                                                     // row of token 8 lb + dj
+    static_assert(G16 == 2 * WNG, "pieces that the swizzle permutes");
     // (8-byte unit u of row r of the staging tile lies at u ^ ((r / 4) % 4), so that no bank is met twice)
-    int stg_src, stg_src8, stg_dst, stg_x;
+    int stg_src, stg_src8, stg_dst, stg_x, stg_g;
     auto row_addresses = [&]() __attribute__((always_inline)) {
         const int l = fresh_lane(), g = l >> 5;
-        jb = (l & 15) >> 1; jo = l & 1; dj = l & 7; d_o = (l >> 3) & 1; lb = l >> 4;
-        res_row_p = 8 * (jb >> 2) + 4 * g + (jb & 3);
-        res_row_i = 16 * (jb >> 2) + 8 * g + (jb & 3);
-        out_row = 16 * (lb & 1) + 8 * (dj >> 2) + 4 * (lb >> 1) + (dj & 3);
-        out_xor = swz<G16>(out_row);
+        const int jb = (l & 15) >> 1, jo = l & 1;                   // source side
+        dj = l & 7; d_o = (l >> 3) & 1; lb = l >> 4;
+        auto at = [&](int r, int piece) __attribute__((always_inline)) { return r * C + 16 * ((2 * wn + piece) ^ swz<G16>(r)); };
+        res_p = at(8 * (jb >> 2) + 4 * g + (jb & 3), lb & 1) + 8 * jo;
+        res_i = at(16 * (jb >> 2) + 8 * g + (jb & 3), lb & 1) + 8 * jo;
+        out_at = at(16 * (lb & 1) + 8 * (dj >> 2) + 4 * (lb >> 1) + (dj & 3), d_o);
         stg_src = (16 * jo + jb) * 32 + 8 * (lb ^ (jb >> 2));
         stg_src8 = (16 * jo + jb + 8) * 32 + 8 * (lb ^ (jb >> 2) ^ 2);
         stg_dst = (l & 31) * 32;
         stg_x = (l >> 2) & 3;
+        stg_g = g;
     };
-    auto res_read = [&](const int8_t* tile, int ct, auto perm_c, v2i (&rw)[2]) __attribute__((always_inline)) {
+    auto res_read = [&](const int8_t* tile, int g, auto perm_c, v2i (&rw)[2]) __attribute__((always_inline)) {      // channel tile g WNG + wn
         constexpr bool perm = decltype(perm_c)::value;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int r = perm ? res_row_p + 16 * h : res_row_i + 4 * h;
-            const int8_t* a = tile + r * C + 16 * ((2 * ct + (lb & 1)) ^ swz<G16>(r)) + 8 * jo;
+            // (4 rows on, the swizzle differs by G16 / 4)
+            const int8_t* a = tile + (perm ? res_p + 16 * h * C : (res_i ^ (h * (G16 / 4) * 16)) + 4 * h * C) + 32 * WNG * g;
             rw[h] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3)))*)(a));
         }
     };
@@ -283,9 +302,9 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
         constexpr bool perm = decltype(perm_c)::value;
         if (perm) {
             v2i* d = reinterpret_cast<v2i*>(stg + stg_dst);
-            d[(2 * lg) ^ stg_x] = v2i{w[0], w[1]}; d[(2 * lg + 1) ^ stg_x] = v2i{w[2], w[3]};
+            d[(2 * stg_g) ^ stg_x] = v2i{w[0], w[1]}; d[(2 * stg_g + 1) ^ stg_x] = v2i{w[2], w[3]};
         } else {
-            int* d = reinterpret_cast<int*>(stg + stg_dst + 4 * lg);
+            int* d = reinterpret_cast<int*>(stg + stg_dst + 4 * stg_g);
 #pragma unroll
             for (int u = 0; u < 4; ++u) d[2 * (u ^ stg_x)] = w[u];
         }
@@ -295,8 +314,8 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
         const v2i b = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3)))*)(stg + stg_src8));
         return v4i{a[0], a[1], b[0], b[1]};
     };
-    auto act_put = [&](int tt, int ct, const v4i& w) __attribute__((always_inline)) {      // results of (token tile, channel tile) into the token tile
-        *reinterpret_cast<v4i*>(act + (32 * tt + out_row) * C + 16 * ((2 * ct + d_o) ^ out_xor)) = w;
+    auto act_put = [&](int tt, int g, const v4i& w) __attribute__((always_inline)) {      // results of (token tile, channel tile g WNG + wn) into the token tile
+        *reinterpret_cast<v4i*>(act + 32 * tt * C + out_at + 32 * WNG * g) = w;
     };
 
     // a lane's 16 results of a tile in 64-bit arithmetic, channel ch of W; results in the low byte
@@ -318,7 +337,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     // ... of a residual layer; the residual rows come from global memory
     auto unit_slow_res = [&](const v16i& a, const DenseW& W, const ResRq& rr, const int8_t* res, int tt, int ct, auto perm_c) __attribute__((always_inline)) -> v4i {
         constexpr bool perm = decltype(perm_c)::value;
-        const int ch = 32 * ct + lj;
+        const int l = lane_again(), lg = l >> 5, ch = 32 * ct + (l & 31);
         const int32_t b = W.rq_b[ch], c = W.rq_c[ch], bias = W.bias ? W.bias[ch] : 0;
         v4i w;
 #pragma unroll
@@ -464,7 +483,9 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     v4i ew = {}, es = {};
     v2i rw[2] = {}, rwn[2] = {};
     bool fast = false;
-    auto cst_at = [&](int b, int row) __attribute__((always_inline)) -> v4i { return *reinterpret_cast<const v4i*>(set_at(b) + SETW + 16 * row); };
+    auto cst_at = [&](int b, int row) __attribute__((always_inline)) -> v4i {      // of this lane's row of 32
+        return *reinterpret_cast<const v4i*>(set_at(b) + SETW + 16 * (row + (lane_again() & 31)));
+    };
     const int8_t* const tab = P.table;
 
     if (front) {
@@ -473,6 +494,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
         load_ln(tab);
         load_range(L0, ic<0>(), ic<NPR>(), BR());
         if constexpr (LY::NPROJ > 1) load_range(L1, ic<0>(), ic<NPR>(), BR()); else load_range(L1, ic<0>(), ic<NP1>(), B1());
+        const int tid = 64 * wv + lane_again();
         lds[LY::LUT + (tid & 255)] = (int8_t)requant64(shiftgelu_raw((int32_t)(int8_t)tid, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c);
         const ResRq rr1 = make_res(P.res1);
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(LY::NPROJ > 1 && LY::SETR % (1024 * NW) == 0 ? NPR : 0) : "memory");
@@ -485,18 +507,18 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
         Rq64 pq = {};
         v4i pqn = {};
         auto ct_of = [&](int g) __attribute__((always_inline)) -> int { return g * WNG + wn; };        // channel tile of tile g
-        auto proj_res = [&](int g, int t) __attribute__((always_inline)) { res_read(act + 32 * (wm * TT + t) * C, ct_of(g), std::true_type(), rwn); };
+        auto proj_res = [&](int g, int t) __attribute__((always_inline)) { res_read(act + 32 * (wm * TT + t) * C, g, std::true_type(), rwn); };
         auto proj_out = [&](int g, auto par_c, auto i_c) __attribute__((always_inline)) {      // piece i of tile g: 16 TT results, then its last rows
             constexpr int i = decltype(i_c)::value, t = i / 16, e = i % 16, par = decltype(par_c)::value;
             if constexpr (i == NOT) { es = stg_get(); return; }
-            else if constexpr (i == NOT + 1) { act_put(wm * TT + TT - 1, ct_of(g), es); return; }
+            else if constexpr (i == NOT + 1) { act_put(wm * TT + TT - 1, g, es); return; }
             else {
                 if constexpr (e == 0) { rw[0] = rwn[0]; rw[1] = rwn[1]; }
                 eo[e & 3] = out_res(pa[par][t][e], pq, rr1, (int32_t)(int8_t)((uint32_t)rw[e >> 3][(e >> 2) & 1] >> (8 * (e & 3))));
                 if constexpr ((e & 3) == 3) { int w = pack4<true>(eo); pin(w); ew[e >> 2] = w; }
                 if constexpr (e == 8 && t + 1 < TT) proj_res(g, t + 1);
                 if constexpr (e == 3 && t > 0) es = stg_get();
-                if constexpr (e == 11 && t > 0) act_put(wm * TT + t - 1, ct_of(g), es);
+                if constexpr (e == 11 && t > 0) act_put(wm * TT + t - 1, g, es);
                 if constexpr (e == 15) stg_put(ew, std::true_type());
             }
         };
@@ -505,7 +527,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
             static_for<TT>([&](auto t_c) __attribute__((always_inline)) {
                 constexpr int t = decltype(t_c)::value;
                 stg_put(unit_slow_res(pa[decltype(par_c)::value][t], P.proj, rr1, P.x, wm * TT + t, ct_of(g), std::true_type()), std::true_type());
-                act_put(wm * TT + t, ct_of(g), stg_get());
+                act_put(wm * TT + t, g, stg_get());
             });
         };
         static_for<LY::NPROJ>([&](auto s_c) __attribute__((always_inline)) {
@@ -534,7 +556,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
                         spread(ic<0>(), ic<NOT + 2>(), ic<EF>(), ic<NMT>(), ic<mt>(), [&](auto i) __attribute__((always_inline)) { proj_out(g - 1, ic<(g - 1) & 1>(), i); });
                         if constexpr (mt == NMT - 1) proj_slow(g - 1, ic<(g - 1) & 1>());
                     }
-                    if constexpr (mt == 0) pqn = cst_at(b, (p * WNG + wn) * 32 + lj);
+                    if constexpr (mt == 0) pqn = cst_at(b, (p * WNG + wn) * 32);
                     if constexpr (mt == NMT - 1) { pq = as_rq64(pqn); fast = __builtin_amdgcn_ballot_w64(pq.b != 0 && rr1.ok) == ~0ull; }
                 },
                 [&]() __attribute__((always_inline)) { sync(); },
@@ -585,8 +607,10 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
         Rq hq[N1];
         bool hfast = false;
         uint32_t gl[LAG + 4];
+        const int hl = fresh_lane();
+        int8_t* const h_out = act + (wn1 * N1 * 32 + (hl & 31)) * HP + 32 * wm1 * T1 + 16 * (hl >> 5);
         auto h_at = [&](int hbuf, int u) __attribute__((always_inline)) -> int8_t* {
-            return act + hbuf * LY::HB + ((wn1 * N1 + u / T1) * 32 + lj) * HP + 32 * (wm1 * T1 + u % T1) + 16 * lg;
+            return h_out + hbuf * LY::HB + (u / T1) * 32 * HP + 32 * (u % T1);
         };
         // piece i of a channel tile's results, or of the last ones' packing; u0: first unit (tile of 32 x 32) of the channel tile
         auto gelu_out = [&](int hbuf, auto u0_c, auto i_c) __attribute__((always_inline)) {
@@ -608,10 +632,11 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
             if (hfast) return;
             static_for<N1 * T1>([&](auto u_c) __attribute__((always_inline)) {
                 constexpr int u = decltype(u_c)::value;
-                *reinterpret_cast<v4i*>(h_at(hbuf, u)) = unit_slow(ha[u / T1][u % T1], P.fc1, chunk * FC + (wn1 * N1 + u / T1) * 32 + lj, true);
+                *reinterpret_cast<v4i*>(h_at(hbuf, u)) = unit_slow(ha[u / T1][u % T1], P.fc1, chunk * FC + (wn1 * N1 + u / T1) * 32 + (lane_again() & 31), true);
             });
         };
-        const int hl = fresh_lane();
+        const int r2 = 8 * wv + (hl >> 3);
+        v2 = (uint32_t)(r2 * F + 16 * ((hl & 7) ^ swz<8>(r2)));
 #pragma unroll
         for (int i = 0; i < 4; ++i) x2[i] = (hl & 31) * FC + 16 * ((2 * i + (hl >> 5)) ^ swz<8>(hl & 31));
         const int8_t* h0 = act + (16 * (hl >> 5) + ((hl & 15) >> 1)) * HP + 32 * wm * TT + (hl & 16) + 8 * (hl & 1);
@@ -649,7 +674,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
                     body(m_c);
                     if constexpr (m == 0) {
 #pragma unroll
-                        for (int k = 0; k < N1; ++k) hc[k] = cst_at(b, (wn1 * N1 + k) * 32 + lj);
+                        for (int k = 0; k < N1; ++k) hc[k] = cst_at(b, (wn1 * N1 + k) * 32);
                     }
                     if constexpr (m == NM1 - 1) {
                         bool ok = true;
@@ -722,12 +747,11 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
         // constants of fc2 for the epilogue, requested before the loads that follow
         v4i fb[3];
 #pragma unroll
-        for (int j = 0; j < 3; ++j) fb[j] = *reinterpret_cast<const v4i*>(tab + TB_FC2(C) + 16 * (32 * (j * WNG + wn) + lj));
+        for (int j = 0; j < 3; ++j) fb[j] = *reinterpret_cast<const v4i*>(tab + TB_FC2(C) + 16 * (32 * (j * WNG + wn) + (lane_again() & 31)));
         {
-            const v4i r = tile_buffer(P.xhat);
-            const uint32_t dst = tile_dst(LY::SET + LY::SETB);
+            const Tile l = act_tile(P.xhat, LY::SET + LY::SETB);
             f2(0, (NC - 1) & 1, std::false_type(), [&](auto m) __attribute__((always_inline)) {
-                spread(ic<0>(), ic<NPA>(), ic<0>(), ic<(NM2 / 2 > 0 ? NM2 / 2 : 1)>(), m, [&](auto i) __attribute__((always_inline)) { act_piece(r, dst, i); });
+                spread(ic<0>(), ic<NPA>(), ic<0>(), ic<(NM2 / 2 > 0 ? NM2 / 2 : 1)>(), m, [&](auto i) __attribute__((always_inline)) { act_piece(l, i); });
             }, none, none);
         }
         const ResRq rr2 = make_res(P.res2);
@@ -744,9 +768,9 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
 #pragma unroll
             for (int t = 0; t < TT; ++t) asm volatile("" : "+a"(acc[j][t]));      // (not to be copied out before)
         auto f2_res = [&](int u) __attribute__((always_inline)) {
-            res_read(set_at(1) + 32 * (wm * TT + u % TT) * C, (u / TT) * WNG + wn, std::false_type(), rwn);
+            res_read(set_at(1) + 32 * (wm * TT + u % TT) * C, u / TT, std::false_type(), rwn);
         };
-        auto f2_put = [&](int u, const v4i& w) __attribute__((always_inline)) { act_put(wm * TT + u % TT, (u / TT) * WNG + wn, w); };
+        auto f2_put = [&](int u, const v4i& w) __attribute__((always_inline)) { act_put(wm * TT + u % TT, u / TT, w); };
         row_addresses();
         f2_res(0);
         static_for<3 * TT>([&](auto u_c) __attribute__((always_inline)) {
@@ -782,9 +806,10 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     if (!P.next) {                                                  // only the block's output leaves
         constexpr int NI = M * PP / 64;
         const __amdgpu_buffer_rsrc_t yb = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uniform_ptr(P.y + m0 * C)), 0, rows * C, 0x00020000);
+        const int l = lane_again();
 #pragma unroll
         for (int i = 0; i < (NI + NW - 1) / NW; ++i) {
-            const int s = 64 * (NW * i + wv) + lane, r = s / PP, p = s % PP;
+            const int s = 64 * (NW * i + wv) + l, r = s / PP, p = s % PP;
             if (s < M * PP) __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const v4i*>(act + r * C + 16 * (p ^ swz<G16>(r))), yb,
                                                                   ((r & ~31) + token_of_row(r & 31)) * C + 16 * p, 0, 0);
         }
@@ -842,7 +867,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     auto qkv_slow = [&](int g, auto par_c) __attribute__((always_inline)) {
         if (fast) return;
         static_for<TT>([&](auto t_c) __attribute__((always_inline)) {
-            stg_put(unit_slow(pa[decltype(par_c)::value][decltype(t_c)::value], P.qkv_w, (g * WNG + wn) * 32 + lj, false), std::true_type());
+            stg_put(unit_slow(pa[decltype(par_c)::value][decltype(t_c)::value], P.qkv_w, (g * WNG + wn) * 32 + (lane_again() & 31), false), std::true_type());
             qkv_put(g, decltype(t_c)::value, stg_get(), true);
         });
     };
@@ -862,7 +887,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
                     spread(ic<0>(), ic<NOT + 2>(), ic<EF>(), ic<NMT>(), ic<mt>(), [&](auto i) __attribute__((always_inline)) { qkv_out(s * PT + p - 1, ic<par>(), i); });
                     if constexpr (mt == NMT - 1) qkv_slow(s * PT + p - 1, ic<par>());
                 }
-                if constexpr (mt == 0) rqn = cst_at(b, (p * WNG + wn) * 32 + lj);
+                if constexpr (mt == 0) rqn = cst_at(b, (p * WNG + wn) * 32);
                 if constexpr (mt == NMT - 1) { rq = as_rq(rqn); fast = __builtin_amdgcn_ballot_w64(rq.lo <= rq.hi) == ~0ull; }
             },
             [&]() __attribute__((always_inline)) {
