@@ -131,9 +131,8 @@ int ivit_linear_requant(void* stream, const int8_t* x, const int8_t* w, const in
  *   kernel  which Dense kernel runs; results are identical for every choice (Sec. 3.2 fixes the arithmetic, not
  *           the schedule), so this is a switch for tests and measurements:
  *           IVIT_KERNEL_AUTO            chosen from the shape;
- *           IVIT_KERNEL_MANY_ROWS       what layers with many rows run on where no faster kernel takes them: the one
- *                                       that keeps a slab of the weights in LDS, or for shapes it does not take
- *                                       the one for any shape with its largest tiles, however few the rows;
+ *           IVIT_KERNEL_MANY_ROWS       the one that keeps a slab of the weights in LDS, or for shapes it does not
+ *                                       take the one for any shape with tiles of 128 x 128, however few the rows;
  *           IVIT_KERNEL_REG_STATIONARY  the kernels that keep the weights in registers; they take K = 384, 768 or
  *                                       1536 (and K = 192 for layers without a residual) with N % 32 == 0 only,
  *                                       other shapes give IVIT_ERR_SHAPE.

@@ -4,7 +4,9 @@
 
 namespace ivit {
 
-constexpr int64_t kTileRows = 128;       // the tallest tile of the kernel for any shape (gemm_st.hip)
+// The tallest tile of the kernel for any shape (gemm_st.hip) that is taken without a look at the row stride; its tiles of 192 and 256 rows are
+// taken only where their own offsets fit (linear_st_one_round, big_tiles).
+constexpr int64_t kTileRows = 128;
 
 // That kernel addresses the rows of a tile by 32-bit byte offsets from the tile's first one; they are kept below kTileBytes =
 // 2^31, where it does not matter whether anything on the way takes them as signed.  kTileBytes is also the size in its buffer

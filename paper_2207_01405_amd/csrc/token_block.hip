@@ -19,9 +19,9 @@
 // wavefront and 164 with two).  So the results of a channel tile are requantised between the products of the next one, spread
 // evenly, loads are three instructions, and where the tokens of a workgroup divide among eight wavefronts there are eight, which
 // leaves 128 registers beside 128 accumulation registers to each: forwards of 197 tokens, four wavefronts against eight, one model again
-// and again (three models in turn), DeiT-S batch 64 687 -> 652 us (687 -> 652) and batch 128 1035 -> 980 (1047 -> 1000), DeiT-T batch 128
-// 640 -> 576 (640 -> 574) and batch 256 1018 -> 937 (1090 -> 955).  Nothing may be spilled: with 29 registers in scratch memory DeiT-S batch
-// 128 took 1028 (1062), as stores and reloads wait for the weights in flight and go through HBM (91 -> 108 MB a launch).
+// and again (three models in turn), DeiT-S batch 64 687 -> 650 us (688 -> 650) and batch 128 1013 -> 946 (1024 -> 970), DeiT-T batch 128
+// 615 -> 538 (614 -> 538) and batch 256 1004 -> 845 (1019 -> 863).  Nothing may be spilled: with 29 registers in scratch memory DeiT-S
+// batch 128 took 5 % longer (6 %), as stores and reloads wait for the weights in flight and go through HBM (91 -> 108 MB a launch).
 #include "token_block_common.hpp"
 #include <algorithm>
 #include <type_traits>
@@ -248,8 +248,9 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     // workgroups.  A forward's weights are larger than an L2, so they are not there from the launch before, and a set is
     // requested only about a set's products ahead.
     // (Requested where the next wait for loads is a set's products or a LayerNorm away.)
-    // Three models' inputs in turn, without and with it: DeiT-S batch 128 1175 -> 1023 us, DeiT-T batch 256 901 -> 828, Swin-T batch 128
-    // 1653 -> 1506; requested all at once at the start, where the first barrier waits for it, DeiT-T batch 128 544 instead of 522.
+    // Without and with it, three models in turn (one model again and again): DeiT-S batch 64 666 -> 650 us (666 -> 650), batch 128 1096 -> 970
+    // (929 -> 946), DeiT-T batch 256 911 -> 863 (852 -> 845), Swin-T batch 128 1514 -> 1438 (1513 -> 1438); requested all at once at
+    // the start, where the first barrier waits for it, DeiT-T batch 128 544 instead of 522.
     const uint32_t warm_n = min(max(gridDim.x / 8, 1u), 32u), warm_i = blockIdx.x / 8;
     auto warm = [&](const int8_t* p, uint32_t bytes) __attribute__((always_inline)) {
         if (warm_n >= 4 && warm_i < warm_n)

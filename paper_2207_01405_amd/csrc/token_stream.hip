@@ -9,8 +9,11 @@
 // ready.  Barriers (seven) stand only where token rows change hands.  The whole hidden layer lies in LDS, and a wavefront's
 // tile of xhat stays in its registers for the residual of the last layer.
 //
-// What bounds it at C = 384 is instructions: the second MLP layer, which has one epilogue, takes 640 cycles per 48 KB of weights
-// (76 bytes a cycle), the others 900 to 1100.  Without the loads a launch of 49 workgroups takes 17.5 of 26 us, without the products 25.
+// What bounds it at C = 384 is half the stream of weights and half what stands between its parts.  Of 50 to 52 thousand cycles of a
+// workgroup (49 to 253 of them; read from the cycle counter in a copy) proj takes 3.0, the first MLP layer 11.2 to 13.0, the second 5.4 to 7.2
+// and qkv 6.9, that is 460 cycles per 48 KB of weights in the second MLP layer, which has one epilogue, and 770 to 1080 in the others.  The first
+// tiles and units take 5 to 6 to arrive, the two LayerNorms with their barriers 6.3, the results of the second MLP layer with theirs 6.0, and
+// the barriers behind proj and the first MLP layer, where the slowest wavefront is waited for, 4.7.
 // token_block.hip's buffers of 48 KB, one set in flight that first waits for a latency, took 34 us for 161 workgroups, this 28.
 #include "token_block_common.hpp"
 
