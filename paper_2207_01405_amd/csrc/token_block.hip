@@ -140,7 +140,8 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
 
     extern __shared__ __align__(1024) int8_t lds[];
     int8_t* act = lds + LY::ACT;
-    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int tid = threadIdx.x, lane = tid & 63, lj = lane & 31, lg = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wv % WNG, wm = wv / WNG, wn1 = wv % WN1, wm1 = wv / WN1;
     int8_t* stg = lds + LY::STG + wv * LY::STGB;
     const int64_t m0 = (int64_t)blockIdx.x * M;
@@ -152,14 +153,23 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
 
     auto sync = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
     auto sync_lds = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-    // The lane's number, counted anew at each use: no register holds it, or what a phase derives from it, from one phase to the next
-    // (kept so, these addresses are 20 of the 128 registers that a wavefront of the eight has beside its accumulation registers).
-    auto fresh_lane = []() __attribute__((always_inline)) -> int {
+    // What a phase derives from the lane it derives anew, from a copy that the compiler cannot trace to the lane: kept from one phase to the
+    // next these addresses are 20 of the 128 registers that a wavefront of the eight has beside its accumulation registers.  Where the MLP's
+    // accumulators, activations and first results leave no register for the lane either it is counted anew, and so it is for what comes
+    // again with every set, channel tile or token tile (counted anew everywhere DeiT-T batch 256 takes 1.5 % longer).
+    constexpr bool TIGHT = 4 * KS * T1 + 16 * (3 * TT + N1 * T1) > 160;
+    auto fresh_lane = [&]() __attribute__((always_inline)) -> int {
         int l;
-        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-        __builtin_assume(l >= 0 && l < 64);
+        if constexpr (TIGHT) {
+            asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+            __builtin_assume(l >= 0 && l < 64);
+        } else {
+            l = lane;
+            pin(l);
+        }
         return l;
     };
+    auto lane_again = [&]() __attribute__((always_inline)) -> int { if constexpr (TIGHT) return fresh_lane(); else return lane; };
     auto settle = []() __attribute__((always_inline)) {             // the matrix instructions issued so far have written their results
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
@@ -169,11 +179,6 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     // ---- loads into LDS.  A set of rows (proj, fc1, qkv) is contiguous in memory, a set of fc2 is 128 bytes of every row,
     // a token tile has its rows permuted (LDS row i holds token 32 (i / 32) + token_of_row(i % 32)).  Load instruction
     // n = NW i + wavefront covers 16-byte slots 64 n .. 64 n + 63; what differs from piece i to i + 3 is a constant step.
-    const int lane = fresh_lane(), lj = lane & 31, lg = lane >> 5;
-    // The same for what comes again with every set, channel tile or token tile: counted anew where the MLP's accumulators, activations and
-    // first results leave no register to keep it in, kept otherwise (anew everywhere DeiT-T batch 256 takes 1.5 % longer).
-    constexpr bool TIGHT = 4 * KS * T1 + 16 * (3 * TT + N1 * T1) > 160;
-    auto lane_again = [&]() __attribute__((always_inline)) -> int { if constexpr (TIGHT) return fresh_lane(); else return lane; };
     uint32_t vr[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -495,7 +500,6 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
         load_ln(tab);
         load_range(L0, ic<0>(), ic<NPR>(), BR());
         if constexpr (LY::NPROJ > 1) load_range(L1, ic<0>(), ic<NPR>(), BR()); else load_range(L1, ic<0>(), ic<NP1>(), B1());
-        const int tid = 64 * wv + lane_again();
         lds[LY::LUT + (tid & 255)] = (int8_t)requant64(shiftgelu_raw((int32_t)(int8_t)tid, P.gelu_p), P.gelu_rq.b, P.gelu_rq.c);
         const ResRq rr1 = make_res(P.res1);
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(LY::NPROJ > 1 && LY::SETR % (1024 * NW) == 0 ? NPR : 0) : "memory");
