@@ -175,7 +175,7 @@ hipError_t run_blocks(hipStream_t s, const int8_t* x, int8_t* y, const ivit_bloc
     // the constants of the fused launches live where the separate kernels would have put the hidden layer
     const size_t slot = up256(ivit::token_block_table_bytes(d->C, d->F));
     const int slots = (int)std::min<size_t>((size_t)R * d->F / slot, (size_t)n_blocks + 1);
-    if (!ivit::token_block_takes(d->C, d->F, R) || slots < 1) {
+    if (!ivit::token_block_takes(d->C, d->F, R, n_blocks) || slots < 1) {
         // block l reads cur and writes into the other ping-pong buffer; the last producer writes y directly
         const int8_t* cur = x;
         for (int l = 0; l < n_blocks; ++l) {

@@ -73,7 +73,7 @@ struct TokenBlockArgs {
 size_t token_block_table_bytes(int C, int F);
 constexpr int kTableLaunches = 15;       // launches whose constants one table launch prepares
 hipError_t launch_token_tables(hipStream_t s, const TokenBlockArgs* a, int n);      // n <= kTableLaunches
-bool token_block_takes(int C, int F, int64_t R);
+bool token_block_takes(int C, int F, int64_t R, int n_blocks);
 hipError_t launch_token_block(hipStream_t s, const TokenBlockArgs& a);
 bool token_stream_takes(int C, int F, int64_t R);       // the form of launch_token_block for few rows (token_stream.hip)
 hipError_t launch_token_stream(hipStream_t s, const TokenBlockArgs& a);

@@ -925,10 +925,13 @@ hipError_t launch_tb(hipStream_t s, const TokenBlockArgs& a) {
 
 }  // namespace
 
-bool token_block_takes(int C, int F, int64_t R) {
+bool token_block_takes(int C, int F, int64_t R, int n_blocks) {
     // C = 384: with few tiles a CU spends its time on fetching the layers' 1.7 MB of weights through one workgroup; the
     // separate kernels spread each layer over the chip.  Whole forwards, fused against separate, F = 4 C (token_stream.hip): DeiT-S
     // batch 4 378 against 350 us, 6 (1182 rows) 368 against 372, 8 (1576) 367 against 382, 16 382 against 452, 25 413 against 542.
+    // The constants' launch and the two ends of a stack cost the same however few blocks it has, so short ones need more rows: time fused /
+    // separate, one block 1576 rows 1.13, 2364 1.06, 2758 0.99; two 1576 1.05, 1970 1.02, 2364 1.00; three 1576 1.03, 1970 0.99; four
+    // 1576 1.015, 1970 0.98; six 1379 1.01, 1576 1.00; eight 1379 1.00.
     // Other F: DeiT-S's sizes in the form with shared sets, batch 24 (4728 rows) 570 against 556, 32 (6304) 591 against 661.
     // What is left beyond full rounds of tiles is cheap in the form for few rows: batch 168 (33096 rows, 328 of them beyond) 1481
     // against 1567 us with separate kernels, 184 (36248) 1567 against 1731.
@@ -944,13 +947,14 @@ bool token_block_takes(int C, int F, int64_t R) {
         const int64_t need = (C == 96 ? 3 : 2) * (int64_t)F;
         if (R < (C == 384 ? need : std::min(need, 64 * (int64_t)num_cus()))) return false;
     }
-    if (C == 384 && R < (F == 4 * C ? 1300 : 5120)) return false;
+    if (C == 384 && R < (F == 4 * C ? 1300 + (n_blocks < 8 ? 1400 / n_blocks : 0) : 5120)) return false;
     // A little more than one full round of workgroups at a longer MLP: the rest is a launch of its own (launch_token_block) that walks the whole
     // MLP for a few rows in the form with shared sets, which is the longer the larger F is.  Three blocks of 197 tokens, rows beyond the round:
     // time fused / separate on two boxes: F = 3072 722 1.13 and 1.05, 1510 1.07 and 0.99, 3480 1.03 and 0.96; F = 2048 722 1.07 and 0.97, 1510 1.03
     // and 0.94; F = 1664 131 1.03, 722 1.01, 1510 0.98; F = 256 to 1280 131 to 5056 0.88 to 0.99; F = 8192 3480 1.10.
-    const int64_t round = 128 * (int64_t)num_cus();
-    if (C == 384 && F > 4 * C && R > round && R - round < std::min(round / 9, 2 * (int64_t)(F - 4 * C))) return false;
+    // One block: F = 1536 131 rows 1.02, 722 1.01, 1116 1.01, 1904 0.99; F = 512 1.02, 1.01, 1.00, 1.00; two blocks 0.92 to 0.98.
+    const int64_t round = 128 * (int64_t)num_cus(), beyond = F > 4 * C ? std::min(round / 9, 2 * (int64_t)(F - 4 * C)) : n_blocks == 1 ? round / 32 : 0;
+    if (C == 384 && R > round && R - round < beyond) return false;
     return (C == 96 || C == 192 || C == 384) && F >= 2 * FC && F % FC == 0 && R >= 1 && R < (1 << 30) && (int64_t)F * C < (1 << 30);
 }
 

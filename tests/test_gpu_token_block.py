@@ -107,11 +107,11 @@ def test_rows_beyond_full_rounds_of_workgroups(ivit, C, H, F, rows_per_cu, more)
 
 @pytest.mark.parametrize("C,H,F,R,fused", [(96, 3, 512, 197, True), (96, 3, 640, 1919, False), (96, 3, 640, 1920, True),
                                            (192, 3, 896, 197, True), (192, 3, 1024, 2047, False), (192, 3, 1024, 2048, True),
-                                           (192, 3, 8192, 197, False), (192, 3, 16384, 16384, True), (96, 3, 8192, 16383, False), (384, 6, 1536, 1299, False),
-                                           (384, 6, 1536, 1300, True), (384, 6, 1536, 5119, True), (384, 6, 1408, 5119, False), (384, 6, 1408, 5120, True),
+                                           (192, 3, 8192, 197, False), (192, 3, 16384, 16384, True), (96, 3, 8192, 16383, False), (384, 6, 1536, 2699, False),
+                                           (384, 6, 1536, 2700, True), (384, 6, 1536, 5119, True), (384, 6, 1408, 5119, False), (384, 6, 1408, 5120, True),
                                            (384, 6, 3072, 6143, False), (384, 6, 3072, 6144, True), (384, 6, 3072, 32768, True),
                                            (384, 6, 3072, 32769, False), (384, 6, 3072, 35839, False), (384, 6, 3072, 35840, True),
-                                           (384, 6, 8192, 36407, False), (384, 6, 8192, 36408, True), (384, 6, 1408, 32769, True)])
+                                           (384, 6, 8192, 36407, False), (384, 6, 8192, 36408, True), (384, 6, 1408, 33791, False), (384, 6, 1408, 33792, True)])
 def test_long_mlps_need_rows(ivit, C, H, F, R, fused):
     """Which side of the line between the block kernel and the separate ones a stack is on, and that both give the same."""
     d = dict(B=R, T=1, C=C, H=H, F=F)
@@ -120,6 +120,18 @@ def test_long_mlps_need_rows(ivit, C, H, F, R, fused):
     ivit.ivit_trace_begin(64)
     got, want = _run(ivit, d, x, blocks, None)
     kinds = [r[1] for r in ivit.ivit_trace_end(64)]
+    assert np.array_equal(got, want) and (11 in kinds) == fused
+
+
+@pytest.mark.parametrize("n,R,F,fused", [(2, 1999, 1536, False), (2, 2000, 1536, True), (7, 1499, 1536, False), (7, 1500, 1536, True), (8, 1299, 1536, False),
+                                         (8, 1300, 1536, True), (2, 32769, 256, True)])
+def test_short_stacks_need_rows(ivit, n, R, F, fused):
+    """The line between the block kernel and the separate ones at width 384, for stacks of more than one block."""
+    cfg, blocks = _blocks(384, 6, F, 1, n, "as drawn")
+    x = synth.make_rows(11, R, 384)
+    ivit.ivit_trace_begin(128)
+    got, want = _run(ivit, dict(B=R, T=1, C=384, H=6, F=F), x, blocks, None)
+    kinds = [r[1] for r in ivit.ivit_trace_end(128)]
     assert np.array_equal(got, want) and (11 in kinds) == fused
 
 
@@ -160,7 +172,7 @@ def test_two_wavefronts_on_a_simd_store_what_they_computed(ivit, C, H, F, R):
 def test_few_rows(ivit, C, H, R, regime):
     """token_stream.hip at the edges of its range and of its tiles (32 tokens, 64 beyond 32 a CU), all requantisation forms."""
     d = dict(B=R, T=1, C=C, H=H, F=4 * C)
-    cfg, blocks = _blocks(C, H, 4 * C, 1, 2, regime)
+    cfg, blocks = _blocks(C, H, 4 * C, 1, 8 if C == 384 and R < 2000 else 2, regime)      # (as many as that kernel takes the rows from)
     got, want = _run(ivit, d, synth.make_rows(9 + R, R, C), blocks, synth.make_final_ln(cfg) if R % 2 else None)
     assert np.array_equal(got, want)
 
