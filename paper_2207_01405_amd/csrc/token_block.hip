@@ -153,8 +153,8 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
 
     auto sync = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
     auto sync_lds = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-    // What a phase derives from the lane it derives anew, from a copy that the compiler cannot trace to the lane: kept from one phase to the
-    // next these addresses are 20 of the 128 registers that a wavefront of the eight has beside its accumulation registers.  Where the MLP's
+    // With eight wavefronts what a phase derives from the lane it derives anew, from a copy that the compiler cannot trace to the lane: kept from
+    // one phase to the next these addresses are 20 of the 128 registers that a wavefront has beside its accumulation registers.  Where the MLP's
     // accumulators, activations and first results leave no register for the lane either it is counted anew, and so it is for what comes
     // again with every set, channel tile or token tile (counted anew everywhere DeiT-T batch 256 takes 1.5 % longer).
     constexpr bool TIGHT = 4 * KS * T1 + 16 * (3 * TT + N1 * T1) > 160;
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
             __builtin_assume(l >= 0 && l < 64);
         } else {
             l = lane;
-            pin(l);
+            if constexpr (NW == 8) pin(l);
         }
         return l;
     };
@@ -256,9 +256,12 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
     // Without and with it, three models in turn (one model again and again): DeiT-S batch 64 666 -> 650 us (666 -> 650), batch 128 1096 -> 970
     // (929 -> 946), DeiT-T batch 256 911 -> 863 (852 -> 845), Swin-T batch 128 1514 -> 1438 (1513 -> 1438); requested all at once at
     // the start, where the first barrier waits for it, DeiT-T batch 128 544 instead of 522.
+    // Not for what four wavefronts take at widths 96 and 192, where all of it is 0.1 to 0.5 MB: blocks of width 96 were 1 to 3 % slower with it,
+    // whether it had anything to do or not (four blocks of 392 rows 77.5 -> 79.5 us, of 50176 144.8 -> 148.4).
+    constexpr bool WARM = NW == 8 || C == 384;
     const uint32_t warm_n = min(max(gridDim.x / 8, 1u), 32u), warm_i = blockIdx.x / 8;
     auto warm = [&](const int8_t* p, uint32_t bytes) __attribute__((always_inline)) {
-        if (warm_n >= 4 && warm_i < warm_n)
+        if (WARM && warm_n >= 4 && warm_i < warm_n)
             for (uint32_t at = (warm_i * 64 * NW + 64 * wv + fresh_lane()) * 128; at < bytes; at += warm_n * 64 * NW * 128)
                 dma4(uniform_ptr(p), at, lds0 + LY::SINK);
     };
@@ -645,7 +648,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
 #pragma unroll
         for (int i = 0; i < 4; ++i) x2[i] = (hl & 31) * FC + 16 * ((2 * i + (hl >> 5)) ^ swz<8>(hl & 31));
         const int8_t* h0 = act + (16 * (hl >> 5) + ((hl & 15) >> 1)) * HP + 32 * wm * TT + (hl & 16) + 8 * (hl & 1);
-        constexpr int RB = RD;                                      // ring of weight fragments of fc2
+        constexpr int RB = TIGHT ? 3 : 4;                           // ring of weight fragments of fc2: requested RB - 1 steps ahead
         v4i af[2][TT], b2[RB];
         auto read_a = [&](int hbuf, auto kk_c) __attribute__((always_inline)) {
             constexpr int kk = decltype(kk_c)::value;
@@ -665,6 +668,7 @@ __global__ __launch_bounds__(64 * NW) void token_block_kernel(TokenBlockArgs P) 
             constexpr int k = decltype(k_c)::value;
             if constexpr (k == 0) read_a(hbuf, ic<0>());
             read_b(b, k_c);
+            if constexpr (k == RD - 2 && RB > RD) read_b(b, ic<RD - 1>());
         };
         // body(m): the loads and whatever else goes with product m; after(): loads to start once this set's memory is free
         auto f1 = [&](const int8_t* w0, int b, int hbuf, auto body, auto after, auto next) __attribute__((always_inline)) {
